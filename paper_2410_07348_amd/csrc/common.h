@@ -172,6 +172,9 @@ hipError_t launch_perm_small(const Dims &d, const Workspace &w, const CapArgs &c
 hipError_t launch_balance(const Dims &d, const Workspace &w, const float *out_gate, float tau,
                           hipStream_t s, int router_rows = 0);
 
+// float32 layers, any supported shape: float32 matrix cores
+hipError_t launch_ffn_f32(const FfnArgs &a, int which, hipStream_t s);
+
 hipError_t launch_ffn_generic(const FfnArgs &a, bool bf16, int which, hipStream_t s);
 bool ffn_mfma_supported(const Dims &d);
 hipError_t launch_ffn_mfma(const FfnArgs &a, int which, hipStream_t s);
@@ -210,6 +213,8 @@ __device__ inline float wave_max(float v) {
     for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, kWave));
     return v;
 }
+
+__device__ inline float silu_f(float z) { return z / (1.f + expf(-z)); }
 
 __device__ inline float to_f32(float v) { return v; }
 __device__ inline float to_f32(bf16_t v) { return (float)v; }

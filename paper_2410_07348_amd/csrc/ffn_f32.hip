@@ -1,0 +1,420 @@
+// Grouped SwiGLU FFN of the float32 layers on the float32 matrix cores (gfx950,
+// v_mfma_f32_16x16x4_f32: float32 products and float32 accumulation, no
+// narrower type anywhere).
+//
+//   GEMM1: h[r,f]    = silu(W1_e[f,:] . x_r) * (W3_e[f,:] . x_r),  x_r = x[src_of[r] / k]
+//   GEMM2: yffn[r,d] = W2_e[d,:] . h[r,:]
+// for every FFN expert e (paper Eq.2) and the rows r of its group, any D and F
+// that are multiples of 8.
+//
+// Two kernels share the operand layout.  A K slab is 32 floats, 128 bytes of a
+// row; lane l holds 4 consecutive floats (chunk l / 16 of a half slab) of row
+// l % 16, and component j of the four feeds MFMA j: the k of one MFMA are then
+// 4 (l / 16) + j, in another order than the memory's but the same for both
+// operands.  The weight fragment is the first operand, so a lane ends up with
+// four consecutive output columns of one row: one 16-byte store.
+//  * k_ffn_f32: tiles of BM x BN.  One MFMA keeps a SIMD busy for 32 cycles and
+//    needs a quarter of a 16-byte operand read, so the tile kernel is bound by
+//    the matrix cores (154 TFLOP/s in a large product on this card) with plain
+//    register-staged loads: slabs kt + 1 and kt + 2 are on their way in registers
+//    while slab kt is multiplied from one of two LDS buffers, and several small
+//    workgroups share a CU and fill each other's barriers.  The loop has no branch
+//    (one slab ahead instead of two: 159 / 102 us; a loop that could leave in the
+//    middle: 178 us, the accumulators were copied around).  2731 rows, D = 768,
+//    F = 2048: GEMM1 17.2 GFLOP in 153 us, GEMM2 8.6 GFLOP in 89 us (one thread per
+//    output element, plain FMA: 7560 and 3700 us).
+//  * k_ffn_f32_stream: a few rows per expert, bound by the weight stream.  One
+//    workgroup per (16 rows of an expert, 64 weight rows); its eight waves take
+//    the K slabs in turn, load their operands straight into registers, and the
+//    eight partial sums are added through LDS in wave order.
+// Rows past the end of a group are clamped on load and masked on store; columns
+// past the end of K are zero in both operands.
+#include "common.h"
+
+#include <type_traits>
+
+namespace moepp {
+
+struct F32Args {
+    const float *A;          // GEMM1: x [T, ld] row-major; GEMM2: h, K-slab-major over h_rows rows
+    const float *B;          // [n_ffn] matrices [Nb, K] in panels of K slabs (panel_row)
+    float *C;                // GEMM1: h, K-slab-major over h_rows rows; GEMM2: yffn [R, ld] row-major
+    const int32_t *offsets;  // [n_ffn + 1]
+    const int32_t *src_of;   // GEMM1 only
+    int ld, h_rows, K;
+    int Nb;                  // rows of B per expert (2F or D)
+    int Nc;                  // columns of C (F or D)
+    int n_ffn, topk;
+    int Nt;                  // column tiles of the kernel per expert
+};
+
+// Logical weight row L of a matrix: for GEMM1 blocks of 64, 32 rows of W1 and the
+// same 32 of W3 (also where the last block has fewer, so that silu's argument and
+// its multiplier always sit 32 rows apart).  Returns the packed row; a row that
+// does not exist gives row 0 (its output columns are never stored).
+template <bool SWIGLU>
+__device__ inline int packed_of_logical(int L, int Nb) {
+    if constexpr (SWIGLU) {
+        const int b = L / 64, up = (L % 64) / 32, r = L % 32;
+        const int F = Nb / 2, rem = F - 32 * b, bs = rem < 32 ? rem : 32;
+        return r < bs ? 64 * b + up * bs + r : 0;
+    } else {
+        return L < Nb ? L : 0;
+    }
+}
+
+// Tile `u` of the list (expert, block of BM rows, column tile) with the row
+// blocks of an expert fastest; false past the end.  Every lane takes part.
+struct F32Tile {
+    int e, row0, row_end, nt;
+};
+__device__ inline bool locate_tile(const F32Args &a, int bm, int lane, F32Tile &t) {
+    const int eq = lane < a.n_ffn ? lane : a.n_ffn;
+    const int o_lo = a.offsets[eq], o_hi = a.offsets[eq < a.n_ffn ? eq + 1 : eq];
+    const int tiles_q = (o_hi - o_lo + bm - 1) / bm * a.Nt;      // 0 for an expert without rows
+    int incl = tiles_q;
+#pragma unroll
+    for (int d = 1; d < kWave; d <<= 1) {
+        const int up = __shfl_up(incl, d, kWave);
+        if (lane >= d) incl += up;
+    }
+    const int total = __builtin_amdgcn_readlane(incl, kWave - 1);
+    // workgroup w runs on XCD w % 8: each XCD takes a consecutive eighth of the list, so
+    // the workgroups that share its L2 share weight rows (row blocks are fastest)
+    const int per = (total + 7) / 8, in = blockIdx.x / 8;
+    const int u = (blockIdx.x % 8) * per + in;
+    if (in >= per || u >= total) return false;
+    t.e = __builtin_ctzll(__ballot(incl > u));
+    const int local = u - __builtin_amdgcn_readlane(incl - tiles_q, t.e);
+    const int lo = __builtin_amdgcn_readlane(o_lo, t.e);
+    t.row_end = __builtin_amdgcn_readlane(o_hi, t.e);
+    const int mt = (t.row_end - lo + bm - 1) / bm;
+    t.nt = local / mt;
+    t.row0 = lo + (local - t.nt * mt) * bm;
+    return true;
+}
+
+// Four accumulator values (columns c .. c + 3 of row `row`) to memory.
+template <bool SWIGLU>
+__device__ inline void store4(const F32Args &a, int row, int c, f32x4 v) {
+    if constexpr (SWIGLU)
+        *reinterpret_cast<f32x4 *>(a.C + slab_row(row, c / kSlab, a.h_rows, a.Nc) + c % kSlab) = v;
+    else
+        *reinterpret_cast<f32x4 *>(a.C + (size_t)row * a.ld + c) = v;
+}
+__device__ inline f32x4 swiglu4(f32x4 z, f32x4 g) {
+    f32x4 o;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) o[i] = silu_f(z[i]) * g[i];
+    return o;
+}
+
+// LDS rows are 128 bytes, half of the 64 banks; a 16-byte operand read is served
+// in lane sets that pair rows {0-3, 12-15} at one chunk with rows {4-11} at the
+// next: with this swizzle of the chunk index they all land on different banks.
+__device__ inline int f32_swz(int row) { return (row >> 1) & 7; }
+
+// RAG: K is not a multiple of 32, the last slab is narrower
+template <bool SWIGLU, bool RAG, int BM, int BN, int WM, int WN>
+__global__ __launch_bounds__(WM *WN *kWave) void k_ffn_f32(F32Args a) {
+    constexpr int NT = WM * WN * kWave;
+    constexpr int TM = BM / WM, TN = BN / WN, MB = TM / 16, NB = TN / 16;
+    constexpr int CA = BM * 8 / NT, CB = BN * 8 / NT;          // 16-byte chunks per thread and slab
+    constexpr int STAGE = (BM + BN) * 128;
+    static_assert(BM * 8 % NT == 0 && BN * 8 % NT == 0 && kPanel % BN == 0 && (!SWIGLU || TN % 64 == 0), "tile");
+    __shared__ __attribute__((aligned(16))) char lds[2 * STAGE];
+    const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
+    const int wm = wave / WN, wn = wave % WN, l16 = lane % 16, lq = lane / 16;
+    F32Tile t;
+    if (!locate_tile(a, BM, lane, t)) return;
+    const int K = a.K, KT = (K + kSlab - 1) / kSlab;
+
+    // ---- chunk c = tid + i NT of a slab: row c / 8, LDS slot c % 8 holds global chunk slot ^ swz(row)
+    // Pointers into the first slab; full slabs are a constant step apart, so a load costs one
+    // 64-bit add.  The rows of a narrower last slab (K % 32 columns) are as many floats wide.
+    const float *pa[CA], *pb[CB];
+    int a_row[CA], b_row[CB], a_kc[CA], b_kc[CB];
+#pragma unroll
+    for (int i = 0; i < CA; ++i) {
+        const int c = tid + i * NT, m = c / 8;
+        int r = t.row0 + m;
+        r = r < t.row_end ? r : t.row_end - 1;
+        a_row[i] = SWIGLU ? a.src_of[r] / a.topk : r;
+        a_kc[i] = 4 * ((c % 8) ^ f32_swz(m));
+        pa[i] = a.A + (size_t)a_row[i] * (SWIGLU ? a.ld : kSlab) + a_kc[i];
+    }
+    const int n0 = t.nt * BN, p = n0 / kPanel;
+    const int p_rows = a.Nb - p * kPanel < kPanel ? a.Nb - p * kPanel : kPanel;
+    const float *Bp = a.B + (size_t)t.e * a.Nb * K + (size_t)p * kPanel * K;     // this tile's panel
+#pragma unroll
+    for (int i = 0; i < CB; ++i) {
+        const int c = tid + i * NT, n = c / 8;
+        // (a row that does not exist: row 0 of the panel)
+        const int q = packed_of_logical<SWIGLU>(n0 + n, a.Nb) - p * kPanel;
+        b_row[i] = q > 0 ? q : 0;
+        b_kc[i] = 4 * ((c % 8) ^ f32_swz(n));
+        pb[i] = Bp + b_row[i] * kSlab + b_kc[i];
+    }
+    const size_t a_step = SWIGLU ? kSlab : (size_t)a.h_rows * kSlab, b_step = (size_t)p_rows * kSlab;
+    f32x4 ra[2][CA], rb[2][CB];
+    // (no branch around a load: after a join the compiler waits for every load in flight)
+    auto load = [&](int kt, f32x4 *ra, f32x4 *rb) {
+        kt = kt < KT ? kt : KT - 1;
+        const int w = RAG && K - kt * kSlab < kSlab ? K - kt * kSlab : kSlab;    // columns of the slab
+#pragma unroll
+        for (int i = 0; i < CA; ++i) {
+            const float *q = pa[i] + kt * a_step;
+            if constexpr (RAG) {
+                q -= SWIGLU ? 0 : a_row[i] * (kSlab - w);
+                q -= a_kc[i] < w ? 0 : a_kc[i];
+            }
+            ra[i] = *reinterpret_cast<const f32x4 *>(q);
+        }
+#pragma unroll
+        for (int i = 0; i < CB; ++i) {
+            const float *q = pb[i] + kt * b_step;
+            if constexpr (RAG) {
+                q -= b_row[i] * (kSlab - w);
+                q -= b_kc[i] < w ? 0 : b_kc[i];
+            }
+            rb[i] = *reinterpret_cast<const f32x4 *>(q);
+        }
+    };
+    auto store = [&](int kt, char *st, const f32x4 *ra, const f32x4 *rb) {
+        const int w = RAG ? K - kt * kSlab : kSlab;            // <= 0 past the last slab
+        const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int i = 0; i < CA; ++i)
+            *reinterpret_cast<f32x4 *>(st + (tid + i * NT) * 16) = !RAG || a_kc[i] < w ? ra[i] : zero;
+#pragma unroll
+        for (int i = 0; i < CB; ++i)
+            *reinterpret_cast<f32x4 *>(st + BM * 128 + (tid + i * NT) * 16) = !RAG || b_kc[i] < w ? rb[i] : zero;
+    };
+
+    f32x4 acc[NB][MB];
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+        for (int i = 0; i < MB; ++i) acc[j][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    int rd[2];
+#pragma unroll
+    for (int s = 0; s < 2; ++s) rd[s] = l16 * 128 + (((4 * s + lq) ^ f32_swz(l16)) << 4);
+    auto compute = [&](const char *st) {
+        const char *sa = st + wm * TM * 128, *sb = st + (BM + wn * TN) * 128;
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            f32x4 fa[MB], fb[NB];
+#pragma unroll
+            for (int i = 0; i < MB; ++i) fa[i] = *reinterpret_cast<const f32x4 *>(sa + i * 16 * 128 + rd[s]);
+#pragma unroll
+            for (int j = 0; j < NB; ++j) fb[j] = *reinterpret_cast<const f32x4 *>(sb + j * 16 * 128 + rd[s]);
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+#pragma unroll
+                for (int j = 0; j < NB; ++j)
+#pragma unroll
+                    for (int i = 0; i < MB; ++i)
+                        acc[j][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[j][v], fa[i][v], acc[j][i], 0, 0, 0);
+        }
+    };
+    // Slab kt is multiplied from LDS buffer kt % 2 while slabs kt + 1 and kt + 2 are on their
+    // way in registers.  A buffer is refilled after the barrier that follows its last reads.
+    load(0, ra[0], rb[0]);
+    load(1, ra[1], rb[1]);
+    store(0, lds, ra[0], rb[0]);
+    load(2, ra[0], rb[0]);
+    lds_barrier();
+    int kt = 0;
+    for (; kt + 1 < KT; kt += 2) {
+        store(kt + 1, lds + STAGE, ra[1], rb[1]);
+        load(kt + 3, ra[1], rb[1]);
+        compute(lds);
+        lds_barrier();                     // the loads stay in flight
+        store(kt + 2, lds, ra[0], rb[0]);  // (past the last slab: never read)
+        load(kt + 4, ra[0], rb[0]);
+        compute(lds + STAGE);
+        lds_barrier();
+    }
+    if (kt < KT) compute(lds);
+
+    // acc[j][i][v]: row wm TM + 16 i + l16, weight row wn TN + 16 j + 4 lq + v
+#pragma unroll
+    for (int i = 0; i < MB; ++i) {
+        const int row = t.row0 + wm * TM + 16 * i + l16;
+        if (row >= t.row_end) continue;
+        if constexpr (SWIGLU) {
+#pragma unroll
+            for (int j = 0; j < NB; ++j) {
+                if (j % 4 >= 2) continue;                        // blocks 0, 1 of four: W1; 2, 3: W3
+                const int c = (n0 + wn * TN) / 2 + 32 * (j / 4) + 16 * (j % 4) + 4 * lq;
+                if (c < a.Nc) store4<true>(a, row, c, swiglu4(acc[j][i], acc[j + 2][i]));
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < NB; ++j) {
+                const int c = n0 + wn * TN + 16 * j + 4 * lq;
+                if (c < a.Nc) store4<false>(a, row, c, acc[j][i]);
+            }
+        }
+    }
+}
+
+constexpr int kF32StreamWaves = 8;
+template <bool SWIGLU>
+__global__ __launch_bounds__(kF32StreamWaves *kWave) void k_ffn_f32_stream(F32Args a) {
+    __shared__ __attribute__((aligned(16))) float part[kF32StreamWaves][4][kWave][4];   // 32 KB
+    const int tid = threadIdx.x, lane = tid % kWave, l16 = lane % 16, lq = lane / 16;
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    F32Tile t;
+    if (!locate_tile(a, 16, lane, t)) return;
+    const int K = a.K, KT = (K + kSlab - 1) / kSlab;
+    int r = t.row0 + l16;
+    r = r < t.row_end ? r : t.row_end - 1;
+    const int a_row = SWIGLU ? a.src_of[r] / a.topk : r;
+    const int n0 = t.nt * 64, p = n0 / kPanel;
+    const int p_rows = a.Nb - p * kPanel < kPanel ? a.Nb - p * kPanel : kPanel;
+    const float *Bp = a.B + (size_t)t.e * a.Nb * K + (size_t)p * kPanel * K;
+    int b_row[4];
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+        const int q = packed_of_logical<SWIGLU>(n0 + 16 * b + l16, a.Nb) - p * kPanel;
+        b_row[b] = q > 0 ? q : 0;
+    }
+    struct Slab {
+        f32x4 a[2], b[4][2];
+    };
+    auto load = [&](int kt, Slab &s) {
+        kt = kt < KT ? kt : KT - 1;
+        const int w = K - kt * kSlab < kSlab ? K - kt * kSlab : kSlab;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int k = 16 * h + 4 * lq, kc = k < w ? k : 0;
+            const float *q = SWIGLU ? a.A + (size_t)a_row * a.ld + kt * kSlab + kc
+                                    : a.A + (size_t)kt * a.h_rows * kSlab + (size_t)a_row * w + kc;
+            s.a[h] = *reinterpret_cast<const f32x4 *>(q);
+#pragma unroll
+            for (int b = 0; b < 4; ++b)
+                s.b[b][h] = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(
+                    Bp + (size_t)kt * p_rows * kSlab + b_row[b] * w + kc));
+        }
+    };
+    f32x4 acc[4];
+#pragma unroll
+    for (int b = 0; b < 4; ++b) acc[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+    auto mul = [&](int kt, const Slab &s) {
+        const int w = K - kt * kSlab;                            // > 0 for a slab that exists
+        const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const bool in = 16 * h + 4 * lq < w;
+            const f32x4 fa = in ? s.a[h] : zero;
+#pragma unroll
+            for (int b = 0; b < 4; ++b) {
+                const f32x4 fb = in ? s.b[b][h] : zero;
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    acc[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[v], fa[v], acc[b], 0, 0, 0);
+            }
+        }
+    };
+    // slabs wave, wave + 8, ...; two in flight
+    Slab s0, s1;
+    load(wave, s0);
+    load(wave + kF32StreamWaves, s1);
+    for (int kt = wave; kt < KT; kt += 2 * kF32StreamWaves) {
+        mul(kt, s0);
+        load(kt + 2 * kF32StreamWaves, s0);
+        if (kt + kF32StreamWaves < KT) mul(kt + kF32StreamWaves, s1);
+        load(kt + 3 * kF32StreamWaves, s1);
+    }
+#pragma unroll
+    for (int b = 0; b < 4; ++b) *reinterpret_cast<f32x4 *>(part[wave][b][lane]) = acc[b];
+    __syncthreads();
+    // thread (block b, lane l): the four sums of that lane, in wave order
+    const int b = tid / kWave;
+    if (b >= (SWIGLU ? 2 : 4)) return;
+    auto sum = [&](int blk) {
+        f32x4 s = *reinterpret_cast<const f32x4 *>(part[0][blk][lane]);
+#pragma unroll
+        for (int w = 1; w < kF32StreamWaves; ++w) s += *reinterpret_cast<const f32x4 *>(part[w][blk][lane]);
+        return s;
+    };
+    const int row = t.row0 + l16;
+    const int c = (SWIGLU ? n0 / 2 : n0) + 16 * b + 4 * lq;
+    if (row >= t.row_end || c >= a.Nc) return;
+    if constexpr (SWIGLU) store4<true>(a, row, c, swiglu4(sum(b), sum(b + 2)));
+    else store4<false>(a, row, c, sum(b));
+}
+
+hipError_t launch_ffn_f32(const FfnArgs &f, int which, hipStream_t s) {
+    if (f.d.T == 0 || f.d.n_ffn == 0) return hipSuccess;
+    F32Args a;
+    a.offsets = f.offsets;
+    a.src_of = f.src_of;
+    a.n_ffn = f.d.n_ffn;
+    a.topk = f.d.k;
+    a.h_rows = f.h_rows;
+    a.ld = f.d.D;
+    if (which == 0) {
+        a.A = (const float *)f.x;
+        a.B = (const float *)f.w13;
+        a.C = (float *)f.h;
+        a.K = f.d.D;
+        a.Nb = 2 * f.d.F;
+        a.Nc = f.d.F;
+    } else {
+        a.A = (const float *)f.h;
+        a.B = (const float *)f.w2;
+        a.C = (float *)f.yffn;
+        a.K = f.d.F;
+        a.Nb = a.Nc = f.d.D;
+    }
+    const int logical = which == 0 ? (f.d.F + 31) / 32 * 64 : f.d.D;             // logical weight rows
+    const long long slots = (long long)f.d.T * f.d.k;
+    const long long groups = slots < f.d.n_ffn ? slots : f.d.n_ffn;              // experts with rows, at most
+    // workgroups for tiles of bm x bn: an upper bound of the device's list, in eighths
+    auto blocks = [&](int bm, int bn) {
+        a.Nt = (logical + bn - 1) / bn;
+        return ((slots / bm + groups) * a.Nt + 7) / 8 * 8;
+    };
+    auto go = [&](auto kernel, long long n, int threads) {
+        if (n > 0x7fffffffLL) return hipErrorInvalidConfiguration;
+        hipLaunchKernelGGL(kernel, dim3((unsigned)n), dim3(threads), 0, s, a);
+        return hipGetLastError();
+    };
+    const bool ragged = a.K % kSlab != 0;
+    auto tiles = [&](auto bm_c, auto bn_c, auto wm_c, auto wn_c) {
+        constexpr int BM = decltype(bm_c)::value, BN = decltype(bn_c)::value;
+        constexpr int WM = decltype(wm_c)::value, WN = decltype(wn_c)::value, NT = WM * WN * kWave;
+        const long long n = blocks(BM, BN);
+        if constexpr (BN / WN % 64 == 0) {
+            if (which == 0)
+                return ragged ? go(k_ffn_f32<true, true, BM, BN, WM, WN>, n, NT)
+                              : go(k_ffn_f32<true, false, BM, BN, WM, WN>, n, NT);
+        }
+        if (which == 0) return hipErrorInvalidValue;
+        return ragged ? go(k_ffn_f32<false, true, BM, BN, WM, WN>, n, NT)
+                      : go(k_ffn_f32<false, false, BM, BN, WM, WN>, n, NT);
+    };
+    typedef std::integral_constant<int, 1> c1;
+    typedef std::integral_constant<int, 2> c2;
+    typedef std::integral_constant<int, 32> c32;
+    typedef std::integral_constant<int, 64> c64;
+    typedef std::integral_constant<int, 128> c128;
+    // At most 16 slots per FFN expert: one block of 16 rows covers an expert's group, and
+    // the weights are what there is to move.
+    if (slots <= 16ll * f.d.n_ffn) {
+        const long long n = blocks(16, 64);
+        return which == 0 ? go(k_ffn_f32_stream<true>, n, kF32StreamWaves * kWave)
+                          : go(k_ffn_f32_stream<false>, n, kF32StreamWaves * kWave);
+    }
+    // The largest tile that still gives every CU several workgroups: the last, partly filled
+    // round costs more than the larger tile saves.  2731 rows, D = 768, F = 2048, 8 experts:
+    // GEMM1 (1504 tiles of 64 x 128) 153 us, with 32 x 64 tiles 174, with 128 x 128 199;
+    // GEMM2 (1100 tiles of 32 x 64) 92, with 32 x 32 tiles 89, with 64 x 64 101, 64 x 128 132.
+    if (blocks(64, 128) >= 1024) return tiles(c64{}, c128{}, c2{}, c2{});
+    if (which == 0) return tiles(c32{}, c64{}, c2{}, c1{});
+    return blocks(32, 64) >= 2048 ? tiles(c32{}, c64{}, c2{}, c2{}) : tiles(c32{}, c32{}, c2{}, c2{});
+}
+
+}  // namespace moepp

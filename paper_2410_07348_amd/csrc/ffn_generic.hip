@@ -1,8 +1,8 @@
 // Grouped SwiGLU FFN for any supported shape and activation type, plain fp32
 // FMA: one thread per output element.  FFN_e(x) = W2_e (silu(W1_e x) * (W3_e x))
 // for the rows of every FFN expert e (the FFN experts of paper Eq.2).  This is
-// the path of the float32 layers and the fallback for shapes the MFMA kernels
-// do not cover.
+// the fallback for bf16 shapes the MFMA kernels do not cover, and what variant 1
+// runs for every shape and type.
 #include "common.h"
 
 namespace moepp {
@@ -12,8 +12,6 @@ __device__ inline int expert_of_row(const int32_t *offsets, int n_ffn, int r) {
     while (e + 1 < n_ffn && r >= offsets[e + 1]) ++e;
     return e;
 }
-
-__device__ inline float silu_f(float z) { return z / (1.f + expf(-z)); }
 
 // h[r,f] = silu(W1_e[f,:] x_r) * (W3_e[f,:] x_r), x_r = x[src_of[r] / k]
 template <typename AT>

@@ -1,0 +1,31 @@
+"""FFN kernels at the edges of their tiles and dispatch rules, every case against the oracle
+on all tokens with the tolerances of tests/helpers.py: widths that leave a narrower last K
+slab (D % 32, F % 32), fewer rows than a tile, groups that end inside one, token counts on
+both sides of a rule."""
+import pytest
+
+from workloads import LayerShape, make_inputs
+
+from helpers import check_layer, gpu_forward
+
+pytestmark = pytest.mark.gpu
+
+
+def check(**kw):
+    s = LayerShape("edge", n_zero=1, n_copy=1, n_const=2, seed=8100, **kw)
+    print("shape", s, flush=True)
+    inp = make_inputs(s)
+    print("  ", check_layer(s, inp, gpu_forward(s, inp)), flush=True)
+
+
+# 4 experts, top-2: weight streaming up to T = 32, above it tiles of 32 x 64 (GEMM1) and
+# 32 x 32 (GEMM2); 64 x 128 tiles from 1024 of them on
+@pytest.mark.parametrize("D,F", [(8, 8), (24, 40), (64, 32), (104, 72), (264, 1000), (768, 512)])
+@pytest.mark.parametrize("T", [1, 2, 31, 32, 33, 257])
+def test_f32(T, D, F):
+    check(T=T, D=D, F=F, n_ffn=4, act="f32")
+
+
+@pytest.mark.parametrize("T,D,F", [(4096, 520, 1032), (2500, 2048, 256), (2500, 96, 2080)])
+def test_f32_large_tiles(T, D, F):
+    check(T=T, D=D, F=F, n_ffn=4, act="f32", k=3)
