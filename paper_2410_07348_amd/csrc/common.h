@@ -71,6 +71,22 @@ __host__ __device__ inline size_t panel_row(int n, int s, int N, int K) {
     return (size_t)p * kPanel * K + slab_row(n - p * kPanel, s, rows, K);
 }
 
+// Logical row L of the packed W1/W3 matrix (SWIGLU) or of W2, as the tiled kernels
+// number them: for W1/W3 blocks of 64, 32 rows of W1 and the same 32 of W3, also where
+// the last block has fewer, so that silu's argument and its multiplier always sit
+// 32 rows apart.  Returns the packed row; a row that does not exist gives row 0 (its
+// output columns are never stored).
+template <bool SWIGLU>
+__device__ inline int packed_of_logical(int L, int Nb) {
+    if constexpr (SWIGLU) {
+        const int b = L / (2 * kPackBlk), up = L % (2 * kPackBlk) / kPackBlk, r = L % kPackBlk;
+        const int rem = Nb / 2 - kPackBlk * b, bs = rem < kPackBlk ? rem : kPackBlk;
+        return r < bs ? 2 * kPackBlk * b + up * bs + r : 0;
+    } else {
+        return L < Nb ? L : 0;
+    }
+}
+
 struct Dims {
     int T, D, F;
     int n_ffn, n_zero, n_copy, n_const, N;

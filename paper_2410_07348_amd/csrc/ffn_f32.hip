@@ -48,21 +48,6 @@ struct F32Args {
     int Nt;                  // column tiles of the kernel per expert
 };
 
-// Logical weight row L of a matrix: for GEMM1 blocks of 64, 32 rows of W1 and the
-// same 32 of W3 (also where the last block has fewer, so that silu's argument and
-// its multiplier always sit 32 rows apart).  Returns the packed row; a row that
-// does not exist gives row 0 (its output columns are never stored).
-template <bool SWIGLU>
-__device__ inline int packed_of_logical(int L, int Nb) {
-    if constexpr (SWIGLU) {
-        const int b = L / 64, up = (L % 64) / 32, r = L % 32;
-        const int F = Nb / 2, rem = F - 32 * b, bs = rem < 32 ? rem : 32;
-        return r < bs ? 64 * b + up * bs + r : 0;
-    } else {
-        return L < Nb ? L : 0;
-    }
-}
-
 // Tile `u` of the list (expert, block of BM rows, column tile) with the row
 // blocks of an expert fastest; false past the end.  Every lane takes part.
 struct F32Tile {

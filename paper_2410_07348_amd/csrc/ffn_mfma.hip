@@ -136,7 +136,13 @@ __device__ inline void wait_and_barrier() {
 
 // TAIL: this launch computes what the main launch (tiles of 2 BM rows) left
 // over, as half tiles of BM rows; the tiles are numbered as in the main launch.
-template <class G, bool SWIGLU, bool TAIL = false>
+// RAG: widths that are not multiples of 64.  The last K slab may be narrower than 32
+// columns and the K loop is padded to an even number of at least 4 K tiles: 16-byte
+// pieces past the last column come from a page of zeros, for both operands.  A last
+// block of fewer than 32 rows of W1 and of W3 is read as if each had 32.
+__device__ __align__(16) const unsigned char zero_page[16] = {};
+
+template <class G, bool SWIGLU, bool TAIL = false, bool RAG = false>
 __global__ __launch_bounds__(G::NT, 1) void k_grouped_gemm(GemmArgs a) {
     constexpr int EBM = TAIL ? 2 * G::BM : G::BM;      // tile height of the numbering
     constexpr int BM = G::BM, BN = G::BN, WN = G::WN, NT = G::NT, NL = G::NL, RB = G::RB, CPR = G::CPR;
@@ -258,6 +264,12 @@ __global__ __launch_bounds__(G::NT, 1) void k_grouped_gemm(GemmArgs a) {
     const int kc = slot ^ G::swz(r_thr);         // global chunk within the K tile
     const bf16_t *pa[CA];
     const bf16_t *pb[CB];
+    static_assert(!RAG || (BK == kSlab && G::MI == 16), "ragged widths: one slab per K tile");
+    const bf16_t *const zeros = reinterpret_cast<const bf16_t *>(zero_page);
+    const int KF = a.K / kSlab, KW = a.K % kSlab;          // RAG: full slabs, columns of the last one
+    const bf16_t *la[RAG ? CA : 1], *lb[RAG ? CB : 1];    // RAG: pieces of slab KF
+    // elements of A from one K tile to the next
+    const size_t a_kstep = SWIGLU ? (size_t)BK : (size_t)(BK / kSlab) * a.h_rows * kSlab;
     size_t b_kstep = 0;                          // elements of B from one K tile to the next
     static_assert(BN == kPanel, "one tile of B rows is one panel of the packed weights");
     // rows of A (of x through src_of for GEMM1, of h for GEMM2) this thread loads for a tile
@@ -278,6 +290,23 @@ __global__ __launch_bounds__(G::NT, 1) void k_grouped_gemm(GemmArgs a) {
         }
         const bf16_t *Be = a.B + (size_t)t_e * a.Nb * a.K;
         const int n0 = t_nt * BN;
+        if constexpr (RAG) {
+            const int rows = a.Nb - n0 < BN ? a.Nb - n0 : BN;
+            b_kstep = (size_t)rows * kSlab;
+            const bool in = kc * 8 < KW;
+#pragma unroll
+            for (int i = 0; i < CA; ++i)
+                la[i] = !in ? zeros : pa[i] + KF * a_kstep - (SWIGLU ? 0 : (size_t)src[i] * (kSlab - KW));
+#pragma unroll
+            for (int i = 0; i < CB; ++i) {
+                // (a row that does not exist: row 0 of the panel, its columns are never stored)
+                const int q = packed_of_logical<SWIGLU>(n0 + r_thr + i * (NL / CPR), a.Nb) - n0;
+                const int n = q > 0 ? q : 0;
+                pb[i] = Be + (size_t)n0 * a.K + n * kSlab + kc * 8;
+                lb[i] = !in ? zeros : pb[i] + KF * b_kstep - n * (kSlab - KW);
+            }
+            return;
+        }
 #pragma unroll
         for (int i = 0; i < CB; ++i) {
             int n = n0 + r_thr + i * (NL / CPR);
@@ -289,14 +318,18 @@ __global__ __launch_bounds__(G::NT, 1) void k_grouped_gemm(GemmArgs a) {
     };
     const int wave_off = __builtin_amdgcn_readfirstlane(wave) * 1024;   // this wave's 1 KB of each load group
 
-    const int KT = a.K / BK;
-    // elements of A from one K tile to the next
-    const size_t a_kstep = SWIGLU ? (size_t)BK : (size_t)(BK / kSlab) * a.h_rows * kSlab;
+    const int KT = !RAG ? a.K / BK : a.K <= 2 * kSlab ? 4 : (a.K + 2 * kSlab - 1) / (2 * kSlab) * 2;
     // Load q of the LPT = CA + CB wave-wide loads that make up a tile.
     auto issue_one = [&](int q, int kt, char *__restrict__ stage) {
         char *sa = stage + wave_off;
         char *sb = sa + BM * RB;
-        if (q < CA)
+        if constexpr (RAG) {
+            const bf16_t *p = kt < KF ? (q < CA ? pa[q < CA ? q : 0] + kt * a_kstep : pb[q < CA ? 0 : q - CA] + kt * b_kstep)
+                              : kt == KF ? (q < CA ? la[q < CA ? q : 0] : lb[q < CA ? 0 : q - CA])
+                                         : zeros;
+            char *dst = q < CA ? sa + q * (NL / CPR) * RB : sb + (q - CA) * (NL / CPR) * RB;
+            __builtin_amdgcn_global_load_lds((gptr_t)p, (lptr_t)dst, 16, 0, 0);
+        } else if (q < CA)
             __builtin_amdgcn_global_load_lds((gptr_t)(pa[q] + kt * a_kstep),
                                              (lptr_t)(sa + q * (NL / CPR) * RB), 16, 0, 0);
         else
@@ -348,12 +381,6 @@ __global__ __launch_bounds__(G::NT, 1) void k_grouped_gemm(GemmArgs a) {
     auto mfma16 = [&](bf16x8 b, bf16x8 a_, auto &c) {
         if constexpr (MI == 16) c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b, a_, c, 0, 0, 0);
     };
-    auto mfma_step = [&](const bf16x8 *fa, const bf16x8 *fb) {
-#pragma unroll
-        for (int j = 0; j < NB; ++j)
-#pragma unroll
-            for (int i = 0; i < MB; ++i) mfma32(fb[j], fa[i], acc[j][i]);
-    };
     // One K step with its memory operations spread evenly between the MFMAs:
     // first the operand reads of the NEXT step (from `st`, step `ks_rd`, into
     // fa_n/fb_n), then N_LOAD of the loads of tile kt_issue.  A wave issues in
@@ -399,7 +426,8 @@ __global__ __launch_bounds__(G::NT, 1) void k_grouped_gemm(GemmArgs a) {
     // the loads).  Expects K tiles 0 .. NS-2 of the tile to be in flight.
     auto main_loop = [&](auto loader_c) {
         constexpr bool LOADER = decltype(loader_c)::value;
-        if constexpr (NS >= 3) {
+        {
+            static_assert(NS >= 3, "a ring");
             // Ring of NS stages, tile kt in stage (S0 + kt) % NS.  The workgroup
             // barrier sits before the LAST MFMA step of a tile, not after it:
             // once every wave has issued (and received) all operand reads of
@@ -467,36 +495,6 @@ __global__ __launch_bounds__(G::NT, 1) void k_grouped_gemm(GemmArgs a) {
             tail(std::integral_constant<int, 2>{});
             tail(std::integral_constant<int, 3>{});
             static_assert(NS <= 5, "tail unrolling covers NS - 1 <= 4 tiles");
-        } else {
-            static_assert(G::LW == G::WM * WN && !G::PERSIST, "the two-stage path loads with every wave");
-            // Two stages: refill the stage that was computed last with the next
-            // tile, then run the MFMAs of this one.  `rd` and `wr` never overlap
-            // (restrict), so the operand reads are not made to wait on those loads.
-            auto k_tile = [&](const char *__restrict__ rd, char *__restrict__ wr, int kt_issue, bool issue) {
-                if (issue) issue_tile(kt_issue, wr);
-#pragma unroll
-                for (int ks = 0; ks < KS; ++ks) {
-                    bf16x8 fa[MB], fb[NB];
-                    read_frags(rd, ks, fa, fb);
-                    mfma_step(fa, fb);
-                }
-            };
-            int st_rd = 0, st_wr = NS - 1;      // ring positions: tile kt lives in stage kt % NS
-            for (int kt = 0; kt < KT; ++kt) {
-                // Tile kt has landed when the loads of the younger tiles are the
-                // only ones outstanding.  The wait, the barrier and the compiler
-                // fence are one asm block so that nothing else makes this wave wait
-                // for the younger loads (a fence builtin would: those loads are LDS
-                // writes too).  lgkmcnt(0): this wave's operand reads of the
-                // previous tile are complete before any wave refills that stage.
-                if (kt + NS - 2 < KT)
-                    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((NS - 2) * LPT) : "memory");
-                else
-                    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-                k_tile(lds + st_rd * STAGE, lds + st_wr * STAGE, kt + NS - 1, kt + NS - 1 < KT);
-                st_rd = st_rd + 1 == NS ? 0 : st_rd + 1;
-                st_wr = st_wr + 1 == NS ? 0 : st_wr + 1;
-            }
         }
     };
 
@@ -752,9 +750,10 @@ __global__ __launch_bounds__(G::NT, 1) void k_grouped_gemm(GemmArgs a) {
                 for (int c = tid; c < HB * OCPR; c += NT) {
                     const int sl = c / (HB * 4), m = (c / 4) % HB, q = c % 4;
                     const int row = row0 + ep * HB + m, col = c_col0 + sl * kSlab + q * 8;
+                    const int w = RAG ? slab_width(col / kSlab, a.Nc) : kSlab;
                     if (row < row_end && col < a.Nc)
                         *reinterpret_cast<bf16x8 *>(a.C + (size_t)(col / kSlab) * a.h_rows * kSlab +
-                                                    (size_t)row * kSlab + q * 8) =
+                                                    (size_t)row * w + q * 8) =
                             *reinterpret_cast<const bf16x8 *>(patch + m * OUT_STRIDE + (sl * 4 + q) * 16);
                 }
             } else {
@@ -834,7 +833,7 @@ bool ffn_mfma_supported(const Dims &d) { return d.D % 64 == 0 && d.F % 64 == 0; 
 
 // TAILG: geometry (half the tile height of G) of a second launch that takes
 // over a sparsely filled last round of G's tiles; void: none.
-template <class G, class TAILG = void>
+template <class G, class TAILG = void, bool RAG = false>
 static hipError_t launch_cfg(const FfnArgs &f, int which, hipStream_t s) {
     GemmArgs a;
     a.offsets = f.offsets;
@@ -860,13 +859,14 @@ static hipError_t launch_cfg(const FfnArgs &f, int which, hipStream_t s) {
         a.Nc = f.d.D;
     }
     constexpr int BM = G::BM, BN = G::BN;
-    a.n_ntiles = (a.Nb + BN - 1) / BN;
+    const int logical = which == 0 ? (f.d.F + 31) / 32 * 64 : f.d.D;    // rows of B, blocks of W1 and W3 whole
+    a.n_ntiles = (logical + BN - 1) / BN;
     const long long rows = (long long)f.d.T * f.d.k;
     const long long max_mtiles = (rows + BM - 1) / BM + f.d.n_ffn;   // upper bound of sum ceil(count_e/BM)
     const long long rnd = 8 * 8 * 4;   // whole rounds of one patch (GM x GN tiles) per XCD
     long long blocks = (max_mtiles * a.n_ntiles + rnd - 1) / rnd * rnd;
     if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
-    if (a.K / G::BK < G::NS - 1) return hipErrorInvalidConfiguration;   // the ring starts with NS-1 K tiles in flight
+    if (!RAG && a.K / G::BK < G::NS - 1) return hipErrorInvalidConfiguration;   // the ring starts with NS-1 K tiles in flight
     a.jstride = 0;
     if (G::PERSIST) {
         // one workgroup per CU (the LDS ring fills a CU), a multiple of 8 so that
@@ -897,9 +897,9 @@ static hipError_t launch_cfg(const FfnArgs &f, int which, hipStream_t s) {
         if (tail) a.cut_grid = (int)blocks;
     }
     if (which == 0)
-        hipLaunchKernelGGL((k_grouped_gemm<G, true>), grid, block, 0, s, a);
+        hipLaunchKernelGGL((k_grouped_gemm<G, true, false, RAG>), grid, block, 0, s, a);
     else
-        hipLaunchKernelGGL((k_grouped_gemm<G, false>), grid, block, 0, s, a);
+        hipLaunchKernelGGL((k_grouped_gemm<G, false, false, RAG>), grid, block, 0, s, a);
     if constexpr (!std::is_void<TAILG>::value) if (tail) {
         // same grid and numbering; a workgroup finds at most one half tile, none
         // when the main launch kept its last round
@@ -918,8 +918,10 @@ hipError_t launch_ffn_mfma(const FfnArgs &f, int which, hipStream_t s) {
     // of 5 (the whole 160 KB of LDS), which needs at least 4 K tiles; shorter
     // reductions use two 64-deep stages.
     const int K = which == 0 ? f.d.D : f.d.F;
-    if (K / 32 < 4)                       // too few K tiles to fill a ring of stages
-        return launch_cfg<Geo<256, 256, 2, 4, 64, 2>>(f, which, s);
+    // Widths that are not multiples of 64, and reductions too short for the ring's four
+    // K tiles: the same kernel with the K loop padded by zeros.
+    if (f.d.D % 64 != 0 || f.d.F % 64 != 0 || K < 128)
+        return launch_cfg<Geo<128, 256, 2, 4, 32, 5, 4, true, 16>, void, true>(f, which, s);
     // Few rows per expert (decoding, small batches): the GEMMs only stream
     // the weights, so use 128-row tiles: half of the (mostly wasted)
     // matrix work of a 256-row tile per byte of weights, bound by HBM instead.

@@ -301,15 +301,16 @@ moepp_status do_ffn(moepp_ctx *c, hipStream_t s, int T, const void *x, const voi
     // a handful of rows per expert: the kernels that only stream the weights
     // (variant 3 keeps the tiled kernels, so that tests can compare the two)
     const bool decode = mfma && c->variant != 3 && ffn_decode_supported(a.d);
-    // float32 layers: every shape has a matrix-core kernel (variant 1 keeps the plain FMA kernels)
-    const bool f32 = !bf && c->variant == 0;
+    // On the automatic variant every shape has a matrix-core kernel, also the float32 layers and
+    // the bf16 widths that variants 2 and 3 refuse (variant 1 keeps the plain FMA kernels).
+    const bool f32 = !bf && c->variant == 0, tiled = mfma || (bf && c->variant == 0);
     hipError_t e = hipSuccess;
     for (int which = 0; which < 2 && e == hipSuccess; ++which) {
         KernelTimer kt(c, s, which == 0 ? MOEPP_K_GEMM1 : MOEPP_K_GEMM2);
         e = decode ? launch_ffn_decode(a, which, s)
-            : mfma ? launch_ffn_mfma(a, which, s)
-            : f32  ? launch_ffn_f32(a, which, s)
-                   : launch_ffn_generic(a, bf, which, s);
+            : tiled ? launch_ffn_mfma(a, which, s)
+            : f32   ? launch_ffn_f32(a, which, s)
+                    : launch_ffn_generic(a, bf, which, s);
     }
     return e == hipSuccess ? MOEPP_OK : MOEPP_EHIP;
 }

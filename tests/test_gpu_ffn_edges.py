@@ -29,3 +29,16 @@ def test_f32(T, D, F):
 @pytest.mark.parametrize("T,D,F", [(4096, 520, 1032), (2500, 2048, 256), (2500, 96, 2080)])
 def test_f32_large_tiles(T, D, F):
     check(T=T, D=D, F=F, n_ffn=4, act="f32", k=3)
+
+
+# bf16 widths that are not multiples of 64 (zero-padded K loop), also with fewer than the
+# four K tiles the ring starts with, and reductions of 64 (variants 0 and 2)
+@pytest.mark.parametrize("D,F", [(8, 8), (24, 40), (72, 136), (128, 96), (104, 64), (520, 1032), (1000, 1416)])
+@pytest.mark.parametrize("T", [1, 33, 127, 300])
+def test_bf16_ragged_widths(T, D, F):
+    check(T=T, D=D, F=F, n_ffn=4)
+
+
+@pytest.mark.parametrize("D,F", [(64, 128), (128, 64), (64, 64)])
+def test_bf16_short_reduction(D, F):
+    check(T=900, D=D, F=F, n_ffn=4, k=3)
