@@ -324,9 +324,13 @@ __global__ __launch_bounds__(G::NT, 1) void k_grouped_gemm(GemmArgs a) {
         char *sa = stage + wave_off;
         char *sb = sa + BM * RB;
         if constexpr (RAG) {
-            const bf16_t *p = kt < KF ? (q < CA ? pa[q < CA ? q : 0] + kt * a_kstep : pb[q < CA ? 0 : q - CA] + kt * b_kstep)
-                              : kt == KF ? (q < CA ? la[q < CA ? q : 0] : lb[q < CA ? 0 : q - CA])
-                                         : zeros;
+            // (all three addresses first, then selects: a branch around a direct-to-LDS load
+            // would make the compiler wait for every load in flight)
+            const bool is_a = q < CA;
+            const bf16_t *p = is_a ? pa[is_a ? q : 0] + kt * a_kstep : pb[is_a ? 0 : q - CA] + kt * b_kstep;
+            const bf16_t *l = is_a ? la[is_a ? q : 0] : lb[is_a ? 0 : q - CA];
+            l = kt == KF ? l : zeros;
+            p = kt < KF ? p : l;
             char *dst = q < CA ? sa + q * (NL / CPR) * RB : sb + (q - CA) * (NL / CPR) * RB;
             __builtin_amdgcn_global_load_lds((gptr_t)p, (lptr_t)dst, 16, 0, 0);
         } else if (q < CA)
