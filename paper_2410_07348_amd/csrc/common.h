@@ -129,6 +129,7 @@ struct RouterArgs {
     float *topk_w;
     float *alpha1;
     int32_t *chunk_hist;  // MFMA router: [workgroup][N] selections per expert, or null
+    float *partial;       // router_small_bytes() of scratch for partial dot products
     double *bal_partial;  // MFMA router: [workgroup][kMaxExperts] sums of Softmax(G(x))_i over the
                           // workgroup's tokens (for P_i of Eq.7), or null
 };
@@ -157,13 +158,22 @@ struct CombineArgs {
 // Launchers (each returns hipGetLastError() after its launches).
 // `bf16` selects the activation type; `which` selects GEMM1 / GEMM2.
 hipError_t launch_router_generic(const RouterArgs &a, bool bf16, hipStream_t s);
-// T <= kRouterSmallT only; partial: router_small_bytes() of scratch.  With perm_ws
-// (T <= kRouterFusedT only) the second kernel also does the permutation of the
-// call's T*k slots (counts, kept, offsets, row_of, src_of of *perm_ws, capacities
-// *perm_cap), as launch_perm_small would.
-hipError_t launch_router_small(const RouterArgs &a, bool bf16, float *partial, hipStream_t s,
-                               const Workspace *perm_ws = nullptr, const CapArgs *perm_cap = nullptr);
+// T <= kRouterSmallT only.  With perm_ws (T <= kRouterFusedT only) the second kernel also
+// does the permutation of the call's T*k slots (counts, kept, offsets, row_of, src_of of
+// *perm_ws, capacities *perm_cap), as launch_perm_small would.
+hipError_t launch_router_small(const RouterArgs &a, bool bf16, hipStream_t s, const Workspace *perm_ws = nullptr,
+                               const CapArgs *perm_cap = nullptr);
+// More tokens, any width and type, while router_split_max(d) >= 1; leaves the histogram of
+// the permutation (chunks of kRouterSlicedTok tokens) and the statistics' sums like the
+// matrix-core router.
+constexpr int kRouterSlicedTok = 64;
+hipError_t launch_router_sliced(const RouterArgs &a, bool bf16, hipStream_t s);
 size_t router_small_bytes();
+// Slices of D whose partial dot products [slice][T][N + 2 n_const] fit RouterArgs::partial, at most
+// kRouterSplits; and the kernel that adds them up and finishes (residual, softmax, Top-K, histogram)
+constexpr int kRouterSplits = 32;
+int router_split_max(const Dims &d);
+hipError_t launch_router_final(const RouterArgs &a, int splits, hipStream_t s);
 bool router_mfma_supported(const Dims &d);
 hipError_t launch_router_mfma(const RouterArgs &a, hipStream_t s);
 int router_mfma_block_tokens(const Dims &d);

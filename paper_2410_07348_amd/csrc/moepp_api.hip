@@ -185,6 +185,7 @@ moepp_status do_route(moepp_ctx *c, hipStream_t s, int T, const void *x, const f
     a.alpha1 = c->ws.alpha1;
     a.chunk_hist = nullptr;
     a.bal_partial = nullptr;
+    a.partial = c->ws.router_partial;
     moepp_status st = MOEPP_OK;
     const bool mfma = use_mfma_router(c, a.d, &st);
     if (st != MOEPP_OK) return st;
@@ -198,32 +199,31 @@ moepp_status do_route(moepp_ctx *c, hipStream_t s, int T, const void *x, const f
     KernelTimer kt(c, s, MOEPP_K_ROUTER);
     const bool bf16 = c->desc.act == MOEPP_BF16;
     hipError_t e;
+    const bool sliced = !mfma && c->variant == 0 && router_split_max(a.d) >= 1;
     if (c->variant == 0 && T <= kRouterFusedT) {
         // a handful of tokens: the router's second kernel also groups the slots by expert
-        e = launch_router_small(a, bf16, c->ws.router_partial, s, &c->ws, &c->cap);
+        e = launch_router_small(a, bf16, s, &c->ws, &c->cap);
         c->perm_valid = e == hipSuccess;
         c->perm_T = T;
         c->perm_k = k;
     } else if (c->variant == 0 && T <= kRouterSmallT) {
-        e = launch_router_small(a, bf16, c->ws.router_partial, s);
-    } else if (mfma) {
-        // the permutation of a call with few slots runs in one workgroup and counts for itself
-        if ((long long)T * k > kPermSmallSlots) {
-            a.chunk_hist = c->ws.chunk_hist;
-            c->hist_valid = true;
-            c->hist_T = T;
-            c->hist_k = k;
-            c->hist_chunk_slots = router_mfma_block_tokens(a.d) * k;
-        }
-        // with the load-balance statistics on, the kernel also adds up the softmax of its tokens
-        const int tok = router_mfma_block_tokens(a.d);
+        e = launch_router_small(a, bf16, s);
+    } else if (mfma || sliced) {
+        // the router counts its selections, per block of tokens, for the permutation
+        const int tok = mfma ? router_mfma_block_tokens(a.d) : kRouterSlicedTok;
+        a.chunk_hist = c->ws.chunk_hist;
+        c->hist_valid = true;
+        c->hist_T = T;
+        c->hist_k = k;
+        c->hist_chunk_slots = tok * k;
+        // with the load-balance statistics on, it also adds up the softmax of its tokens
         const int wgs = (T + tok - 1) / tok;
         if (c->bal_tau > 0.0 && wgs <= kBalWaves) {
             a.bal_partial = c->ws.bal_partial;
             c->bal_rows = wgs;
             c->bal_T = T;
         }
-        e = launch_router_mfma(a, s);
+        e = mfma ? launch_router_mfma(a, s) : launch_router_sliced(a, bf16, s);
     } else {
         e = launch_router_generic(a, bf16, s);
     }
@@ -235,7 +235,9 @@ moepp_status do_permute(moepp_ctx *c, hipStream_t s, int T, int k) {
     c->last_T = T;
     c->last_k = k;
     hipError_t e = hipSuccess;
-    if (T > 0 && T * k <= kPermSmallSlots) {
+    // chunks: the router's workgroups when it has counted this call's selections
+    const bool counted = c->hist_valid && c->hist_T == T && c->hist_k == k;
+    if (T > 0 && T * k <= kPermSmallSlots && !counted) {
         // (nothing to do when the router kernel of this very call has done it; the
         // capacities it used are still the current ones, see moepp_set_capacity)
         if (!(c->perm_valid && c->perm_T == T && c->perm_k == k)) {
@@ -250,8 +252,6 @@ moepp_status do_permute(moepp_ctx *c, hipStream_t s, int T, int k) {
         }
         return e == hipSuccess ? MOEPP_OK : MOEPP_EHIP;
     }
-    // chunks: the router's workgroups when it has counted this call's selections
-    const bool counted = c->hist_valid && c->hist_T == T && c->hist_k == k;
     const int chunk_slots = counted ? c->hist_chunk_slots : kPermChunk;
     c->hist_valid = false;
     if (!counted) {

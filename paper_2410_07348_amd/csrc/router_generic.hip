@@ -1,6 +1,6 @@
-// Router for any supported shape and activation type, plain fp32 FMA.
+// Routers for any supported shape and activation type, plain fp32 FMA.
 //
-// One wavefront per token computes, in one pass over x:
+// k_router_generic: one wavefront per token computes, in one pass over x:
 //   G(x) = W x (+ W_g G(x_prev)) (+ bias)            (paper Eq.2 / Eq.6)
 //   Softmax over all N experts and Top-K of G(x)     (Eq.1)
 //   a1 of every constant expert, Softmax(W_c x)_1    (Eq.5)
@@ -113,11 +113,14 @@ __global__ __launch_bounds__(kRouterWaves *kWave) void k_router_generic(RouterAr
 // load rate.  Here the reduction over D is cut into up to kRsSplits slices:
 // workgroup (slice, token block) writes the partial dot products of its slice,
 // and a second kernel adds the slices of a token in slice order (the result is
-// the same on every run) and finishes as above.
+// the same on every run) and finishes as above.  The float32 layers, and the bf16
+// widths that the matrix-core router does not take, run the same way with more tokens:
+// one wave per token reads every router weight once per token (22 us at T = 2048,
+// D = 768, 24 rows; sliced 12.9).
 constexpr int kRsTok = 64;      // tokens per workgroup
 constexpr int kRsBK = 64;       // K elements per LDS tile
 constexpr int kRsStr = kRsBK + 4;   // floats per LDS tile row: 16-byte reads of 16 consecutive rows cover all banks
-constexpr int kRsSplits = 32;   // slices at most
+constexpr int kRsSplits = kRouterSplits;   // slices at most
 
 // RPT: weight rows per thread; the four waves share 4 RPT >= N + 2 n_const rows
 // (rows past the last are zero in LDS, so the inner loop has no conditions).
@@ -263,46 +266,122 @@ __global__ __launch_bounds__(kPermSmallWaves *kWave) void k_router_small_final_p
         // compute on the last token and store nothing
         const int tok = tid >> 2;
         const int tk = tok < T ? tok : T - 1;
-        router_token_quad(a, (size_t)tk, tok < T, tid & 3, dots + tk * DSTR, nullptr, s_idx + tk * K);
+        router_token_quad<kMaxExperts / 4>(a, (size_t)tk, tok < T, tid & 3, dots + tk * DSTR, nullptr, s_idx + tk * K);
     }
     __syncthreads();
     perm_small_body(a.d, w, cap, s_idx, s_rank, s_first, s_limit);
+}
+
+// The second kernel of a router that has split D, for blocks of 64 tokens: the slices of
+// every dot product are added in slice order, then as in the one-kernel router.
+constexpr int kRouterFinalTok = kRouterSlicedTok, kRouterFinalThreads = 512;
+template <int ROWS>
+__global__ __launch_bounds__(kRouterFinalThreads) void k_router_final(RouterArgs a, int splits) {
+    constexpr int TOK = kRouterFinalTok, NT = kRouterFinalThreads;
+    constexpr int MAXN = ROWS < kMaxExperts ? ROWS : kMaxExperts, DSTR = ROWS + 1;
+    __shared__ __attribute__((aligned(16))) float prevs[TOK * (MAXN + 4)];
+    __shared__ __attribute__((aligned(16))) float wres[MAXN * (MAXN + 4)];
+    __shared__ float dots[TOK * DSTR];
+    __shared__ float sbias[MAXN];
+    __shared__ int s_hist[MAXN];
+    const int tid = threadIdx.x, t0 = blockIdx.x * TOK;
+    const int T = a.d.T, N = a.d.N, rows = N + 2 * a.d.n_const;
+    const int n_tok = min(TOK, T - t0), rs = residual_stride(N);
+    const float *part = a.partial + (size_t)t0 * rows;
+    for (int c = tid; c < n_tok * rows; c += NT) {
+        float sum = 0.f;
+        for (int s0 = 0; s0 < splits; s0 += 8) {           // eight loads in flight
+            float v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = s0 + u < splits ? part[(size_t)(s0 + u) * T * rows + c] : 0.f;
+#pragma unroll
+            for (int u = 0; u < 8; ++u) sum += v[u];
+        }
+        dots[(c / rows) * DSTR + c % rows] = sum;
+    }
+    if (a.prev_gate) {
+        for (int c = tid; c < n_tok * N; c += NT) prevs[(c / N) * rs + c % N] = a.prev_gate[(size_t)t0 * N + c];
+        for (int c = tid; c < N * N; c += NT) wres[(c / N) * rs + c % N] = a.W_res[c];
+        zero_residual_pad(prevs, n_tok, N, NT);
+        zero_residual_pad(wres, N, N, NT);
+    }
+    if (tid < N) {
+        sbias[tid] = a.bias ? a.bias[tid] : 0.f;
+        s_hist[tid] = 0;
+    }
+    __syncthreads();
+    router_finish<TOK, NT, ROWS, 1>(a, t0, dots, prevs, wres, sbias, s_hist);
+}
+
+int router_split_max(const Dims &d) {
+    const size_t slice = (size_t)d.T * (d.N + 2 * d.n_const) * sizeof(float);
+    const size_t n = router_small_bytes() / slice;
+    return (int)(n < kRouterSplits ? n : kRouterSplits);
+}
+
+hipError_t launch_router_final(const RouterArgs &a, int splits, hipStream_t s) {
+    const int rows = a.d.N + 2 * a.d.n_const;
+    const dim3 grid((a.d.T + kRouterFinalTok - 1) / kRouterFinalTok), block(kRouterFinalThreads);
+    if (rows <= 32) hipLaunchKernelGGL(k_router_final<32>, grid, block, 0, s, a, splits);
+    else if (rows <= 64) hipLaunchKernelGGL(k_router_final<64>, grid, block, 0, s, a, splits);
+    else hipLaunchKernelGGL(k_router_final<kMaxRouterRows>, grid, block, 0, s, a, splits);
+    return hipGetLastError();
 }
 
 size_t router_small_bytes() {
     return (size_t)kRsSplits * kRouterSmallT * kMaxRouterRows * sizeof(float);
 }
 
-hipError_t launch_router_small(const RouterArgs &a, bool bf16, float *partial, hipStream_t s,
-                               const Workspace *perm_ws, const CapArgs *perm_cap) {
-    if (a.d.T == 0) return hipSuccess;
-    if (a.d.T > kRouterSmallT) return hipErrorInvalidValue;
+// First kernel of the sliced routers: slices of whole K tiles, at most max_splits of them.
+// Returns their number through *n_splits.
+static hipError_t launch_router_partial(const RouterArgs &a, bool bf16, int max_splits, int *n_splits, hipStream_t s) {
     const int tiles = (a.d.D + kRsBK - 1) / kRsBK;
-    const int per = (tiles + kRsSplits - 1) / kRsSplits;        // K tiles per slice
+    const int per = (tiles + max_splits - 1) / max_splits;      // K tiles per slice
     const int slice = per * kRsBK;
-    const int n_splits = (a.d.D + slice - 1) / slice;           // <= kRsSplits
-    const dim3 grid(n_splits, (a.d.T + kRsTok - 1) / kRsTok), block(4 * kWave);
+    *n_splits = (a.d.D + slice - 1) / slice;                    // <= max_splits
+    const dim3 grid(*n_splits, (a.d.T + kRsTok - 1) / kRsTok), block(4 * kWave);
     const int rows = a.d.N + 2 * a.d.n_const;
     auto go = [&](auto rpt) {
         constexpr int RPT = decltype(rpt)::value;
         if (bf16)
-            hipLaunchKernelGGL((k_router_small_partial<bf16_t, RPT>), grid, block, 0, s, a, slice, partial);
+            hipLaunchKernelGGL((k_router_small_partial<bf16_t, RPT>), grid, block, 0, s, a, slice, a.partial);
         else
-            hipLaunchKernelGGL((k_router_small_partial<float, RPT>), grid, block, 0, s, a, slice, partial);
+            hipLaunchKernelGGL((k_router_small_partial<float, RPT>), grid, block, 0, s, a, slice, a.partial);
     };
     static_assert(kMaxRouterRows <= 80, "rows per thread");
     if (rows <= 24) go(std::integral_constant<int, 6>());
     else if (rows <= 40) go(std::integral_constant<int, 10>());
     else go(std::integral_constant<int, 20>());
+    return hipGetLastError();
+}
+
+hipError_t launch_router_small(const RouterArgs &a, bool bf16, hipStream_t s, const Workspace *perm_ws,
+                               const CapArgs *perm_cap) {
+    if (a.d.T == 0) return hipSuccess;
+    if (a.d.T > kRouterSmallT) return hipErrorInvalidValue;
+    int n_splits = 0;
+    const hipError_t e = launch_router_partial(a, bf16, kRouterSplits, &n_splits, s);
+    if (e != hipSuccess) return e;
     if (perm_ws) {
         if (a.d.T > kRouterFusedT || perm_cap == nullptr) return hipErrorInvalidValue;
         hipLaunchKernelGGL(k_router_small_final_perm, dim3(1), dim3(kPermSmallWaves * kWave), 0, s, a, n_splits,
-                           partial, *perm_ws, *perm_cap);
+                           a.partial, *perm_ws, *perm_cap);
         return hipGetLastError();
     }
     hipLaunchKernelGGL(k_router_small_final, dim3((a.d.T + kRouterWaves - 1) / kRouterWaves),
-                       dim3(kRouterWaves * kWave), 0, s, a, n_splits, partial);
+                       dim3(kRouterWaves * kWave), 0, s, a, n_splits, a.partial);
     return hipGetLastError();
+}
+
+hipError_t launch_router_sliced(const RouterArgs &a, bool bf16, hipStream_t s) {
+    if (a.d.T == 0) return hipSuccess;
+    // slices until there are some 512 workgroups, as far as the partial sums fit
+    const int blocks = (a.d.T + kRsTok - 1) / kRsTok, fit = router_split_max(a.d);
+    if (fit < 1) return hipErrorInvalidValue;
+    int want = (512 + blocks - 1) / blocks, n_splits = 0;
+    want = want < fit ? want : fit;
+    const hipError_t e = launch_router_partial(a, bf16, want, &n_splits, s);
+    return e == hipSuccess ? launch_router_final(a, n_splits, s) : e;
 }
 
 hipError_t launch_router_generic(const RouterArgs &a, bool bf16, hipStream_t s) {

@@ -53,10 +53,12 @@ __device__ inline int rt_swz(int row) { return (row >> 1) & 7; }
 // NBLK: 32-row blocks of weight rows; PF: tiles prefetched in registers;
 // TOK: tokens per workgroup (4 threads per token); WPE: waves per SIMD the
 // register budget is sized for (several small workgroups share a CU, so that
-// one can compute while another waits at its barrier).
-template <int NBLK, int PF, int TOK, int WPE>
-__global__ __launch_bounds__(4 * TOK, WPE) void k_router_mfma(RouterArgs a) {
-    constexpr int kRtTok = TOK, kRtThreads = 4 * TOK, TB = TOK / 32;
+// one can compute while another waits at its barrier); KG: groups of TOK / 16 waves in
+// the workgroup, each with LDS stages of its own, that take every KG-th K tile; SPLIT: workgroup (b, s) leaves
+// the partial dot products of slice s of D in a.partial, and another kernel finishes.
+template <int NBLK, int PF, int TOK, int WPE, int KG, bool SPLIT>
+__global__ __launch_bounds__(4 * TOK * KG, WPE) void k_router_mfma(RouterArgs a) {
+    constexpr int kRtTok = TOK, kRtThreads = 4 * TOK, TB = TOK / 32, NT = kRtThreads * KG;
     constexpr int kRtXBytes = kRtTok * kRtRow;            // x part of a stage
     constexpr int ROWS = NBLK * 32;
     constexpr int PIECE = ROWS * kRtRow;                  // one bf16 piece of the weight tile
@@ -65,19 +67,25 @@ __global__ __launch_bounds__(4 * TOK, WPE) void k_router_mfma(RouterArgs a) {
     constexpr int WL = (WCH + kRtThreads - 1) / kRtThreads;   // weight chunks per thread and tile
     constexpr int STAGE = kRtXBytes + WBYTES;
     constexpr int DSTR = ROWS + 1;                        // floats per token in `dots`
-    constexpr int E_BYTES = (2 * kRtTok * DSTR + kRtTok * (kMaxExperts + 1) +
-                             kMaxExperts * kMaxExperts + 2 * kMaxExperts) * 4;
-    constexpr int LDS_BYTES = 2 * STAGE > E_BYTES ? 2 * STAGE : E_BYTES;
+    constexpr int MAXN = ROWS < kMaxExperts ? ROWS : kMaxExperts;    // N <= N + 2 n_const <= ROWS
+    constexpr int RSTR = MAXN + 4;                        // >= residual_stride(N)
+    constexpr int E_BYTES = (2 * KG * kRtTok * DSTR + (kRtTok + MAXN) * RSTR + 2 * MAXN + 4) * 4;
+    constexpr int LDS_BYTES = 2 * KG * STAGE > E_BYTES ? 2 * KG * STAGE : E_BYTES;
     static_assert(LDS_BYTES <= 160 * 1024 && PF % 2 == 0, "LDS / PF");
     __shared__ __attribute__((aligned(16))) char lds[LDS_BYTES];
 
-    const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
+    const int tid = threadIdx.x % kRtThreads, lane = tid % kWave, wave = tid / kWave;   // in the group
+    const int grp = KG == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / kRtThreads);
+    char *const glds = lds + grp * 2 * STAGE;             // the group's two stages
     const int l32 = lane % 32, lh = lane / 32;
     const int tb = wave % TB, kh = wave / TB;             // token block, K-step parity
     const int D = a.d.D, N = a.d.N, nc = a.d.n_const, T = a.d.T;
     const int rows = N + 2 * nc;
     const int t0 = blockIdx.x * kRtTok;
-    const int KT = D / kRtBK;                             // a multiple of PF (the launcher checks)
+    static_assert(!SPLIT || KG == 1, "one of the two");
+    // K tiles of a group or slice: a multiple of PF (the launcher checks)
+    const int KT = D / kRtBK / (SPLIT ? (int)gridDim.y : KG);
+    const int kt_first = SPLIT ? blockIdx.y * KT : 0;
 
     // ---- tile loads ------------------------------------------------------------
     // x chunk c = tid + threads i (i = 0, 1): tile row c / 8, LDS slot c % 8 holds
@@ -114,6 +122,7 @@ __global__ __launch_bounds__(4 * TOK, WPE) void k_router_mfma(RouterArgs a) {
         kt = kt < KT ? kt : KT - 1;                       // past the end: harmless reload of the last tile
         kt += rot;
         kt = kt < KT ? kt : kt - KT;
+        kt = SPLIT ? kt_first + kt : kt * KG + grp;
 #pragma unroll
         for (int i = 0; i < 2; ++i)      // x is read once: streamed past the caches' retention
             xq[i] = __builtin_nontemporal_load(reinterpret_cast<const bf16x8 *>(px[i] + (size_t)kt * (kRtBK * 2)));
@@ -150,7 +159,7 @@ __global__ __launch_bounds__(4 * TOK, WPE) void k_router_mfma(RouterArgs a) {
     for (int c = tid; c < 2 * 3 * (ROWS - rows) * (kRtRow / 16); c += kRtThreads) {
         const int st = c / (3 * (ROWS - rows) * (kRtRow / 16)), q = c % (3 * (ROWS - rows) * (kRtRow / 16));
         const int pc = q / ((ROWS - rows) * (kRtRow / 16)), o = q % ((ROWS - rows) * (kRtRow / 16));
-        *reinterpret_cast<f32x4 *>(lds + st * STAGE + kRtXBytes + pc * PIECE + rows * kRtRow + o * 16) =
+        *reinterpret_cast<f32x4 *>(glds + st * STAGE + kRtXBytes + pc * PIECE + rows * kRtRow + o * 16) =
             f32x4{0.f, 0.f, 0.f, 0.f};
     }
 
@@ -187,51 +196,55 @@ __global__ __launch_bounds__(4 * TOK, WPE) void k_router_mfma(RouterArgs a) {
     // contiguous runs, was measured and is slower than one tile per period.)
 #pragma unroll
     for (int p = 0; p < PF; ++p) load_regs(p, xr[p], wr[p]);
-    store_regs(lds, xr[0], wr[0]);
+    store_regs(glds, xr[0], wr[0]);
     load_regs(PF, xr[0], wr[0]);
     // The epilogue's own operands (this block's previous-layer logits, W_g of the
     // gating residual, the bias) are asked for now and wait in registers: loaded
     // after the loop, their latency would sit on every workgroup's critical path.
     const int n_tok = min(kRtTok, T - t0);
-    constexpr int PGN = ROWS / 4;                                      // >= N / 4
-    constexpr int WRN = (ROWS * ROWS + kRtThreads - 1) / kRtThreads;   // >= N N / threads
+    const int gtid = threadIdx.x;
+    constexpr int PGN = (kRtTok * MAXN + NT - 1) / NT;    // >= tokens N / threads
+    constexpr int WRN = (MAXN * MAXN + NT - 1) / NT;      // >= N N / threads
     float pg[PGN], wg[WRN], bs = 0.f;
 #pragma unroll
     for (int i = 0; i < PGN; ++i) {
-        const int c = tid + kRtThreads * i;
-        pg[i] = a.prev_gate && c < n_tok * N ? a.prev_gate[(size_t)t0 * N + c] : 0.f;
+        const int c = gtid + NT * i;
+        pg[i] = !SPLIT && a.prev_gate && c < n_tok * N ? a.prev_gate[(size_t)t0 * N + c] : 0.f;
     }
 #pragma unroll
     for (int i = 0; i < WRN; ++i) {
-        const int c = tid + kRtThreads * i;
-        wg[i] = a.prev_gate && c < N * N ? a.W_res[c] : 0.f;
+        const int c = gtid + NT * i;
+        wg[i] = !SPLIT && a.prev_gate && c < N * N ? a.W_res[c] : 0.f;
     }
-    if (a.bias && tid < N) bs = a.bias[tid];
+    if (!SPLIT && a.bias && gtid < N) bs = a.bias[gtid];
     lds_barrier();
     for (int kt0 = 0; kt0 < KT; kt0 += PF) {
 #pragma unroll
         for (int s = 0; s < PF; ++s) {
             const int kt = kt0 + s, q = (s + 1) % PF;     // q: slot of tile kt+1
+            // The operand reads of tile kt go out first; splitting the weights of tile
+            // kt+1 is arithmetic that runs while they, and the MFMAs, are on their way.
+            mfma_tile(glds + (s & 1) * STAGE);
             // tile kt+1: registers -> the stage that tile kt-1 was read from (every
             // wave passed the barrier after those reads), then refill the slot
-            store_regs(lds + ((s + 1) & 1) * STAGE, xr[q], wr[q]);
+            store_regs(glds + ((s + 1) & 1) * STAGE, xr[q], wr[q]);
             load_regs(kt + 1 + PF, xr[q], wr[q]);
-            mfma_tile(lds + (s & 1) * STAGE);
             lds_barrier();                // tile kt+1 visible, tile kt read by all; loads stay in flight
         }
     }
 
     // ---- epilogue -------------------------------------------------------------
     // (the loop ended with a barrier: the stages are dead)
-    float *dots = reinterpret_cast<float *>(lds);               // [kRtTok][DSTR]  K-step parity 0
-    float *dots1 = dots + kRtTok * DSTR;                        // [kRtTok][DSTR]  K-step parity 1
-    float *prevs = dots1 + kRtTok * DSTR;                       // [kRtTok][N + 1]
-    float *wres = prevs + kRtTok * (kMaxExperts + 1);           // [N][N]
-    float *sbias = wres + kMaxExperts * kMaxExperts;            // [N]
-    int *s_hist = reinterpret_cast<int *>(sbias + kMaxExperts); // [N] selections per expert
+    constexpr int DOTS = kRtTok * DSTR;
+    float *prevs = reinterpret_cast<float *>(lds);              // [kRtTok][residual_stride(N)]
+    float *wres = prevs + kRtTok * RSTR;                        // [N][residual_stride(N)]
+    float *dots = wres + MAXN * RSTR;                           // [KG * 2][kRtTok][DSTR] by group and K-step parity
+    float *sbias = dots + 2 * KG * DOTS;                        // [N]
+    int *s_hist = reinterpret_cast<int *>(sbias + MAXN);        // [N] selections per expert
+    const int rs = residual_stride(N);
     // acc[b][v]: weight row b*32 + 8*(v/4) + 4*lh + v%4, token tb*32 + l32
     {
-        float *dst = kh == 0 ? dots : dots1;
+        float *dst = dots + (2 * grp + kh) * DOTS;
 #pragma unroll
         for (int b = 0; b < NBLK; ++b)
 #pragma unroll
@@ -239,75 +252,36 @@ __global__ __launch_bounds__(4 * TOK, WPE) void k_router_mfma(RouterArgs a) {
                 dst[(tb * 32 + l32) * DSTR + b * 32 + 8 * (v / 4) + 4 * lh + (v % 4)] =
                     acc_hi[b][v] + acc_lo[b][v];
     }
+    if constexpr (SPLIT) {
+        // partial dot products of this slice of D, [slice][T][rows]
+        __syncthreads();
+        float *dst = a.partial + ((size_t)blockIdx.y * T + t0) * rows;
+        for (int c = gtid; c < n_tok * rows; c += NT) {
+            const int o = (c / rows) * DSTR + c % rows;
+            dst[c] = dots[o] + dots[DOTS + o];
+        }
+        return;
+    }
     if (a.prev_gate) {
 #pragma unroll
         for (int i = 0; i < PGN; ++i) {
-            const int c = tid + kRtThreads * i;
-            if (c < n_tok * N) prevs[(c / N) * (N + 1) + c % N] = pg[i];
+            const int c = gtid + NT * i;
+            if (c < n_tok * N) prevs[(c / N) * rs + c % N] = pg[i];
         }
 #pragma unroll
         for (int i = 0; i < WRN; ++i) {
-            const int c = tid + kRtThreads * i;
-            if (c < N * N) wres[c] = wg[i];
+            const int c = gtid + NT * i;
+            if (c < N * N) wres[(c / N) * rs + c % N] = wg[i];
         }
+        zero_residual_pad(prevs, n_tok, N, NT);
+        zero_residual_pad(wres, N, N, NT);
     }
-    if (tid < N) {                 // N <= 64 < threads
-        sbias[tid] = bs;
-        s_hist[tid] = 0;
+    if (gtid < N) {                // N <= 64 < threads
+        sbias[gtid] = bs;
+        s_hist[gtid] = 0;
     }
     __syncthreads();
-
-    // logits, all threads: element c -> (token c / rows, row c % rows)
-    for (int c = tid; c < n_tok * rows; c += kRtThreads) {
-        const int tt = c / rows, i = c % rows;
-        float L = dots[tt * DSTR + i] + dots1[tt * DSTR + i];
-        if (i < N) {
-            if (a.prev_gate) {
-                const float *pr = prevs + tt * (N + 1);
-                const float *wr = wres + i * N;
-                float r0 = 0.f, r1 = 0.f;
-                int m = 0;
-                for (; m + 1 < N; m += 2) {
-                    r0 = fmaf(wr[m], pr[m], r0);
-                    r1 = fmaf(wr[m + 1], pr[m + 1], r1);
-                }
-                if (m < N) r0 = fmaf(wr[m], pr[m], r0);
-                L += r0 + r1;
-            }
-            L += sbias[i];
-        }
-        dots[tt * DSTR + i] = L;
-    }
-    __syncthreads();
-
-    // Softmax, Top-K, a1: threads 4 tok .. 4 tok + 3 share token tok (every thread
-    // runs this, so the shuffles are whole; tokens past the end compute on a copy of
-    // the last token and store nothing)
-    {
-        const int tok = tid >> 2;
-        // (prevs is free again: the probabilities of the load-balance statistics go there)
-        router_token_quad(a, (size_t)(t0 + tok), tok < n_tok, tid & 3, dots + tok * DSTR,
-                          a.chunk_hist ? s_hist : nullptr, nullptr,
-                          a.bal_partial ? prevs + tok * (N + 1) : nullptr);
-    }
-    // out_gate block [n_tok, N] is contiguous in memory: coalesced copy from LDS
-    for (int c = tid; c < n_tok * N; c += kRtThreads)
-        a.out_gate[(size_t)t0 * N + c] = dots[(c / N) * DSTR + c % N];
-    if (a.chunk_hist || a.bal_partial) __syncthreads();
-    if (a.chunk_hist)
-        for (int c = tid; c < N; c += kRtThreads) a.chunk_hist[(size_t)blockIdx.x * N + c] = s_hist[c];
-    if (a.bal_partial && tid < 4 * N) {
-        // sum of Softmax(G(x))_e over the workgroup's tokens (P_e of Eq.7 is the mean over all
-        // tokens): threads 4 e .. 4 e + 3 add a quarter of the tokens each, in token order, and
-        // the four sums are added as (0 + 1) + (2 + 3): the same on every run
-        const int e = tid >> 2, part = tid & 3;
-        double sum = 0.0;
-        for (int tt = part * (kRtTok / 4); tt < (part + 1) * (kRtTok / 4); ++tt)
-            sum += (double)prevs[tt * (N + 1) + e];
-        sum += __shfl_xor(sum, 1, kWave);
-        sum += __shfl_xor(sum, 2, kWave);
-        if (part == 0) a.bal_partial[(size_t)blockIdx.x * kMaxExperts + e] = sum;
-    }
+    router_finish<kRtTok, NT, ROWS, 2 * KG>(a, t0, dots, prevs, wres, sbias, s_hist);
 }
 
 bool router_mfma_supported(const Dims &d) {
@@ -331,17 +305,39 @@ hipError_t launch_router_mfma(const RouterArgs &a, hipStream_t s) {
     const int nblk = (rows + 31) / 32;
     const int KT = a.d.D / kRtBK;
     const int tok = router_mfma_block_tokens(a.d);
-    const dim3 grid((a.d.T + tok - 1) / tok);
-    if (nblk == 1) {
-        if (tok == 128)
-            hipLaunchKernelGGL((k_router_mfma<1, 4, 128, 2>), grid, dim3(512), 0, s, a);
-        else if (KT % 4 == 0)
-            hipLaunchKernelGGL((k_router_mfma<1, 4, 64, 3>), grid, dim3(256), 0, s, a);
-        else
-            hipLaunchKernelGGL((k_router_mfma<1, 2, 64, 3>), grid, dim3(256), 0, s, a);
-    } else {
-        hipLaunchKernelGGL((k_router_mfma<2, 2, 64, 2>), grid, dim3(256), 0, s, a);
+    const int blocks = (a.d.T + tok - 1) / tok;
+    const dim3 grid(blocks);
+    // Few blocks of tokens and a long reduction: slices of D in workgroups of their own, up to
+    // some 512 of them, an even number of tiles each, as far as the partial sums fit their
+    // buffer; a second kernel finishes.  T = 777, D = 4096: 20.4 us against 26.4 in one kernel,
+    // T = 2048: 22.9 against 29.9; at D = 768 the second launch costs more than the shorter
+    // loop saves (T = 1500: 13.5 against 12.4, T = 4096 with 52 rows: 26 against 21).
+    int splits = 1;
+    if (KT >= 24 && blocks <= 64)
+        for (int sp = 2; sp <= KT / 2; ++sp)
+            if (KT % (2 * sp) == 0 && (long long)blocks * sp <= 512 && sp <= router_split_max(a.d)) splits = sp;
+    if (splits > 1) {
+        const dim3 g2(blocks, splits);
+        if (nblk == 1) hipLaunchKernelGGL((k_router_mfma<1, 2, 64, 3, 1, true>), g2, dim3(256), 0, s, a);
+        else hipLaunchKernelGGL((k_router_mfma<2, 2, 64, 2, 1, true>), g2, dim3(256), 0, s, a);
+        return launch_router_final(a, splits, s);
     }
+    // 64-token workgroups take two K tiles at a time, in two groups of four waves: a tile is a
+    // serial chain (loads, split, LDS, barrier, MFMA) and there are at most a few workgroups
+    // per CU.  T = 16384, D = 2048: 35.6 -> 20.8 us; T = 4096, D = 768, 52 rows: 38 -> 20.6
+    // (10 of it the epilogue's LDS bank conflicts).  Four groups: the same.
+    if (tok == 128)
+        hipLaunchKernelGGL((k_router_mfma<1, 4, 128, 2, 1, false>), grid, dim3(512), 0, s, a);
+    else if (nblk == 1 && KT % 8 == 0)
+        hipLaunchKernelGGL((k_router_mfma<1, 4, 64, 2, 2, false>), grid, dim3(512), 0, s, a);
+    else if (nblk == 1 && KT % 4 == 0)
+        hipLaunchKernelGGL((k_router_mfma<1, 2, 64, 2, 2, false>), grid, dim3(512), 0, s, a);
+    else if (nblk == 1)
+        hipLaunchKernelGGL((k_router_mfma<1, 2, 64, 3, 1, false>), grid, dim3(256), 0, s, a);
+    else if (KT % 4 == 0)
+        hipLaunchKernelGGL((k_router_mfma<2, 2, 64, 2, 2, false>), grid, dim3(512), 0, s, a);
+    else
+        hipLaunchKernelGGL((k_router_mfma<2, 2, 64, 2, 1, false>), grid, dim3(256), 0, s, a);
     return hipGetLastError();
 }
 

@@ -1,12 +1,13 @@
-"""FFN kernels at the edges of their tiles and dispatch rules, every case against the oracle
+"""Kernels at the edges of their tiles and dispatch rules, every case against the oracle
 on all tokens with the tolerances of tests/helpers.py: widths that leave a narrower last K
 slab (D % 32, F % 32), fewer rows than a tile, groups that end inside one, token counts on
 both sides of a rule."""
+import numpy as np
 import pytest
 
 from workloads import LayerShape, make_inputs
 
-from helpers import check_layer, gpu_forward
+from helpers import check_layer, gpu_forward, make_layer
 
 pytestmark = pytest.mark.gpu
 
@@ -42,3 +43,19 @@ def test_bf16_ragged_widths(T, D, F):
 @pytest.mark.parametrize("D,F", [(64, 128), (128, 64), (64, 64)])
 def test_bf16_short_reduction(D, F):
     check(T=900, D=D, F=F, n_ffn=4, k=3)
+
+
+# routers between the few-token one (T <= 256) and the 128-token blocks (T >= 24576): two groups
+# of waves (tiles % 8, % 4, neither), slices of D (24 tiles of 64 or more, at most 64 blocks), one
+# and two blocks of weight rows, widths for the sliced FMA router (also more than 64 rows)
+@pytest.mark.parametrize("D", [128, 256, 512, 1408, 1536, 4096, 72])
+@pytest.mark.parametrize("n_ffn,n_const,k", [(3, 2, 2), (37, 7, 3), (52, 8, 8)])
+@pytest.mark.parametrize("T", [257, 321])
+def test_router(T, D, n_ffn, n_const, k):
+    s = LayerShape("edge", T=T, D=D, F=64, n_ffn=n_ffn, n_zero=1, n_copy=1, n_const=n_const, k=k,
+                   bias="normal", seed=8200)
+    inp = make_inputs(s)
+    L = make_layer(s)
+    cap = L.capacity(T, 1.1, 0.75)
+    res = gpu_forward(s, inp, layer=L, cap=cap, balance_tau=0.75)
+    print("  ", s, check_layer(s, inp, res, cap=np.array(cap, np.int32), balance_tau=0.75), flush=True)
