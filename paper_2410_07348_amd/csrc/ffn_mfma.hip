@@ -74,14 +74,8 @@ typedef __attribute__((address_space(3))) void *lptr_t;
 // Tile geometry.  BK K-elements per LDS stage; NS stages form a ring, NS - 1
 // tiles are in flight (or being computed) at any time.
 // LW_ of the WM*WN waves issue the tile loads (0: all of them).
-// MI_: edge of the MFMA block, 32 (v_mfma_f32_32x32x16_bf16) or 16 (v_mfma_f32_16x16x32_bf16).
-template <int BM_, int BN_, int WM_, int WN_, int BK_, int NS_, int LW_ = 0, bool PERSIST_ = false,
-          int MI_ = 32>
+template <int BM_, int BN_, int WM_, int WN_, int BK_, int NS_, int LW_ = 0>
 struct Geo {
-    static constexpr int MI = MI_;
-    static constexpr bool PAIR = MI_ == 16;            // GEMM1 issues the A loads of two K tiles together
-    static_assert(MI_ == 32 || (MI_ == 16 && BK_ == 32 && NS_ >= 3), "16x16x32 blocks: one MFMA K step per 32-deep stage, ring path");
-    static constexpr bool PERSIST = PERSIST_;          // one workgroup per CU runs tile after tile
     static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, BK = BK_, NS = NS_;
     static constexpr int NT = WM * WN * kWave;         // threads
     static constexpr int LW = LW_ ? LW_ : WM * WN;     // waves that issue the tile loads
@@ -89,30 +83,22 @@ struct Geo {
     static constexpr int RB = BK * 2;                  // bytes per tile row
     static constexpr int CPR = RB / 16;                // 16-byte slots per tile row
     static constexpr int TM = BM / WM, TN = BN / WN;   // wave tile
-    static constexpr int MB = TM / 32, NB = TN / 32;   // 32x32 MFMA blocks per wave
     static constexpr int CA = BM * CPR / NL, CB = BN * CPR / NL;   // loads per loading thread and tile
     static constexpr int STAGE = (BM + BN) * RB;
-    static constexpr int KS = BK / 16;                 // MFMA K steps per stage
+    static constexpr int PER_CU = NS * STAGE <= 80 * 1024 ? 2 : 1;     // workgroups that fit the LDS of a CU
     static constexpr int LPT = CA + CB;                // wave-wide loads per thread and tile
-    static constexpr int LPS = LPT / KS;               // tile loads per loading thread and K step
-    static_assert(LPT % KS == 0, "tile loads per K step");
     static_assert(TM % 32 == 0 && TN % 64 == 0, "wave tile");
     static_assert((BM * CPR) % NL == 0 && (BN * CPR) % NL == 0 && (NL / CPR) % 16 == 0, "chunks");
-    static_assert(BK == 32 || BK == 64, "BK");
+    static_assert(BK == 32, "one MFMA K step per stage");
     // XOR swizzle of the 16-byte slots of a tile row.  The LDS has 64 banks of
     // 4 bytes (256 bytes) and serves a b128 operand read in four passes of 16
     // lanes; a pass takes lanes {0-3, 12-15, 20-27} or {4-11, 16-19, 28-31} of
     // a half wave (measured: two lanes of one such set that address the same
-    // banks cost an extra pass).  The 32x32 operand read (lane l: row l % 32,
-    // one slot per half wave) wants any 16 consecutive rows at one logical
-    // slot on 16 different bank groups; the 16x16 operand read (lane l: row
-    // l % 16, slot l / 16, 64-byte rows) wants that of rows {0-3, 12-15} at
-    // one slot together with rows {4-11} at the next, which a swizzle by
-    // row / 2 gives and the swizzle by row / 4 does not (two passes per set).
-    __device__ static int swz(int row) {
-        if constexpr (MI == 16) return (row / 2) % CPR;
-        else return (row / (256 / RB)) % CPR;
-    }
+    // banks cost an extra pass).  The 16x16 operand read (lane l: row l % 16,
+    // slot l / 16, 64-byte rows) wants rows {0-3, 12-15} at one slot together
+    // with rows {4-11} at the next on different banks, which a swizzle by row / 2
+    // gives.
+    __device__ static int swz(int row) { return (row / 2) % CPR; }
 };
 
 // s_waitcnt vmcnt(VM) lgkmcnt(0), then the workgroup barrier.  The wait is
@@ -134,37 +120,66 @@ __device__ inline void wait_and_barrier() {
     asm volatile("" ::: "memory");
 }
 
-// TAIL: this launch computes what the main launch (tiles of 2 BM rows) left
-// over, as half tiles of BM rows; the tiles are numbered as in the main launch.
+template <class G, bool SWIGLU>
+struct Epilogue {
+    // The output tile goes through LDS in EP passes of HB rows (one pass for
+    // GEMM1, whose tile is half as wide after SwiGLU).
+    static constexpr int OUT_W = SWIGLU ? G::BN / 2 : G::BN;   // output tile width (elements)
+    static constexpr int OUT_STRIDE = OUT_W * 2 + 16;          // bytes, padded
+    static constexpr int EP = SWIGLU || G::BM < 256 ? 1 : 2;
+    static constexpr int HB = G::BM / EP;
+    static constexpr int OUT_BYTES = HB * OUT_STRIDE;
+    static constexpr int LDS_BYTES = G::NS * G::STAGE > OUT_BYTES ? G::NS * G::STAGE : OUT_BYTES;
+};
+
+// Lane q holds group q: one vector load of the offsets, a wave-wide prefix sum of the
+// tile counts, a ballot to find the group of a tile (a scalar loop over the groups costs
+// a dependent memory round trip per group).
+struct GroupTiles {
+    int o_lo, o_hi;          // rows of the group
+    int mt_q;                // its tiles of EBM rows (0 for lanes past the last group)
+    int incl;                // inclusive prefix sum over lanes of mt_q * n_ntiles
+};
+__device__ inline GroupTiles group_tiles(const GemmArgs &a, int lane, int ebm) {
+    GroupTiles t;
+    const int gq = lane < a.n_ffn ? lane : a.n_ffn;
+    t.o_lo = a.offsets[gq];
+    t.o_hi = a.offsets[gq < a.n_ffn ? gq + 1 : gq];
+    t.mt_q = (t.o_hi - t.o_lo + ebm - 1) / ebm;
+    t.incl = t.mt_q * a.n_ntiles;
+#pragma unroll
+    for (int d = 1; d < kWave; d <<= 1) {
+        const int up = __shfl_up(t.incl, d, kWave);
+        if (lane >= d) t.incl += up;
+    }
+    return t;
+}
+
+// The tiles of one geometry by all workgroups of a launch.
+// TAIL: what the geometry with tiles of 2 BM rows left over, as half tiles of BM
+// rows; the tiles are numbered as there.
 // RAG: widths that are not multiples of 64.  The last K slab may be narrower than 32
 // columns and the K loop is padded to an even number of at least 4 K tiles: 16-byte
 // pieces past the last column come from a page of zeros, for both operands.  A last
 // block of fewer than 32 rows of W1 and of W3 is read as if each had 32.
 __device__ __align__(16) const unsigned char zero_page[16] = {};
 
-template <class G, bool SWIGLU, bool TAIL = false, bool RAG = false>
-__global__ __launch_bounds__(G::NT, 1) void k_grouped_gemm(GemmArgs a) {
+template <class G, bool SWIGLU, bool TAIL, bool RAG, bool STREAM>
+__device__ __forceinline__ void gemm_tiles(const GemmArgs &a, const GroupTiles &gt, char *const lds) {
     constexpr int EBM = TAIL ? 2 * G::BM : G::BM;      // tile height of the numbering
     constexpr int BM = G::BM, BN = G::BN, WN = G::WN, NT = G::NT, NL = G::NL, RB = G::RB, CPR = G::CPR;
-    constexpr int TM = G::TM, TN = G::TN, MB = G::MB, NB = G::NB, CA = G::CA, CB = G::CB;
-    constexpr int STAGE = G::STAGE, NS = G::NS, BK = G::BK, KS = G::KS;
-    // The output tile goes through LDS in EP passes of HB rows (one pass for
-    // GEMM1, whose tile is half as wide after SwiGLU).
-    constexpr int OUT_W = SWIGLU ? BN / 2 : BN;   // output tile width (elements)
-    constexpr int OUT_STRIDE = OUT_W * 2 + 16;    // bytes, padded
-    constexpr int EP = SWIGLU || BM < 256 ? 1 : 2;
-    constexpr int HB = BM / EP;
-    constexpr int OUT_BYTES = HB * OUT_STRIDE;
+    constexpr int TM = G::TM, TN = G::TN, CA = G::CA, CB = G::CB;
+    constexpr int STAGE = G::STAGE, NS = G::NS, BK = G::BK;
+    typedef Epilogue<G, SWIGLU> E;
+    constexpr int OUT_W = E::OUT_W, OUT_STRIDE = E::OUT_STRIDE, EP = E::EP, HB = E::HB, OUT_BYTES = E::OUT_BYTES;
     static_assert(TM <= HB && HB % TM == 0, "a wave's rows belong to one epilogue pass");
-    constexpr int LDS_BYTES = NS * STAGE > OUT_BYTES ? NS * STAGE : OUT_BYTES;
-    __shared__ __attribute__((aligned(16))) char lds[LDS_BYTES];
-    // A persistent workgroup (G::PERSIST) runs tile after tile.  The stages
+    // A workgroup runs tile after tile.  The stages
     // the epilogue's LDS patch does not touch, S0 .. NS-1, take the first K
     // tiles of the NEXT output tile while the epilogue of this one runs, so
     // every output tile's ring starts at stage S0.
-    constexpr int S0 = G::PERSIST ? (OUT_BYTES + STAGE - 1) / STAGE : 0;
-    constexpr int EARLY = G::PERSIST ? NS - S0 : 0;      // K tiles issued before the epilogue
-    static_assert(!G::PERSIST || (EARLY >= 1 && EARLY <= NS - 1), "stages free during the epilogue");
+    constexpr int S0 = (OUT_BYTES + STAGE - 1) / STAGE;
+    constexpr int EARLY = NS - S0;      // K tiles issued before the epilogue
+    static_assert(EARLY >= 1 && EARLY <= NS - 1, "stages free during the epilogue");
 
     const int tid = threadIdx.x;
     const int lane = tid % kWave;
@@ -189,19 +204,7 @@ __global__ __launch_bounds__(G::NT, 1) void k_grouped_gemm(GemmArgs a) {
     // is computed once), only the sharing in L2 it is built for is lost.
     constexpr int GM = 8, GN = 4, NXCD = 8;
     const int Nt = a.n_ntiles;
-    // Lane q holds group q: one vector load of the offsets, a wave-wide prefix
-    // sum of the tile counts, a ballot to find the group of a tile (a scalar
-    // loop over the groups costs a dependent memory round trip per group).
-    const int gq = lane < a.n_ffn ? lane : a.n_ffn;
-    const int o_lo = a.offsets[gq];
-    const int o_hi = a.offsets[gq < a.n_ffn ? gq + 1 : gq];
-    const int mt_q = (o_hi - o_lo + EBM - 1) / EBM;            // 0 for lanes past the last group
-    int incl = mt_q * Nt;                                       // inclusive prefix sum over lanes
-#pragma unroll
-    for (int d = 1; d < kWave; d <<= 1) {
-        const int up = __shfl_up(incl, d, kWave);
-        if (lane >= d) incl += up;
-    }
+    const int o_lo = gt.o_lo, o_hi = gt.o_hi, mt_q = gt.mt_q, incl = gt.incl;
     const int total = __builtin_amdgcn_readlane(incl, kWave - 1);
     // A last round that fills at most half of the workgroups costs a whole
     // tile time with most of the chip idle: those tiles [cut, total) go to the
@@ -264,14 +267,14 @@ __global__ __launch_bounds__(G::NT, 1) void k_grouped_gemm(GemmArgs a) {
     const int kc = slot ^ G::swz(r_thr);         // global chunk within the K tile
     const bf16_t *pa[CA];
     const bf16_t *pb[CB];
-    static_assert(!RAG || (BK == kSlab && G::MI == 16), "ragged widths: one slab per K tile");
+    static_assert(BK == kSlab, "one slab per K tile");
     const bf16_t *const zeros = reinterpret_cast<const bf16_t *>(zero_page);
     const int KF = a.K / kSlab, KW = a.K % kSlab;          // RAG: full slabs, columns of the last one
     const bf16_t *la[RAG ? CA : 1], *lb[RAG ? CB : 1];    // RAG: pieces of slab KF
     // elements of A from one K tile to the next
     const size_t a_kstep = SWIGLU ? (size_t)BK : (size_t)(BK / kSlab) * a.h_rows * kSlab;
     size_t b_kstep = 0;                          // elements of B from one K tile to the next
-    static_assert(BN == kPanel, "one tile of B rows is one panel of the packed weights");
+    static_assert(kPanel % BN == 0, "a tile's rows of B lie in one panel of the packed weights");
     // rows of A (of x through src_of for GEMM1, of h for GEMM2) this thread loads for a tile
     auto gather_rows = [&](int t_row0, int t_row_end, int *src) {
 #pragma unroll
@@ -289,10 +292,9 @@ __global__ __launch_bounds__(G::NT, 1) void k_grouped_gemm(GemmArgs a) {
                            : a.A + (size_t)(kc / 4) * a.h_rows * kSlab + (size_t)src[i] * kSlab + (kc % 4) * 8;
         }
         const bf16_t *Be = a.B + (size_t)t_e * a.Nb * a.K;
-        const int n0 = t_nt * BN;
+        const int n0 = t_nt * BN, p0 = n0 / kPanel * kPanel;    // first rows of the tile and of its panel
+        b_kstep = (size_t)(BK / kSlab) * (a.Nb - p0 < kPanel ? a.Nb - p0 : kPanel) * kSlab;
         if constexpr (RAG) {
-            const int rows = a.Nb - n0 < BN ? a.Nb - n0 : BN;
-            b_kstep = (size_t)rows * kSlab;
             const bool in = kc * 8 < KW;
 #pragma unroll
             for (int i = 0; i < CA; ++i)
@@ -300,9 +302,9 @@ __global__ __launch_bounds__(G::NT, 1) void k_grouped_gemm(GemmArgs a) {
 #pragma unroll
             for (int i = 0; i < CB; ++i) {
                 // (a row that does not exist: row 0 of the panel, its columns are never stored)
-                const int q = packed_of_logical<SWIGLU>(n0 + r_thr + i * (NL / CPR), a.Nb) - n0;
+                const int q = packed_of_logical<SWIGLU>(n0 + r_thr + i * (NL / CPR), a.Nb) - p0;
                 const int n = q > 0 ? q : 0;
-                pb[i] = Be + (size_t)n0 * a.K + n * kSlab + kc * 8;
+                pb[i] = Be + (size_t)p0 * a.K + n * kSlab + kc * 8;
                 lb[i] = !in ? zeros : pb[i] + KF * b_kstep - n * (kSlab - KW);
             }
             return;
@@ -313,8 +315,6 @@ __global__ __launch_bounds__(G::NT, 1) void k_grouped_gemm(GemmArgs a) {
             n = n < a.Nb ? n : a.Nb - 1;
             pb[i] = Be + panel_row(n, kc / 4, a.Nb, a.K) + (kc % 4) * 8;
         }
-        const int b_rows = a.Nb - n0 < BN ? a.Nb - n0 : BN;     // rows of this tile's panel
-        b_kstep = (size_t)(BK / kSlab) * b_rows * kSlab;
     };
     const int wave_off = __builtin_amdgcn_readfirstlane(wave) * 1024;   // this wave's 1 KB of each load group
 
@@ -338,7 +338,7 @@ __global__ __launch_bounds__(G::NT, 1) void k_grouped_gemm(GemmArgs a) {
                                              (lptr_t)(sa + q * (NL / CPR) * RB), 16, 0, 0);
         else
             __builtin_amdgcn_global_load_lds((gptr_t)(pb[q - CA] + kt * b_kstep),
-                                             (lptr_t)(sb + (q - CA) * (NL / CPR) * RB), 16, 0, 0);
+                                             (lptr_t)(sb + (q - CA) * (NL / CPR) * RB), 16, 0, STREAM ? 2 : 0);
     };
     auto issue_tile = [&](int kt, char *__restrict__ stage) {
 #pragma unroll
@@ -353,73 +353,14 @@ __global__ __launch_bounds__(G::NT, 1) void k_grouped_gemm(GemmArgs a) {
     };
 
     // ---- MFMA operand addressing --------------------------------------------
-    // lane l reads row (l % 32) of a 32-row block, K half (l / 32) of each 16-wide step
-    const int l32 = lane % 32, lh = lane / 32;
-    int rd_off[KS];
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks)
-        rd_off[ks] = l32 * RB + (((2 * ks + lh) ^ G::swz(l32)) << 4);
     const int a_base = (wm * TM) * RB;
     const int b_base = BM * RB + (wn * TN) * RB;
-
-    // accumulators: 32x32 blocks of 16 registers, or 16x16 blocks of 4
-    constexpr int MI = G::MI;
-    constexpr int NBX = TN / MI, MBX = TM / MI;
-    typedef typename std::conditional<MI == 32, f32x16, f32x4>::type acc_t;
-    acc_t acc[NBX][MBX];
-    // 16x16x32 blocks: lane l reads row (l % 16) of a 16-row block, 16-byte chunk l / 16 of its 64-byte row
+    // accumulators: 16x16 blocks of 4 registers
+    constexpr int NBX = TN / 16, MBX = TM / 16;
+    f32x4 acc[NBX][MBX];
+    // lane l reads row (l % 16) of a 16-row block, 16-byte chunk l / 16 of its 64-byte row
     const int l16 = lane % 16, lq = lane / 16;
     const int rd16 = l16 * RB + ((lq ^ G::swz(l16)) << 4);
-
-    auto read_frags = [&](const char *st, int ks, bf16x8 *fa, bf16x8 *fb) {
-#pragma unroll
-        for (int i = 0; i < MB; ++i)
-            fa[i] = *reinterpret_cast<const bf16x8 *>(st + a_base + i * 32 * RB + rd_off[ks]);
-#pragma unroll
-        for (int j = 0; j < NB; ++j)
-            fb[j] = *reinterpret_cast<const bf16x8 *>(st + b_base + j * 32 * RB + rd_off[ks]);
-    };
-    auto mfma32 = [&](bf16x8 b, bf16x8 a_, auto &c) {
-        if constexpr (MI == 32) c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b, a_, c, 0, 0, 0);
-    };
-    auto mfma16 = [&](bf16x8 b, bf16x8 a_, auto &c) {
-        if constexpr (MI == 16) c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b, a_, c, 0, 0, 0);
-    };
-    // One K step with its memory operations spread evenly between the MFMAs:
-    // first the operand reads of the NEXT step (from `st`, step `ks_rd`, into
-    // fa_n/fb_n), then N_LOAD of the loads of tile kt_issue.  A wave issues in
-    // order: a burst of reads or loads between two MFMAs leaves the matrix
-    // core idle, a single one does not.
-    auto mfma_step_mem = [&](const bf16x8 *fa, const bf16x8 *fb, int ks, bool do_read,
-                             const char *__restrict__ st, int ks_rd, bf16x8 *fa_n, bf16x8 *fb_n,
-                             auto n_load_c, int kt_issue, char *__restrict__ wr) {
-        constexpr int N_LOAD = decltype(n_load_c)::value;
-        constexpr int N_READ = MB + NB, OPS = N_READ + N_LOAD, SLOTS = MB * NB;
-#pragma unroll
-        for (int j = 0; j < NB; ++j)
-#pragma unroll
-            for (int i = 0; i < MB; ++i) {
-                mfma32(fb[j], fa[i], acc[j][i]);
-                const int idx = j * MB + i;
-                __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int o = 0; o < OPS; ++o) {
-                    if (o * SLOTS / OPS != idx) continue;
-                    if (o >= N_READ) {
-                        issue_one(ks * N_LOAD + o - N_READ, kt_issue, wr);
-                    } else if (do_read) {
-                        // order of first use by the next step: fb[0], fa[0..], fb[1..]
-                        if (o == 0)
-                            fb_n[0] = *reinterpret_cast<const bf16x8 *>(st + b_base + rd_off[ks_rd]);
-                        else if (o <= MB)
-                            fa_n[o - 1] = *reinterpret_cast<const bf16x8 *>(st + a_base + (o - 1) * 32 * RB + rd_off[ks_rd]);
-                        else
-                            fb_n[o - MB] = *reinterpret_cast<const bf16x8 *>(st + b_base + (o - MB) * 32 * RB + rd_off[ks_rd]);
-                    }
-                }
-                __builtin_amdgcn_sched_barrier(0);
-            }
-    };
 
     constexpr int LPT = G::LPT;
 
@@ -428,82 +369,18 @@ __global__ __launch_bounds__(G::NT, 1) void k_grouped_gemm(GemmArgs a) {
     // LW waves do; the others run the same code without them (two copies of
     // everything below, chosen once per wave, each free of branches around
     // the loads).  Expects K tiles 0 .. NS-2 of the tile to be in flight.
-    auto main_loop = [&](auto loader_c) {
-        constexpr bool LOADER = decltype(loader_c)::value;
-        {
-            static_assert(NS >= 3, "a ring");
-            // Ring of NS stages, tile kt in stage (S0 + kt) % NS.  The workgroup
-            // barrier sits before the LAST MFMA step of a tile, not after it:
-            // once every wave has issued (and received) all operand reads of
-            // tile kt, the stage of tile kt-1 can be refilled and the first
-            // operands of tile kt+1 can be read, all while the matrix cores
-            // still work on the last step of tile kt.  Operands are double
-            // buffered in registers.  The loop body is branch-free (the last
-            // NS-1 tiles are peeled off), which keeps the compiler's wait-count
-            // tracking exact.  Needs KT >= NS-1.
-            static_assert(KS % 2 == 0, "operand double buffering assumes an even number of K steps");
-            bf16x8 fa[2][MB], fb[2][NB];
-            // One tile.  cur / nxt / wr are three different stages (restrict):
-            // the loads that refill wr never make the operand reads wait.  VM =
-            // loads of younger tiles that may still be in flight when tile kt+1
-            // is needed.
-            auto k_tile = [&](const char *__restrict__ cur, const char *__restrict__ nxt,
-                              char *__restrict__ wr, int kt_issue, auto vm_c, auto issue_c, auto last_c) {
-                constexpr int VM = decltype(vm_c)::value;
-                constexpr bool ISSUE = decltype(issue_c)::value, LAST = decltype(last_c)::value;
-                typedef std::integral_constant<int, ISSUE && LOADER ? G::LPS : 0> n_load_t;
-#pragma unroll
-                for (int ks = 0; ks < KS; ++ks) {
-                    if (ks + 1 < KS) {
-                        // operands of this step: read during the previous step
-                        __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0) only
-                        __builtin_amdgcn_sched_barrier(0);
-                        mfma_step_mem(fa[ks & 1], fb[ks & 1], ks, true, cur, ks + 1, fa[(ks + 1) & 1],
-                                      fb[(ks + 1) & 1], n_load_t{}, kt_issue, wr);
-                    } else {
-                        if constexpr (!LAST) wait_and_barrier<VM>();   // tile kt+1 landed; my reads of tile kt complete
-                        else __builtin_amdgcn_s_waitcnt(0xC07F);
-                        __builtin_amdgcn_sched_barrier(0);
-                        mfma_step_mem(fa[ks & 1], fb[ks & 1], ks, !LAST, nxt, 0, fa[0], fb[0], n_load_t{}, kt_issue, wr);
-                    }
-                }
-            };
-            int s_cur = S0, s_nxt = (S0 + 1) % NS, s_wr = (S0 + NS - 1) % NS;
-            auto rotate = [&]() {
-                s_wr = s_cur;
-                s_cur = s_nxt;
-                s_nxt = s_nxt + 1 == NS ? 0 : s_nxt + 1;
-            };
-            typedef std::true_type yes_t;
-            typedef std::false_type no_t;
-            wait_and_barrier<(NS - 2) * LPT>();     // tile 0 landed
-            read_frags(lds + S0 * STAGE, 0, fa[0], fb[0]);
-            for (int kt = 0; kt < KT - (NS - 1); ++kt) {
-                k_tile(lds + s_cur * STAGE, lds + s_nxt * STAGE, lds + s_wr * STAGE, kt + NS - 1,
-                       std::integral_constant<int, (NS - 3) * LPT + (KS - 1) * G::LPS>{}, yes_t{}, no_t{});
-                rotate();
-            }
-            // the last NS-1 tiles: nothing left to issue, fewer loads in flight
-            auto tail = [&](auto t_c) {
-                constexpr int t = decltype(t_c)::value;
-                if constexpr (t < NS - 1) {
-                    constexpr int younger = NS - 3 - t > 0 ? NS - 3 - t : 0;
-                    k_tile(lds + s_cur * STAGE, lds + s_nxt * STAGE, lds + s_wr * STAGE, 0,
-                           std::integral_constant<int, younger * LPT>{}, no_t{},
-                           std::integral_constant<bool, t == NS - 2>{});
-                    rotate();
-                }
-            };
-            tail(std::integral_constant<int, 0>{});
-            tail(std::integral_constant<int, 1>{});
-            tail(std::integral_constant<int, 2>{});
-            tail(std::integral_constant<int, 3>{});
-            static_assert(NS <= 5, "tail unrolling covers NS - 1 <= 4 tiles");
-        }
-    };
-
-    // ---- the same K loop with 16x16x32 MFMA blocks ----------------------------
-    // Measured on register operands with random data (the chip is power limited
+    //
+    // Ring of NS stages, tile kt in stage (S0 + kt) % NS.  The workgroup barrier
+    // sits before the second half of a tile's MFMAs, not after it: once every wave
+    // has issued (and received) all operand reads of tile kt, the stage of tile kt-1
+    // can be refilled and the first operands of tile kt+1 can be read, all while the
+    // matrix cores still work on tile kt.  The loop body is branch-free (the last
+    // NS-1 tiles are peeled off), which keeps the compiler's wait-count tracking
+    // exact.  Memory operations go one by one between the MFMAs: a wave issues in
+    // order, and a burst of reads or loads between two MFMAs leaves the matrix core
+    // idle, a single one does not.
+    //
+    // Why 16x16x32 blocks: measured on register operands with random data (the chip is power limited
     // there), v_mfma_f32_16x16x32_bf16 sustains 2130 TFLOP/s where
     // v_mfma_f32_32x32x16_bf16 sustains 1870: a quarter of the accumulator
     // registers move per instruction for half of the flops.  One MFMA covers
@@ -514,7 +391,7 @@ __global__ __launch_bounds__(G::NT, 1) void k_grouped_gemm(GemmArgs a) {
     // operands and the first A operands of the next tile (B is double
     // buffered in registers; tiles come in pairs so that the buffer index is a
     // compile-time constant: K % 64 == 0 makes the number of tiles even).
-    auto main_loop16 = [&](auto loader_c) {
+    auto main_loop = [&](auto loader_c) {
         constexpr bool LOADER = decltype(loader_c)::value;
         constexpr int NB16 = TN / 16, MBH = TM / 32;          // B blocks; A blocks per phase
         constexpr int SLOTS = NB16 * MBH;                      // MFMAs per phase
@@ -527,7 +404,7 @@ __global__ __launch_bounds__(G::NT, 1) void k_grouped_gemm(GemmArgs a) {
         // out in this order: during the tile that refills T's stage the CB loads
         // of B(T), during the next one A(T)[0], A(T+1)[0], A(T)[1], A(T+1)[1], ...
         // and then B(T+1).  (A(T) leaves one tile time later than otherwise.)
-        constexpr bool PAIR = SWIGLU && G::PAIR;
+        constexpr bool PAIR = SWIGLU;
         constexpr int PL0 = CB - CB / 2, PL1 = CB / 2;                       // even tile: B only
         constexpr int QL0 = (2 * CA + CB) - (2 * CA + CB) / 2, QL1 = (2 * CA + CB) / 2;   // odd tile
         // (at most one memory operation per MFMA in the default geometry; smaller
@@ -568,7 +445,8 @@ __global__ __launch_bounds__(G::NT, 1) void k_grouped_gemm(GemmArgs a) {
             for (int j = 0; j < NB16; ++j)
 #pragma unroll
                 for (int i = 0; i < MBH; ++i) {
-                    mfma16(fb[P][j], fa[PH][i], acc[j][PH * MBH + i]);
+                    acc[j][PH * MBH + i] =
+                        __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[P][j], fa[PH][i], acc[j][PH * MBH + i], 0, 0, 0);
                     const int idx = j * MBH + i;
                     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -662,8 +540,6 @@ __global__ __launch_bounds__(G::NT, 1) void k_grouped_gemm(GemmArgs a) {
     };
 
     // ---- epilogue: registers -> LDS patch -> 16-byte stores --------------------
-    // acc[j][i][v]: output row m = wm*TM + i*32 + l32,
-    //               B row n = wn*TN + j*32 + 8*(v/4) + 4*lh + v%4
     // The weight fragment is the first MFMA operand, so a lane holds four
     // consecutive output columns of one row (8-byte LDS writes).
     // `early` tiles of the NEXT output tile (pointers already set) are issued
@@ -681,69 +557,35 @@ __global__ __launch_bounds__(G::NT, 1) void k_grouped_gemm(GemmArgs a) {
         for (int ep = 0; ep < EP; ++ep) {
             if (ep > 0) lds_sync();                    // the previous pass has left the patch
             if ((wm * TM) / HB == ep) {
-                if constexpr (MI == 16) {
-                    // 16x16 blocks: acc[j][i][v] is output row wm*TM + i*16 + l16,
-                    // B row wn*TN + j*16 + 4*lq + v; B rows come in blocks of 32
-                    // rows of W1 then 32 rows of W3 (GEMM1), so 16-row block j
-                    // pairs with block j + 2
+                // 16x16 blocks: acc[j][i][v] is output row wm*TM + i*16 + l16,
+                // B row wn*TN + j*16 + 4*lq + v; B rows come in blocks of 32
+                // rows of W1 then 32 rows of W3 (GEMM1), so 16-row block j
+                // pairs with block j + 2
 #pragma unroll
-                    for (int i = 0; i < MBX; ++i) {
-                        const int m = wm * TM + i * 16 + l16 - ep * HB;
-                        char *orow = patch + m * OUT_STRIDE;
-                        if constexpr (SWIGLU) {
-#pragma unroll
-                            for (int jp = 0; jp < NBX / 2; ++jp) {
-                                const int jg = (jp / 2) * 4 + jp % 2;             // silu's argument
-                                const int c0 = (wn * TN) / 2 + (jp / 2) * 32 + (jp % 2) * 16 + 4 * lq;
-                                bf16x4 o;
-#pragma unroll
-                                for (int q = 0; q < 4; ++q)
-                                    o[q] = (bf16_t)(fast_silu(acc[jg][i][q]) * acc[jg + 2][i][q]);
-                                *reinterpret_cast<bf16x4 *>(orow + c0 * 2) = o;
-                            }
-                        } else {
-#pragma unroll
-                            for (int j = 0; j < NBX; ++j) {
-                                const int c0 = wn * TN + j * 16 + 4 * lq;
-                                bf16x4 o;
-#pragma unroll
-                                for (int q = 0; q < 4; ++q) o[q] = (bf16_t)acc[j][i][q];
-                                *reinterpret_cast<bf16x4 *>(orow + c0 * 2) = o;
-                            }
-                        }
-                    }
-                } else {
-#pragma unroll
-                for (int i = 0; i < MB; ++i) {
-                    const int m = wm * TM + i * 32 + l32 - ep * HB;
+                for (int i = 0; i < MBX; ++i) {
+                    const int m = wm * TM + i * 16 + l16 - ep * HB;
                     char *orow = patch + m * OUT_STRIDE;
                     if constexpr (SWIGLU) {
 #pragma unroll
-                        for (int j = 0; j < NB; j += 2) {
-                            const int c0 = (wn * TN + j * 32) / 2 + 4 * lh;   // 32 columns per block pair
+                        for (int jp = 0; jp < NBX / 2; ++jp) {
+                            const int jg = (jp / 2) * 4 + jp % 2;             // silu's argument
+                            const int c0 = (wn * TN) / 2 + (jp / 2) * 32 + (jp % 2) * 16 + 4 * lq;
+                            bf16x4 o;
 #pragma unroll
-                            for (int g = 0; g < 4; ++g) {
-                                bf16x4 o;
-#pragma unroll
-                                for (int q = 0; q < 4; ++q)
-                                    o[q] = (bf16_t)(fast_silu(acc[j][i][4 * g + q]) * acc[j + 1][i][4 * g + q]);
-                                *reinterpret_cast<bf16x4 *>(orow + (c0 + 8 * g) * 2) = o;
-                            }
+                            for (int q = 0; q < 4; ++q)
+                                o[q] = (bf16_t)(fast_silu(acc[jg][i][q]) * acc[jg + 2][i][q]);
+                            *reinterpret_cast<bf16x4 *>(orow + c0 * 2) = o;
                         }
                     } else {
 #pragma unroll
-                        for (int j = 0; j < NB; ++j) {
-                            const int c0 = wn * TN + j * 32 + 4 * lh;
+                        for (int j = 0; j < NBX; ++j) {
+                            const int c0 = wn * TN + j * 16 + 4 * lq;
+                            bf16x4 o;
 #pragma unroll
-                            for (int g = 0; g < 4; ++g) {
-                                bf16x4 o;
-#pragma unroll
-                                for (int q = 0; q < 4; ++q) o[q] = (bf16_t)acc[j][i][4 * g + q];
-                                *reinterpret_cast<bf16x4 *>(orow + (c0 + 8 * g) * 2) = o;
-                            }
+                            for (int q = 0; q < 4; ++q) o[q] = (bf16_t)acc[j][i][q];
+                            *reinterpret_cast<bf16x4 *>(orow + c0 * 2) = o;
                         }
                     }
-                }
                 }
             }
             lds_sync();
@@ -792,35 +634,26 @@ __global__ __launch_bounds__(G::NT, 1) void k_grouped_gemm(GemmArgs a) {
             // the tile just finished (and never used): no branch around a
             // load, so the compiler adds no wait for one.
             int n_e = e, n_row0 = row0, n_row_end = row_end, n_nt = nt;
-            bool more = false;
-            if constexpr (G::PERSIST) {
-                j += a.jstride;
-                more = locate(j, n_e, n_row0, n_row_end, n_nt);
-                if constexpr (LOADER) gather_rows(n_row0, n_row_end, src);
-            }
+            j += a.jstride;
+            const bool more = locate(j, n_e, n_row0, n_row_end, n_nt);
+            if constexpr (LOADER) gather_rows(n_row0, n_row_end, src);
 #pragma unroll
             for (int jj = 0; jj < NBX; ++jj)
 #pragma unroll
                 for (int i = 0; i < MBX; ++i)
 #pragma unroll
-                    for (int v = 0; v < (int)(sizeof(acc_t) / sizeof(float)); ++v) acc[jj][i][v] = 0.f;
-            if constexpr (MI == 16) main_loop16(loader_c);
-            else main_loop(loader_c);
+                    for (int v = 0; v < 4; ++v) acc[jj][i][v] = 0.f;
+            main_loop(loader_c);
             __syncthreads();                    // all waves done reading the stages
-            if constexpr (!G::PERSIST) {
-                epilogue(lds, lds, std::integral_constant<int, 0>{});
-                return;
-            } else {
-                // The first K tiles of the next output tile go out before the
-                // epilogue, into the stages the epilogue does not use, the
-                // others after it.
-                if constexpr (LOADER) set_pointers(n_e, n_nt, src);
-                epilogue(lds, lds, std::integral_constant<int, LOADER ? EARLY : 0>{});
-                if (!more) break;
-                lds_sync();                     // the epilogue has left its LDS patch
-                if constexpr (LOADER) issue_range(EARLY, NS - 1, lds);
-                e = n_e; row0 = n_row0; row_end = n_row_end; nt = n_nt;
-            }
+            // The first K tiles of the next output tile go out before the
+            // epilogue, into the stages the epilogue does not use, the
+            // others after it.
+            if constexpr (LOADER) set_pointers(n_e, n_nt, src);
+            epilogue(lds, lds, std::integral_constant<int, LOADER ? EARLY : 0>{});
+            if (!more) break;
+            lds_sync();                     // the epilogue has left its LDS patch
+            if constexpr (LOADER) issue_range(EARLY, NS - 1, lds);
+            e = n_e; row0 = n_row0; row_end = n_row_end; nt = n_nt;
         }
         // loads into LDS must not outlive the workgroup
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -833,11 +666,26 @@ __global__ __launch_bounds__(G::NT, 1) void k_grouped_gemm(GemmArgs a) {
     }
 }
 
+// TAILG: geometry (half the tile height of G) that takes over a sparsely filled last
+// round of G's tiles in the same launch; void: none.
+template <class G, bool SWIGLU, class TAILG, bool RAG, bool STREAM>
+__global__ __launch_bounds__(G::NT, G::PER_CU) void k_grouped_gemm(GemmArgs a) {
+    constexpr bool HAS_TAIL = !std::is_void<TAILG>::value;
+    typedef typename std::conditional<HAS_TAIL, TAILG, G>::type TG;
+    constexpr int B0 = Epilogue<G, SWIGLU>::LDS_BYTES, B1 = Epilogue<TG, SWIGLU>::LDS_BYTES;
+    __shared__ __attribute__((aligned(16))) char lds[B0 > B1 ? B0 : B1];
+    // (2 TailG::BM == G::BM: the tail numbers the same tiles)
+    const GroupTiles gt = group_tiles(a, threadIdx.x % kWave, G::BM);
+    gemm_tiles<G, SWIGLU, false, RAG, STREAM>(a, gt, lds);
+    if constexpr (HAS_TAIL) {
+        __syncthreads();                       // every wave has left the LDS
+        gemm_tiles<TG, SWIGLU, true, RAG, STREAM>(a, gt, lds);
+    }
+}
+
 bool ffn_mfma_supported(const Dims &d) { return d.D % 64 == 0 && d.F % 64 == 0; }
 
-// TAILG: geometry (half the tile height of G) of a second launch that takes
-// over a sparsely filled last round of G's tiles; void: none.
-template <class G, class TAILG = void, bool RAG = false>
+template <class G, class TAILG = void, bool RAG = false, bool STREAM = false>
 static hipError_t launch_cfg(const FfnArgs &f, int which, hipStream_t s) {
     GemmArgs a;
     a.offsets = f.offsets;
@@ -871,47 +719,41 @@ static hipError_t launch_cfg(const FfnArgs &f, int which, hipStream_t s) {
     long long blocks = (max_mtiles * a.n_ntiles + rnd - 1) / rnd * rnd;
     if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
     if (!RAG && a.K / G::BK < G::NS - 1) return hipErrorInvalidConfiguration;   // the ring starts with NS-1 K tiles in flight
-    a.jstride = 0;
-    if (G::PERSIST) {
-        // one workgroup per CU (the LDS ring fills a CU), a multiple of 8 so that
-        // workgroup w runs on XCD w % 8 and owns tiles w/8, w/8 + jstride, ...
-        static int n_cu = 0;
-        if (n_cu == 0) {
-            int dev = 0, v = 0;
-            if (hipGetDevice(&dev) != hipSuccess ||
-                hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || v < 8)
-                v = 256;
-            n_cu = v / 8 * 8;
-        }
-        if (blocks > n_cu) blocks = n_cu;
-        a.jstride = (int)(blocks / 8);
+    // as many workgroups as the CUs hold, a multiple of 8 so that workgroup w runs on XCD
+    // w % 8 and owns tiles w/8, w/8 + jstride, ...
+    static int n_cu = 0;
+    if (n_cu == 0) {
+        int dev = 0, v = 0;
+        if (hipGetDevice(&dev) != hipSuccess ||
+            hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || v < 8)
+            v = 256;
+        n_cu = v / 8 * 8;
     }
-    dim3 grid((unsigned)blocks), block(G::NT);
+    if (blocks > (long long)n_cu * G::PER_CU) blocks = (long long)n_cu * G::PER_CU;
+    a.jstride = (int)(blocks / 8);
+    const dim3 grid((unsigned)blocks), block(G::NT);
     a.cut_grid = 0;
-    bool tail = false;
     if constexpr (!std::is_void<TAILG>::value) {
-        static_assert(G::PERSIST && TAILG::PERSIST && 2 * TAILG::BM == G::BM && TAILG::BN == G::BN &&
-                          TAILG::BK == G::BK && TAILG::NS == G::NS,
-                      "the tail launch halves the tiles of the main launch");
-        // With few rounds a sparsely filled last one is worth a second launch
-        // (measured: +6 to +12 % at 3 - 5 rounds, +2 % at 13); with many it
-        // costs little, the few busy CUs also clock higher (nothing at 36).
-        // The host knows an upper bound of the number of rounds only.
-        tail = max_mtiles * a.n_ntiles < 24 * blocks;
-        if (tail) a.cut_grid = (int)blocks;
+        static_assert(2 * TAILG::BM == G::BM && TAILG::BN == G::BN &&
+                          TAILG::BK == G::BK && TAILG::NS == G::NS && TAILG::NT == G::NT,
+                      "the tail halves the tiles");
+        // With few rounds a sparsely filled last one is worth splitting (measured: +6 to
+        // +12 % at 3 - 5 rounds, +2 % at 13); with many it costs little, the few busy CUs
+        // also clock higher (nothing at 36).  The host knows an upper bound of the number
+        // of rounds only.
+        if (max_mtiles * a.n_ntiles < 24 * blocks) {
+            a.cut_grid = (int)blocks;
+            if (which == 0)
+                hipLaunchKernelGGL((k_grouped_gemm<G, true, TAILG, RAG, STREAM>), grid, block, 0, s, a);
+            else
+                hipLaunchKernelGGL((k_grouped_gemm<G, false, TAILG, RAG, STREAM>), grid, block, 0, s, a);
+            return hipGetLastError();
+        }
     }
     if (which == 0)
-        hipLaunchKernelGGL((k_grouped_gemm<G, true, false, RAG>), grid, block, 0, s, a);
+        hipLaunchKernelGGL((k_grouped_gemm<G, true, void, RAG, STREAM>), grid, block, 0, s, a);
     else
-        hipLaunchKernelGGL((k_grouped_gemm<G, false, false, RAG>), grid, block, 0, s, a);
-    if constexpr (!std::is_void<TAILG>::value) if (tail) {
-        // same grid and numbering; a workgroup finds at most one half tile, none
-        // when the main launch kept its last round
-        if (which == 0)
-            hipLaunchKernelGGL((k_grouped_gemm<TAILG, true, true>), grid, dim3(TAILG::NT), 0, s, a);
-        else
-            hipLaunchKernelGGL((k_grouped_gemm<TAILG, false, true>), grid, dim3(TAILG::NT), 0, s, a);
-    }
+        hipLaunchKernelGGL((k_grouped_gemm<G, false, void, RAG, STREAM>), grid, block, 0, s, a);
     return hipGetLastError();
 }
 
@@ -919,21 +761,44 @@ hipError_t launch_ffn_mfma(const FfnArgs &f, int which, hipStream_t s) {
     if (f.d.T == 0 || f.d.n_ffn == 0) return hipSuccess;
     // Default: 256x256 tile, 8 waves of which the first 4 issue the tile loads,
     // 16x16x32 MFMA blocks, persistent workgroups, 32-deep K stages in a ring
-    // of 5 (the whole 160 KB of LDS), which needs at least 4 K tiles; shorter
-    // reductions use two 64-deep stages.
+    // of 5 (the whole 160 KB of LDS), which needs at least 4 K tiles.
+    typedef Geo<256, 256, 2, 4, 32, 5, 4> Full;
+    typedef Geo<128, 256, 2, 4, 32, 5, 4> Half;
+    // 128x128 tiles, four waves, two workgroups per CU: twice the operand bytes per flop of
+    // Full, four times as many workgroups.
+    typedef Geo<128, 128, 2, 2, 32, 5> Small;
     const int K = which == 0 ? f.d.D : f.d.F;
+    const long long slots = (long long)f.d.T * f.d.k;
+    const bool ragged = f.d.D % 64 != 0 || f.d.F % 64 != 0 || K < 128;
+    // Few rows per expert (small batches): the GEMMs only stream the weights, so use
+    // 128-row tiles: half of the (mostly wasted) matrix work of a 256-row tile per byte
+    // of weights, bound by HBM instead.
+    const bool few = ragged || slots <= 128ll * f.d.n_ffn;
+    // How many tiles that makes if the router spreads its slots evenly.
+    const int bm = few ? 128 : 256;
+    const long long rows = slots / f.d.N + 1;
+    const long long n_tiles = (rows + bm - 1) / bm * f.d.n_ffn * (((which == 0 ? 2ll * f.d.F : f.d.D) + 255) / 256);
+    // Small tiles where the others leave the chip half empty.  GEMM2, us with / without:
+    // 48 tiles 18 / 31 (T = 300, D = 768), 64 tiles 21 / 31 (T = 200, D = 1024), 96 tiles 47 / 64
+    // (T = 400, D = 1536); Full, whose last round of up to 128 tiles runs as halves: 48 tiles
+    // 20 / 31 (T = 1500, D = 768), but 96 tiles 33 / 32 and 44 / 38 (T = 4096, D = 768, 16 and 32
+    // experts); 192 tiles, one round without halves, 50 / 54 (T = 8192, D = 1024); 256 tiles 40 / 41.
+    const bool small = few ? n_tiles <= 128 : n_tiles <= 64 || (n_tiles > 128 && n_tiles <= 208);
     // Widths that are not multiples of 64, and reductions too short for the ring's four
-    // K tiles: the same kernel with the K loop padded by zeros.
-    if (f.d.D % 64 != 0 || f.d.F % 64 != 0 || K < 128)
-        return launch_cfg<Geo<128, 256, 2, 4, 32, 5, 4, true, 16>, void, true>(f, which, s);
-    // Few rows per expert (decoding, small batches): the GEMMs only stream
-    // the weights, so use 128-row tiles: half of the (mostly wasted)
-    // matrix work of a 256-row tile per byte of weights, bound by HBM instead.
-    if ((long long)f.d.T * f.d.k <= 128ll * f.d.n_ffn)
-        return launch_cfg<Geo<128, 256, 1, 4, 32, 5, 0, true>>(f, which, s);
-    if (f.no_tail) return launch_cfg<Geo<256, 256, 2, 4, 32, 5, 4, true, 16>>(f, which, s);
-    return launch_cfg<Geo<256, 256, 2, 4, 32, 5, 4, true, 16>, Geo<128, 256, 2, 4, 32, 5, 4, true, 16>>(
-        f, which, s);
+    // K tiles: the K loop is padded by zeros.
+    if (ragged)
+        return small ? launch_cfg<Small, void, true>(f, which, s) : launch_cfg<Half, void, true>(f, which, s);
+    // The weights past the caches (non-temporal) where each is read by one tile and they do not
+    // fit the 256 MB memory-side cache anyway.  T = 777, D = 4096, F = 5632: 251 and 124 us
+    // against 262 and 133, and the layer's other operands stay cached (router 20.7 -> 19.9,
+    // combine 13.6 -> 11.1 us); T = 400, D = 1536, F = 4096 (604 MB): GEMM1 77 / 83, GEMM2 42 / 47.
+    // At 151 - 201 MB, called again and again: 32 against 23 us.
+    const bool stream = few && 6.0 * f.d.n_ffn * f.d.D * f.d.F > 256.0 * (1 << 20);
+    if (f.no_tail) return few ? launch_cfg<Half>(f, which, s) : launch_cfg<Full>(f, which, s);
+    if (small)
+        return stream ? launch_cfg<Small, void, false, true>(f, which, s) : launch_cfg<Small>(f, which, s);
+    if (few) return stream ? launch_cfg<Half, void, false, true>(f, which, s) : launch_cfg<Half>(f, which, s);
+    return launch_cfg<Full, Half>(f, which, s);
 }
 
 }  // namespace moepp

@@ -59,3 +59,19 @@ def test_router(T, D, n_ffn, n_const, k):
     cap = L.capacity(T, 1.1, 0.75)
     res = gpu_forward(s, inp, layer=L, cap=cap, balance_tau=0.75)
     print("  ", s, check_layer(s, inp, res, cap=np.array(cap, np.int32), balance_tau=0.75), flush=True)
+
+
+# tile geometries of the bf16 FFN: 128x128 tiles (few tiles, or one round of 129 - 208 large
+# ones), half tiles as the rest of a launch of large ones, weights past the caches (more than
+# 256 MB of them), group sizes around the tile heights
+@pytest.mark.parametrize("T,D,F,n_ffn,bias", [(40, 192, 320, 3, "none"), (300, 320, 192, 2, "normal"),
+                                              (1300, 256, 256, 4, "normal"), (2600, 1024, 128, 16, "none"),
+                                              (3000, 704, 1408, 5, "normal"), (700, 3072, 448, 33, "normal"),
+                                              (1500, 64, 1000, 7, "none")])
+def test_bf16_tile_geometries(T, D, F, n_ffn, bias):
+    check(T=T, D=D, F=F, n_ffn=n_ffn, bias=bias)
+
+
+@pytest.mark.parametrize("T", [130, 600])
+def test_bf16_streamed_weights(T):
+    check(T=T, D=1536, F=4096, n_ffn=8)
