@@ -216,20 +216,22 @@ __global__ __launch_bounds__(kRouterWaves *kWave) void k_router_small_final(Rout
 // logits (gating residual, bias) with all threads, does softmax / Top-K / a1 with
 // four threads per token, and then groups the T*k selections, which it still
 // holds in LDS, by expert like k_perm_small does.
+// (PER: router_token_quad)
+template <int PER>
 __global__ __launch_bounds__(kPermSmallWaves *kWave) void k_router_small_final_perm(RouterArgs a, int n_splits,
                                                                                   const float *partial, Workspace w,
                                                                                   CapArgs cap) {
     constexpr int NT = kPermSmallWaves * kWave;
-    constexpr int DSTR = kMaxRouterRows + 1;
+    constexpr int DSTR = kMaxRouterRows + 1, MAXN = 4 * PER;
     __shared__ float dots[kRouterFusedT * DSTR];
-    __shared__ float prevs[kRouterFusedT * (kMaxExperts + 1)];
-    __shared__ float wres[kMaxExperts * kMaxExperts];
-    __shared__ float sbias[kMaxExperts];
+    __shared__ __attribute__((aligned(16))) float prevs[kRouterFusedT * (MAXN + 4)];
+    __shared__ __attribute__((aligned(16))) float wres[MAXN * (MAXN + 4)];
+    __shared__ float sbias[MAXN];
     __shared__ int s_idx[kRouterFusedT * kMaxTopK];
     __shared__ int s_rank[kPermSmallWaves][kMaxExperts];
     __shared__ int s_first[kMaxExperts], s_limit[kMaxExperts];
     const int tid = threadIdx.x;
-    const int T = a.d.T, N = a.d.N, K = a.d.k, rows = N + 2 * a.d.n_const;
+    const int T = a.d.T, N = a.d.N, K = a.d.k, rows = N + 2 * a.d.n_const, rs = residual_stride(N);
     for (int c = tid; c < T * rows; c += NT) {
         // element c = (token c / rows, row c % rows) of every slice; all loads first, then the sum in slice order
         float v[kRsSplits];
@@ -241,24 +243,28 @@ __global__ __launch_bounds__(kPermSmallWaves *kWave) void k_router_small_final_p
         dots[(c / rows) * DSTR + c % rows] = sum;
     }
     if (a.prev_gate) {
-        for (int c = tid; c < T * N; c += NT) prevs[(c / N) * (kMaxExperts + 1) + c % N] = a.prev_gate[c];
-        for (int c = tid; c < N * N; c += NT) wres[c] = a.W_res[c];
+        for (int c = tid; c < T * N; c += NT) prevs[(c / N) * rs + c % N] = a.prev_gate[c];
+        for (int c = tid; c < N * N; c += NT) wres[(c / N) * rs + c % N] = a.W_res[c];
+        zero_residual_pad(prevs, T, N, NT);
+        zero_residual_pad(wres, N, N, NT);
     }
     if (tid < N) sbias[tid] = a.bias ? a.bias[tid] : 0.f;
     __syncthreads();
+    // consecutive threads: consecutive tokens of one row of W_res, or, with fewer tokens than
+    // that is worth, consecutive rows of one token; the padded rows keep both off one bank
     for (int c = tid; c < T * N; c += NT) {
-        const int tt = c / N, i = c % N;
+        const int tt = T >= 16 ? c % T : c / N, i = T >= 16 ? c / T : c % N;
         float L = dots[tt * DSTR + i];
         if (a.prev_gate) {
-            const float *pr = prevs + tt * (kMaxExperts + 1);
-            const float *wr = wres + i * N;
-            float r = 0.f;
-            for (int m = 0; m < N; ++m) r = fmaf(wr[m], pr[m], r);
-            L += r;
+            f32x4 pv[MAXN / 4];
+#pragma unroll
+            for (int m = 0; m < MAXN / 4; ++m)
+                if (4 * m < N) pv[m] = *reinterpret_cast<const f32x4 *>(prevs + tt * rs + 4 * m);
+            L += gating_residual<MAXN>(wres + i * rs, pv, N);
         }
         L += sbias[i];
         dots[tt * DSTR + i] = L;        // only this thread reads or writes the element
-        a.out_gate[c] = L;
+        a.out_gate[(size_t)tt * N + i] = L;
     }
     __syncthreads();
     {
@@ -266,7 +272,7 @@ __global__ __launch_bounds__(kPermSmallWaves *kWave) void k_router_small_final_p
         // compute on the last token and store nothing
         const int tok = tid >> 2;
         const int tk = tok < T ? tok : T - 1;
-        router_token_quad<kMaxExperts / 4>(a, (size_t)tk, tok < T, tid & 3, dots + tk * DSTR, nullptr, s_idx + tk * K);
+        router_token_quad<PER>(a, (size_t)tk, tok < T, tid & 3, dots + tk * DSTR, nullptr, s_idx + tk * K);
     }
     __syncthreads();
     perm_small_body(a.d, w, cap, s_idx, s_rank, s_first, s_limit);
@@ -364,8 +370,13 @@ hipError_t launch_router_small(const RouterArgs &a, bool bf16, hipStream_t s, co
     if (e != hipSuccess) return e;
     if (perm_ws) {
         if (a.d.T > kRouterFusedT || perm_cap == nullptr) return hipErrorInvalidValue;
-        hipLaunchKernelGGL(k_router_small_final_perm, dim3(1), dim3(kPermSmallWaves * kWave), 0, s, a, n_splits,
-                           a.partial, *perm_ws, *perm_cap);
+        auto go = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3(1), dim3(kPermSmallWaves * kWave), 0, s, a, n_splits, a.partial, *perm_ws,
+                               *perm_cap);
+        };
+        if (a.d.N <= 20) go(k_router_small_final_perm<5>);
+        else if (a.d.N <= 32) go(k_router_small_final_perm<8>);
+        else go(k_router_small_final_perm<kMaxExperts / 4>);
         return hipGetLastError();
     }
     hipLaunchKernelGGL(k_router_small_final, dim3((a.d.T + kRouterWaves - 1) / kRouterWaves),
