@@ -75,3 +75,12 @@ def test_bf16_tile_geometries(T, D, F, n_ffn, bias):
 @pytest.mark.parametrize("T", [130, 600])
 def test_bf16_streamed_weights(T):
     check(T=T, D=1536, F=4096, n_ffn=8)
+
+
+# weight-streaming FFN: one fragment per workgroup in GEMM2 (few experts), two; several units per
+# workgroup; both sides of T k = 8 N and 16 n_ffn; the few-token router's one-workgroup end with
+# 1 .. 64 tokens; a combine in pieces of a token
+@pytest.mark.parametrize("T", [1, 2, 15, 16, 17, 32, 33, 63, 64])
+@pytest.mark.parametrize("D,F,n_ffn", [(256, 512, 4), (1280, 256, 12), (512, 2048, 33)])
+def test_bf16_few_rows(T, D, F, n_ffn):
+    check(T=T, D=D, F=F, n_ffn=n_ffn, bias="normal")
