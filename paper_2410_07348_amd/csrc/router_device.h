@@ -126,16 +126,27 @@ __device__ inline void router_finish(const RouterArgs &a, int t0, float *dots, f
                 for (int m = 0; m < MAXN / 4; ++m)
                     if (4 * m < N) pv[m] = *reinterpret_cast<const f32x4 *>(prevs + tt * rs + 4 * m);
             }
-            for (int i = i0; i < rows; i += STEP) {
-                float L = dots[tt * DSTR + i];
+            // all dot products first: the writes below would order the reads of the next row behind them
+            constexpr int PER = (ROWS + STEP - 1) / STEP;
+            float L[PER];
 #pragma unroll
-                for (int g = 1; g < G; ++g) L += dots[(g * TOK + tt) * DSTR + i];
-                if (i < N) {
-                    if (a.prev_gate) L += gating_residual<MAXN>(wres + i * rs, pv, N);
-                    L += sbias[i];
-                }
-                dots[tt * DSTR + i] = L;
+            for (int u = 0; u < PER; ++u) {
+                const int i = min(i0 + u * STEP, rows - 1);
+                L[u] = dots[tt * DSTR + i];
+#pragma unroll
+                for (int g = 1; g < G; ++g) L[u] += dots[(g * TOK + tt) * DSTR + i];
             }
+#pragma unroll
+            for (int u = 0; u < PER; ++u) {
+                const int i = i0 + u * STEP;
+                if (i < N) {
+                    if (a.prev_gate) L[u] += gating_residual<MAXN>(wres + i * rs, pv, N);
+                    L[u] += sbias[i];
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < PER; ++u)
+                if (i0 + u * STEP < rows) dots[tt * DSTR + i0 + u * STEP] = L[u];
         }
     }
     __syncthreads();

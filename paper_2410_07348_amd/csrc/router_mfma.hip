@@ -100,16 +100,24 @@ __global__ __launch_bounds__(4 * TOK * KG, WPE) void k_router_mfma(RouterArgs a)
     }
     // Weight chunk c = tid + threads i: row c / 16, floats 4 (c % 16) .. + 3 of the
     // tile's 64 columns, read as float32 from W (router rows) or W_c (the rows after
-    // them) and split into three bf16 pieces on the way into LDS; rows past the
-    // last are never loaded (their LDS rows are zeroed once, below).
+    // them) and split into three bf16 pieces on the way into LDS.  Dot products of rows
+    // past the last are never read.  A load that only some threads issue sits behind a
+    // branch, and after its join the compiler waits for more loads than it has to: with
+    // two row blocks, or slices, every thread loads, the last row where there is none
+    // (T = 4096, 52 rows: 21.0 -> 19.7 us, T = 777, D = 4096: 19.9 -> 18.8); with one row block in
+    // one kernel the extra loads cost what the waits do (T = 8192: 12.6 against 13.0).
+    constexpr bool ALL = NBLK > 1 || SPLIT;
+    static_assert(WCH % kRtThreads == 0, "whole weight chunks per thread");
     const float *pw[WL];
-    int w_lds[WL];                                         // LDS offset of the chunk's hi piece; -1: no chunk
+    int w_lds[WL];                                         // LDS offset of the chunk's hi piece
+    bool w_in[WL];
 #pragma unroll
     for (int i = 0; i < WL; ++i) {
-        const int c = tid + kRtThreads * i, r = c / 16, kq = c % 16;
-        const bool act = r < rows;
-        pw[i] = (!act ? a.W_g : r < N ? a.W_g + (size_t)r * D : a.W_c + (size_t)(r - N) * D) + kq * 4;
-        w_lds[i] = act ? r * kRtRow + ((((kq >> 1) ^ rt_swz(r)) << 4) | ((kq & 1) << 3)) : -1;
+        const int c = tid + kRtThreads * i, row = c / 16, kq = c % 16;
+        w_in[i] = ALL || row < rows;
+        const int r = row < rows ? row : rows - 1;
+        pw[i] = (r < N ? a.W_g + (size_t)r * D : a.W_c + (size_t)(r - N) * D) + kq * 4;
+        w_lds[i] = row * kRtRow + ((((kq >> 1) ^ rt_swz(row)) << 4) | ((kq & 1) << 3));
     }
     bf16x8 xr[PF][2];
     f32x4 wr[PF][WL];
@@ -128,7 +136,7 @@ __global__ __launch_bounds__(4 * TOK * KG, WPE) void k_router_mfma(RouterArgs a)
             xq[i] = __builtin_nontemporal_load(reinterpret_cast<const bf16x8 *>(px[i] + (size_t)kt * (kRtBK * 2)));
 #pragma unroll
         for (int i = 0; i < WL; ++i)
-            if (w_lds[i] >= 0) wq[i] = *reinterpret_cast<const f32x4 *>(pw[i] + (size_t)kt * kRtBK);
+            if (w_in[i]) wq[i] = *reinterpret_cast<const f32x4 *>(pw[i] + (size_t)kt * kRtBK);
     };
     typedef bf16_t bf16x4 __attribute__((ext_vector_type(4)));
     auto store_regs = [&](char *stage, const bf16x8 *xq, const f32x4 *wq) {
@@ -137,7 +145,7 @@ __global__ __launch_bounds__(4 * TOK * KG, WPE) void k_router_mfma(RouterArgs a)
             *reinterpret_cast<bf16x8 *>(stage + (tid + kRtThreads * i) * 16) = xq[i];
 #pragma unroll
         for (int i = 0; i < WL; ++i)
-            if (w_lds[i] >= 0) {
+            if (w_in[i]) {
                 // w = hi + mid + lo exactly: 3 x 8 significand bits cover float32's 24
                 bf16x4 hi, mid, lo;
 #pragma unroll
@@ -155,14 +163,6 @@ __global__ __launch_bounds__(4 * TOK * KG, WPE) void k_router_mfma(RouterArgs a)
                 *reinterpret_cast<bf16x4 *>(p + 2 * PIECE) = lo;
             }
     };
-    // weight rows past the last one: zero in both stages, never written again
-    for (int c = tid; c < 2 * 3 * (ROWS - rows) * (kRtRow / 16); c += kRtThreads) {
-        const int st = c / (3 * (ROWS - rows) * (kRtRow / 16)), q = c % (3 * (ROWS - rows) * (kRtRow / 16));
-        const int pc = q / ((ROWS - rows) * (kRtRow / 16)), o = q % ((ROWS - rows) * (kRtRow / 16));
-        *reinterpret_cast<f32x4 *>(glds + st * STAGE + kRtXBytes + pc * PIECE + rows * kRtRow + o * 16) =
-            f32x4{0.f, 0.f, 0.f, 0.f};
-    }
-
     f32x16 acc_hi[NBLK], acc_lo[NBLK];
 #pragma unroll
     for (int b = 0; b < NBLK; ++b)
