@@ -313,7 +313,7 @@ moepp_status moepp_get_balance(moepp_ctx *ctx, const float **f, const float **P,
 
 /*
  * Kernel-variant selection, for tests and tuning: 0 = automatic (default;
- * calls with at most 256 tokens use a router that splits the reduction over
+ * calls with at most 64 tokens use a router that splits the reduction over
  * D across workgroups, in plain fp32 FMA, for either activation type),
  * 1 = force the generic kernels (any supported shape, plain fp32 FMA),
  * 2 = require the MFMA kernels (EUNSUPPORTED at call time if the shape or

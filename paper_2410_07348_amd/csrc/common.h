@@ -15,10 +15,8 @@ constexpr int kMaxTopK = 8;       // K
 constexpr int kMaxConst = 8;      // constant experts
 constexpr int kWave = 64;         // CDNA wavefront
 
-// Calls with at most this many tokens take the router that splits the
-// reduction over D across workgroups.
-constexpr int kRouterSmallT = 256;
-// ... and up to this many its second kernel also does the permutation
+// Calls with at most this many tokens take the FMA router that splits the reduction
+// over D across workgroups and does the permutation in its second kernel.
 constexpr int kRouterFusedT = 64;
 
 // Permutation: one wave owns a chunk of consecutive slots: kPermChunk of them,
@@ -158,11 +156,11 @@ struct CombineArgs {
 // Launchers (each returns hipGetLastError() after its launches).
 // `bf16` selects the activation type; `which` selects GEMM1 / GEMM2.
 hipError_t launch_router_generic(const RouterArgs &a, bool bf16, hipStream_t s);
-// T <= kRouterSmallT only.  With perm_ws (T <= kRouterFusedT only) the second kernel also
-// does the permutation of the call's T*k slots (counts, kept, offsets, row_of, src_of of
-// *perm_ws, capacities *perm_cap), as launch_perm_small would.
-hipError_t launch_router_small(const RouterArgs &a, bool bf16, hipStream_t s, const Workspace *perm_ws = nullptr,
-                               const CapArgs *perm_cap = nullptr);
+// T <= kRouterFusedT only.  The second kernel also does the permutation of the call's T*k
+// slots (counts, kept, offsets, row_of, src_of of perm_ws, capacities perm_cap), as
+// launch_perm_small would.
+hipError_t launch_router_small(const RouterArgs &a, bool bf16, hipStream_t s, const Workspace &perm_ws,
+                               const CapArgs &perm_cap);
 // More tokens, any width and type, while router_split_max(d) >= 1; leaves the histogram of
 // the permutation (chunks of kRouterSlicedTok tokens) and the statistics' sums like the
 // matrix-core router.

@@ -199,18 +199,16 @@ moepp_status do_route(moepp_ctx *c, hipStream_t s, int T, const void *x, const f
     KernelTimer kt(c, s, MOEPP_K_ROUTER);
     const bool bf16 = c->desc.act == MOEPP_BF16;
     hipError_t e;
-    const bool sliced = !mfma && c->variant == 0 && router_split_max(a.d) >= 1;
+    const bool sliced = c->variant == 0 && !mfma && router_split_max(a.d) >= 1;
     if (c->variant == 0 && T <= kRouterFusedT) {
         // a handful of tokens: the router's second kernel also groups the slots by expert
-        e = launch_router_small(a, bf16, s, &c->ws, &c->cap);
+        e = launch_router_small(a, bf16, s, c->ws, c->cap);
         c->perm_valid = e == hipSuccess;
         c->perm_T = T;
         c->perm_k = k;
-    } else if (c->variant == 0 && T <= kRouterSmallT) {
-        e = launch_router_small(a, bf16, s);
     } else if (mfma || sliced) {
         // the router counts its selections, per block of tokens, for the permutation
-        const int tok = mfma ? router_mfma_block_tokens(a.d) : kRouterSlicedTok;
+        const int tok = sliced ? kRouterSlicedTok : router_mfma_block_tokens(a.d);
         a.chunk_hist = c->ws.chunk_hist;
         c->hist_valid = true;
         c->hist_T = T;
@@ -223,7 +221,7 @@ moepp_status do_route(moepp_ctx *c, hipStream_t s, int T, const void *x, const f
             c->bal_rows = wgs;
             c->bal_T = T;
         }
-        e = mfma ? launch_router_mfma(a, s) : launch_router_sliced(a, bf16, s);
+        e = sliced ? launch_router_sliced(a, bf16, s) : launch_router_mfma(a, s);
     } else {
         e = launch_router_generic(a, bf16, s);
     }

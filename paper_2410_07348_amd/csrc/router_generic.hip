@@ -113,7 +113,8 @@ __global__ __launch_bounds__(kRouterWaves *kWave) void k_router_generic(RouterAr
 // load rate.  Here the reduction over D is cut into up to kRsSplits slices:
 // workgroup (slice, token block) writes the partial dot products of its slice,
 // and a second kernel adds the slices of a token in slice order (the result is
-// the same on every run) and finishes as above.  The float32 layers, and the bf16
+// the same on every run) and finishes as above: one workgroup for up to 64 tokens, which
+// goes on with the permutation, else k_router_final.  The float32 layers, and the bf16
 // widths that the matrix-core router does not take, run the same way with more tokens:
 // one wave per token reads every router weight once per token (22 us at T = 2048,
 // D = 768, 24 rows; sliced 12.9).
@@ -135,9 +136,11 @@ __global__ __launch_bounds__(4 * kWave) void k_router_small_partial(RouterArgs a
     const int k_begin = blockIdx.x * slice, k_end = min(k_begin + slice, D);
     constexpr int V = ActVec<AT>::N;
     const AT *x = static_cast<const AT *>(a.x);
-    f32x4 acc[RPT];
+    // Products are added up in chains of 8, four for half a tile, then the halves: chains over a
+    // whole slice would be further from the exact sum than the one-kernel router's tree is.
+    float tot[RPT];
 #pragma unroll
-    for (int j = 0; j < RPT; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < RPT; ++j) tot[j] = 0.f;
     for (int k0 = k_begin; k0 < k_end; k0 += kRsBK) {
         // x tile [64 tokens][64 k] and weight tile [4 RPT rows][64 k], zero past k_end and past the last row
         for (int c = tid; c < kRsTok * (kRsBK / V); c += 4 * kWave) {
@@ -163,16 +166,23 @@ __global__ __launch_bounds__(4 * kWave) void k_router_small_partial(RouterArgs a
         }
         __syncthreads();
         // wave rg owns rows rg, rg + 4, ...: the weight reads are broadcasts.
-        // acc[j][i] collects the k with k % 4 == i.
+        // acc[j][i] collects the k with k % 4 == i of half a tile.
+        for (int half = 0; half < kRsBK; half += kRsBK / 2) {
+            f32x4 acc[RPT];
+#pragma unroll
+            for (int j = 0; j < RPT; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll 4
-        for (int kk = 0; kk < kRsBK; kk += 4) {
-            const f32x4 xv = *reinterpret_cast<const f32x4 *>(&sx[tok][kk]);
+            for (int kk = half; kk < half + kRsBK / 2; kk += 4) {
+                const f32x4 xv = *reinterpret_cast<const f32x4 *>(&sx[tok][kk]);
 #pragma unroll
-            for (int j = 0; j < RPT; ++j) {
-                const f32x4 wv = *reinterpret_cast<const f32x4 *>(&sw[rg + 4 * j][kk]);
+                for (int j = 0; j < RPT; ++j) {
+                    const f32x4 wv = *reinterpret_cast<const f32x4 *>(&sw[rg + 4 * j][kk]);
 #pragma unroll
-                for (int i = 0; i < 4; ++i) acc[j][i] = fmaf(wv[i], xv[i], acc[j][i]);
+                    for (int i = 0; i < 4; ++i) acc[j][i] = fmaf(wv[i], xv[i], acc[j][i]);
+                }
             }
+#pragma unroll
+            for (int j = 0; j < RPT; ++j) tot[j] += (acc[j][0] + acc[j][1]) + (acc[j][2] + acc[j][3]);
         }
         __syncthreads();
     }
@@ -180,35 +190,8 @@ __global__ __launch_bounds__(4 * kWave) void k_router_small_partial(RouterArgs a
         float *dst = partial + ((size_t)blockIdx.x * T + t0 + tok) * rows;
 #pragma unroll
         for (int j = 0; j < RPT; ++j)
-            if (rg + 4 * j < rows) dst[rg + 4 * j] = (acc[j][0] + acc[j][1]) + (acc[j][2] + acc[j][3]);
+            if (rg + 4 * j < rows) dst[rg + 4 * j] = tot[j];
     }
-}
-
-__global__ __launch_bounds__(kRouterWaves *kWave) void k_router_small_final(RouterArgs a, int n_splits,
-                                                                           const float *partial) {
-    __shared__ float dots[kRouterWaves][kMaxRouterRows];
-    __shared__ float wres[kMaxExperts * kMaxExperts];
-    const int lane = threadIdx.x % kWave;
-    const int w = threadIdx.x / kWave;
-    const int t = blockIdx.x * kRouterWaves + w;
-    const int rows = a.d.N + 2 * a.d.n_const;
-    const bool active = t < a.d.T;
-    stage_wres(a, wres);
-    if (active) {
-        for (int r = lane; r < rows; r += kWave) {
-            // all loads first (a fixed trip count lets them be issued together), then the sum in slice order
-            float v[kRsSplits];
-#pragma unroll
-            for (int sp = 0; sp < kRsSplits; ++sp)
-                v[sp] = sp < n_splits ? partial[((size_t)sp * a.d.T + t) * rows + r] : 0.f;
-            float sum = 0.f;
-#pragma unroll
-            for (int sp = 0; sp < kRsSplits; ++sp) sum += v[sp];
-            dots[w][r] = sum;
-        }
-    }
-    __syncthreads();
-    if (active) router_tail(a, t, lane, dots[w], wres);
 }
 
 // The second kernel and the permutation in one launch, for T <= kRouterFusedT: one
@@ -296,12 +279,11 @@ __global__ __launch_bounds__(kRouterFinalThreads) void k_router_final(RouterArgs
     const float *part = a.partial + (size_t)t0 * rows;
     for (int c = tid; c < n_tok * rows; c += NT) {
         float sum = 0.f;
-        for (int s0 = 0; s0 < splits; s0 += 8) {           // eight loads in flight
+        for (int s0 = 0; s0 < splits; s0 += 8) {           // eight loads in flight, added up as a tree
             float v[8];
 #pragma unroll
             for (int u = 0; u < 8; ++u) v[u] = s0 + u < splits ? part[(size_t)(s0 + u) * T * rows + c] : 0.f;
-#pragma unroll
-            for (int u = 0; u < 8; ++u) sum += v[u];
+            sum += ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
         }
         dots[(c / rows) * DSTR + c % rows] = sum;
     }
@@ -335,7 +317,7 @@ hipError_t launch_router_final(const RouterArgs &a, int splits, hipStream_t s) {
 }
 
 size_t router_small_bytes() {
-    return (size_t)kRsSplits * kRouterSmallT * kMaxRouterRows * sizeof(float);
+    return (size_t)kRsSplits * 256 * kMaxRouterRows * sizeof(float);     // all slices of 256 tokens with the most rows
 }
 
 // First kernel of the sliced routers: slices of whole K tiles, at most max_splits of them.
@@ -361,26 +343,20 @@ static hipError_t launch_router_partial(const RouterArgs &a, bool bf16, int max_
     return hipGetLastError();
 }
 
-hipError_t launch_router_small(const RouterArgs &a, bool bf16, hipStream_t s, const Workspace *perm_ws,
-                               const CapArgs *perm_cap) {
+hipError_t launch_router_small(const RouterArgs &a, bool bf16, hipStream_t s, const Workspace &perm_ws,
+                               const CapArgs &perm_cap) {
     if (a.d.T == 0) return hipSuccess;
-    if (a.d.T > kRouterSmallT) return hipErrorInvalidValue;
+    if (a.d.T > kRouterFusedT) return hipErrorInvalidValue;
     int n_splits = 0;
     const hipError_t e = launch_router_partial(a, bf16, kRouterSplits, &n_splits, s);
     if (e != hipSuccess) return e;
-    if (perm_ws) {
-        if (a.d.T > kRouterFusedT || perm_cap == nullptr) return hipErrorInvalidValue;
-        auto go = [&](auto kernel) {
-            hipLaunchKernelGGL(kernel, dim3(1), dim3(kPermSmallWaves * kWave), 0, s, a, n_splits, a.partial, *perm_ws,
-                               *perm_cap);
-        };
-        if (a.d.N <= 20) go(k_router_small_final_perm<5>);
-        else if (a.d.N <= 32) go(k_router_small_final_perm<8>);
-        else go(k_router_small_final_perm<kMaxExperts / 4>);
-        return hipGetLastError();
-    }
-    hipLaunchKernelGGL(k_router_small_final, dim3((a.d.T + kRouterWaves - 1) / kRouterWaves),
-                       dim3(kRouterWaves * kWave), 0, s, a, n_splits, a.partial);
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(1), dim3(kPermSmallWaves * kWave), 0, s, a, n_splits, a.partial, perm_ws,
+                           perm_cap);
+    };
+    if (a.d.N <= 20) go(k_router_small_final_perm<5>);
+    else if (a.d.N <= 32) go(k_router_small_final_perm<8>);
+    else go(k_router_small_final_perm<kMaxExperts / 4>);
     return hipGetLastError();
 }
 
