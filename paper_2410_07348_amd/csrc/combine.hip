@@ -15,7 +15,8 @@
 namespace moepp {
 
 constexpr int kCombineWaves = 4;
-constexpr int kCombineSplitT = 2048;     // tokens up to which a wave takes a piece of a token
+// tokens up to which a wave takes a piece of a token, for Top-2 and for more slots
+constexpr int kCombineSplitT = 2048, kCombineSplitTMany = 1024;
 
 // KMAX: slots the kernel is unrolled for (2: the paper's Top-2 layers keep their
 // per-slot plan in a handful of registers; kMaxTopK: any k).
@@ -103,7 +104,9 @@ hipError_t launch_combine(const CombineArgs &a, bool bf16, hipStream_t s) {
     // before it: pieces of one 16-byte access per lane (T = 64,
     // D = 4096: 9.4 -> 4.6 us; T = 777: 11.3 -> 7.0; T = 1500, D = 768: 5.8 -> 5.2).
     const int step = kWave * (bf16 ? ActVec<bf16_t>::N : ActVec<float>::N);
-    const int span = a.d.T <= kCombineSplitT ? step : (a.d.D + step - 1) / step * step;
+    // With more than two slots the plan is what a piece costs: T = 1999, k = 3, D = 1000 10.3 us in two
+    // pieces, 8.0 whole; T = 1000, k = 4, D = 1536 7.7 in three, 9.0 whole.
+    const int span = a.d.T <= (a.d.k <= 2 ? kCombineSplitT : kCombineSplitTMany) ? step : (a.d.D + step - 1) / step * step;
     const dim3 grid((a.d.T + kCombineWaves - 1) / kCombineWaves, (a.d.D + span - 1) / span);
     const dim3 block(kCombineWaves * kWave);
     if (a.d.k <= 2) {

@@ -793,11 +793,13 @@ hipError_t launch_ffn_mfma(const FfnArgs &f, int which, hipStream_t s) {
     // against 262 and 133, and the layer's other operands stay cached (router 20.7 -> 19.9,
     // combine 13.6 -> 11.1 us); T = 400, D = 1536, F = 4096 (604 MB): GEMM1 77 / 83, GEMM2 42 / 47.
     // At 151 - 201 MB, called again and again: 32 against 23 us.
-    const bool stream = few && 6.0 * f.d.n_ffn * f.d.D * f.d.F > 256.0 * (1 << 20);
+    // The same for one 256-row tile per expert (T = 2048, D = 4096: layer 535 -> 525 us).
+    const bool stream = (few || rows <= 224) && 6.0 * f.d.n_ffn * f.d.D * f.d.F > 256.0 * (1 << 20);
     if (f.no_tail) return few ? launch_cfg<Half>(f, which, s) : launch_cfg<Full>(f, which, s);
     if (small)
         return stream ? launch_cfg<Small, void, false, true>(f, which, s) : launch_cfg<Small>(f, which, s);
     if (few) return stream ? launch_cfg<Half, void, false, true>(f, which, s) : launch_cfg<Half>(f, which, s);
+    if (stream) return launch_cfg<Full, Half, false, true>(f, which, s);
     return launch_cfg<Full, Half>(f, which, s);
 }
 
