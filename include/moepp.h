@@ -248,10 +248,11 @@ moepp_status moepp_get_intermediates(moepp_ctx *ctx, const float **alpha1,
 enum {
     MOEPP_K_ROUTER = 0,  /* router GEMM + residual + softmax + top-k         */
     MOEPP_K_HIST = 1,    /* permute: per-chunk histogram; 0 when the router kernel
-                            has counted its own selections (bf16 layers on the
-                            matrix-core router) and for calls with at most 4096
-                            slots, where one kernel does all three steps and is
-                            reported as MOEPP_K_SCATTER                       */
+                            has counted its own selections (every router of the
+                            automatic variant from 65 tokens on, and the matrix-core
+                            router); without its counts calls with at most 4096 slots
+                            do all three steps in one kernel, reported as
+                            MOEPP_K_SCATTER                                   */
     MOEPP_K_SCAN = 2,    /* permute: exclusive scan as a kernel of its own; 0 up to
                             2048 chunks (scan and scatter are one kernel)    */
     MOEPP_K_SCATTER = 3, /* permute: (scan and) stable scatter; 0 for calls with at

@@ -150,7 +150,7 @@ __global__ __launch_bounds__(WM *WN *kWave) void k_ffn_f32(F32Args a) {
         for (int i = 0; i < CA; ++i) {
             const float *q = pa[i] + kt * a_step;
             if constexpr (RAG) {
-                q -= SWIGLU ? 0 : a_row[i] * (kSlab - w);
+                q -= SWIGLU ? (size_t)0 : (size_t)a_row[i] * (kSlab - w);
                 q -= a_kc[i] < w ? 0 : a_kc[i];
             }
             ra[i] = *reinterpret_cast<const f32x4 *>(q);

@@ -1,5 +1,4 @@
-// Grouped SwiGLU FFN on the bf16 matrix cores (gfx950, v_mfma_f32_16x16x32_bf16 by
-// default, v_mfma_f32_32x32x16_bf16 as an option).
+// Grouped SwiGLU FFN on the bf16 matrix cores (gfx950, v_mfma_f32_16x16x32_bf16).
 //
 // For every FFN expert e and the rows r of its group (paper Eq.2: the FFN
 // experts of the layer; group sizes are ragged, they follow the routing):
@@ -12,14 +11,13 @@
 // group offsets (no host sync): expert e owns ceil(count_e / BM) M tiles; the
 // numbering walks patches of 8 x 4 tiles and deals the patches to the eight
 // XCDs round-robin, so that the tiles that run together on one XCD share their
-// A and B panels in that XCD's L2.  In the default (persistent) geometry one
-// workgroup per CU walks the tile list with stride gridDim; it looks up and
+// A and B panels in that XCD's L2.  As many workgroups as the CUs hold walk
+// the tile list with stride gridDim; a workgroup looks up and
 // gathers the rows of its next tile while the current one computes and issues
 // that tile's first K stages before the epilogue of the current one.  When
 // the whole problem is only a few rounds of tiles, a last round that fills at
-// most half of the workgroups is left to a second launch of the same kernel
-// with tiles of half the height (twice as many workgroups busy for about half
-// as long).
+// most half of the workgroups is run as tiles of half the height (twice as many
+// workgroups busy for about half as long) at the end of the same launch.
 // A rows of GEMM1 are gathered straight from x through src_of (no permuted
 // copy of x is ever written).  K tiles of 32 elements travel from memory
 // straight into a ring of LDS stages (global_load_lds, 16-byte chunks

@@ -7,8 +7,8 @@
 // workgroup adds up the histogram rows its waves need itself (a few thousand
 // chunks at most: the rows are 4 N bytes each and sit in L2), or two kernels
 // with a single-workgroup scan when there are more chunks than that; calls with
-// few slots do all of it in one workgroup (k_perm_small, or, with a handful of
-// tokens, the last kernel of the few-token router).  Integer work only and no ordering left
+// few slots whose router has not counted do all of it in one workgroup (k_perm_small, or,
+// with a handful of tokens, the last kernel of the few-token router).  Integer work only and no ordering left
 // to atomics, so the result is the same on every run: rows of one expert are
 // ordered by ascending slot index q = t*k + s.
 //
