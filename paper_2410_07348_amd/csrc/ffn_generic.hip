@@ -1,8 +1,7 @@
 // Grouped SwiGLU FFN for any supported shape and activation type, plain fp32
 // FMA: one thread per output element.  FFN_e(x) = W2_e (silu(W1_e x) * (W3_e x))
-// for the rows of every FFN expert e (the FFN experts of paper Eq.2).  This is
-// the fallback for bf16 shapes the MFMA kernels do not cover, and what variant 1
-// runs for every shape and type.
+// for the rows of every FFN expert e (the FFN experts of paper Eq.2).  What variant 1
+// runs for every shape and type; the automatic variant has matrix-core kernels for all.
 #include "common.h"
 
 namespace moepp {
