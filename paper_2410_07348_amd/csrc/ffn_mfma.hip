@@ -61,7 +61,10 @@ struct GemmArgs {
 
 // silu(z) = z / (1 + e^-z) with the hardware exp2 and reciprocal (1 ulp each:
 // far inside the rounding of the bf16 result).  A correctly rounded division
-// costs ten more instructions per element, a third of the epilogue.
+// costs ten more instructions per element, a third of the epilogue.  The ragged
+// instances (RAG, below) use silu_f all the same: their layers ran with it before they had
+// matrix-core kernels, and below z = -87 the hardware reciprocal's result is flushed to zero
+// (T = 1999, D = 1000, F = 1416: GEMM1 36 us, with the hardware functions 33).
 __device__ inline float fast_silu(float z) {
     return z * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(-1.44269504088896340736f * z));
 }
@@ -570,8 +573,10 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs &a, const GroupTiles &
                             const int c0 = (wn * TN) / 2 + (jp / 2) * 32 + (jp % 2) * 16 + 4 * lq;
                             bf16x4 o;
 #pragma unroll
-                            for (int q = 0; q < 4; ++q)
-                                o[q] = (bf16_t)(fast_silu(acc[jg][i][q]) * acc[jg + 2][i][q]);
+                            for (int q = 0; q < 4; ++q) {
+                                const float z = acc[jg][i][q];
+                                o[q] = (bf16_t)((RAG ? silu_f(z) : fast_silu(z)) * acc[jg + 2][i][q]);
+                            }
                             *reinterpret_cast<bf16x4 *>(orow + c0 * 2) = o;
                         }
                     } else {

@@ -84,3 +84,28 @@ def test_bf16_streamed_weights(T):
 @pytest.mark.parametrize("D,F,n_ffn", [(256, 512, 4), (1280, 256, 12), (512, 2048, 33)])
 def test_bf16_few_rows(T, D, F, n_ffn):
     check(T=T, D=D, F=F, n_ffn=n_ffn, bias="normal")
+
+
+# SiLU of the ragged bf16 layers is expf and a division, as in the plain FMA kernels.  x has a
+# single one and W3 is one, so both kernels see the same z = W1 exactly, and it runs through
+# every bfloat16 of magnitude 2^-8 .. 88: h must be the same bit for bit, and within half a
+# bfloat16 ulp (2^-9 of the value, and a few float32 ulps) of z / (1 + e^-z) * 1.
+@pytest.mark.parametrize("T", [1, 300])
+def test_ragged_silu(T):
+    mag = (np.arange(0x3B80, 0x42B1, dtype=np.uint32) << 16).view(np.float32)
+    z = np.concatenate([mag, -mag])
+    s = LayerShape("silu", T=T, D=8, F=(z.size + 7) // 8 * 8, n_ffn=1, n_zero=0, n_copy=0, n_const=0, k=1,
+                   residual=False, seed=8300)
+    inp = make_inputs(s)
+    inp["x"][:] = 0.0
+    inp["x"][:, 3] = 1.0
+    inp["w1"][:] = 0.0
+    inp["w1"][0, :z.size, 3] = z
+    inp["w3"][:] = 0.0
+    inp["w3"][0, :, 3] = 1.0
+    a, b = gpu_forward(s, inp), gpu_forward(s, inp, variant=1)
+    want = z.astype(np.float64) / (1.0 + np.exp(-z.astype(np.float64)))
+    err = np.abs(a["h"][:, :z.size] - want) / np.abs(want)
+    print("silu error * 2^8", err.max() * 256, "differ", (a["h"] != b["h"]).sum(), flush=True)
+    assert err.max() <= 1.0 / 256
+    assert np.array_equal(a["h"], b["h"])
