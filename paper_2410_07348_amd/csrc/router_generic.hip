@@ -250,9 +250,9 @@ __global__ __launch_bounds__(kPermSmallWaves *kWave) void k_router_small_final_p
         a.out_gate[(size_t)tt * N + i] = L;
     }
     __syncthreads();
-    {
-        // every thread runs this (the shuffles are wave-wide); threads past the last token
-        // compute on the last token and store nothing
+    if (tid / kWave * kWave < 4 * T) {
+        // whole waves (the shuffles are wave-wide); threads past the last token compute on the
+        // last token and store nothing
         const int tok = tid >> 2;
         const int tk = tok < T ? tok : T - 1;
         router_token_quad<PER>(a, (size_t)tk, tok < T, tid & 3, dots + tk * DSTR, nullptr, s_idx + tk * K);

@@ -1,0 +1,51 @@
+"""The end of the routers (softmax, Top-K) on logits that are known exactly: every router the
+dispatch can take, by size and type."""
+import numpy as np
+import pytest
+
+from workloads import LayerShape, make_inputs
+
+from helpers import gpu_forward
+
+pytestmark = pytest.mark.gpu
+
+# (act, T, D): few tokens; sliced FMA router (float32, a bf16 width it alone takes); matrix-core
+# router, one kernel, slices of D, 128-token blocks
+ROUTERS = [("f32", 40, 64), ("bf16", 40, 512), ("f32", 100, 64), ("bf16", 300, 1000), ("bf16", 100, 768),
+           ("bf16", 300, 768), ("bf16", 300, 4096), ("bf16", 24576, 512)]
+
+
+def one_hot_shape(act, T, D, **kw):
+    kw = dict(dict(n_ffn=6, n_zero=2, n_copy=2, n_const=2, k=8, residual=False, seed=8400), **kw)
+    return LayerShape("numerics", T=T, D=D, F=64, act=act, **kw)
+
+
+def exact_logits(s, inp, col=5):
+    """x[t] = 1 + t % 4 in one column, W_g[i] = -2.75 i there: logits -2.75 i (1 + t % 4), exact
+    in float32 whatever the order of the sums."""
+    inp["x"][:] = 0.0
+    inp["x"][:, col] = 1.0 + np.arange(s.T) % 4
+    inp["W_g"][:] = 0.0
+    inp["W_g"][:, col] = -2.75 * np.arange(s.N)
+    return -2.75 * np.arange(s.N)[None, :] * (1.0 + np.arange(s.T) % 4)[:, None]
+
+
+@pytest.mark.parametrize("act,T,D", ROUTERS)
+def test_softmax_is_accurate_to_float32(act, T, D):
+    """Relative error, weight by weight, down to logits 77 apart: expf within 1 ulp (2^-23) in
+    numerator and sum, N / 4 + 2 additions and a division of half an ulp each."""
+    s = one_hot_shape(act, T, D)
+    inp = make_inputs(s)
+    L = exact_logits(s, inp)
+    res = gpu_forward(s, inp, balance_tau=0.75, intermediates=False)
+    assert np.array_equal(res["out_gate"].astype(np.float64), L)
+    assert np.array_equal(res["topk_idx"], np.tile(np.arange(s.k), (T, 1)))
+    p = np.exp(L)                                   # the largest logit is 0
+    p /= p.sum(axis=1, keepdims=True)
+    bound = (2 + (s.N // 4 + 2 + 1) / 2) * 2.0 ** -23
+    e_w = (np.abs(res["topk_w"] - p[:, :s.k]) / p[:, :s.k]).max()
+    P = p.mean(axis=0)
+    e_P = (np.abs(res["P"] - P) / P).max()
+    print("router", act, T, D, "topk_w", e_w, "P", e_P, "bound", bound, flush=True)
+    assert e_w <= bound
+    assert e_P <= bound + 2.0 ** -24                # (added up in float64, rounded once)
