@@ -34,6 +34,16 @@ __device__ inline void router_token_quad(const RouterArgs &a, size_t t, bool val
         if (q + 4 * j < N) sum += expf(v[j] - mx);
     sum += __shfl_xor(sum, 1, kWave);
     sum += __shfl_xor(sum, 2, kWave);
+    if (probs) {
+#pragma unroll
+        for (int j = 0; j < PER; ++j)
+            if (q + 4 * j < N) probs[q + 4 * j] = valid ? expf(v[j] - mx) / sum : 0.f;
+    }
+    // A NaN logit (which makes sum, and with it all weights of the token, NaN) is selected like
+    // -infinity: all four threads have to agree on the winner, or each takes an expert of its own
+    // out of the race and after a few rounds there is none left to select.
+#pragma unroll
+    for (int j = 0; j < PER; ++j) v[j] = v[j] == v[j] ? v[j] : -INFINITY;
     unsigned open = 0;                          // of this thread's experts: not selected yet
 #pragma unroll
     for (int j = 0; j < PER; ++j) open |= (q + 4 * j < N ? 1u : 0u) << j;
@@ -67,11 +77,6 @@ __device__ inline void router_token_quad(const RouterArgs &a, size_t t, bool val
     if (valid)
         for (int j = q; j < nc; j += 4)
             a.alpha1[t * nc + j] = 1.f / (1.f + expf(Lr[N + 2 * j + 1] - Lr[N + 2 * j]));
-    if (probs) {
-#pragma unroll
-        for (int j = 0; j < PER; ++j)
-            if (q + 4 * j < N) probs[q + 4 * j] = valid ? expf(v[j] - mx) / sum : 0.f;
-    }
 }
 
 // Rows of W_res and of the previous logits in LDS: a multiple of four floats, so that

@@ -49,3 +49,28 @@ def test_softmax_is_accurate_to_float32(act, T, D):
     print("router", act, T, D, "topk_w", e_w, "P", e_P, "bound", bound, flush=True)
     assert e_w <= bound
     assert e_P <= bound + 2.0 ** -24                # (added up in float64, rounded once)
+
+
+@pytest.mark.parametrize("act,T,D", ROUTERS)
+def test_a_nan_token_stays_alone(act, T, D):
+    """A NaN in one row of x makes all its logits NaN.  Its slots still go to k different experts
+    (the lowest indices, as with equal logits), the counts add up, and every other token gets the
+    bits it gets beside a token of zeros, whose logits are equal.  k > ceil(N / 4): the four
+    threads of a token hold two experts each."""
+    s = one_hot_shape(act, T, D, n_ffn=4, n_zero=1, n_copy=1, k=3)
+    assert s.N == 8
+    inp = make_inputs(s)
+    t = T // 2 + 1
+    inp["x"][t] = 0.0
+    ref = gpu_forward(s, inp, intermediates=False)
+    inp["x"][t, 9] = np.nan
+    res = gpu_forward(s, inp, intermediates=False)
+    print("nan token", act, T, D, res["topk_idx"][t].tolist(), res["counts"].tolist(), flush=True)
+    assert res["topk_idx"][t].tolist() == [0, 1, 2]
+    assert res["counts"].sum() == T * s.k
+    for name in ("counts", "offsets", "row_of", "topk_idx"):
+        assert np.array_equal(res[name], ref[name]), name
+    others = np.arange(T) != t
+    for name in ("out", "out_gate", "topk_w"):
+        assert np.array_equal(res[name][others], ref[name][others]), name
+        assert np.isnan(res[name][t]).all(), name
