@@ -49,10 +49,13 @@ __device__ inline void router_tail(const RouterArgs &a, int t, int lane, const f
     const float p = e / wave_sum(e);
 
     // Top-K by K rounds of wave-wide argmax on (logit desc, index asc)
-    float cand = L;
+    // (a NaN is selected like -infinity; a lane without an expert, or whose expert is taken, holds
+    // -infinity at an index that loses against every other)
+    float cand = L == L ? L : -INFINITY;
+    int cand_i = mine ? lane : 0x7fffffff;
     for (int s = 0; s < K; ++s) {
         float bv = cand;
-        int bi = lane;
+        int bi = cand_i;
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) {
             float ov = __shfl_xor(bv, o, kWave);
@@ -63,7 +66,10 @@ __device__ inline void router_tail(const RouterArgs &a, int t, int lane, const f
             }
         }
         float pw = __shfl(p, bi, kWave);
-        if (lane == bi) cand = -INFINITY;
+        if (lane == bi) {
+            cand = -INFINITY;
+            cand_i = 0x7fffffff;
+        }
         if (lane == 0) {
             a.topk_idx[(size_t)t * K + s] = bi;
             a.topk_w[(size_t)t * K + s] = pw;

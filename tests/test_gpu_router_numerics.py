@@ -51,8 +51,9 @@ def test_softmax_is_accurate_to_float32(act, T, D):
     assert e_P <= bound + 2.0 ** -24                # (added up in float64, rounded once)
 
 
-@pytest.mark.parametrize("act,T,D", ROUTERS)
-def test_a_nan_token_stays_alone(act, T, D):
+# (variant 1: the router with one wave per token)
+@pytest.mark.parametrize("act,T,D,variant", [r + (0,) for r in ROUTERS] + [("f32", 40, 64, 1), ("bf16", 300, 512, 1)])
+def test_a_nan_token_stays_alone(act, T, D, variant):
     """A NaN in one row of x makes all its logits NaN.  Its slots still go to k different experts
     (the lowest indices, as with equal logits), the counts add up, and every other token gets the
     bits it gets beside a token of zeros, whose logits are equal.  k > ceil(N / 4): the four
@@ -62,9 +63,9 @@ def test_a_nan_token_stays_alone(act, T, D):
     inp = make_inputs(s)
     t = T // 2 + 1
     inp["x"][t] = 0.0
-    ref = gpu_forward(s, inp, intermediates=False)
+    ref = gpu_forward(s, inp, variant, intermediates=False)
     inp["x"][t, 9] = np.nan
-    res = gpu_forward(s, inp, intermediates=False)
+    res = gpu_forward(s, inp, variant, intermediates=False)
     print("nan token", act, T, D, res["topk_idx"][t].tolist(), res["counts"].tolist(), flush=True)
     assert res["topk_idx"][t].tolist() == [0, 1, 2]
     assert res["counts"].sum() == T * s.k
@@ -74,3 +75,19 @@ def test_a_nan_token_stays_alone(act, T, D):
     for name in ("out", "out_gate", "topk_w"):
         assert np.array_equal(res[name][others], ref[name][others]), name
         assert np.isnan(res[name][t]).all(), name
+
+
+@pytest.mark.parametrize("act,T,D,variant", [r + (0,) for r in ROUTERS] + [("f32", 40, 64, 1), ("bf16", 300, 512, 1)])
+def test_masked_experts(act, T, D, variant):
+    """A bias of -infinity on all experts but one: it takes weight 1, the other slots go to the
+    masked experts of the lowest indices, each once, with weight 0."""
+    s = one_hot_shape(act, T, D)
+    inp = make_inputs(s)
+    exact_logits(s, inp)
+    inp["bias"] = np.full(s.N, -np.inf, np.float32)
+    inp["bias"][4] = 0.0
+    res = gpu_forward(s, inp, variant, intermediates=False)
+    order = [4] + [i for i in range(s.N) if i != 4]
+    assert np.array_equal(res["topk_idx"], np.tile(order[:s.k], (T, 1)))
+    assert np.array_equal(res["topk_w"], np.tile([1.0] + [0.0] * (s.k - 1), (T, 1)))
+    assert np.isfinite(res["out"]).all()
