@@ -91,3 +91,31 @@ def test_masked_experts(act, T, D, variant):
     assert np.array_equal(res["topk_idx"], np.tile(order[:s.k], (T, 1)))
     assert np.array_equal(res["topk_w"], np.tile([1.0] + [0.0] * (s.k - 1), (T, 1)))
     assert np.isfinite(res["out"]).all()
+
+
+@pytest.mark.parametrize("act,T,D,variant", [r + (0,) for r in ROUTERS] + [("bf16", 300, 512, 1)])
+def test_infinite_router_operands(act, T, D, variant):
+    """W_g = -infinity for one expert in a column where x is positive takes that expert out of the
+    race, W_g = +infinity gives an infinite logit, and an infinite activation infinite logits of the
+    weights' signs: not NaN, and nothing else changes."""
+    s = one_hot_shape(act, T, D)
+    inp = make_inputs(s)
+    L = exact_logits(s, inp)
+    inp["x"][:, 7] = 0.5
+    inp["W_g"][3, 7] = -np.inf
+    res = gpu_forward(s, inp, variant, intermediates=False)
+    L[:, 3] = -np.inf
+    assert np.array_equal(res["out_gate"].astype(np.float64), L)
+    assert np.array_equal(res["topk_idx"], np.tile([i for i in range(s.N) if i != 3][:s.k], (T, 1)))
+    assert np.isfinite(res["topk_w"]).all() and np.isfinite(res["out"]).all()
+    inp["W_g"][3, 7] = np.inf
+    res = gpu_forward(s, inp, variant, intermediates=False)
+    assert np.all(res["out_gate"][:, 3] == np.inf) and np.all(res["topk_idx"][:, 0] == 3)
+    inp["W_g"][3, 7] = 0.0
+    sign = np.where(np.arange(s.N) % 3 == 1, -1.0, 1.0)
+    inp["W_g"][:, 11] = 0.25 * sign
+    inp["x"][T // 2, 11] = np.inf
+    L = -2.75 * np.arange(s.N)[None, :] * (1.0 + np.arange(T) % 4)[:, None]
+    L[T // 2] = np.inf * sign
+    res = gpu_forward(s, inp, variant, intermediates=False)
+    assert np.array_equal(res["out_gate"].astype(np.float64), L)
