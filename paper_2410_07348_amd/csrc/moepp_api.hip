@@ -210,18 +210,17 @@ moepp_status do_route(moepp_ctx *c, hipStream_t s, int T, const void *x, const f
         // the router counts its selections, per block of tokens, for the permutation
         const int tok = sliced ? kRouterSlicedTok : router_mfma_block_tokens(a.d);
         a.chunk_hist = c->ws.chunk_hist;
-        c->hist_valid = true;
         c->hist_T = T;
         c->hist_k = k;
         c->hist_chunk_slots = tok * k;
         // with the load-balance statistics on, it also adds up the softmax of its tokens
         const int wgs = (T + tok - 1) / tok;
-        if (c->bal_tau > 0.0 && wgs <= kBalWaves) {
-            a.bal_partial = c->ws.bal_partial;
-            c->bal_rows = wgs;
-            c->bal_T = T;
-        }
+        const bool sums = c->bal_tau > 0.0 && wgs <= kBalWaves;
+        if (sums) a.bal_partial = c->ws.bal_partial;
         e = sliced ? launch_router_sliced(a, bf16, s) : launch_router_mfma(a, s);
+        c->hist_valid = e == hipSuccess;
+        c->bal_rows = sums && e == hipSuccess ? wgs : 0;
+        c->bal_T = T;
     } else {
         e = launch_router_generic(a, bf16, s);
     }

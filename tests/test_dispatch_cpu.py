@@ -1,0 +1,59 @@
+"""What the calls of the C ABI launch, by kernel instance and grid, without a GPU: the driver
+tests/dispatch/launch_log.c takes the place of the HIP runtime's launch functions."""
+import os
+import re
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+F32, BF16 = 0, 1
+OK, EHIP = 0, -4
+
+
+@pytest.fixture(scope="module")
+def launches(tmp_path_factory):
+    """launches(commands) -> per command (status, [(kernel, grid, threads), ...])"""
+    from paper_2410_07348_amd import binding
+    binding.load_library()
+    lib = binding.lib_path()
+    exe = str(tmp_path_factory.mktemp("dispatch") / "launch_log")
+    subprocess.run(["gcc", "-std=c11", "-O1", "-Wall", "-rdynamic", "-I", os.path.join(ROOT, "include"),
+                    os.path.join(ROOT, "tests", "dispatch", "launch_log.c"), lib, "-ldl",
+                    "-Wl,-rpath," + os.path.dirname(lib), "-Wl,--allow-shlib-undefined", "-o", exe], check=True)
+    filt = shutil.which("c++filt") or "/opt/rocm/llvm/bin/llvm-cxxfilt"
+
+    def run(commands):
+        r = subprocess.run([exe], input="\n".join(commands) + "\n", capture_output=True, text=True, check=True)
+        text = subprocess.run([filt], input=r.stdout, capture_output=True, text=True, check=True).stdout
+        out, cur = [], []
+        for line in text.splitlines():
+            if line.startswith("status "):
+                out.append((int(line.split()[1]), cur))
+                cur = []
+            else:
+                m = re.match(r"launch (?:void )?(?:moepp::)?(.*) (\d+) (\d+) (\d+) (\d+)$", line)
+                name = re.sub(r"\(.*\)$", "", m.group(1)).replace("moepp::", "").replace("__bf16", "bf16")
+                cur.append((name, tuple(int(v) for v in m.groups()[1:4]), int(m.group(5))))
+        assert len(out) == len(commands), text
+        return out
+    return run
+
+
+def ctx(T, D, F, n_ffn, k=2, act=BF16, n_zero=1, n_copy=1, n_const=2):
+    return "ctx %d %d %d %d %d %d %d %d %d" % (T, D, F, n_ffn, n_zero, n_copy, n_const, k, act)
+
+
+def names(result):
+    return [n for n, _, _ in result[1]]
+
+
+@pytest.mark.parametrize("T,D,act", [(300, 768, BF16), (5000, 768, BF16), (300, 72, BF16), (5000, 64, F32), (30, 64, F32)])
+def test_a_failed_router_leaves_nothing_for_the_permutation(launches, T, D, act):
+    """When the router's launch fails its histogram was never written: a permutation that follows
+    counts for itself."""
+    r = launches([ctx(T, D, 64, 4, act=act), "fail 1", "route %d 2" % T, "fail 0", "permute %d 2" % T])
+    assert r[2] == (EHIP, [])
+    assert r[4][0] == OK
+    assert names(r[4])[0] in ("k_perm_small", "k_perm_hist"), names(r[4])
