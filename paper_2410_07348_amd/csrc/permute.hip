@@ -325,8 +325,11 @@ hipError_t launch_balance(const Dims &d, const Workspace &w, const float *out_ga
                           hipStream_t s, int router_rows) {
     if (d.T == 0) return hipSuccess;
     if (router_rows > kBalWaves) return hipErrorInvalidValue;
-    if (router_rows <= 0)
+    if (router_rows <= 0) {
         hipLaunchKernelGGL(k_balance_partial, dim3(kBalWaves / 4), dim3(4 * kWave), 0, s, d, w, out_gate);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
     hipLaunchKernelGGL(k_balance_final, dim3(1), dim3(kBalFinalWaves * kWave), 0, s, d, w, tau,
                        router_rows > 0 ? router_rows : kBalWaves);
     return hipGetLastError();

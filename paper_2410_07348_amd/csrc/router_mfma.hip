@@ -323,7 +323,8 @@ hipError_t launch_router_mfma(const RouterArgs &a, hipStream_t s) {
         const dim3 g2(blocks, splits);
         if (nblk == 1) hipLaunchKernelGGL((k_router_mfma<1, 2, 64, 3, 1, true>), g2, dim3(256), 0, s, a);
         else hipLaunchKernelGGL((k_router_mfma<2, 2, 64, 2, 1, true>), g2, dim3(256), 0, s, a);
-        return launch_router_final(a, splits, s);
+        const hipError_t e = hipGetLastError();
+        return e == hipSuccess ? launch_router_final(a, splits, s) : e;
     }
     // 64-token workgroups take two K tiles at a time, in two groups of four waves: a tile is a
     // serial chain (loads, split, LDS, barrier, MFMA) and there are at most a few workgroups

@@ -6,7 +6,7 @@
  *
  * Reads one command a line from stdin:
  *   ctx T_max D F n_ffn n_zero n_copy n_const k act     a new context
- *   variant V | fail 0/1 | capacity C (-1: off) | balance TAU
+ *   variant V | fail 0/1/2 (2: the next launch only) | capacity C (-1: off) | balance TAU
  *   forward T k | route T k | permute T k | ffn T k | combine T k
  * and prints "launch NAME gx gy gz threads" per kernel and "status S" per command.
  */
@@ -59,7 +59,11 @@ int hipLaunchKernel(const void *host, dim grid, dim block, void **args, size_t s
     (void)args;
     (void)shared;
     (void)stream;
-    if (fail_launch) return last_error = 719;
+    if (fail_launch) {
+        if (fail_launch == 2) fail_launch = 0;
+        return last_error = 719;
+    }
+    last_error = 0;                                 /* only the last call's error is kept */
     const char *name = "?";
     for (int i = 0; i < n_table; ++i)
         if (table[i].host == host) name = table[i].name;

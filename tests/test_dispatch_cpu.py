@@ -57,3 +57,13 @@ def test_a_failed_router_leaves_nothing_for_the_permutation(launches, T, D, act)
     assert r[2] == (EHIP, [])
     assert r[4][0] == OK
     assert names(r[4])[0] in ("k_perm_small", "k_perm_hist"), names(r[4])
+
+
+@pytest.mark.parametrize("T,D,act,before", [(777, 4096, BF16, []), (300, 72, BF16, []), (30, 64, F32, []),
+                                            (30, 64, F32, ["route 30 2", "permute 30 2"])])
+def test_the_first_of_two_launches_may_fail(launches, T, D, act, before):
+    """Routers that split D, and the statistics, are two kernels: a failure of the first one alone
+    is reported, whether or not the runtime still knows of it after the second."""
+    call = "permute" if before else "route"
+    cmds = [ctx(T, D, 64, 4, act=act), "balance 0.75"] + before + ["fail 2", "%s %d 2" % (call, T)]
+    assert launches(cmds)[-1] == (EHIP, [])
