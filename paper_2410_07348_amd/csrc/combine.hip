@@ -106,7 +106,9 @@ hipError_t launch_combine(const CombineArgs &a, bool bf16, hipStream_t s) {
     const int step = kWave * (bf16 ? ActVec<bf16_t>::N : ActVec<float>::N);
     // With more than two slots the plan is what a piece costs: T = 1999, k = 3, D = 1000 10.3 us in two
     // pieces, 8.0 whole; T = 1000, k = 4, D = 1536 7.7 in three, 9.0 whole.
-    const int span = a.d.T <= (a.d.k <= 2 ? kCombineSplitT : kCombineSplitTMany) ? step : (a.d.D + step - 1) / step * step;
+    const int steps = (a.d.D + step - 1) / step;
+    // (as many pieces as the grid's second dimension takes)
+    const int span = step * (a.d.T <= (a.d.k <= 2 ? kCombineSplitT : kCombineSplitTMany) ? (steps + 65534) / 65535 : steps);
     const dim3 grid((a.d.T + kCombineWaves - 1) / kCombineWaves, (a.d.D + span - 1) / span);
     const dim3 block(kCombineWaves * kWave);
     if (a.d.k <= 2) {

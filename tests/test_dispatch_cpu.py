@@ -2,7 +2,6 @@
 tests/dispatch/launch_log.c takes the place of the HIP runtime's launch functions."""
 import os
 import re
-import shutil
 import subprocess
 
 import pytest
@@ -22,11 +21,12 @@ def launches(tmp_path_factory):
     subprocess.run(["gcc", "-std=c11", "-O1", "-Wall", "-rdynamic", "-I", os.path.join(ROOT, "include"),
                     os.path.join(ROOT, "tests", "dispatch", "launch_log.c"), lib, "-ldl",
                     "-Wl,-rpath," + os.path.dirname(lib), "-Wl,--allow-shlib-undefined", "-o", exe], check=True)
-    filt = shutil.which("c++filt") or "/opt/rocm/llvm/bin/llvm-cxxfilt"
 
     def run(commands):
         r = subprocess.run([exe], input="\n".join(commands) + "\n", capture_output=True, text=True, check=True)
-        text = subprocess.run([filt], input=r.stdout, capture_output=True, text=True, check=True).stdout
+        # (DF16b is __bf16, which older c++filts do not know)
+        text = subprocess.run(["c++filt"], input=r.stdout.replace("DF16b", "t"), capture_output=True, text=True,
+                              check=True).stdout
         out, cur = [], []
         for line in text.splitlines():
             if line.startswith("status "):
@@ -34,7 +34,7 @@ def launches(tmp_path_factory):
                 cur = []
             else:
                 m = re.match(r"launch (?:void )?(?:moepp::)?(.*) (\d+) (\d+) (\d+) (\d+)$", line)
-                name = re.sub(r"\(.*\)$", "", m.group(1)).replace("moepp::", "").replace("__bf16", "bf16")
+                name = re.sub(r"\(.*\)$", "", m.group(1)).replace("moepp::", "").replace("unsigned short", "bf16")
                 cur.append((name, tuple(int(v) for v in m.groups()[1:4]), int(m.group(5))))
         assert len(out) == len(commands), text
         return out
@@ -67,3 +67,15 @@ def test_the_first_of_two_launches_may_fail(launches, T, D, act, before):
     call = "permute" if before else "route"
     cmds = [ctx(T, D, 64, 4, act=act), "balance 0.75"] + before + ["fail 2", "%s %d 2" % (call, T)]
     assert launches(cmds)[-1] == (EHIP, [])
+
+
+@pytest.mark.parametrize("T,D,k,act", [(1, 1 << 25, 2, BF16), (1, 1 << 25, 2, F32), (1000, 1 << 25, 4, F32), (64, 4096, 2, BF16)])
+def test_combine_covers_any_width_within_the_grid(launches, T, D, k, act):
+    """Pieces of a token lie along the grid's second dimension, which takes 65535 workgroups; whole
+    accesses of 64 lanes, all columns covered."""
+    r = launches([ctx(T, D, 64, 0, k=k, act=act, n_zero=1, n_copy=1, n_const=2), "combine %d %d" % (T, k)])
+    (name, grid, threads), = r[1][1]
+    assert name.startswith("k_combine") and threads == 256
+    assert grid[0] == (T + 3) // 4 and grid[1] <= 65535 and grid[2] == 1
+    if D == 4096:
+        assert grid[1] == 8                      # one 16-byte access per lane and piece
