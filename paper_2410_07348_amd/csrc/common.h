@@ -203,7 +203,7 @@ hipError_t launch_ffn_generic(const FfnArgs &a, bool bf16, int which, hipStream_
 bool ffn_mfma_supported(const Dims &d);
 hipError_t launch_ffn_mfma(const FfnArgs &a, int which, hipStream_t s);
 
-// few rows per expert (T * k <= 16 n_ffn and <= 8 N): weight-streaming kernels
+// few rows per expert (at most 16, by a rule on experts and weights): weight-streaming kernels
 bool ffn_decode_supported(const Dims &d);
 hipError_t launch_ffn_decode(const FfnArgs &a, int which, hipStream_t s);
 

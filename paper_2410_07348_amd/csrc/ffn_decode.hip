@@ -258,14 +258,23 @@ static hipError_t dispatch_steps(int S, int which, int fr, int n_wg, const Decod
     }
 }
 
-// At most 8 rows per expert if the router spreads its slots evenly: an expert with more than 16
-// streams its weights once per block of 16, and the tiled kernel, which reads them once for up to
-// 128 rows, is as fast from there on.  D = 4096, F = 5632, 16 experts of 20, top-2, both GEMMs:
-// T = 64 351 us here, 351 tiled; T = 80 352 / 352; T = 100 408 / 353; T = 128 456 / 354;
-// D = 768: T = 64 34 / 36, T = 100 38 / 37, T = 128 43 / 36.
+// An expert with more than 16 rows streams its weights once per block of 16, and the tiled kernel,
+// which reads them once for up to 128 rows, is faster once most experts do.  But few experts leave
+// the tiled kernel a part-filled chip, and weights that the caches hold are cheap to read again.  So
+// the limit is a number of rows per expert (if the router spreads its slots evenly; never more
+// slots than 16 per FFN expert), by the number of FFN experts and the bytes of their weights.  Top-2
+// layer here / tiled, us, D x F:
+//   16 rows: 2 experts, 4096 x 5632 81 / 105; 3 117 / 138; 12, 768 x 1024 (57 MB) 37.6 / 41.5
+//   14 rows: 8, 1536 x 4096 (302 MB) 88 / 97; 10 109 / 123; 8, 4096 x 5632 (1.1 GB) 245 / 232
+//   12 rows: 8, 4096 x 5632 212 / 226; 12, 1536 x 4096 114 / 131
+//   10 rows: 16, 768 x 1024 (75 MB) 39 / 42; 24 49 / 53; 16, 1024 x 2048 (201 MB) 70 / 64
+//    8 rows and more: 16, 1536 x 4096 134 / 128 at 9; 32, 768 x 2048 91 / 81 at 12
+// (with more experts how the tiles fill their last round decides: 24, 1536 x 4096 at 9 191 / 201)
 bool ffn_decode_supported(const Dims &d) {
     const long long slots = (long long)d.T * d.k;
-    return d.n_ffn > 0 && d.n_ffn <= kWave && slots <= 16ll * d.n_ffn && slots <= 8ll * d.N &&
+    const double mb = 6e-6 * d.n_ffn * d.D * d.F;
+    const int rows = d.n_ffn <= 3 || mb <= 64.0 ? 16 : d.n_ffn <= 12 ? (mb <= 400.0 ? 14 : 12) : mb <= 128.0 ? 10 : 8;
+    return d.n_ffn > 0 && d.n_ffn <= kWave && slots <= 16ll * d.n_ffn && slots <= (long long)rows * d.N &&
            d.D % 256 == 0 && d.F % 256 == 0 && d.D <= kDecMaxSteps * 256 && d.F <= kDecMaxSteps * 256;
 }
 

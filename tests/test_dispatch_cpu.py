@@ -79,3 +79,20 @@ def test_combine_covers_any_width_within_the_grid(launches, T, D, k, act):
     assert grid[0] == (T + 3) // 4 and grid[1] <= 65535 and grid[2] == 1
     if D == 4096:
         assert grid[1] == 8                      # one 16-byte access per lane and piece
+
+
+# Weight-streaming FFN or tiles, by rows per expert, number of experts and bytes of weights; the
+# first five are shapes of the GPU tests that are there for the weight-streaming kernels
+@pytest.mark.parametrize("T,D,F,n_ffn,n_const,k,decode", [
+    (48, 512, 512, 6, 2, 2, True), (40, 512, 768, 6, 2, 2, True), (64, 1024, 256, 8, 2, 2, True),
+    (7, 256, 512, 3, 2, 3, True), (30, 1280, 1536, 4, 2, 2, True),
+    (16, 4096, 5632, 2, 0, 2, True), (17, 4096, 5632, 2, 0, 2, False), (64, 768, 1024, 8, 0, 2, True),
+    (56, 1536, 4096, 8, 0, 2, True), (64, 1536, 4096, 8, 0, 2, False), (48, 4096, 5632, 8, 0, 2, True),
+    (52, 4096, 5632, 8, 0, 2, False), (80, 768, 1024, 16, 0, 2, True), (88, 768, 1024, 16, 0, 2, False),
+    (64, 768, 2048, 16, 0, 2, True), (66, 768, 2048, 16, 0, 2, False), (64, 4096, 5632, 16, 2, 2, True),
+    (100, 4096, 5632, 16, 2, 2, False), (64, 1000, 1416, 16, 2, 2, False)])
+def test_which_ffn_takes_few_rows(launches, T, D, F, n_ffn, n_const, k, decode):
+    zc = 1 if n_const else 0
+    r = launches([ctx(T, D, F, n_ffn, k=k, n_zero=zc, n_copy=zc, n_const=n_const), "forward %d %d" % (T, k)])
+    ffn = [n for n in names(r[1]) if n.startswith(("k_ffn", "k_grouped"))]
+    assert len(ffn) == 2 and all(n.startswith("k_ffn_decode<" if decode else "k_grouped_gemm<") for n in ffn), ffn

@@ -78,7 +78,7 @@ def test_bf16_streamed_weights(T):
 
 
 # weight-streaming FFN: one fragment per workgroup in GEMM2 (few experts), two; several units per
-# workgroup; both sides of T k = 8 N and 16 n_ffn; the few-token router's one-workgroup end with
+# workgroup; both sides of T k = 16 n_ffn; the few-token router's one-workgroup end with
 # 1 .. 64 tokens; a combine in pieces of a token
 @pytest.mark.parametrize("T", [1, 2, 15, 16, 17, 32, 33, 63, 64])
 @pytest.mark.parametrize("D,F,n_ffn", [(256, 512, 4), (1280, 256, 12), (512, 2048, 33)])
