@@ -96,3 +96,11 @@ def test_which_ffn_takes_few_rows(launches, T, D, F, n_ffn, n_const, k, decode):
     r = launches([ctx(T, D, F, n_ffn, k=k, n_zero=zc, n_copy=zc, n_const=n_const), "forward %d %d" % (T, k)])
     ffn = [n for n in names(r[1]) if n.startswith(("k_ffn", "k_grouped"))]
     assert len(ffn) == 2 and all(n.startswith("k_ffn_decode<" if decode else "k_grouped_gemm<") for n in ffn), ffn
+
+
+def test_shapes_reach_the_instances_their_gpu_tests_name(launches):
+    from test_gpu_ffn_edges import INSTANCES
+    for kw, gemm1, gemm2 in INSTANCES:
+        act, k = (F32 if kw.get("act") == "f32" else BF16), kw.get("k", 2)
+        r = launches([ctx(kw["T"], kw["D"], kw["F"], kw["n_ffn"], k=k, act=act), "forward %d %d" % (kw["T"], k)])
+        assert [n for n in names(r[1]) if n.startswith(("k_ffn", "k_grouped"))] == [gemm1, gemm2]

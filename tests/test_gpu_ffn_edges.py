@@ -7,7 +7,7 @@ import pytest
 
 from workloads import LayerShape, make_inputs
 
-from helpers import check_layer, gpu_forward, make_layer
+from helpers import check_layer, gpu_forward, make_layer, sample_tokens
 
 pytestmark = pytest.mark.gpu
 
@@ -75,6 +75,37 @@ def test_bf16_tile_geometries(T, D, F, n_ffn, bias):
 @pytest.mark.parametrize("T", [130, 600])
 def test_bf16_streamed_weights(T):
     check(T=T, D=1536, F=4096, n_ffn=8)
+
+
+# Kernel instances that take shapes of their own to reach, GEMM1 and GEMM2 (tests/test_dispatch_cpu.py
+# checks that these shapes launch them): float32 tiles of 64 x 128 with a narrower last slab in GEMM2,
+# and 32 x 64 there; 128 x 256 tiles with a narrower last slab of h; 256 x 256 tiles with streamed
+# weights, which all run as half tiles in GEMM2 and leave 16 of 272 to them in GEMM1.
+FULL, HALF = "Geo<256, 256, 2, 4, 32, 5, 4>", "Geo<128, 256, 2, 4, 32, 5, 4>"
+INSTANCES = [
+    (dict(T=4096, D=1024, F=1000, n_ffn=4, k=3, act="f32"), "k_ffn_f32<true, false, 64, 128, 2, 2>",
+     "k_ffn_f32<false, true, 64, 128, 2, 2>"),
+    (dict(T=4096, D=512, F=256, n_ffn=4, k=3, act="f32"), "k_ffn_f32<true, false, 32, 64, 2, 1>",
+     "k_ffn_f32<false, false, 32, 64, 2, 2>"),
+    (dict(T=300, D=1000, F=424, n_ffn=40), "k_grouped_gemm<%s, true, void, true, false>" % HALF,
+     "k_grouped_gemm<%s, false, void, true, false>" % HALF),
+    (dict(T=2000, D=1536, F=2176, n_ffn=16), "k_grouped_gemm<%s, true, %s, false, true>" % (FULL, HALF),
+     "k_grouped_gemm<%s, false, %s, false, true>" % (FULL, HALF)),
+]
+
+
+@pytest.mark.parametrize("kw", [i[0] for i in INSTANCES])
+def test_instances(kw):
+    s = LayerShape("edge", n_zero=1, n_copy=1, n_const=2, seed=8100, **kw)
+    print("shape", s, flush=True)
+    inp = make_inputs(s)
+    res = gpu_forward(s, inp)
+    if kw["n_ffn"] == 16:
+        # the streamed launch: one tile of rows per expert, and a rest for the half tiles
+        assert max(res["counts"][:16]) <= 256
+        left = 16 * (2 * s.F // 256) % 256
+        assert 0 < left <= 128 and 16 * (s.D // 256) <= 128
+    print("  ", check_layer(s, inp, res, tok_list=sample_tokens(s, res["topk_idx"], 256)), flush=True)
 
 
 # weight-streaming FFN: one fragment per workgroup in GEMM2 (few experts), two; several units per
