@@ -82,13 +82,18 @@ __device__ inline void router_token_quad(const RouterArgs &a, size_t t, bool val
 // Rows of W_res and of the previous logits in LDS: a multiple of four floats, so that
 // they are read 16 bytes at a time, and an odd multiple, so that 16 rows read at one
 // column lie on different banks.
-__device__ inline int residual_stride(int N) { return ((N + 3) / 4 | 1) * 4; }
+__host__ __device__ constexpr int residual_stride(int N) { return ((N + 3) / 4 | 1) * 4; }
+// ... and of the arrays that hold them for any N up to max_n: the widest row.
+constexpr int residual_stride_max(int max_n) {
+    int w = 0;
+    for (int n = 1; n <= max_n; ++n) w = residual_stride(n) > w ? residual_stride(n) : w;
+    return w;
+}
 // Zeros behind the N columns of n rows, up to the next multiple of four, with all threads.
 __device__ inline void zero_residual_pad(float *rows, int n, int N, int threads) {
     const int pad = -N & 3;
     for (int c = threadIdx.x; c < n * pad; c += threads) rows[(c / pad) * residual_stride(N) + N + c % pad] = 0.f;
 }
-constexpr int kResidualStride = kMaxExperts + 4;
 
 // (W_g G(x_prev))_i of one token (Eq.6): row i of W_res (LDS, residual_stride(N)) times the
 // token's previous logits.  Even and odd terms are added up apart.
@@ -157,9 +162,10 @@ __device__ inline void router_finish(const RouterArgs &a, int t0, float *dots, f
     }
     __syncthreads();
     // Softmax, Top-K, a1: threads 4 tok .. 4 tok + 3 share token tok (whole waves
-    // run this, so the shuffles are whole; tokens past the end compute on a copy of
-    // the last token and store nothing)
+    // run this, so the shuffles are whole; tokens past the end compute on whatever their
+    // part of `dots` holds and store nothing)
     static_assert(4 * TOK <= NT, "four threads per token");
+    static_assert(residual_stride_max(MAXN) > MAXN, "N + 1 probabilities of a token fit its row of prevs");
     if (tid < 4 * TOK) {
         const int tok = tid >> 2;
         // (prevs is free again: the probabilities of the load-balance statistics go there)

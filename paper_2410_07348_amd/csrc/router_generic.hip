@@ -213,8 +213,8 @@ __global__ __launch_bounds__(kPermSmallWaves *kWave) void k_router_small_final_p
     constexpr int NT = kPermSmallWaves * kWave;
     constexpr int DSTR = kMaxRouterRows + 1, MAXN = 4 * PER;
     __shared__ float dots[kRouterFusedT * DSTR];
-    __shared__ __attribute__((aligned(16))) float prevs[kRouterFusedT * (MAXN + 4)];
-    __shared__ __attribute__((aligned(16))) float wres[MAXN * (MAXN + 4)];
+    __shared__ __attribute__((aligned(16))) float prevs[kRouterFusedT * residual_stride_max(MAXN)];
+    __shared__ __attribute__((aligned(16))) float wres[MAXN * residual_stride_max(MAXN)];
     __shared__ float sbias[MAXN];
     __shared__ int s_idx[kRouterFusedT * kMaxTopK];
     __shared__ int s_rank[kPermSmallWaves][kMaxExperts];
@@ -274,8 +274,8 @@ template <int ROWS>
 __global__ __launch_bounds__(kRouterFinalThreads) void k_router_final(RouterArgs a, int splits) {
     constexpr int TOK = kRouterFinalTok, NT = kRouterFinalThreads;
     constexpr int MAXN = ROWS < kMaxExperts ? ROWS : kMaxExperts, DSTR = ROWS + 1;
-    __shared__ __attribute__((aligned(16))) float prevs[TOK * (MAXN + 4)];
-    __shared__ __attribute__((aligned(16))) float wres[MAXN * (MAXN + 4)];
+    __shared__ __attribute__((aligned(16))) float prevs[TOK * residual_stride_max(MAXN)];
+    __shared__ __attribute__((aligned(16))) float wres[MAXN * residual_stride_max(MAXN)];
     __shared__ float dots[TOK * DSTR];
     __shared__ float sbias[MAXN];
     __shared__ int s_hist[MAXN];

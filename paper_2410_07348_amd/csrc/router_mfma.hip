@@ -68,7 +68,7 @@ __global__ __launch_bounds__(4 * TOK * KG, WPE) void k_router_mfma(RouterArgs a)
     constexpr int STAGE = kRtXBytes + WBYTES;
     constexpr int DSTR = ROWS + 1;                        // floats per token in `dots`
     constexpr int MAXN = ROWS < kMaxExperts ? ROWS : kMaxExperts;    // N <= N + 2 n_const <= ROWS
-    constexpr int RSTR = MAXN + 4;                        // >= residual_stride(N)
+    constexpr int RSTR = residual_stride_max(MAXN);       // >= residual_stride(N)
     constexpr int E_BYTES = (2 * KG * kRtTok * DSTR + (kRtTok + MAXN) * RSTR + 2 * MAXN + 4) * 4;
     constexpr int LDS_BYTES = 2 * KG * STAGE > E_BYTES ? 2 * KG * STAGE : E_BYTES;
     static_assert(LDS_BYTES <= 160 * 1024 && PF % 2 == 0, "LDS / PF");
