@@ -248,11 +248,11 @@ moepp_status moepp_get_intermediates(moepp_ctx *ctx, const float **alpha1,
 enum {
     MOEPP_K_ROUTER = 0,  /* router GEMM + residual + softmax + top-k         */
     MOEPP_K_HIST = 1,    /* permute: per-chunk histogram; 0 when the router kernel
-                            has counted its own selections (every router of the
-                            automatic variant from 65 tokens on, and the matrix-core
-                            router); without its counts calls with at most 4096 slots
-                            do all three steps in one kernel, reported as
-                            MOEPP_K_SCATTER                                   */
+                            has counted its own selections (the matrix-core router,
+                            and the automatic variant's other routers from 65 tokens
+                            up to 655360 dot products, T (N + 2 n_const)); without its
+                            counts calls with at most 4096 slots do all three steps in
+                            one kernel, reported as MOEPP_K_SCATTER            */
     MOEPP_K_SCAN = 2,    /* permute: exclusive scan as a kernel of its own; 0 up to
                             2048 chunks (scan and scatter are one kernel)    */
     MOEPP_K_SCATTER = 3, /* permute: (scan and) stable scatter; 0 for calls with at
@@ -318,9 +318,10 @@ moepp_status moepp_get_balance(moepp_ctx *ctx, const float **f, const float **P,
  * D across workgroups, in plain fp32 FMA, for either activation type),
  * 1 = force the generic kernels (any supported shape, plain fp32 FMA),
  * 2 = require the MFMA kernels (EUNSUPPORTED at call time if the shape or
- * type has none), 3 = as 2, and the grouped GEMM leaves a sparsely filled last
- * round of tiles to its main launch instead of a second launch with tiles of
- * half the height (same results bit for bit; lets a test compare the two).
+ * type has none), 3 = as 2, with the plainest form of the grouped GEMM: no tiles
+ * of half the height in a sparsely filled last round, no 128 x 128 tiles, no
+ * streamed weights (same results bit for bit; lets a test compare them), and
+ * never the weight-streaming kernels for few rows per expert.
  */
 moepp_status moepp_set_variant(moepp_ctx *ctx, int32_t variant);
 

@@ -20,8 +20,8 @@ constexpr int kWave = 64;         // CDNA wavefront
 constexpr int kRouterFusedT = 64;
 
 // Permutation: one wave owns a chunk of consecutive slots: kPermChunk of them,
-// or the slots of one workgroup of the MFMA router when that kernel has
-// counted them (at least 64 tokens).
+// or the slots of one block of tokens of the router when that has counted
+// them (at least 64 tokens).
 constexpr int kPermChunk = 4 * kWave;
 constexpr int kPermMinChunkTokens = 64;
 // Up to this many chunks every scatter wave adds up the histogram rows itself
@@ -107,7 +107,7 @@ struct Workspace {
     void *yffn;          // [T_max*k, D] act
     double *bal_partial; // [kBalWaves][kMaxExperts] partial sums of Softmax(G(x))
     float *bal;          // f [N], P [N], L_b [1]  (Eq.7)
-    float *router_partial; // router_small_bytes(): per-slice dot products of the few-token router
+    float *router_partial; // router_small_bytes(): per-slice dot products of the routers that split D
 };
 
 // Expert capacities (Eq.8), by value in the kernel arguments.  on = false: unlimited.
@@ -126,10 +126,10 @@ struct RouterArgs {
     int32_t *topk_idx;
     float *topk_w;
     float *alpha1;
-    int32_t *chunk_hist;  // MFMA router: [workgroup][N] selections per expert, or null
+    int32_t *chunk_hist;  // [block of tokens][N] selections per expert, or null
     float *partial;       // router_small_bytes() of scratch for partial dot products
-    double *bal_partial;  // MFMA router: [workgroup][kMaxExperts] sums of Softmax(G(x))_i over the
-                          // workgroup's tokens (for P_i of Eq.7), or null
+    double *bal_partial;  // [block of tokens][kMaxExperts] sums of Softmax(G(x))_i over the
+                          // block's tokens (for P_i of Eq.7), or null
 };
 
 struct FfnArgs {
@@ -142,7 +142,7 @@ struct FfnArgs {
     void *h;              // [h_rows, F] K-slab-major; rows < R are written
     void *yffn;           // [R,D] row-major
     int h_rows;           // T_max * k
-    bool no_tail;         // tests: leave a sparsely filled last round of tiles to the main launch
+    bool no_tail;         // tests (variant 3): one tile geometry, no half tiles, cached weights
 };
 
 struct CombineArgs {

@@ -386,8 +386,8 @@ hipError_t launch_ffn_f32(const FfnArgs &f, int which, hipStream_t s) {
     typedef std::integral_constant<int, 32> c32;
     typedef std::integral_constant<int, 64> c64;
     typedef std::integral_constant<int, 128> c128;
-    // At most 16 slots per FFN expert: one block of 16 rows covers an expert's group, and
-    // the weights are what there is to move.
+    // At most 16 slots per FFN expert: one block of 16 rows covers most experts' groups (a larger
+    // group streams its weights once per block), and the weights are what there is to move.
     if (slots <= 16ll * f.d.n_ffn) {
         const long long n = blocks(16, 64);
         return which == 0 ? go(k_ffn_f32_stream<true>, n, kF32StreamWaves * kWave)

@@ -49,14 +49,14 @@ struct GemmArgs {
     const int32_t *src_of;   // GEMM1 only
     int ld;                  // row length of the row-major operand (x or yffn)
     int h_rows;              // rows of the slab-major h buffer
-    int K;                   // reduction length (multiple of 64)
+    int K;                   // reduction length (a multiple of 64, of 8 in the RAG instances)
     int Nb;                  // rows of B per expert (2F or D)
     int Nc;                  // columns of C (F or D)
     int n_ffn, topk;
     int n_ntiles;
-    int jstride;             // persistent kernel: workgroups per XCD
+    int jstride;             // workgroups per XCD
     int cut_grid;            // > 0: the tiles of a last, at most half-filled round of cut_grid
-                             // workgroups are left to the tail kernel (halves of 128 rows)
+                             // workgroups run as halves of 128 rows at the end of the launch
 };
 
 // silu(z) = z / (1 + e^-z) with the hardware exp2 and reciprocal (1 ulp each:
@@ -196,8 +196,7 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs &a, const GroupTiles &
     // XCDs round-robin, so at any time the 8 XCDs hold 8 neighbouring patches
     // (same rows, next columns): what one XCD fetched from HBM the others
     // find in the memory-side cache.  Tile j of XCD x is run by workgroup
-    // x + 8*(j % jstride), jstride = workgroups per XCD (persistent kernel) or
-    // by workgroup x + 8*j (one tile per workgroup).  The order is computed
+    // x + 8*(j % jstride), jstride = workgroups per XCD.  The order is computed
     // here from the group offsets.
     // Assumes the part this library is written for, MI355X in its default (SPX)
     // partition mode: 8 XCDs of 32 CUs, workgroup w dispatched to XCD w % 8.  On
@@ -208,8 +207,8 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs &a, const GroupTiles &
     const int o_lo = gt.o_lo, o_hi = gt.o_hi, mt_q = gt.mt_q, incl = gt.incl;
     const int total = __builtin_amdgcn_readlane(incl, kWave - 1);
     // A last round that fills at most half of the workgroups costs a whole
-    // tile time with most of the chip idle: those tiles [cut, total) go to the
-    // tail launch, which runs them as twice as many half tiles.
+    // tile time with most of the chip idle: those tiles [cut, total) are left to the
+    // second half of the kernel, which runs them as twice as many half tiles.
     int cut = total;
     if (a.cut_grid > 0) {
         const int n_left = total % a.cut_grid;
@@ -786,6 +785,8 @@ hipError_t launch_ffn_mfma(const FfnArgs &f, int which, hipStream_t s) {
     // (T = 400, D = 1536); Full, whose last round of up to 128 tiles runs as halves: 48 tiles
     // 20 / 31 (T = 1500, D = 768), but 96 tiles 33 / 32 and 44 / 38 (T = 4096, D = 768, 16 and 32
     // experts); 192 tiles, one round without halves, 50 / 54 (T = 8192, D = 1024); 256 tiles 40 / 41.
+    // Layers with and without the window from 129 to 208: 144 - 168 tiles 0.92 - 0.96 (six shapes),
+    // 192 - 200 between 0.92 and 1.03 (eight).
     const bool small = few ? n_tiles <= 128 : n_tiles <= 64 || (n_tiles > 128 && n_tiles <= 208);
     // Widths that are not multiples of 64, and reductions too short for the ring's four
     // K tiles: the K loop is padded by zeros.
@@ -797,6 +798,9 @@ hipError_t launch_ffn_mfma(const FfnArgs &f, int which, hipStream_t s) {
     // combine 13.6 -> 11.1 us); T = 400, D = 1536, F = 4096 (604 MB): GEMM1 77 / 83, GEMM2 42 / 47.
     // At 151 - 201 MB, called again and again: 32 against 23 us.
     // The same for one 256-row tile per expert (T = 2048, D = 4096: layer 535 -> 525 us).
+    // (These rules take the router to spread its slots evenly.  Layers of 16 experts of which one or
+    // two take most slots, 65 - 4096 tokens at D = 768, 1536, 4096: 0.82 - 1.01 of the time with
+    // four-wave 128-row tiles and cached weights.)
     const bool stream = (few || rows <= 224) && 6.0 * f.d.n_ffn * f.d.D * f.d.F > 256.0 * (1 << 20);
     if (f.no_tail) return few ? launch_cfg<Half>(f, which, s) : launch_cfg<Full>(f, which, s);
     if (small)

@@ -18,16 +18,16 @@ struct moepp_ctx {
     Workspace ws;
     size_t ws_bytes;
     const float *bias;
-    int variant;          // 0 auto, 1 generic, 2 require MFMA, 3 as 2 without the GEMM tail launch
+    int variant;          // 0 auto, 1 generic, 2 require MFMA, 3 as 2 in its plainest form (see moepp_set_variant)
     CapArgs cap;          // expert capacities (Eq.8); cap.on = false: unlimited
     double bal_tau;       // > 0: collect the load-balance statistics (Eq.7) with this tau
     const float *last_out_gate;   // logits of the last routed call (read by the statistics)
     int last_T, last_k;
-    // the MFMA router leaves a histogram per workgroup for the permutation of the same call
     int bal_rows;         // > 0: the router kernel of call (bal_T) left this many rows of Softmax sums
     int bal_T;
     bool perm_valid;      // the few-token router kernel has already grouped the slots of call (perm_T, perm_k)
     int perm_T, perm_k;
+    // the router of call (hist_T, hist_k) has left a histogram per block of tokens for the permutation
     bool hist_valid;
     int hist_T, hist_k, hist_chunk_slots;
     bool timing;

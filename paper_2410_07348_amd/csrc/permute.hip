@@ -228,8 +228,8 @@ __global__ __launch_bounds__(kPermSmallWaves *kWave) void k_perm_small(Dims d, W
 // ---- load-balance statistics (Eq.7) ---------------------------------------
 // Pass 1: wave g takes tokens g, g + kBalWaves, ...; lane i owns expert i,
 // recomputes Softmax(G(x_t))_i from the logits the router wrote and adds it
-// up in fp64 (not needed when the matrix-core router has left the sums of its
-// workgroups' tokens itself).  Pass 2: one workgroup adds the per-wave sums in a fixed order
+// up in fp64 (not needed when the router has left the sums of its blocks of
+// tokens itself).  Pass 2: one workgroup adds the per-wave sums in a fixed order
 // (the result is the same on every run), P_i = sum / T, f_i = counts_i / T,
 // L_b = sum_i eta_i f_i P_i with eta = 1 for FFN experts, tau for the others.
 __global__ __launch_bounds__(4 * kWave) void k_balance_partial(Dims d, Workspace w, const float *out_gate) {

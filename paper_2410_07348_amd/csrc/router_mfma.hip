@@ -328,7 +328,7 @@ hipError_t launch_router_mfma(const RouterArgs &a, hipStream_t s) {
     }
     // 64-token workgroups take two K tiles at a time, in two groups of four waves: a tile is a
     // serial chain (loads, split, LDS, barrier, MFMA) and there are at most a few workgroups
-    // per CU.  T = 16384, D = 2048: 35.6 -> 20.8 us; T = 4096, D = 768, 52 rows: 38 -> 20.6
+    // per CU.  T = 16384, D = 2048: 28.4 -> 22.0 us by events; T = 4096, D = 768, 52 rows: 38 -> 20.6
     // (10 of it the epilogue's LDS bank conflicts).  Four groups: the same.
     if (tok == 128)
         hipLaunchKernelGGL((k_router_mfma<1, 4, 128, 2, 1, false>), grid, dim3(512), 0, s, a);

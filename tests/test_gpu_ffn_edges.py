@@ -45,7 +45,7 @@ def test_bf16_short_reduction(D, F):
     check(T=900, D=D, F=F, n_ffn=4, k=3)
 
 
-# routers between the few-token one (T <= 256) and the 128-token blocks (T >= 24576): two groups
+# routers between the few-token one (T <= 64) and the 128-token blocks (T >= 24576): two groups
 # of waves (tiles % 8, % 4, neither), slices of D (24 tiles of 64 or more, at most 64 blocks), one
 # and two blocks of weight rows, widths for the sliced FMA router (also more than 64 rows)
 @pytest.mark.parametrize("D", [128, 256, 512, 1408, 1536, 4096, 72])

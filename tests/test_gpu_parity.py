@@ -453,11 +453,11 @@ def test_mfma_and_generic_kernels_agree():
 
 def test_gemm_tail_launch_is_bitwise_the_single_launch():
     """A problem of a few rounds of tiles whose last round is sparsely filled is
-    finished by a second launch with half-height tiles: same bits as one launch,
-    and right against the oracle."""
+    finished with half-height tiles in the same launch: same bits as with whole tiles
+    only (variant 3), and right against the oracle."""
     s = small_shape("tail", T=9000, D=512, F=1024, n_ffn=5, seed=131)
     inp = make_inputs(s)
-    a = gpu_forward(s, inp, variant=3)               # the default geometry without the tail launch
+    a = gpu_forward(s, inp, variant=3)               # the default geometry without half tiles
     b = gpu_forward(s, inp, variant=2)
     m_tiles = int(sum(-(-int(c) // 256) for c in b["counts"][:s.n_ffn]))
     left1, left2 = m_tiles * (2 * s.F // 256) % 256, m_tiles * (s.D // 256) % 256
