@@ -8,7 +8,7 @@ import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 F32, BF16 = 0, 1
-OK, EHIP = 0, -4
+OK, EUNSUPPORTED, EHIP = 0, -2, -4
 
 
 @pytest.fixture(scope="module")
@@ -93,9 +93,14 @@ def test_combine_covers_any_width_within_the_grid(launches, T, D, k, act):
     (100, 4096, 5632, 16, 2, 2, False), (64, 1000, 1416, 16, 2, 2, False)])
 def test_which_ffn_takes_few_rows(launches, T, D, F, n_ffn, n_const, k, decode):
     zc = 1 if n_const else 0
-    r = launches([ctx(T, D, F, n_ffn, k=k, n_zero=zc, n_copy=zc, n_const=n_const), "forward %d %d" % (T, k)])
-    ffn = [n for n in names(r[1]) if n.startswith(("k_ffn", "k_grouped"))]
-    assert len(ffn) == 2 and all(n.startswith("k_ffn_decode<" if decode else "k_grouped_gemm<") for n in ffn), ffn
+    call = "forward %d %d" % (T, k)
+    r = launches([ctx(T, D, F, n_ffn, k=k, n_zero=zc, n_copy=zc, n_const=n_const), call, "variant 2", call, "variant 3", call])
+    for i, few in ((1, decode), (3, decode), (5, False)):
+        if i > 1 and D % 128:
+            assert r[i] == (EUNSUPPORTED, [])
+            continue
+        ffn = [n for n in names(r[i]) if n.startswith(("k_ffn", "k_grouped"))]
+        assert len(ffn) == 2 and all(n.startswith("k_ffn_decode<" if few else "k_grouped_gemm<") for n in ffn), ffn
 
 
 def test_shapes_reach_the_instances_their_gpu_tests_name(launches):
