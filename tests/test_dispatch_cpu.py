@@ -1,4 +1,4 @@
-"""What the calls of the C ABI launch, by kernel instance and grid, without a GPU: the driver
+"""What the calls of the C ABI launch, by kernel instance and grid, without a GPU: the program
 tests/dispatch/launch_log.c takes the place of the HIP runtime's launch functions."""
 import os
 import re
