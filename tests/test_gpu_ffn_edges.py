@@ -159,20 +159,20 @@ def test_ragged_silu(T):
     assert np.array_equal(a["h"], b["h"])
 
 
-# float32 layers on split operands (D and F multiples of 32): 128 x 256 tiles, 128 x 128 and 64 x 64 ones, an
-# odd and an even number of slabs, the smallest widths that take it, groups that end inside a tile; the rule
-# is looked at in tests/test_dispatch_cpu.py
-SPLIT = [
-    (dict(T=4096, D=544, F=992, n_ffn=12), "<true, 128, 256, 2, 4>", "<false, 64, 64, 2, 2>"),
-    (dict(T=700, D=736, F=1024, n_ffn=6), "<true, 128, 128, 4, 2>", "<false, false, 32, 32, 2, 2>"),
-    (dict(T=333, D=512, F=512, n_ffn=16, bias="normal"), "<true, 64, 64, 4, 1>", "<false, false, 32, 32, 2, 2>"),
-    (dict(T=3000, D=1024, F=256, n_ffn=4, k=3, bias="normal"), "<true, 128, 128, 4, 2>", "<false, 128, 256, 2, 4>"),
-    (dict(T=2000, D=768, F=384, n_ffn=8, k=3), "<true, 128, 128, 4, 2>", "<false, 128, 128, 2, 4>"),
+# float32 layers from 16 rows per expert up to 2250, widths that are multiples of 32: 64 x 128, 32 x 64 and
+# 32 x 32 tiles, an odd and an even number of slabs, groups that end inside a tile; the instances are looked
+# at in tests/test_dispatch_cpu.py
+F32_TILES = [
+    (dict(T=4096, D=544, F=992, n_ffn=12), "<true, false, 64, 128, 2, 2>", "<false, false, 32, 64, 2, 2>"),
+    (dict(T=700, D=736, F=1024, n_ffn=6), "<true, false, 32, 64, 2, 1>", "<false, false, 32, 32, 2, 2>"),
+    (dict(T=333, D=512, F=512, n_ffn=16, bias="normal"), "<true, false, 32, 64, 2, 1>", "<false, false, 32, 32, 2, 2>"),
+    (dict(T=3000, D=1024, F=256, n_ffn=4, k=3, bias="normal"), "<true, false, 32, 64, 2, 1>", "<false, false, 64, 128, 2, 2>"),
+    (dict(T=2000, D=768, F=384, n_ffn=8, k=3), "<true, false, 32, 64, 2, 1>", "<false, false, 32, 64, 2, 2>"),
 ]
 
 
-@pytest.mark.parametrize("kw", [i[0] for i in SPLIT])
-def test_f32_split(kw):
+@pytest.mark.parametrize("kw", [i[0] for i in F32_TILES])
+def test_f32_tiles(kw):
     s = LayerShape("edge", n_zero=1, n_copy=1, n_const=2, seed=8100, act="f32", **kw)
     print("shape", s, flush=True)
     inp = make_inputs(s)
@@ -180,9 +180,40 @@ def test_f32_split(kw):
     print("  ", check_layer(s, inp, res, tok_list=sample_tokens(s, res["topk_idx"], 256)), flush=True)
 
 
-def test_f32_split_of_the_largest_floats_and_infinities():
-    """The largest finite float does not overflow in its first piece, and infinite or NaN operands give
-    what the plain FMA kernels give: the same elements of h infinite (with their sign), NaN and finite."""
+@pytest.mark.parametrize("scale", [1.0, 1e-18])
+@pytest.mark.parametrize("n", [1, 4])
+def test_f32_products_are_float32_products(n, scale):
+    """Rows of h with n numbers that are not zero, down to 1e-36: every term of a sum is rounded at most
+    once with its addition, 2^-24 of what is added up (and half the smallest float where that is below
+    the normal ones), so yffn is within n 2^-24 of the sum of its terms' magnitudes."""
+    s = LayerShape("edge", T=3000, D=1024, F=512, n_ffn=4, n_zero=0, n_copy=0, n_const=0, k=1, act="f32",
+                   residual=False, seed=8400)
+    inp = make_inputs(s)
+    cols = [5, 77, 300, 511][:n]
+    w1 = np.zeros_like(inp["w1"])
+    w1[:, cols] = inp["w1"][:, cols]
+    inp["w1"] = w1
+    inp["x"] = (inp["x"] * scale).astype(np.float32)
+    res = gpu_forward(s, inp)
+    assert np.abs(res["h"][:, cols]).max() > 1e-2 * scale * scale and not np.delete(res["h"], cols, axis=1).any()
+    worst = 0.0
+    for e in range(s.n_ffn):
+        rows = slice(res["offsets"][e], res["offsets"][e + 1])
+        h, w2 = res["h"][rows][:, cols].astype(np.float64), inp["w2"][e][:, cols].astype(np.float64)
+        err = np.abs(res["yffn"][rows] - h @ w2.T)
+        bound = n * (2.0 ** -24 * (np.abs(h) @ np.abs(w2).T) + 2.0 ** -150)
+        worst = max(worst, (err / bound).max())
+    print("nonzero", n, "scale", scale, "error / bound", worst, flush=True)
+    assert worst <= 1.0
+
+
+# NaN of both signs, and with nothing but the lowest bits of the significand set
+NANS = np.array([0x7fc00000, 0xffc00000, 0x7f800001, 0xff80ffff], np.uint32).view(np.float32)
+
+
+def test_f32_largest_floats_infinities_and_nan():
+    """The largest finite float does not overflow, and infinite or NaN operands give what the plain FMA
+    kernels give: the same elements of h infinite (with their sign), NaN and finite."""
     s = LayerShape("edge", T=3000, D=1024, F=512, n_ffn=4, n_zero=0, n_copy=0, n_const=0, k=1, act="f32",
                    residual=False, seed=8400)
     inp = make_inputs(s)
@@ -205,12 +236,21 @@ def test_f32_split_of_the_largest_floats_and_infinities():
     x[4::7, 8] = np.nan
     inp["w1"][0, 3, 9] = np.inf
     inp["w3"][1, 4, 10] = -np.inf
+    for i, nan in enumerate(NANS):
+        x[4 + 7 * i::28, 8] = nan
+        inp["w1"][2, 10 + i, 9] = nan
+        inp["w3"][3, 20 + i, 10] = nan
     a, b = gpu_forward(s, inp), gpu_forward(s, inp, variant=1)
     assert np.array_equal(a["src_of"], b["src_of"])
     for name in ("h", "yffn"):
         ha, hb = a[name], b[name]
         for what in (np.isnan, np.isposinf, np.isneginf):
             assert np.array_equal(what(ha), what(hb)), (name, what.__name__)
+    rows = np.nonzero(np.isin(a["src_of"], np.arange(4, s.T, 7)))[0]
+    assert np.isnan(a["h"][rows]).all()
+    for i in range(len(NANS)):
+        assert np.isnan(a["h"][a["offsets"][2]:a["offsets"][3], 10 + i]).all()
+        assert np.isnan(a["h"][a["offsets"][3]:a["offsets"][4], 20 + i]).all()
 
 
 # combine: instances for 2, 4 and 8 slots, in pieces of a token and whole
