@@ -264,31 +264,36 @@ __device__ inline float lanes_sum(float v) {
     return v;
 }
 
-// Three bf16 pieces of four floats, w = hi + mid + lo exactly: hi is w cut off after 8 significand
-// bits (so that no finite w overflows), mid the rest rounded to 8 bits, lo what is left, at most 8 bits.
+// Three bf16 pieces of four floats, w = hi + mid + lo: hi is w cut off after 8 significand bits (so that no
+// finite w overflows), mid the rest rounded to 8 bits, lo what is left, at most 8 bits.  bf16 has none of the
+// bits of a float32 below 2^-133: `lost` collects the words that lo is cut from, whose lower halves are zero
+// unless a w was too small for its pieces.  (w infinite or NaN: mid and lo are NaN, hi may be infinite for either.)
 typedef bf16_t bf16x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 struct Split4 {
     u32x2 hi, mid, lo;
 };
-__device__ inline Split4 split4(f32x4 w) {
+__device__ inline Split4 split4(f32x4 w, uint32_t &lost) {
+    constexpr uint32_t UPPER = 0x07060302;                            // the upper halves of two words
     Split4 s;
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
         const uint32_t a = __float_as_uint(w[2 * i]), b = __float_as_uint(w[2 * i + 1]);
-        s.hi[i] = __builtin_amdgcn_perm(b, a, 0x07060302);            // the upper halves of a and b
+        s.hi[i] = __builtin_amdgcn_perm(b, a, UPPER);
         const float ra = w[2 * i] - __uint_as_float(a & 0xffff0000u);
         const float rb = w[2 * i + 1] - __uint_as_float(b & 0xffff0000u);
-        bf16x2 m, l;
+        bf16x2 m;
         m[0] = (bf16_t)ra;
         m[1] = (bf16_t)rb;
         s.mid[i] = __builtin_bit_cast(uint32_t, m);
-        l[0] = (bf16_t)(ra - __uint_as_float(s.mid[i] << 16));
-        l[1] = (bf16_t)(rb - __uint_as_float(s.mid[i] & 0xffff0000u));
-        s.lo[i] = __builtin_bit_cast(uint32_t, l);
+        const uint32_t la = __float_as_uint(ra - __uint_as_float(s.mid[i] << 16));
+        const uint32_t lb = __float_as_uint(rb - __uint_as_float(s.mid[i] & 0xffff0000u));
+        s.lo[i] = __builtin_amdgcn_perm(lb, la, UPPER);
+        asm("v_or3_b32 %0, %1, %2, %0" : "+v"(lost) : "v"(la), "v"(lb));
     }
     return s;
 }
+__device__ inline bool split_lost(uint32_t lost) { return (lost & 0xffffu) != 0; }
 
 __device__ inline float wave_sum(float v) {
 #pragma unroll

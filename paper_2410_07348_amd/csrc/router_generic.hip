@@ -118,7 +118,8 @@ __global__ __launch_bounds__(kRouterWaves *kWave) void k_router_generic(RouterAr
 // The reduction over D is cut into slices of 32 columns, a wave each, whose operands go straight
 // from memory into the registers of the matrix instruction: for each of TB blocks of 16 tokens and RB
 // blocks of 16 weight rows lane l holds row l % 16, columns 8 (l / 16) .. + 7.  bf16 layers: the
-// float32 weights are split into three exact bf16 pieces, so all products are exact; float32 layers:
+// float32 weights are split into three exact bf16 pieces, so all products are exact (weights that have no such
+// pieces, and infinities and NaN on either side, go to the float32 instruction); float32 layers:
 // v_mfma_f32_16x16x4_f32, column 8 (l / 16) + j in instruction j.  The waves of a
 // workgroup meet in LDS.  (One thread per token with the tile in LDS, plain FMA: every thread read each
 // weight from LDS, 5300 cycles for 64 columns, any number of tokens.)
@@ -176,6 +177,7 @@ __device__ inline void few_dots(const RouterArgs &a, int t0, int first, int stri
         for (int i = 0; i < TB; ++i)
 #pragma unroll
             for (int j = 0; j < RB; ++j) part[q][i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    uint32_t lost = 0;
     auto mul = [&](int ks, Slice &s) {
         if (ks >= n) return;                               // (the same for the whole wave)
         if (32 * ks + 8 * lq >= D) {                       // columns past the last: zero in both operands
@@ -189,7 +191,7 @@ __device__ inline void few_dots(const RouterArgs &a, int t0, int first, int stri
 #pragma unroll
         for (int j = 0; j < RB; ++j) {
             if constexpr (BF16) {
-                const Split4 p0 = split4(s.w[j][0]), p1 = split4(s.w[j][1]);
+                const Split4 p0 = split4(s.w[j][0], lost), p1 = split4(s.w[j][1], lost);
                 auto join = [](u32x2 u, u32x2 v) {
                     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
                     return __builtin_bit_cast(bf16x8, u32x4{u[0], u[1], v[0], v[1]});
@@ -253,17 +255,47 @@ __device__ inline void few_dots(const RouterArgs &a, int t0, int first, int stri
         mul(ks + stride, s1);
         if (ks + 3 * stride < n) load(ks + 3 * stride, s1);
     }
-    // (an infinity is all in the hi products: its lower pieces, and what meets a piece that is zero, are NaN)
+    bool odd = false;
 #pragma unroll
     for (int i = 0; i < TB; ++i)
 #pragma unroll
-        for (int j = 0; j < RB; ++j)
+        for (int j = 0; j < RB; ++j) {
+            acc[i][j] = part[0][i][j] + part[1][i][j];
+            if constexpr (!BF16) acc[i][j] += part[2][i][j] + part[3][i][j];
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const float hi = part[0][i][j][v], sum = hi + part[1][i][j][v];
-                if constexpr (BF16) acc[i][j][v] = __builtin_isinf(hi) ? hi : sum;
-                else acc[i][j][v] = sum + (part[2][i][j][v] + part[3][i][j][v]);
-            }
+            for (int v = 0; v < 4; ++v) odd |= !__builtin_isfinite(acc[i][j][v]);
+        }
+    if constexpr (BF16) {
+        // What the pieces do not give comes from the float32 instruction: sums that are not finite (the lower
+        // pieces of an infinity are NaN, and hi of a NaN may be infinite), one by one, so that no token
+        // depends on another; all of them when a weight was too small for its pieces.
+        const bool small = __ballot(split_lost(lost)) != 0;
+        if (small || __ballot(odd) != 0) {
+            // (block by block: few registers, or fewer waves of the others fit a SIMD)
+#pragma unroll
+            for (int i = 0; i < TB; ++i)
+#pragma unroll
+                for (int j = 0; j < RB; ++j) {
+                    f32x4 plain = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+                    for (int ks = first; ks < n; ks += stride) {
+                        const int k = 32 * ks + 8 * lq, at = min(k, D - 8);
+                        const bool in = k < D;             // columns past the last: zero in both operands
+                        const ActVec<AT> x = load_vec(px[i] + at);
+#pragma unroll
+                        for (int u = 0; u < 2; ++u) {
+                            const f32x4 w = *reinterpret_cast<const f32x4 *>(pw[j] + at + 4 * u);
+#pragma unroll
+                            for (int c = 0; c < 4; ++c)
+                                plain = __builtin_amdgcn_mfma_f32_16x16x4f32(in ? w[c] : 0.f, in ? x.get(4 * u + c) : 0.f, plain, 0, 0, 0);
+                        }
+                    }
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+                        if (small || !__builtin_isfinite(acc[i][j][v])) acc[i][j][v] = plain[v];
+                }
+        }
+    }
     // (the wave's first slice of them)
     for (int ks = first + (max(n - first, 0) + stride - 1) / stride * stride; ks < n_all; ks += stride) residual(32 * (ks - n));
 }

@@ -140,3 +140,45 @@ def test_infinite_previous_logits_stay_with_their_token(act, T, D, n_ffn):
     for name in ("out_gate", "topk_idx", "topk_w"):
         assert np.array_equal(res[name][others], ref[name][others]), name
     assert np.array_equal(res["alpha1"], ref["alpha1"])
+
+
+# NaN of both signs, and with nothing but the lowest bits of the significand set
+NANS = np.array([0x7fc00000, 0xffc00000, 0x7f800001, 0xff80ffff], np.uint32).view(np.float32)
+
+
+@pytest.mark.parametrize("act,T,D,variant", [r + (0,) for r in ROUTERS] + [("bf16", 3, 64, 0), ("bf16", 300, 512, 1)])
+def test_nan_weights(act, T, D, variant):
+    """A NaN among the weights of an expert makes its logit NaN, whatever the NaN's bits, and nothing
+    else; a NaN in W_c the a1 of its constant expert."""
+    s = one_hot_shape(act, T, D)
+    inp = make_inputs(s)
+    L = exact_logits(s, inp)
+    inp["x"][:, 7] = 0.5
+    inp["W_c"][:, :, 7] = 0.0
+    ref = gpu_forward(s, inp, variant)
+    for i, nan in enumerate(NANS):
+        inp["W_g"][1 + 2 * i, 7] = nan
+        L[:, 1 + 2 * i] = np.nan
+        inp["W_c"][1, 1, 7] = nan
+        res = gpu_forward(s, inp, variant)
+        assert np.array_equal(res["out_gate"].astype(np.float64), L, equal_nan=True), hex(nan.view(np.uint32))
+        assert np.isnan(res["topk_w"]).all()
+        assert np.array_equal(res["alpha1"][:, 0], ref["alpha1"][:, 0])
+        assert np.isnan(res["alpha1"][:, 1]).all()
+
+
+# (every router but the matrix-core one, whose three bf16 pieces of a weight end at 2^-133)
+@pytest.mark.parametrize("exponent", [-118, -130, -145])
+@pytest.mark.parametrize("act,T,D,variant", [r + (0,) for r in ROUTERS if r[:3] != ("bf16", 24576, 512)] +
+                         [("bf16", 3, 64, 0), ("bf16", 1500, 1536, 0), ("bf16", 300, 512, 1)])
+def test_small_weights_keep_their_bits(act, T, D, variant, exponent):
+    """Logits of one product each, of a weight with all its significand bits down to the smallest
+    float32 and a small integer: the product rounded to float32 once."""
+    s = one_hot_shape(act, T, D)
+    inp = make_inputs(s)
+    exact_logits(s, inp)
+    w = np.ldexp(1.0 + (2 * np.arange(s.N) + 1) * 0.0713, exponent).astype(np.float32)
+    inp["W_g"][:, 5] = w
+    res = gpu_forward(s, inp, variant, intermediates=False)
+    want = (w[None, :] * inp["x"][:, 5:6].astype(np.float64)).astype(np.float32)
+    assert np.array_equal(res["out_gate"], want)
