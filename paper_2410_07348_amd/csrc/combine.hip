@@ -38,10 +38,12 @@ __global__ __launch_bounds__(kCombineWaves *kWave) void k_combine(CombineArgs a,
     const AT *p_v[KMAX];
     bool need_x = false;
     // The token is the same for the whole wave, so its slots come as scalar loads, all of them at once, and
-    // in a piece of a token x as well, whether or not a slot wants it: one after the other, behind a
-    // branch each, they were a memory latency each.  T = 777, D = 4096 7.0 -> 5.6 us; T = 16384, D = 2048 41.5 -> 38;
-    // T = 32768, D = 4096 138.5 -> 134; k = 8, T = 4000, D = 1536 27.7 -> 18.9, k = 4 17.9 -> 11.7 (with an
-    // instance of its own).
+    // in a piece of a token of a layer with copy or constant experts x as well, whether or not a slot wants
+    // it: one after the other, behind a branch each, they were a memory latency each.  T = 777, D = 4096
+    // 7.0 -> 5.6 us; T = 16384, D = 2048 41.5 -> 38; T = 32768, D = 4096 138.5 -> 134; k = 4 (with an instance of its own),
+    // T = 1024, D = 4096 14.7 -> 9.2, T = 16384, D = 1024 39.1 -> 25.4; k = 5 .. 8, whose scalars spill into lanes of vector
+    // registers, 0.66 - 1.0 of the time of before in bf16, 0.69 - 1.05 in float32 (36 sizes).  Without copy and constant
+    // experts nothing wants x: T = 2048, D = 4096 12.3 us when the slots came one by one, 11.9 with x, 9.7 now.
     int idx[KMAX], rows[KMAX];
     float gs[KMAX];
 #pragma unroll
@@ -57,9 +59,9 @@ __global__ __launch_bounds__(kCombineWaves *kWave) void k_combine(CombineArgs a,
     }
     const AT *xt = static_cast<const AT *>(a.x) + (size_t)t * D;
     const int d0 = blockIdx.y * span, d1 = min(D, d0 + span);
-    const bool piece = gridDim.y > 1;
+    const bool early = gridDim.y > 1 && a.d.n_copy + a.d.n_const > 0;
     ActVec<AT> x0;
-    if (piece) x0 = load_vec_stream(xt + min(d0 + lane * V, D - V));
+    if (early) x0 = load_vec_stream(xt + min(d0 + lane * V, D - V));
 #pragma unroll
     for (int s = 0; s < KMAX; ++s) {
         g_row[s] = g_x[s] = g_v[s] = 0.f;
@@ -94,7 +96,7 @@ __global__ __launch_bounds__(kCombineWaves *kWave) void k_combine(CombineArgs a,
 #pragma unroll
         for (int i = 0; i < V; ++i) acc[i] = 0.f;
         ActVec<AT> xv;
-        if (piece && d < d0 + kWave * V) xv = x0;
+        if (early && d < d0 + kWave * V) xv = x0;
         else if (need_x) xv = load_vec_stream(xt + d);
 #pragma unroll
         for (int s = 0; s < KMAX; ++s) {

@@ -258,3 +258,12 @@ def test_f32_largest_floats_infinities_and_nan():
 @pytest.mark.parametrize("T,D,act", [(7, 1032, "bf16"), (7, 1032, "f32"), (2100, 520, "bf16"), (2100, 264, "f32")])
 def test_combine_slots(T, D, k, act):
     check(T=T, D=D, F=64, n_ffn=6, k=k, act=act, bias="normal")
+
+
+# pieces of a token where no, some or every zero-computation expert wants x
+@pytest.mark.parametrize("n_zero,n_copy,n_const", [(0, 0, 0), (2, 0, 0), (0, 2, 0), (1, 0, 2)])
+@pytest.mark.parametrize("T,D,act", [(65, 1032, "bf16"), (1000, 520, "f32")])
+def test_combine_pieces(T, D, act, n_zero, n_copy, n_const):
+    s = LayerShape("edge", T=T, D=D, F=64, n_ffn=4, n_zero=n_zero, n_copy=n_copy, n_const=n_const, act=act, seed=8100)
+    inp = make_inputs(s)
+    print("  ", s, check_layer(s, inp, gpu_forward(s, inp)), flush=True)
