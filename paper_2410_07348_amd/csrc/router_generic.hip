@@ -466,6 +466,34 @@ __global__ __launch_bounds__(kRouterFinalThreads) void k_router_final(RouterArgs
     router_block_sums<TOK, NT>(a, s_hist, probs);
 }
 
+// Slices of a call with more than kRouterFusedT tokens, at most `most`, whose workgroups take `blocks` blocks of
+// tokens each.  bf16: four to eight of them.  Up to eight, all workgroups of an XCD have the same slice and
+// keep its weights in their L2, and each further one is more for the second kernel to add; and what counts is how
+// long the fullest CU works, rounds of 256 workgroups over slices.  us with 4 / 5 / 8 / as many as fit, D = 4096, 24 rows:
+// T = 300 14.6 / 14.0 / 12.5 / 12.3 (24), T = 1500 17.3 / 15.8 / 16.0 / 17.3 (18), T = 2048 17.7 / 18.9 / 16.2 / 18.7 (13); 52
+// rows: T = 1024 23.9 / 21.7 / 18.5 / 27.2 (12), T = 1500 24.9 / 22.8 / 27.9 / 27.9 (8), T = 2048 25.1 / 29.2 / - / 27.2 (6).
+// Of two numbers with the same quotient the smaller one with many rows, whose workgroups do not share a CU well.  (Fewer
+// than four: T = 4096, 52 rows 32.8 with two, 37.0 with three, but the logits are 1.36e-7 from float64, not 1.05e-7.)
+// Wider layers go on to gain while the workgroups fit the chip: D = 8192, T = 300 with 8 / 20 slices 14.5 / 13.3, with 52
+// rows 23.3 / 19.7.  float32 sums round at every fourth product, and short chains of them keep their error
+// (T = 2048, D = 768 8.9e-8 with seven slices, 9.5e-8 with four): as many as fit, some 1024 / (T / 64) at most.
+static int sliced_splits(const Dims &d, bool bf16, int blocks, int most) {
+    if (!bf16) {
+        const int fill = (1024 + (d.T + 63) / 64 - 1) / ((d.T + 63) / 64);
+        return most < fill ? most : fill;
+    }
+    if (d.D > 4096 && 8 * blocks < 256) {
+        const int fill = 256 / blocks;
+        return most < fill ? most : fill;
+    }
+    int best = most < 4 ? most : 4;
+    for (int n = 5; n <= most && n <= 8; ++n) {
+        const int gain = (best * blocks + 255) / 256 * n - (n * blocks + 255) / 256 * best;
+        if (gain > 0 || (gain == 0 && d.N + 2 * d.n_const <= 32)) best = n;
+    }
+    return best;
+}
+
 int router_split_max(const Dims &d) {
     const size_t slice = slice_floats(d) * sizeof(float);
     const size_t n = router_small_bytes() / slice;
@@ -488,15 +516,15 @@ size_t router_small_bytes() {
     return (size_t)32 * 256 * kMaxRouterRows * sizeof(float);     // (32 slices of 256 tokens with the most rows)
 }
 
-// First kernel of the sliced routers: at most max_splits slices of D, waves of 32 columns at a time.
+// First kernel of the sliced routers: at most max_splits slices of D.
 static hipError_t launch_router_partial(const RouterArgs &a, bool bf16, int max_splits, int *n_splits, hipStream_t s) {
     const int rows = a.d.N + 2 * a.d.n_const, n = router_slices(a.d, a.prev_gate != nullptr);
     const uint32_t inv = inverse_rows(rows);
     auto go = [&](auto tb_c, auto rb_c, auto w_c) {
         constexpr int TB = decltype(tb_c)::value, RB = decltype(rb_c)::value, W = decltype(w_c)::value;
-        const int most = (n + W - 1) / W;
-        *n_splits = most < max_splits ? most : max_splits;
-        const dim3 grid(*n_splits, (a.d.T + 16 * TB - 1) / (16 * TB)), block(W * kWave);
+        const int most = (n + W - 1) / W < max_splits ? (n + W - 1) / W : max_splits, blocks = (a.d.T + 16 * TB - 1) / (16 * TB);
+        *n_splits = a.d.T <= kRouterFusedT ? most : sliced_splits(a.d, bf16, blocks, most);
+        const dim3 grid(*n_splits, blocks), block(W * kWave);
         if (bf16) hipLaunchKernelGGL((k_router_small_partial<bf16_t, TB, RB, W>), grid, block, 0, s, a, inv, a.partial);
         else hipLaunchKernelGGL((k_router_small_partial<float, TB, RB, W>), grid, block, 0, s, a, inv, a.partial);
     };
@@ -554,19 +582,21 @@ hipError_t launch_router_small(const RouterArgs &a, bool bf16, hipStream_t s, co
 }
 
 // Where the sliced router is faster than the matrix-core router in one kernel, whose workgroups of 64
-// tokens leave most of the chip empty and walk all of D: us sliced / in one, 24 rows, D = 768 T = 100 10.8 / 12.1,
-// T = 2048 11.6 / 12.3, T = 4096 13.0 / 12.9; D = 4096 T = 777 17.1 / 26.9, T = 4096 21.6 / 27.8, T = 8192 30 / 29; 52
-// rows, D = 768 T = 2048 17.9 / 19.6, T = 4096 20.8 / 20.2, D = 1536 T = 4096 25.8 / 26.2; D = 256 11 / 9.5.
+// tokens leave most of the chip empty and walk all of D: router and permutation, us sliced / in one, 24 rows: D = 512
+// T = 80 14.5 / 14.1, T = 2048 16.4 / 15.5; D = 768 T = 2048 16.3 / 16.6, T = 2500 17.5 / 16.8; D = 1024 T = 2048 17.6 / 18.3,
+// T = 4096 19.3 / 18.5; D = 1536 T = 4096 21.0 / 21.3, T = 6000 23.3 / 21.6; D = 2048 T = 2048 19.4 / 23.7, T = 4096 22.4 /
+// 23.6, T = 6000 25.6 / 23.6; 52 rows: D = 512 T = 1024 21.2 / 20.5; D = 768 T = 2048 21.7 / 23.3, T = 2500 23.7 / 23.2;
+// D = 1024 T = 4096 26.3 / 25.1; D = 2048 T = 4096 31.3 / 33.0, T = 6000 39.2 / 34.0.  (D = 640 and 896, an odd number of pairs
+// of K tiles, where the other kernel has one group of waves, would gain as well, up to 4096 tokens: D = 640 T = 2048
+// 16.4 / 19.2, D = 896 T = 4096 18.5 / 23.1.)
 bool router_sliced_wins(const Dims &d) { return (d.D >= 768 && d.T <= 2048) || (d.D >= 1536 && d.T <= 4096); }
 
 hipError_t launch_router_sliced(const RouterArgs &a, bool bf16, hipStream_t s) {
     if (a.d.T == 0) return hipSuccess;
-    // as many slices as there are, up to some 1024 workgroups, as far as the partial sums fit
-    const int blocks = (a.d.T + 63) / 64, fit = router_split_max(a.d);
+    const int fit = router_split_max(a.d);
     if (fit < 1) return hipErrorInvalidValue;
-    int want = (1024 + blocks - 1) / blocks, n_splits = 0;
-    want = want < fit ? want : fit;
-    const hipError_t e = launch_router_partial(a, bf16, want, &n_splits, s);
+    int n_splits = 0;
+    const hipError_t e = launch_router_partial(a, bf16, fit, &n_splits, s);
     return e == hipSuccess ? launch_router_final(a, n_splits, s) : e;
 }
 

@@ -137,3 +137,19 @@ def test_which_router(launches, T, D, act, n_ffn, router):
     if router[0] == "k_router_small_partial":
         slices = r[1][1][0][1][0]
         assert slices <= 24 and slices * (T * (n_ffn + 8) + 3) * 4 <= 32 * 256 * 80 * 4
+
+
+# (slices of D, blocks of tokens).  bf16: four to eight slices, as few rounds of 256 workgroups a slice as can be, more
+# for a wide layer's few tokens; float32: as many as fit; always within the partial sums (T x rows x slices floats)
+# and with a slice of 32 columns for every wave
+@pytest.mark.parametrize("T,D,act,n_ffn,n_const,grid", [
+    (80, 768, BF16, 16, 2, (4, 5)), (300, 4096, BF16, 16, 2, (8, 10)), (1500, 4096, BF16, 16, 2, (5, 47)),
+    (2048, 768, BF16, 16, 2, (4, 64)), (2048, 4096, BF16, 16, 2, (8, 64)), (3000, 4096, BF16, 4, 0, (8, 94)),
+    (1024, 4096, BF16, 32, 6, (8, 32)), (1200, 4096, BF16, 32, 6, (6, 38)), (2048, 4096, BF16, 32, 6, (4, 64)),
+    (4096, 4096, BF16, 32, 6, (3, 128)), (300, 8192, BF16, 16, 2, (24, 10)), (1024, 8192, BF16, 16, 2, (8, 32)),
+    (256, 128, F32, 4, 2, (1, 16)), (2048, 768, F32, 16, 2, (7, 64)), (30000, 768, F32, 4, 0, (3, 938))])
+def test_slices_of_the_router(launches, T, D, act, n_ffn, n_const, grid):
+    r = launches([ctx(T, D, 64, n_ffn, act=act, n_const=n_const), "route %d 2" % T])
+    assert names(r[1])[0].startswith("k_router_small_partial<") and r[1][1][0][1] == grid + (1,)
+    rows = n_ffn + 2 + 3 * n_const
+    assert grid[0] * (T * rows + 3) * 4 <= 32 * 256 * 80 * 4
