@@ -153,3 +153,28 @@ def test_slices_of_the_router(launches, T, D, act, n_ffn, n_const, grid):
     assert names(r[1])[0].startswith("k_router_small_partial<") and r[1][1][0][1] == grid + (1,)
     rows = n_ffn + 2 + 3 * n_const
     assert grid[0] * (T * rows + 3) * 4 <= 32 * 256 * 80 * 4
+
+
+MFMA = "k_router_mfma<%d, %d, %d, %d, %d>"
+
+
+# blocks of 32 weight rows, tiles prefetched, tokens, waves per SIMD, groups of waves
+@pytest.mark.parametrize("T,D,n_ffn,instance", [
+    (300, 512, 6, (1, 4, 64, 2, 2)), (2100, 1024, 6, (1, 4, 64, 2, 2)), (257, 256, 3, (1, 2, 64, 2, 2)),
+    (2100, 768, 6, (1, 2, 64, 2, 2)), (300, 640, 6, (1, 2, 64, 3, 1)), (2111, 1408, 3, (1, 2, 64, 3, 1)),
+    (300, 512, 34, (2, 2, 64, 2, 2)), (2100, 768, 34, (2, 2, 64, 2, 2)), (2100, 1024, 34, (2, 2, 64, 2, 2)),
+    (300, 640, 34, (2, 2, 64, 2, 1)), (2100, 1408, 34, (2, 2, 64, 2, 1)), (24576, 512, 6, (1, 4, 128, 2, 1))])
+def test_instances_of_the_matrix_core_router(launches, T, D, n_ffn, instance):
+    """The shapes of tests/test_gpu_router_numerics.py and tests/test_gpu_ffn_edges.py that are there for them."""
+    r = launches([ctx(T, D, 64, n_ffn, n_zero=2, n_copy=2), "route %d 2" % T])
+    assert names(r[1]) == [MFMA % instance]
+
+
+def test_the_lists_of_routers_name_the_kernels_they_reach(launches):
+    from test_gpu_router_numerics import MATRIX_CORE, ROUTERS, TWO_BLOCKS
+    for act, T, D in ROUTERS:
+        r = launches([ctx(T, D, 64, 6, n_zero=2, n_copy=2, act=F32 if act == "f32" else BF16), "route %d 2" % T])
+        assert names(r[1])[0].startswith("k_router_mfma<") == ((act, T, D) in MATRIX_CORE), (act, T, D)
+    for T, D in TWO_BLOCKS:
+        r = launches([ctx(T, D, 64, 34, n_zero=2, n_copy=2), "route %d 2" % T])
+        assert names(r[1])[0].startswith("k_router_mfma<2,"), (T, D)

@@ -45,9 +45,9 @@ def test_bf16_short_reduction(D, F):
     check(T=900, D=D, F=F, n_ffn=4, k=3)
 
 
-# routers between the few-token one (T <= 64) and the 128-token blocks (T >= 24576): two groups
-# of waves (tiles % 8, % 4, neither), slices of D (24 tiles of 64 or more, at most 64 blocks), one
-# and two blocks of weight rows, widths for the sliced FMA router (also more than 64 rows)
+# routers between the few-token one (T <= 64) and the 128-token blocks (T >= 24576): the matrix-core one with
+# two groups of waves (D = 128, 256, 512: one pass of its loop over K tiles, or two), one and two blocks of
+# weight rows; slices of 32 columns (wider layers, odd widths, more than 64 rows)
 @pytest.mark.parametrize("D", [128, 256, 512, 1408, 1536, 4096, 72])
 @pytest.mark.parametrize("n_ffn,n_const,k", [(3, 2, 2), (37, 7, 3), (52, 8, 8)])
 @pytest.mark.parametrize("T", [257, 321])
@@ -59,6 +59,13 @@ def test_router(T, D, n_ffn, n_const, k):
     cap = L.capacity(T, 1.1, 0.75)
     res = gpu_forward(s, inp, layer=L, cap=cap, balance_tau=0.75)
     print("  ", s, check_layer(s, inp, res, cap=np.array(cap, np.int32), balance_tau=0.75), flush=True)
+
+
+# the matrix-core router with several passes of its loop: one group of waves (D = 640, 1408), two (D = 768, 1024)
+@pytest.mark.parametrize("n_ffn,n_const,k", [(3, 2, 2), (37, 7, 3)])
+@pytest.mark.parametrize("T,D", [(257, 640), (2111, 768), (2111, 1024), (2111, 1408)])
+def test_matrix_core_router(T, D, n_ffn, n_const, k):
+    test_router(T, D, n_ffn, n_const, k)
 
 
 # the routers on slices of 32 columns: the whole router in one workgroup (T <= 16, up to 80 KB of x and

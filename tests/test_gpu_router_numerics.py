@@ -9,10 +9,12 @@ from helpers import gpu_forward
 
 pytestmark = pytest.mark.gpu
 
-# (act, T, D): few tokens; sliced FMA router (float32, a bf16 width it alone takes); matrix-core
-# router, one kernel, slices of D, 128-token blocks
+# (act, T, D).  Few tokens; slices of 32 columns beyond 64 tokens (float32, a bf16 width that they alone take,
+# widths where they are faster); the matrix-core router: blocks of 64 tokens, one and two groups of waves, several
+# passes of its loop over K tiles, and blocks of 128 tokens (tests/test_dispatch_cpu.py looks at the instances)
+MATRIX_CORE = [("bf16", 300, 640), ("bf16", 2100, 768), ("bf16", 2100, 1024), ("bf16", 24576, 512)]
 ROUTERS = [("f32", 40, 64), ("bf16", 40, 512), ("f32", 100, 64), ("bf16", 300, 1000), ("bf16", 100, 768),
-           ("bf16", 300, 768), ("bf16", 300, 4096), ("bf16", 24576, 512)]
+           ("bf16", 300, 768), ("bf16", 300, 4096)] + MATRIX_CORE
 
 
 def one_hot_shape(act, T, D, **kw):
@@ -121,9 +123,10 @@ def test_infinite_router_operands(act, T, D, variant):
     assert np.array_equal(res["out_gate"].astype(np.float64), L)
 
 
-# (every router, with the matrix-core one in one kernel for one and two blocks of weight rows, and the
-# few-token one in one workgroup)
+# (every router, the matrix-core one for one and two blocks of weight rows, and the few-token one in one
+# workgroup)
 @pytest.mark.parametrize("act,T,D,n_ffn", [r + (6,) for r in ROUTERS] + [("bf16", 300, 512, 6), ("bf16", 300, 512, 34),
+                                                                        ("bf16", 300, 640, 34), ("bf16", 2100, 768, 34),
                                                                         ("bf16", 3, 64, 6), ("f32", 3, 512, 6)])
 def test_infinite_previous_logits_stay_with_their_token(act, T, D, n_ffn):
     """The gating residual is added to the logits of its own token and to nothing else: not to another
@@ -169,7 +172,7 @@ def test_nan_weights(act, T, D, variant):
 
 # (every router but the matrix-core one, whose three bf16 pieces of a weight end at 2^-133)
 @pytest.mark.parametrize("exponent", [-118, -130, -145])
-@pytest.mark.parametrize("act,T,D,variant", [r + (0,) for r in ROUTERS if r[:3] != ("bf16", 24576, 512)] +
+@pytest.mark.parametrize("act,T,D,variant", [r + (0,) for r in ROUTERS if r not in MATRIX_CORE] +
                          [("bf16", 3, 64, 0), ("bf16", 1500, 1536, 0), ("bf16", 300, 512, 1)])
 def test_small_weights_keep_their_bits(act, T, D, variant, exponent):
     """Logits of one product each, of a weight with all its significand bits down to the smallest
@@ -182,3 +185,39 @@ def test_small_weights_keep_their_bits(act, T, D, variant, exponent):
     res = gpu_forward(s, inp, variant, intermediates=False)
     want = (w[None, :] * inp["x"][:, 5:6].astype(np.float64)).astype(np.float32)
     assert np.array_equal(res["out_gate"], want)
+
+
+# the matrix-core router with two blocks of 32 weight rows: one and two groups of waves, one and several passes
+TWO_BLOCKS = [(300, 512), (300, 640), (2100, 768), (2100, 1024), (2100, 1408)]
+
+
+@pytest.mark.parametrize("T,D", TWO_BLOCKS)
+def test_two_blocks_of_weight_rows(T, D):
+    """Exact logits -i (1 + t % 4) / 4 of 40 experts: the softmax as accurate as with one block, and infinite
+    and NaN weights of experts in the second block stay where they are."""
+    s = one_hot_shape("bf16", T, D, n_ffn=34)
+    assert s.N == 40
+    inp = make_inputs(s)
+    exact_logits(s, inp)
+    inp["W_g"][:, 5] = -0.25 * np.arange(s.N)
+    inp["x"][:, 7] = 0.5
+    L = -0.25 * np.arange(s.N)[None, :] * (1.0 + np.arange(T) % 4)[:, None]
+    res = gpu_forward(s, inp, intermediates=False)
+    assert np.array_equal(res["out_gate"].astype(np.float64), L)
+    assert np.array_equal(res["topk_idx"], np.tile(np.arange(s.k), (T, 1)))
+    p = np.exp(L)
+    p /= p.sum(axis=1, keepdims=True)
+    err = (np.abs(res["topk_w"] - p[:, :s.k]) / p[:, :s.k]).max()
+    print("router", T, D, "topk_w", err, flush=True)
+    assert err <= (2 + (s.N // 4 + 2 + 1) / 2) * 2.0 ** -23
+    inp["W_g"][33, 7] = np.inf
+    inp["W_g"][36, 7] = -np.inf
+    res = gpu_forward(s, inp, intermediates=False)
+    L[:, 33], L[:, 36] = np.inf, -np.inf
+    assert np.array_equal(res["out_gate"].astype(np.float64), L)
+    assert np.all(res["topk_idx"][:, 0] == 33)
+    for nan in NANS:
+        inp["W_g"][33, 7], inp["W_g"][36, 7] = 0.0, nan
+        res = gpu_forward(s, inp, intermediates=False)
+        L[:, 33], L[:, 36] = -0.25 * 33 * (1.0 + np.arange(T) % 4), np.nan
+        assert np.array_equal(res["out_gate"].astype(np.float64), L, equal_nan=True)
