@@ -222,15 +222,14 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs &a, const GroupTiles &
 
     // Tiles of this geometry, those in whole rounds of a patch per XCD, and every XCD's share of the rest:
     // the XCDs have an L2 and a fabric port each, so a rest on six of them has three quarters of the
-    // rate.  Patches for the rest, too / shares, us: GEMM1 of 384 ragged tiles 35.1 / 33.5, of 3.4 rounds
-    // (T = 16384, skewed) 144.4 / 142; GEMM2 of 704 small tiles 44.6 / 43.4, of 96 tiles as halves 36.7 / 35.8,
-    // but of 3.4 rounds, whose halves read what the whole tiles have left in the caches, 126.5 / 128: patches
-    // there, and with many rounds, where the rest is little (36 rounds: 0 - 0.4 % slower with shares).  The
+    // rate.  Patches for the rest, too / shares, us: GEMM1 of T = 6000, D = 2048, F = 1408, 4 experts 76.5 / 71.5, of 384
+    // ragged tiles 38.8 / 37.1; GEMM2 of T = 3000, D = 2048, F = 5632, 8 experts 130.6 / 112.4, of T = 6000, D = 1000, F = 2000,
+    // 16 experts 61.9 / 53.7; over 21 sizes of 1.5 to 36 rounds 0.98 of the time in either GEMM, and nothing slower.  The
     // two halves of a tile stay together.
     const int n_mine = TAIL ? 2 * (total - cut) : cut;
     const int n_whole = n_mine / (NXCD * GM * GN) * (NXCD * GM * GN);
-    int n_share = n_whole >= 24 * NXCD * GM * GN ? GM * GN : (n_mine - n_whole + NXCD - 1) / NXCD;
-    if constexpr (TAIL) n_share = !SWIGLU && cut > 0 ? GM * GN : (n_share + 1) & ~1;
+    int n_share = (n_mine - n_whole + NXCD - 1) / NXCD;
+    if constexpr (TAIL) n_share = (n_share + 1) & ~1;
 
     int e = 0, row0 = 0, row_end = 0, nt = 0;                  // the tile being computed
     // tile j of this XCD -> (expert, first row, end of the group, n-tile); false past the end
