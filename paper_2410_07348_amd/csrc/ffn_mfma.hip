@@ -224,11 +224,12 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs &a, const GroupTiles &
     // the XCDs have an L2 and a fabric port each, so a rest on six of them has three quarters of the
     // rate.  Patches for the rest, too / shares, us: GEMM1 of T = 6000, D = 2048, F = 1408, 4 experts 76.5 / 71.5, of 384
     // ragged tiles 38.8 / 37.1; GEMM2 of T = 3000, D = 2048, F = 5632, 8 experts 130.6 / 112.4, of T = 6000, D = 1000, F = 2000,
-    // 16 experts 61.9 / 53.7; over 21 sizes of 1.5 to 36 rounds 0.98 of the time in either GEMM, and nothing slower.  The
-    // two halves of a tile stay together.
+    // 16 experts 61.9 / 53.7; over 20 sizes of 1.5 to 17 rounds 0.98 of the time in either GEMM, and nothing slower.  With
+    // 36 rounds, where the rest is little, whole calls of T = 32768, D = 4096 take 5250 with patches and 5268 with shares
+    // (three runs in turn, 0.3 to 0.4 % each): patches from 24 rounds on.  The two halves of a tile stay together.
     const int n_mine = TAIL ? 2 * (total - cut) : cut;
     const int n_whole = n_mine / (NXCD * GM * GN) * (NXCD * GM * GN);
-    int n_share = (n_mine - n_whole + NXCD - 1) / NXCD;
+    int n_share = n_whole >= 24 * NXCD * GM * GN ? GM * GN : (n_mine - n_whole + NXCD - 1) / NXCD;
     if constexpr (TAIL) n_share = (n_share + 1) & ~1;
 
     int e = 0, row0 = 0, row_end = 0, nt = 0;                  // the tile being computed
