@@ -314,8 +314,8 @@ moepp_status moepp_get_balance(moepp_ctx *ctx, const float **f, const float **P,
 
 /*
  * Kernel-variant selection, for tests and tuning: 0 = automatic (default;
- * calls with at most 64 tokens use a router that splits the reduction over
- * D across workgroups, in plain fp32 FMA, for either activation type),
+ * routers on slices of the reduction over D, the matrix-core router or the
+ * generic one by tokens, widths and type; all of them give float32 logits),
  * 1 = force the generic kernels (any supported shape, plain fp32 FMA),
  * 2 = require the MFMA kernels (EUNSUPPORTED at call time if the shape or
  * type has none), 3 = as 2, with the plainest form of the grouped GEMM: no tiles

@@ -15,8 +15,8 @@ constexpr int kMaxTopK = 8;       // K
 constexpr int kMaxConst = 8;      // constant experts
 constexpr int kWave = 64;         // CDNA wavefront
 
-// Calls with at most this many tokens take the FMA router that splits the reduction
-// over D across workgroups and does the permutation in its second kernel.
+// Calls with at most this many tokens take the router on slices of D whose last kernel also does
+// the permutation.
 constexpr int kRouterFusedT = 64;
 
 // Permutation: one wave owns a chunk of consecutive slots: kPermChunk of them,

@@ -114,7 +114,7 @@ __global__ __launch_bounds__(kRouterWaves *kWave) void k_router_generic(RouterAr
     if (active) router_tail(a, t, lane, dots[w], wres);
 }
 
-// ---- few tokens, float32 layers, widths the matrix-core router does not take --------
+// ---- few tokens, float32 layers, widths the matrix-core router does not take or is slower at --------
 // The reduction over D is cut into slices of 32 columns, a wave each, whose operands go straight
 // from memory into the registers of the matrix instruction: for each of TB blocks of 16 tokens and RB
 // blocks of 16 weight rows lane l holds row l % 16, columns 8 (l / 16) .. + 7.  bf16 layers: the
@@ -126,7 +126,7 @@ __global__ __launch_bounds__(kRouterWaves *kWave) void k_router_generic(RouterAr
 //  * T <= 16 and few bytes: one workgroup does the whole router and the permutation.
 //  * T <= 64: workgroups leave partial dot products, one adds them up in slice order, finishes as
 //    above and goes on with the permutation.
-//  * more tokens (float32 layers, odd widths): workgroups of a slice and 64 tokens, then k_router_final.
+//  * more tokens (where: do_route and router_sliced_wins): workgroups of a slice and 16 or 32 tokens, then k_router_final.
 //    (One wave per token reads every router weight once per token: 22 us at T = 2048, D = 768, 24 rows.)
 // The gating residual (Eq.6) is 32 and more columns of its own, W_res against the previous logits, which
 // follow those of D: no kernel has to bring the two into LDS.
