@@ -196,7 +196,7 @@ hipError_t launch_perm_small(const Dims &d, const Workspace &w, const CapArgs &c
 hipError_t launch_balance(const Dims &d, const Workspace &w, const float *out_gate, float tau,
                           hipStream_t s, int router_rows = 0);
 
-// float32 layers, any supported shape: float32 matrix cores
+// float32 layers, any supported shape: matrix cores, float32 products and sums
 hipError_t launch_ffn_f32(const FfnArgs &a, int which, hipStream_t s);
 
 hipError_t launch_ffn_generic(const FfnArgs &a, bool bf16, int which, hipStream_t s);
@@ -268,11 +268,14 @@ __device__ inline float lanes_sum(float v) {
 // finite w overflows), mid the rest rounded to 8 bits, lo what is left, at most 8 bits.  bf16 has none of the
 // bits of a float32 below 2^-133: `lost` collects the words that lo is cut from, whose lower halves are zero
 // unless a w was too small for its pieces.  (w infinite or NaN: mid and lo are NaN, hi may be infinite for either.)
+// NOW: collected with the split; the compiler by itself keeps the words for later, which costs registers (routers
+// on slices 114 -> 132, two workgroups per CU -> one).
 typedef bf16_t bf16x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 struct Split4 {
     u32x2 hi, mid, lo;
 };
+template <bool NOW = true>
 __device__ inline Split4 split4(f32x4 w, uint32_t &lost) {
     constexpr uint32_t UPPER = 0x07060302;                            // the upper halves of two words
     Split4 s;
@@ -289,7 +292,8 @@ __device__ inline Split4 split4(f32x4 w, uint32_t &lost) {
         const uint32_t la = __float_as_uint(ra - __uint_as_float(s.mid[i] << 16));
         const uint32_t lb = __float_as_uint(rb - __uint_as_float(s.mid[i] & 0xffff0000u));
         s.lo[i] = __builtin_amdgcn_perm(lb, la, UPPER);
-        asm("v_or3_b32 %0, %1, %2, %0" : "+v"(lost) : "v"(la), "v"(lb));
+        if constexpr (NOW) asm("v_or3_b32 %0, %1, %2, %0" : "+v"(lost) : "v"(la), "v"(lb));
+        else lost |= la | lb;
     }
     return s;
 }

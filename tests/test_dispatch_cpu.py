@@ -111,13 +111,20 @@ def test_shapes_reach_the_instances_their_gpu_tests_name(launches):
         assert [n for n in names(r[1]) if n.startswith(("k_ffn", "k_grouped"))] == [gemm1, gemm2]
 
 
-def test_float32_layers_run_on_the_float32_instruction(launches):
-    """Which tiles, by rows per expert and widths."""
-    from test_gpu_ffn_edges import F32_TILES
+def test_float32_layers_on_split_operands(launches):
+    """Which tiles, by rows per expert and widths; widths that are not multiples of 32 and few tiles stay
+    with the float32 instruction."""
+    from test_gpu_ffn_edges import F32_TILES, SPLIT_EXACT
     for kw, gemm1, gemm2 in F32_TILES:
         r = launches([ctx(kw["T"], kw["D"], kw["F"], kw["n_ffn"], k=kw.get("k", 2), act=F32),
                       "forward %d %d" % (kw["T"], kw.get("k", 2))])
-        assert [n for n in names(r[1]) if n.startswith("k_ffn")] == ["k_ffn_f32" + gemm1, "k_ffn_f32" + gemm2], kw
+        assert [n for n in names(r[1]) if n.startswith("k_ffn")] == [gemm1, gemm2], kw
+    for T, D, F, gemm1, gemm2 in SPLIT_EXACT:
+        r = launches([ctx(T, D, F, 4, k=1, act=F32, n_zero=0, n_copy=0, n_const=0), "forward %d 1" % T])
+        assert [n for n in names(r[1]) if n.startswith("k_ffn")] == [gemm1, gemm2], (T, D, F)
+    for D, F in ((768, 2048), (768, 2040), (760, 2048)):
+        r = launches([ctx(2048, D, F, 8, act=F32), "forward 2048 2"])
+        assert ["k_ffn_f32_split" in n for n in names(r[1]) if n.startswith("k_ffn")] == [(D, F) == (768, 2048)] * 2
 
 
 @pytest.mark.parametrize("T,D,act,n_ffn,router", [

@@ -102,15 +102,19 @@ def test_bf16_streamed_weights(T):
 
 
 # Kernel instances that take shapes of their own to reach, GEMM1 and GEMM2 (tests/test_dispatch_cpu.py
-# checks that these shapes launch them): float32 tiles of 64 x 128 with a narrower last slab in GEMM2,
-# and 32 x 64 there; 128 x 256 tiles with a narrower last slab of h; 256 x 256 tiles with streamed
+# checks that these shapes launch them): float32 tiles of 64 x 128 and 32 x 64 with and without a narrower
+# last slab (widths that are not multiples of 32, which the split kernel does not take); 128 x 256 tiles with a narrower last slab of h; 256 x 256 tiles with streamed
 # weights, which all run as half tiles in GEMM2 and leave 16 of 272 to them in GEMM1.
 FULL, HALF = "Geo<256, 256, 2, 4, 32, 5, 4>", "Geo<128, 256, 2, 4, 32, 5, 4>"
 INSTANCES = [
     (dict(T=4096, D=1024, F=1000, n_ffn=4, k=3, act="f32"), "k_ffn_f32<true, false, 64, 128, 2, 2>",
      "k_ffn_f32<false, true, 64, 128, 2, 2>"),
-    (dict(T=4096, D=512, F=256, n_ffn=4, k=3, act="f32"), "k_ffn_f32<true, false, 32, 64, 2, 1>",
+    (dict(T=4096, D=512, F=264, n_ffn=4, k=3, act="f32"), "k_ffn_f32<true, false, 32, 64, 2, 1>",
+     "k_ffn_f32<false, true, 32, 64, 2, 2>"),
+    (dict(T=4096, D=520, F=256, n_ffn=4, k=3, act="f32"), "k_ffn_f32<true, true, 32, 64, 2, 1>",
      "k_ffn_f32<false, false, 32, 64, 2, 2>"),
+    (dict(T=4096, D=1032, F=512, n_ffn=4, k=3, act="f32"), "k_ffn_f32<true, true, 64, 128, 2, 2>",
+     "k_ffn_f32<false, false, 64, 128, 2, 2>"),
     (dict(T=300, D=1000, F=424, n_ffn=40), "k_grouped_gemm<%s, true, void, true, false>" % HALF,
      "k_grouped_gemm<%s, false, void, true, false>" % HALF),
     (dict(T=2000, D=1536, F=2176, n_ffn=16), "k_grouped_gemm<%s, true, %s, false, true>" % (FULL, HALF),
@@ -166,15 +170,19 @@ def test_ragged_silu(T):
     assert np.array_equal(a["h"], b["h"])
 
 
-# float32 layers from 16 rows per expert up to 2250, widths that are multiples of 32: 64 x 128, 32 x 64 and
-# 32 x 32 tiles, an odd and an even number of slabs, groups that end inside a tile; the instances are looked
-# at in tests/test_dispatch_cpu.py
+# float32 layers on split operands (D and F multiples of 32): 128 x 256 tiles, 128 x 128 and 64 x 64 ones, an
+# odd and an even number of slabs, one slab, groups that end inside a tile, and the float32 instruction where it
+# is faster; the rule is looked at in tests/test_dispatch_cpu.py
+WIDE, SQUARE, SMALL = "k_ffn_f32_split<%s, 128, 256, 2, 4>", "k_ffn_f32_split<%s, 128, 128, %s>", "k_ffn_f32_split<%s, 64, 64, %s>"
+PLAIN = "k_ffn_f32<false, false, 32, 32, 2, 2>"
 F32_TILES = [
-    (dict(T=4096, D=544, F=992, n_ffn=12), "<true, false, 64, 128, 2, 2>", "<false, false, 32, 64, 2, 2>"),
-    (dict(T=700, D=736, F=1024, n_ffn=6), "<true, false, 32, 64, 2, 1>", "<false, false, 32, 32, 2, 2>"),
-    (dict(T=333, D=512, F=512, n_ffn=16, bias="normal"), "<true, false, 32, 64, 2, 1>", "<false, false, 32, 32, 2, 2>"),
-    (dict(T=3000, D=1024, F=256, n_ffn=4, k=3, bias="normal"), "<true, false, 32, 64, 2, 1>", "<false, false, 64, 128, 2, 2>"),
-    (dict(T=2000, D=768, F=384, n_ffn=8, k=3), "<true, false, 32, 64, 2, 1>", "<false, false, 32, 64, 2, 2>"),
+    (dict(T=4096, D=544, F=992, n_ffn=12), WIDE % "true", SMALL % ("false", "2, 2")),
+    (dict(T=700, D=736, F=1024, n_ffn=6), "k_ffn_f32<true, false, 32, 64, 2, 1>", PLAIN),
+    (dict(T=333, D=512, F=512, n_ffn=16, bias="normal"), SMALL % ("true", "4, 1"), PLAIN),
+    (dict(T=3000, D=1024, F=256, n_ffn=4, k=3, bias="normal"), SMALL % ("true", "4, 1"), WIDE % "false"),
+    (dict(T=2000, D=768, F=384, n_ffn=8, k=3), SQUARE % ("true", "4, 2"), SQUARE % ("false", "2, 4")),
+    (dict(T=4096, D=1024, F=2048, n_ffn=8), WIDE % "true", WIDE % "false"),
+    (dict(T=9000, D=32, F=96, n_ffn=8), SMALL % ("true", "4, 1"), PLAIN),
 ]
 
 
@@ -187,31 +195,102 @@ def test_f32_tiles(kw):
     print("  ", check_layer(s, inp, res, tok_list=sample_tokens(s, res["topk_idx"], 256)), flush=True)
 
 
+# (T, D, F, GEMM1, GEMM2) with 4 experts and nothing else: every instance
+SPLIT_EXACT = [(3000, 1024, 512, SQUARE % ("true", "4, 2"), SQUARE % ("false", "2, 4")),
+               (4096, 1024, 1024, SMALL % ("true", "4, 1"), SMALL % ("false", "2, 2")),
+               (6000, 512, 512, WIDE % "true", SQUARE % ("false", "2, 4")),
+               (2500, 2048, 256, SMALL % ("true", "4, 1"), WIDE % "false")]
+
+
+def exact_shape(T, D, F):
+    return LayerShape("edge", T=T, D=D, F=F, n_ffn=4, n_zero=0, n_copy=0, n_const=0, k=1, act="f32", residual=False, seed=8400)
+
+
+def only(w, cols):
+    """The columns `cols` of w, zeros elsewhere."""
+    z = np.zeros_like(w)
+    z[..., cols] = w[..., cols]
+    return z
+
+
 @pytest.mark.parametrize("scale", [1.0, 1e-18])
 @pytest.mark.parametrize("n", [1, 4])
-def test_f32_products_are_float32_products(n, scale):
-    """Rows of h with n numbers that are not zero, down to 1e-36: every term of a sum is rounded at most
-    once with its addition, 2^-24 of what is added up (and half the smallest float where that is below
-    the normal ones), so yffn is within n 2^-24 of the sum of its terms' magnitudes."""
-    s = LayerShape("edge", T=3000, D=1024, F=512, n_ffn=4, n_zero=0, n_copy=0, n_const=0, k=1, act="f32",
-                   residual=False, seed=8400)
+@pytest.mark.parametrize("T,D,F", [i[:3] for i in SPLIT_EXACT])
+def test_f32_products_are_float32_products(T, D, F, n, scale):
+    """Rows of h with n numbers that are not zero, down to 1e-36.  Every term of a sum is rounded with its
+    addition, 2^-24 of what is added up, and that at most twice: once among the products of the first
+    pieces, once with the others, whose own roundings are 2^-6 of that, seven a term; half the smallest
+    float more where that is below the normal ones.  A lone term is rounded once."""
+    s = exact_shape(T, D, F)
     inp = make_inputs(s)
-    cols = [5, 77, 300, 511][:n]
+    cols = [5, 77, 130, 201][:n]
     w1 = np.zeros_like(inp["w1"])
     w1[:, cols] = inp["w1"][:, cols]
     inp["w1"] = w1
     inp["x"] = (inp["x"] * scale).astype(np.float32)
     res = gpu_forward(s, inp)
-    assert np.abs(res["h"][:, cols]).max() > 1e-2 * scale * scale and not np.delete(res["h"], cols, axis=1).any()
+    assert np.abs(res["h"][:, cols]).max() > 1e-3 * scale * scale and not np.delete(res["h"], cols, axis=1).any()
     worst = 0.0
     for e in range(s.n_ffn):
         rows = slice(res["offsets"][e], res["offsets"][e + 1])
         h, w2 = res["h"][rows][:, cols].astype(np.float64), inp["w2"][e][:, cols].astype(np.float64)
         err = np.abs(res["yffn"][rows] - h @ w2.T)
-        bound = n * (2.0 ** -24 * (np.abs(h) @ np.abs(w2).T) + 2.0 ** -150)
+        bound = ((n if n > 1 else 0.5) * 2 + n * 7 / 64) * (2.0 ** -24 * (np.abs(h) @ np.abs(w2).T)) + n * 8 * 2.0 ** -150
         worst = max(worst, (err / bound).max())
     print("nonzero", n, "scale", scale, "error / bound", worst, flush=True)
     assert worst <= 1.0
+
+
+@pytest.mark.parametrize("T,D,F", [i[:3] for i in SPLIT_EXACT])
+def test_f32_small_activations(T, D, F):
+    """x of 1e-36 in every third row and of 1e-41, below the normal numbers, in one, against large
+    weights of one column: z and u are one product each, h = z u / (1 + e^-z), all within a few float32
+    roundings (of the product, of e^-z, the sum, the division and the last product)."""
+    s = exact_shape(T, D, F)
+    inp = make_inputs(s)
+    inp["w1"], inp["w3"] = only(inp["w1"], [9]) * np.float32(1e32), only(inp["w3"], [9]) * np.float32(1e32)
+    x = inp["x"]
+    x *= np.float32(1e-30)
+    x[0::3] *= np.float32(1e-6)
+    x[1::30] *= np.float32(1e-11)
+    res = gpu_forward(s, inp)
+    tok, worst = res["src_of"], 0.0
+    for e in range(s.n_ffn):
+        rows = slice(res["offsets"][e], res["offsets"][e + 1])
+        xs = x[tok[rows], 9].astype(np.float64)[:, None]
+        z, u = xs * inp["w1"][e][None, :, 9].astype(np.float64), xs * inp["w3"][e][None, :, 9].astype(np.float64)
+        want = z / (1 + np.exp(-z)) * u
+        big = np.abs(want) > 2.0 ** -120
+        err = np.abs(res["h"][rows] - want)[big] / np.abs(want)[big]
+        # e^-z: its argument is off by 2^-24 |z|
+        worst = max(worst, (err * 2.0 ** 24 / (12 + np.abs(z)[big])).max())
+    print("error / bound", worst, flush=True)
+    assert worst <= 1.0
+
+
+@pytest.mark.parametrize("T,D,F", [i[:3] for i in SPLIT_EXACT])
+def test_f32_rows_do_not_depend_on_their_neighbours(T, D, F):
+    """Tokens with an infinity, with NaN and with numbers below 2^-110 change no bit of another token's
+    row of h and yffn, and weight rows of small numbers none of another column."""
+    s = exact_shape(T, D, F)
+    inp = make_inputs(s)
+    inp["W_g"][:, 20:] = 0.0
+    inp["w2"][:, :, 3] = 0.0
+    a = gpu_forward(s, inp)
+    odd = [T // 2, T // 3, T // 5]
+    x = inp["x"]
+    x[odd[0], 40], x[odd[1], 50] = np.inf, np.nan
+    x[odd[2], 30:] *= np.float32(2.0 ** -118)
+    inp["w1"][:, 3, 20:] *= np.float32(2.0 ** -118)
+    inp["w2"][:, 5] *= np.float32(2.0 ** -118)
+    b = gpu_forward(s, inp)
+    assert (~np.isfinite(b["out_gate"]).all(axis=1)).sum() == 2          # (0 times an infinity or a NaN)
+    # row of every token, whose only slot it is
+    row = [np.argsort(r["src_of"]) for r in (a, b)]
+    tok = np.array([t for t in range(T) if t not in odd])
+    h, y = ([r[name][q[tok]] for r, q in zip((a, b), row)] for name in ("h", "yffn"))
+    assert np.array_equal(np.delete(h[0], 3, axis=1), np.delete(h[1], 3, axis=1))
+    assert np.array_equal(np.delete(y[0], 5, axis=1), np.delete(y[1], 5, axis=1))
 
 
 # NaN of both signs, and with nothing but the lowest bits of the significand set
