@@ -500,6 +500,10 @@ int router_split_max(const Dims &d) {
     return (int)(n < kRouterSplits ? n : kRouterSplits);
 }
 
+// Instances for up to 8, 20 and 24 slices: a load is issued for each slice of the instance.  us with the smallest that
+// fits / with 24: T = 700, D = 1536, 24 rows (7 slices) 10.7 / 12.7, 52 rows 16.4 / 19.4; float32, T = 700, D = 3072 (13 slices)
+// 16.4 / 17.0.  The one-workgroup end below: T = 64, D = 768, 24 rows 10.8 / 12.7, D = 4096 (17 slices) 12.3 / 12.9; with more
+// than 32 experts four slices take 17.5 in either.
 static hipError_t launch_router_final(const RouterArgs &a, int splits, hipStream_t s) {
     const int rows = a.d.N + 2 * a.d.n_const;
     auto go = [&](auto kernel) {
