@@ -795,12 +795,19 @@ hipError_t launch_ffn_mfma(const FfnArgs &f, int which, hipStream_t s) {
     const bool ragged = f.d.D % 64 != 0 || f.d.F % 64 != 0 || K < 128;
     // Few rows per expert (small batches): the GEMMs only stream the weights, so use
     // 128-row tiles: half of the (mostly wasted) matrix work of a 256-row tile per byte
-    // of weights, bound by HBM instead.
-    const bool few = ragged || slots <= 128ll * f.d.n_ffn;
-    // How many tiles that makes if the router spreads its slots evenly.
-    const int bm = few ? 128 : 256;
-    const long long rows = slots / f.d.N + 1;
-    const long long n_tiles = (rows + bm - 1) / bm * f.d.n_ffn * (((which == 0 ? 2ll * f.d.F : f.d.D) + 255) / 256);
+    // of weights, bound by HBM instead.  Near 128 rows half of the experts have a second such
+    // tile, which reads the weights again, and one 256-row tile is faster where such tiles fill the chip or
+    // are few enough to run as halves.  Four layers in turn, so that no weights are cached, us with 128 / 256-row
+    // tiles, 121 and 127 rows per expert: 16 experts, D = 4096, F = 5632 (two layers) 1064 / 1024 and 1175 / 1031; D = 1024, F =
+    // 2048 339 / 319 and 337 / 319; D = 1536, F = 4096 684 / 722 and 831 / 726; 32 experts, D = 768, F = 2048 416 / 442 and 494 / 445;
+    // D = 2048, F = 1408 668 / 684 and 697 / 688; 8 experts, D = 2048 265 / 277 and 304 / 278; 4 experts, D = 4096 (176
+    // tall tiles, one layer) 127 rows 157 / 182.
+    const long long rows = slots / f.d.N + 1;              // per expert, if the router spreads its slots evenly
+    const int n_tiles_n = (int)(((which == 0 ? 2ll * f.d.F : f.d.D) + 255) / 256);
+    const long long tall = (rows + 255) / 256 * f.d.n_ffn * n_tiles_n;
+    const bool few = ragged || (slots <= 128ll * f.d.n_ffn && (rows <= 122 || (tall > 128 && tall < 224)));
+    // How many tiles that makes.
+    const long long n_tiles = few ? (rows + 127) / 128 * f.d.n_ffn * n_tiles_n : tall;
     // Small tiles where the others leave the chip half empty.  GEMM2, us with / without:
     // 48 tiles 18 / 31 (T = 300, D = 768), 64 tiles 21 / 31 (T = 200, D = 1024), 96 tiles 47 / 64
     // (T = 400, D = 1536); Full, whose last round of up to 128 tiles runs as halves: 48 tiles
