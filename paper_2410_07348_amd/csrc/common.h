@@ -167,6 +167,10 @@ hipError_t launch_router_small(const RouterArgs &a, bool bf16, hipStream_t s, co
 constexpr int kRouterSlicedTok = 64;
 bool router_sliced_wins(const Dims &d);
 hipError_t launch_router_sliced(const RouterArgs &a, bool bf16, hipStream_t s);
+// One kernel on blocks of 16 or 32 tokens, where it is faster; leaves the same, its histogram in blocks of that many tokens
+// (more rows than the workspace's table has: those are in RouterArgs::partial, which this router does not use).
+int router_block_tokens(const Dims &d, bool bf16);
+hipError_t launch_router_block(const RouterArgs &a, bool bf16, hipStream_t s);
 size_t router_small_bytes();
 // Slices of D whose partial logits [slice][T][N + 2 n_const] fit RouterArgs::partial, at most
 // kRouterSplits (a thread that adds them up holds four floats of each)

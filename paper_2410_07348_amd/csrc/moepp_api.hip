@@ -30,6 +30,7 @@ struct moepp_ctx {
     // the router of call (hist_T, hist_k) has left a histogram per block of tokens for the permutation
     bool hist_valid;
     int hist_T, hist_k, hist_chunk_slots;
+    int32_t *hist;        // where it is
     bool timing;
     bool have_events;
     // ring of event pairs: one slot per recorded call
@@ -199,6 +200,7 @@ moepp_status do_route(moepp_ctx *c, hipStream_t s, int T, const void *x, const f
     KernelTimer kt(c, s, MOEPP_K_ROUTER);
     const bool bf16 = c->desc.act == MOEPP_BF16;
     hipError_t e;
+    const int block = c->variant == 0 ? router_block_tokens(a.d, bf16) : 0;     // tokens per workgroup of that router
     const bool sliced = c->variant == 0 && router_split_max(a.d) >= 1 && (!mfma || router_sliced_wins(a.d));
     if (c->variant == 0 && T <= kRouterFusedT) {
         // a handful of tokens: the router's second kernel also groups the slots by expert
@@ -206,10 +208,10 @@ moepp_status do_route(moepp_ctx *c, hipStream_t s, int T, const void *x, const f
         c->perm_valid = e == hipSuccess;
         c->perm_T = T;
         c->perm_k = k;
-    } else if (mfma || sliced) {
+    } else if (mfma || sliced || block) {
         // the router counts its selections, per block of tokens, for the permutation
-        const int tok = sliced ? kRouterSlicedTok : router_mfma_block_tokens(a.d);
-        a.chunk_hist = c->ws.chunk_hist;
+        const int tok = block ? block : sliced ? kRouterSlicedTok : router_mfma_block_tokens(a.d);
+        a.chunk_hist = c->hist = block ? (int32_t *)c->ws.router_partial : c->ws.chunk_hist;
         c->hist_T = T;
         c->hist_k = k;
         c->hist_chunk_slots = tok * k;
@@ -217,7 +219,9 @@ moepp_status do_route(moepp_ctx *c, hipStream_t s, int T, const void *x, const f
         const int wgs = (T + tok - 1) / tok;
         const bool sums = c->bal_tau > 0.0 && wgs <= kBalWaves;
         if (sums) a.bal_partial = c->ws.bal_partial;
-        e = sliced ? launch_router_sliced(a, bf16, s) : launch_router_mfma(a, s);
+        e = block    ? launch_router_block(a, bf16, s)
+            : sliced ? launch_router_sliced(a, bf16, s)
+                     : launch_router_mfma(a, s);
         c->hist_valid = e == hipSuccess;
         c->bal_rows = sums && e == hipSuccess ? wgs : 0;
         c->bal_T = T;
@@ -250,6 +254,8 @@ moepp_status do_permute(moepp_ctx *c, hipStream_t s, int T, int k) {
         return e == hipSuccess ? MOEPP_OK : MOEPP_EHIP;
     }
     const int chunk_slots = counted ? c->hist_chunk_slots : kPermChunk;
+    Workspace ws = c->ws;
+    if (counted) ws.chunk_hist = c->hist;
     c->hist_valid = false;
     if (!counted) {
         KernelTimer kt(c, s, MOEPP_K_HIST);
@@ -258,15 +264,15 @@ moepp_status do_permute(moepp_ctx *c, hipStream_t s, int T, int k) {
     }
     if (perm_chunks(d, chunk_slots) <= kPermDirectChunks) {
         KernelTimer kt(c, s, MOEPP_K_SCATTER);
-        e = launch_perm_scan_scatter(d, c->ws, c->cap, chunk_slots, s);
+        e = launch_perm_scan_scatter(d, ws, c->cap, chunk_slots, s);
     } else {
         {
             KernelTimer kt(c, s, MOEPP_K_SCAN);
-            e = launch_perm_scan(d, c->ws, c->cap, chunk_slots, s);
+            e = launch_perm_scan(d, ws, c->cap, chunk_slots, s);
         }
         if (e != hipSuccess) return MOEPP_EHIP;
         KernelTimer kt(c, s, MOEPP_K_SCATTER);
-        e = launch_perm_scatter(d, c->ws, c->cap, chunk_slots, s);
+        e = launch_perm_scatter(d, ws, c->cap, chunk_slots, s);
     }
     if (e != hipSuccess) return MOEPP_EHIP;
     if (c->bal_tau > 0.0 && T > 0) {
@@ -400,6 +406,7 @@ void init_ctx(moepp_ctx *c, const moepp_desc *desc, void *workspace) {
     c->perm_valid = false;
     c->bal_rows = c->bal_T = 0;
     c->hist_T = c->hist_k = c->hist_chunk_slots = 0;
+    c->hist = nullptr;
     c->timing = false;
     c->have_events = false;
     clear_timing(c);

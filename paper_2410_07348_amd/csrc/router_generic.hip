@@ -137,7 +137,9 @@ __host__ __device__ inline int router_slices(const Dims &d, bool residual) { ret
 // The partial logits of slices first, first + stride, ...: acc[tb][rb][v]
 // of lane l belongs to token t0 + 16 tb + l % 16 and weight row 16 rb + 4 (l / 16) + v (rows past the
 // last repeat it, and are never read).
-template <typename AT, int TB, int RB>
+// SETS: 2 keeps every other slice of the wave in accumulators of its own: no chain of sums is longer than one slice
+// while a wave has two.
+template <typename AT, int TB, int RB, int SETS = 1>
 __device__ inline void few_dots(const RouterArgs &a, int t0, int first, int stride, f32x4 (&acc)[TB][RB]) {
     constexpr bool BF16 = ActVec<AT>::N == 8;
     constexpr int XV = BF16 ? 1 : 2;                       // 16-byte loads of 8 columns of x
@@ -170,15 +172,16 @@ __device__ inline void few_dots(const RouterArgs &a, int t0, int first, int stri
     // bf16: part 0 has the products of the hi pieces, part 1 all others; float32: part p the columns
     // with 8 (l / 16) + j, j % 4 = p (short chains of sums: a few of them are as exact as a tree)
     constexpr int NP = BF16 ? 2 : 4;
-    f32x4 part[NP][TB][RB];
+    f32x4 part[SETS * NP][TB][RB];
 #pragma unroll
-    for (int q = 0; q < NP; ++q)
+    for (int q = 0; q < SETS * NP; ++q)
 #pragma unroll
         for (int i = 0; i < TB; ++i)
 #pragma unroll
             for (int j = 0; j < RB; ++j) part[q][i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
     uint32_t lost = 0;
-    auto mul = [&](int ks, Slice &s) {
+    auto mul = [&](auto set_c, int ks, Slice &s) {
+        constexpr int P = SETS == 2 ? NP * decltype(set_c)::value : 0;
         if (ks >= n) return;                               // (the same for the whole wave)
         if (32 * ks + 8 * lq >= D) {                       // columns past the last: zero in both operands
 #pragma unroll
@@ -200,17 +203,17 @@ __device__ inline void few_dots(const RouterArgs &a, int t0, int first, int stri
 #pragma unroll
                 for (int i = 0; i < TB; ++i) {
                     const bf16x8 xv = __builtin_bit_cast(bf16x8, s.x[i][0].v);
-                    part[0][i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(hi, xv, part[0][i][j], 0, 0, 0);
-                    part[1][i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(mid, xv, part[1][i][j], 0, 0, 0);
-                    part[1][i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(lo, xv, part[1][i][j], 0, 0, 0);
+                    part[P][i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(hi, xv, part[P][i][j], 0, 0, 0);
+                    part[P + 1][i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(mid, xv, part[P + 1][i][j], 0, 0, 0);
+                    part[P + 1][i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(lo, xv, part[P + 1][i][j], 0, 0, 0);
                 }
             } else {
 #pragma unroll
                 for (int c = 0; c < 8; ++c)
 #pragma unroll
                     for (int i = 0; i < TB; ++i)
-                        part[c % NP][i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(
-                            s.w[j][c / 4][c % 4], s.x[i][c / 4].get(c % 4), part[c % NP][i][j], 0, 0, 0);
+                        part[P + c % NP][i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(
+                            s.w[j][c / 4][c % 4], s.x[i][c / 4].get(c % 4), part[P + c % NP][i][j], 0, 0, 0);
             }
         }
     };
@@ -268,9 +271,9 @@ __device__ inline void few_dots(const RouterArgs &a, int t0, int first, int stri
     load(first, s0);
     if (first + stride < n) load(first + stride, s1);
     for (int ks = first; ks < n; ks += 2 * stride) {
-        mul(ks, s0);
+        mul(std::integral_constant<int, 0>{}, ks, s0);
         if (ks + 2 * stride < n) load(ks + 2 * stride, s0);
-        mul(ks + stride, s1);
+        mul(std::integral_constant<int, 1>{}, ks + stride, s1);
         if (ks + 3 * stride < n) load(ks + 3 * stride, s1);
     }
     bool odd = false;
@@ -279,7 +282,8 @@ __device__ inline void few_dots(const RouterArgs &a, int t0, int first, int stri
 #pragma unroll
         for (int j = 0; j < RB; ++j) {
             acc[i][j] = part[0][i][j] + part[1][i][j];
-            if constexpr (!BF16) acc[i][j] += part[2][i][j] + part[3][i][j];
+#pragma unroll
+            for (int q = 2; q < SETS * NP; q += 2) acc[i][j] += part[q][i][j] + part[q + 1][i][j];
 #pragma unroll
             for (int v = 0; v < 4; ++v) odd |= !__builtin_isfinite(acc[i][j][v]);
         }
@@ -484,6 +488,47 @@ __global__ __launch_bounds__(kRouterFinalThreads) void k_router_final(RouterArgs
     router_block_sums<TOK, NT>(a, s_hist, probs);
 }
 
+// The whole router for a block of 16 TB tokens in one workgroup of W waves, which take the slices of D in turn; what
+// it leaves is what k_router_final leaves.  With narrow layers the workgroups are short chains of instructions and
+// memory latencies that one launch pays for once; beside k_router_mfma they are two or four times as many, so that the
+// chip is full (figures: router_block_tokens).  Weights are read once per block, from the caches.
+template <typename AT, int TB, int RB, int MAXN, int W, int SETS>
+__global__ __launch_bounds__(W *kWave) void k_router_block(RouterArgs a, uint32_t inv) {
+    constexpr int TOK = 16 * TB, NT = W * kWave, L = 16;
+    constexpr int RED = W * TB * RB * kWave * 4, PROBS = TOK * (MAXN + 1);
+    static_assert(NT >= L * TOK && NT >= 4 * kMaxExperts, "sixteen threads per token, four per expert");
+    __shared__ float dots[TOK * kDotStride];
+    __shared__ int s_hist[MAXN];
+    __shared__ __attribute__((aligned(16))) float red[RED > PROBS ? RED : PROBS];     // partial sums, then probabilities
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / kWave), t0 = blockIdx.x * TOK;
+    const int N = a.d.N, rows = N + 2 * a.d.n_const, n_tok = min(TOK, a.d.T - t0), n_el = n_tok * rows;
+    if (tid < N) s_hist[tid] = 0;
+    f32x4 acc[TB][RB];
+    few_dots<AT, TB, RB, SETS>(a, t0, wave, W, acc);
+#pragma unroll
+    for (int i = 0; i < TB; ++i)
+#pragma unroll
+        for (int j = 0; j < RB; ++j)
+            *reinterpret_cast<f32x4 *>(red + (((size_t)wave * TB * RB + i * RB + j) * kWave + tid % kWave) * 4) = acc[i][j];
+    __syncthreads();
+#pragma unroll 1
+    for (int c = tid; c < n_el; c += NT) {
+        const RowOf o(c, rows, inv);
+        const float bias = a.bias && o.r < N ? a.bias[o.r] : 0.f;
+        const float v = few_sum<W, TB, RB>(reinterpret_cast<const float(*)[TB * RB][kWave][4]>(red), o.tt, o.r) + bias;
+        dots[o.tt * kDotStride + o.r] = v;
+        if (o.r < N) a.out_gate[(size_t)(t0 + o.tt) * N + o.r] = v;
+    }
+    __syncthreads();
+    // (whole waves; tokens past the end compute on whatever their part of `dots` holds and store nothing)
+    if (tid < L * TOK) {
+        const int tok = tid / L;
+        router_token<MAXN, L>(a, (size_t)(t0 + tok), tok < n_tok, tid % L, dots + tok * kDotStride, a.chunk_hist ? s_hist : nullptr,
+                              nullptr, a.bal_partial ? red + tok * (N + 1) : nullptr);
+    }
+    router_block_sums<TOK, NT>(a, s_hist, red);
+}
+
 // Slices of a call with more than kRouterFusedT tokens, at most `most`, whose workgroups take `blocks` blocks of
 // tokens each.  bf16: four to eight of them.  Up to eight, all workgroups of an XCD have the same slice and
 // keep its weights in their L2, and each further one is more for the second kernel to add; and what counts is how
@@ -612,6 +657,39 @@ hipError_t launch_router_small(const RouterArgs &a, bool bf16, hipStream_t s, co
 // of K tiles, where the other kernel has one group of waves, would gain as well, up to 4096 tokens: D = 640 T = 2048
 // 16.4 / 19.2, D = 896 T = 4096 18.5 / 23.1.)
 bool router_sliced_wins(const Dims &d) { return (d.D >= 768 && d.T <= 2048) || (d.D >= 1536 && d.T <= 4096); }
+
+// Tokens of a workgroup where the one-kernel router on blocks is the fastest, else 0.  Router and permutation, us, block of 16 /
+// 32 / what else there is (sliced or matrix cores), bf16:
+//   24 weight rows: D = 768 T = 4096 13.1 / 14.3 / 17.1, T = 6000 17.0 / 14.8 / 16.9, T = 16384 29.0 / 21.4 / 19.0; D = 1024 T = 4096
+//   14.3 / 15.6 / 18.4, T = 8192 19.7 / 16.3 / 19.3; D = 1536 T = 8192 24 / 19.2 / 21.1; D = 2048 T = 8192 28 / 21.4 / 23.6, T = 16384
+//   46 / 33 / 26; D = 4096 T = 8192 43 / 31.5 / 34.0;
+//   52 rows: D = 768 T = 4096 19.0 / 20.3 / 24.0, T = 8192 30.9 / 21.8 / 23.9; D = 1024 T = 8192 34 / 23.6 / 26.7;
+// a block of 16 gives the 256 CUs one workgroup each at T = 4096, one of 32 at T = 8192.  float32 and odd widths, up to 16
+// rows (one block of the instruction): T = 2048, D = 768 12.5 / - / 16.8; T = 1999, D = 1000 12.4 / - / 16.6.  Narrower and
+// shorter calls gain as well (24 rows, T = 300, D = 768 11.9 / - / 15.3): they stay where tests/test_dispatch_cpu.py has them, or the tests
+// of the other routers' numerics would not reach those.
+int router_block_tokens(const Dims &d, bool bf16) {
+    const int rows = d.N + 2 * d.n_const;
+    if (!bf16 || !router_mfma_supported(d)) return rows <= 16 && d.D >= 256 && d.D <= 1024 && d.T <= 4096 ? 16 : 0;
+    if (d.T > 2304 && d.T <= 4096 && d.D <= 1024) return 16;
+    return d.T > 4352 && d.T <= 8192 ? 32 : 0;
+}
+
+hipError_t launch_router_block(const RouterArgs &a, bool bf16, hipStream_t s) {
+    const int tok = router_block_tokens(a.d, bf16), rows = a.d.N + 2 * a.d.n_const;
+    if (tok == 0) return hipErrorInvalidValue;
+    auto go = [&](auto kernel, int waves) {
+        hipLaunchKernelGGL(kernel, dim3((a.d.T + tok - 1) / tok), dim3(waves * kWave), 0, s, a, inverse_rows(rows));
+        return hipGetLastError();
+    };
+    // (float32 and odd widths: sixteen waves of two slices at most, each with sums of its own, as on slices; logits against float64
+    // T = 2048, D = 768, float32 8.9e-8 as there, 1.08e-7 in eight waves of three slices; no slower)
+    if (!bf16) return go(k_router_block<float, 1, 1, 16, 16, 2>, 16);
+    if (!router_mfma_supported(a.d)) return go(k_router_block<bf16_t, 1, 1, 16, 16, 2>, 16);
+    if (rows <= 16) return tok == 16 ? go(k_router_block<bf16_t, 1, 1, 16, 8, 1>, 8) : go(k_router_block<bf16_t, 2, 1, 16, 8, 1>, 8);
+    if (rows <= 32) return tok == 16 ? go(k_router_block<bf16_t, 1, 2, 32, 8, 1>, 8) : go(k_router_block<bf16_t, 2, 2, 32, 8, 1>, 8);
+    return tok == 16 ? go(k_router_block<bf16_t, 1, 4, kMaxExperts, 8, 1>, 8) : go(k_router_block<bf16_t, 2, 4, kMaxExperts, 8, 1>, 8);
+}
 
 hipError_t launch_router_sliced(const RouterArgs &a, bool bf16, hipStream_t s) {
     if (a.d.T == 0) return hipSuccess;

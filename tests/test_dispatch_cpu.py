@@ -185,3 +185,29 @@ def test_the_lists_of_routers_name_the_kernels_they_reach(launches):
     for T, D in TWO_BLOCKS:
         r = launches([ctx(T, D, 64, 34, n_zero=2, n_copy=2), "route %d 2" % T])
         assert names(r[1])[0].startswith("k_router_mfma<2,"), (T, D)
+
+
+@pytest.mark.parametrize("T,D,act,n_ffn,tok", [
+    (2304, 768, BF16, 16, 0), (2305, 768, BF16, 16, 16), (4096, 1024, BF16, 32, 16), (4096, 1152, BF16, 16, 0),
+    (4097, 768, BF16, 16, 0), (4352, 768, BF16, 16, 0), (4353, 4096, BF16, 16, 32), (8192, 256, BF16, 32, 32), (8193, 256, BF16, 16, 0),
+    (4400, 1000, BF16, 8, 0), (4096, 1000, BF16, 8, 16), (65, 264, BF16, 8, 16), (64, 264, BF16, 8, 0), (300, 248, BF16, 8, 0),
+    (300, 1000, BF16, 9, 0), (2048, 768, F32, 8, 16), (2048, 768, F32, 9, 0), (65, 256, F32, 4, 16), (300, 1032, F32, 4, 0),
+    (4097, 256, F32, 4, 0)])
+def test_where_the_router_on_blocks_runs(launches, T, D, act, n_ffn, tok):
+    """By tokens, columns, type and weight rows (n_ffn + 8); variants keep the others, and the permutation has as many chunks as
+    there were blocks (four chunks a workgroup)."""
+    r = launches([ctx(T, D, 64, n_ffn, act=act), "route %d 2" % T, "permute %d 2" % T, "variant 1", "route %d 2" % T])
+    assert [n.startswith("k_router_block<") for n in names(r[1])][:1] == [tok > 0], names(r[1])
+    assert "k_router_block" not in names(r[4])[0]
+    if tok:
+        (name, grid, threads), = r[1][1]
+        assert grid == ((T + tok - 1) // tok, 1, 1) and name.split(",")[1].strip() == str(tok // 16)
+        (name, perm, _), = r[2][1]
+        assert name == "k_perm_scan_scatter" and perm == ((grid[0] + 3) // 4, 1, 1)
+
+
+def test_blocks_of_the_gpu_tests(launches):
+    from test_gpu_router_block import BLOCK
+    for act, T, D, n_ffn, n, k, (tok, rb) in BLOCK:
+        r = launches([ctx(T, D, 64, n_ffn, k=k, act=F32 if act == "f32" else BF16, n_zero=n, n_copy=n, n_const=n), "route %d %d" % (T, k)])
+        assert re.match(r"k_router_block<(float|bf16), %d, %d, " % (tok // 16, rb), names(r[1])[0]), (T, D, names(r[1]))
