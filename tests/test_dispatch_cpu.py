@@ -211,3 +211,17 @@ def test_blocks_of_the_gpu_tests(launches):
     for act, T, D, n_ffn, n, k, (tok, rb) in BLOCK:
         r = launches([ctx(T, D, 64, n_ffn, k=k, act=F32 if act == "f32" else BF16, n_zero=n, n_copy=n, n_const=n), "route %d %d" % (T, k)])
         assert re.match(r"k_router_block<(float|bf16), %d, %d, " % (tok // 16, rb), names(r[1])[0]), (T, D, names(r[1]))
+
+
+def test_halves_of_wide_float32_tiles(launches):
+    """As many workgroups as tiles at most (slots / 128 rows and one more per expert), and half of an XCD's CUs more on each."""
+    from test_gpu_ffn_edges import F32_HALVES
+    for kw, gemm1, gemm2 in F32_HALVES:
+        T, D, F, n, k = kw["T"], kw["D"], kw["F"], kw["n_ffn"], kw.get("k", 2)
+        r = launches([ctx(T, D, F, n, k=k, act=F32, n_zero=kw.get("n_zero", 1), n_copy=kw.get("n_copy", 1), n_const=kw.get("n_const", 2)),
+                      "forward %d %d" % (T, k)])
+        got = [(name, grid[0]) for name, grid, _ in r[1][1] if name.startswith("k_ffn")]
+        for (name, grid), want, cols in zip(got, (gemm1, gemm2), (2 * F, D)):
+            assert want in (None, name), (kw, got)
+            if "128, 256" in name:
+                assert grid == ((T * k // 128 + n) * -(-cols // 256) + 7) // 8 * 8 + 128

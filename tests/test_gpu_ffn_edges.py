@@ -353,3 +353,26 @@ def test_combine_pieces(T, D, act, n_zero, n_copy, n_const):
     s = LayerShape("edge", T=T, D=D, F=64, n_ffn=4, n_zero=n_zero, n_copy=n_copy, n_const=n_const, act=act, seed=8100)
     inp = make_inputs(s)
     print("  ", s, check_layer(s, inp, gpu_forward(s, inp)), flush=True)
+
+
+# wide float32 tiles whose last round runs as halves: (shape, GEMM1, GEMM2); last column tiles of 64 and of 160 columns, groups that
+# end anywhere in a tile
+F32_HALVES = [(dict(T=1683, D=608, F=1568, n_ffn=4, n_zero=0, n_copy=0, n_const=0), WIDE % "true", PLAIN),
+              (dict(T=2048, D=1024, F=2048, n_ffn=8), WIDE % "true", SQUARE % ("false", "2, 4")),
+              (dict(T=2507, D=928, F=1888, n_ffn=4, k=4, n_zero=0, n_copy=0, n_const=0), None, WIDE % "false")]
+
+
+@pytest.mark.parametrize("kw", [i[0] for i in F32_HALVES])
+def test_f32_halves_of_wide_tiles(kw):
+    s = LayerShape("edge", **dict(dict(n_zero=1, n_copy=1, n_const=2, seed=8100, act="f32"), **kw))
+    print("shape", s, flush=True)
+    inp = make_inputs(s)
+    res = gpu_forward(s, inp)
+    print("  ", check_layer(s, inp, res, tok_list=sample_tokens(s, res["topk_idx"], 256)), flush=True)
+
+
+def test_f32_halves_and_whole_tiles_are_the_same_numbers():
+    """Three odd tokens move the groups, and with them the tiles that run as halves (3366 tokens of one slot: 836 to 848 rows per
+    expert): no other token's row changes, nor with operands for the float32 instruction in a half."""
+    for T in (3366, 3300, 3400):
+        test_f32_rows_do_not_depend_on_their_neighbours(T, 608, 1568)
