@@ -114,9 +114,11 @@ __global__ __launch_bounds__(kDecThreads, 1) void k_ffn_decode(DecodeArgs a) {
     // fragment (unit, step s, block b): 16 rows x 32 columns = 1 KB; lane l holds row l % 16,
     // columns 8 (l / 16) .. + 7
     bf16x8 wf[kDecRing][FR];
-    auto load_weights = [&](const Unit &un, int s, bf16x8 *dst) {
-        const size_t off = (size_t)un.e * a.Nb * a.K + (size_t)un.panel * kPanel * a.K +
-                           (size_t)(wave * S + s) * kPanel * kSlab;
+    // (real: false for a unit that does not exist)
+    auto load_weights = [&](const Unit &un, int s, bf16x8 *dst, bool real = true) {
+        const size_t at = (size_t)un.e * a.Nb * a.K + (size_t)un.panel * kPanel * a.K +
+                          (size_t)(wave * S + s) * kPanel * kSlab;
+        const size_t off = real ? at : 0;
         const char *p = reinterpret_cast<const char *>(a.B + off) + l16 * 64 + lq * 16;
 #pragma unroll
         for (int b = 0; b < FR; ++b)
@@ -199,18 +201,21 @@ __global__ __launch_bounds__(kDecThreads, 1) void k_ffn_decode(DecodeArgs a) {
 
     // ---- the stream: unit after unit, S4 positions each --------------------------
     // While position s of a unit is multiplied, position s + kDecRing of the stream
-    // is loaded into the ring slot that s just left: of this unit, or of the next
-    // one (past the last unit of the workgroup: the last unit again, never used).
+    // is loaded into the ring slot that s just left: of this unit, or of the next one, also where that has other
+    // token rows.  Past the last unit every load takes the first line of the weights, which the caches hold: the
+    // last unit's own first steps, once more, were 33 MB from memory at the end of either GEMM (T = 16, D = 4096 GEMM2 106 ->
+    // 101 us; T = 8, D = 1536 29 -> 24; T = 64, D = 768, 32 experts 25.5 -> 19.5, where most workgroups have three units).
     int buf = 0;
     int u = u0;
+    Unit cur = locate(u);
+#pragma unroll
+    for (int r = 0; r < kDecRing; ++r)
+        if (r < S) load_weights(cur, r, wf[r]);
     while (u < u1) {
-        Unit cur = locate(u);
         const int seg_end = min(u1, u + (ppe - cur.panel));    // units that share cur's token operands
         load_tokens(cur);
-#pragma unroll
-        for (int r = 0; r < kDecRing; ++r)
-            if (r < S) load_weights(cur, r, wf[r]);
         for (; u < seg_end; ++u) {
+            const bool more = u + 1 < u1;
             const Unit nxt = locate(u + 1 < u1 ? u + 1 : u1 - 1);
             clear_acc();
 #pragma unroll
@@ -224,7 +229,7 @@ __global__ __launch_bounds__(kDecThreads, 1) void k_ffn_decode(DecodeArgs a) {
                 if (pos < S4) {
                     if (pos < S) load_weights(cur, pos, wf[s % kDecRing]);
                 } else if (pos - S4 < S) {
-                    load_weights(nxt, pos - S4, wf[s % kDecRing]);
+                    load_weights(nxt, pos - S4, wf[s % kDecRing], more);
                 }
                 // (left alone, the compiler moves a load down to its first use, a ring later)
                 __builtin_amdgcn_sched_barrier(0);
@@ -233,8 +238,6 @@ __global__ __launch_bounds__(kDecThreads, 1) void k_ffn_decode(DecodeArgs a) {
             buf ^= 1;
             cur = nxt;
         }
-        // (the next row block's first weights were loaded with another block's or with
-        // this unit's addresses: the segment loop above reloads them; rare)
     }
 }
 
