@@ -303,7 +303,8 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs &a, const GroupTiles &
             src[i] = SWIGLU ? a.src_of[r] : r;
         }
     };
-    auto set_pointers = [&](int t_e, int t_nt, int *src) {
+    // b_rows: a.Nb, or 1 for a tile that does not exist, which loads one row of weights over and over
+    auto set_pointers = [&](int t_e, int t_nt, int *src, int b_rows) {
 #pragma unroll
         for (int i = 0; i < CA; ++i) {
             // (slot -> token here and not where the slots are asked for, which would wait for them)
@@ -333,7 +334,7 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs &a, const GroupTiles &
 #pragma unroll
         for (int i = 0; i < CB; ++i) {
             int n = n0 + r_thr + i * (NL / CPR);
-            n = n < a.Nb ? n : a.Nb - 1;
+            n = n < b_rows ? n : b_rows - 1;
             pb[i] = Be + panel_row(n, kc / 4, a.Nb, a.K) + (kc % 4) * 8;
         }
     };
@@ -645,7 +646,7 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs &a, const GroupTiles &
         int src[CA];
         if constexpr (LOADER) {
             gather_rows(row0, row_end, src);
-            set_pointers(e, nt, src);
+            set_pointers(e, nt, src, a.Nb);
             issue_range(0, NS - 1, lds);
         }
         // the loading waves win instruction arbitration over the others (+1 %, measured)
@@ -653,10 +654,12 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs &a, const GroupTiles &
         for (;;) {
             // The next tile of this workgroup; the rows of x it gathers are
             // fetched now, a whole K loop before they are needed.  When
-            // there is no next tile everything below is done once more for
-            // the tile just finished (and never used): no branch around a
-            // load, so the compiler adds no wait for one.
-            int n_e = e, n_row0 = row0, n_row_end = row_end, n_nt = nt;
+            // there is no next tile everything below is done once more for one row of x or h and
+            // one of the weights, which the caches hold, and never used: no branch around a
+            // load, so the compiler adds no wait for one.  (For the tile just finished, as it was, a launch ended with 16 MB
+            // of loads that nobody wanted: GEMM2 of four cold layers, T = 3672, D = 768, 32 experts 36.4 -> 35.2 us, GEMM1 of T = 1458 48.4 ->
+            // 47.2; 28 sizes 0.99 of the time.)
+            int n_e = e, n_row0 = 0, n_row_end = 1, n_nt = nt;
             j += a.jstride;
             const bool more = locate(j, n_e, n_row0, n_row_end, n_nt);
             if constexpr (LOADER) gather_rows(n_row0, n_row_end, src);
@@ -671,7 +674,7 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs &a, const GroupTiles &
             // The first K tiles of the next output tile go out before the
             // epilogue, into the stages the epilogue does not use, the
             // others after it.
-            if constexpr (LOADER) set_pointers(n_e, n_nt, src);
+            if constexpr (LOADER) set_pointers(n_e, n_nt, src, more ? a.Nb : 1);
             epilogue(lds, lds, std::integral_constant<int, LOADER ? EARLY : 0>{});
             if (!more) break;
             lds_sync();                     // the epilogue has left its LDS patch
