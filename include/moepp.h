@@ -261,7 +261,9 @@ enum {
                             time is part of MOEPP_K_ROUTER                    */
     MOEPP_K_GEMM1 = 4,   /* grouped GEMM W1/W3 + SwiGLU                       */
     MOEPP_K_GEMM2 = 5,   /* grouped GEMM W2                                   */
-    MOEPP_K_COMBINE = 6, /* weighted combine + zero-computation experts       */
+    MOEPP_K_COMBINE = 6, /* weighted combine + zero-computation experts; 0 where a
+                            moepp_layer_forward of a few tokens does it in the kernel
+                            of MOEPP_K_GEMM2                                   */
     MOEPP_K_BALANCE = 7, /* load-balance statistics (only when switched on)    */
     MOEPP_NUM_KERNELS = 8
 };

@@ -210,6 +210,10 @@ hipError_t launch_ffn_mfma(const FfnArgs &a, int which, hipStream_t s);
 // few rows per expert (at most 16, by a rule on experts and weights): weight-streaming kernels
 bool ffn_decode_supported(const Dims &d);
 hipError_t launch_ffn_decode(const FfnArgs &a, int which, hipStream_t s);
+// GEMM2 and the combine in one kernel, where that is faster; leaves yffn and `out` as the two would
+bool ffn_decode_combines(const Dims &d);
+struct CombineArgs;
+hipError_t launch_ffn_decode_combine(const FfnArgs &f, const CombineArgs &c, hipStream_t s);
 
 hipError_t launch_combine(const CombineArgs &a, bool bf16, hipStream_t s);
 

@@ -31,6 +31,8 @@
 // Rows past the end of a row block are clamped on load and masked on store.
 #include "common.h"
 
+#include <math.h>
+
 #include <type_traits>
 
 namespace moepp {
@@ -241,6 +243,160 @@ __global__ __launch_bounds__(kDecThreads, 1) void k_ffn_decode(DecodeArgs a) {
     }
 }
 
+// GEMM2 and the combine (combine.hip, the same operations in the same order) in one kernel, for at most kDecOutT tokens:
+// a workgroup owns 16 columns of the output and takes them through all row blocks of all experts, so that nobody waits for
+// another workgroup.  Weights and the token rows of h travel in one ring of 16 steps (h comes from the caches, 16 rows for
+// every 16 of weights), so nothing drains it between row blocks.  Waves split K; sums and yffn are those of the kernel above, bit
+// by bit.  The code runs once and waits for its instructions: one row block at a time (several in a pass of the ring, where K is
+// short, put more loads in flight and took 8.5 us for one token at D = 768 where this takes 7.3).
+struct DecodeOutArgs {
+    DecodeArgs g;
+    CombineArgs c;
+};
+constexpr int kDecOutT = 48, kDecOutSlots = kDecOutT * kMaxTopK;
+template <int S>
+__global__ __launch_bounds__(kDecThreads, 1) void k_ffn_decode(DecodeOutArgs oa) {
+    constexpr int RING = 16, S4 = (S + RING - 1) / RING * RING;
+    const DecodeArgs &a = oa.g;
+    const CombineArgs &c = oa.c;
+    __shared__ __attribute__((aligned(16))) float part[2][kDecWaves][kWave][4];
+    __shared__ __attribute__((aligned(16))) bf16_t y[kDecOutSlots][16];      // yffn's 16 columns
+    __shared__ int s_idx[kDecOutSlots], s_row[kDecOutSlots];
+    __shared__ float s_w[kDecOutSlots], s_a1[kDecOutT * kMaxConst];
+    __shared__ __attribute__((aligned(16))) bf16_t s_cv[kMaxConst][16];
+    static_assert(kDecOutSlots <= kDecThreads && kDecOutT * kMaxConst <= kDecThreads && 2 * kDecOutT <= kDecThreads, "one pass each");
+    const int tid = threadIdx.x, lane = tid % kWave, l16 = lane % 16, lq = lane / 16;
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int c0 = blockIdx.x * 16, panel = c0 / kPanel;
+
+    // ---- row blocks: lane q looks after expert q
+    const int eq = lane < a.n_ffn ? lane : a.n_ffn;
+    const int o_lo = a.offsets[eq], o_hi = a.offsets[eq < a.n_ffn ? eq + 1 : eq];
+    const int blocks_q = (o_hi - o_lo + 15) / 16, incl = wave_prefix_sum(blocks_q);
+    const int total = __builtin_amdgcn_readlane(incl, kWave - 1);
+    struct Block {
+        int e, row0, nrows;                        // nrows 0: no such block
+    };
+    auto locate = [&](int b) {
+        Block r = {0, 0, 0};
+        if (b < total) {
+            r.e = __builtin_ctzll(__ballot(incl > b));
+            const int lo = __builtin_amdgcn_readlane(o_lo, r.e), hi = __builtin_amdgcn_readlane(o_hi, r.e);
+            r.row0 = lo + 16 * (b - __builtin_amdgcn_readlane(incl - blocks_q, r.e));
+            r.nrows = hi - r.row0 < 16 ? hi - r.row0 : 16;
+        }
+        return r;
+    };
+    // step s of a block (of none: the first lines of the weights and of h)
+    bf16x8 wf[RING], tf[RING];
+    auto load = [&](const Block &b, int s) {
+        const size_t at = b.nrows ? (size_t)b.e * a.Nb * a.K + (size_t)panel * kPanel * a.K + (size_t)(wave * S + s) * kPanel * kSlab + c0 % kPanel * kSlab : 0;
+        wf[s % RING] = __builtin_nontemporal_load(reinterpret_cast<const bf16x8 *>(a.B + at + l16 * kSlab + lq * 8));
+        const int last = b.nrows ? b.row0 + b.nrows - 1 : 0, row = b.row0 + l16 < last ? b.row0 + l16 : last;
+        tf[s % RING] = *reinterpret_cast<const bf16x8 *>(a.A + (size_t)(wave * S + s) * a.h_rows * kSlab + (size_t)row * kSlab + lq * 8);
+    };
+    Block cur = locate(0);
+#pragma unroll
+    for (int s = 0; s < RING; ++s)
+        if (s < S) load(cur, s);
+
+    // what the combine wants, asked for behind the first weights
+    const int T = c.d.T, D = c.d.D, K = c.d.k, nc = c.d.n_const;
+    const int q = min(tid, T * K - 1), item = min(tid, 2 * T - 1), cv = min(tid, 2 * nc - 1);
+    const int idx = c.topk_idx[q], row_q = c.row_of[q];
+    const float w_q = c.topk_w[q];
+    const size_t out_at = (size_t)(item / 2) * D + c0 + item % 2 * 8;        // this thread's eight columns of a token
+    const bf16x8 xv = *reinterpret_cast<const bf16x8 *>((const bf16_t *)c.x + out_at);
+    float a1 = 0.f;
+    bf16x8 cvv = {};
+    if (nc > 0) {
+        a1 = c.alpha1[min(tid, T * nc - 1)];
+        cvv = *reinterpret_cast<const bf16x8 *>((const bf16_t *)c.const_vecs + (size_t)(cv / 2) * D + c0 + cv % 2 * 8);
+    }
+
+    for (int b = 0; b < total; ++b) {
+        const Block nxt = locate(b + 1);
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s = 0; s < S4; ++s) {
+            if (s < S) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[s % RING], tf[s % RING], acc, 0, 0, 0);
+            const int pos = s + RING;
+            if (pos < S4) {
+                if (pos < S) load(cur, pos);
+            } else if (pos - S4 < S) {
+                load(nxt, pos - S4);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        const int buf = b & 1, pl = tid / 2, vh = tid % 2, m = pl % 16, n = 4 * (pl / 16) + 2 * vh;
+        *reinterpret_cast<f32x4 *>(part[buf][wave][lane]) = acc;
+        lds_barrier();
+        if (tid < 128 && m < cur.nrows) {
+            float y0 = 0.f, y1 = 0.f;
+#pragma unroll
+            for (int w = 0; w < kDecWaves; ++w) {
+                y0 += part[buf][w][pl][2 * vh];
+                y1 += part[buf][w][pl][2 * vh + 1];
+            }
+            typedef bf16_t bf16x2 __attribute__((ext_vector_type(2)));
+            bf16x2 o;
+            o[0] = (bf16_t)y0;
+            o[1] = (bf16_t)y1;
+            *reinterpret_cast<bf16x2 *>(&y[cur.row0 + m][n]) = o;
+            *reinterpret_cast<bf16x2 *>(a.C + (size_t)(cur.row0 + m) * a.ld + c0 + n) = o;
+        }
+        cur = nxt;
+    }
+    if (tid < T * K) {
+        s_idx[tid] = idx;
+        s_row[tid] = row_q;
+        s_w[tid] = w_q;
+    }
+    if (tid < T * nc) s_a1[tid] = a1;
+    if (tid < 2 * nc) *reinterpret_cast<bf16x8 *>(&s_cv[tid / 2][tid % 2 * 8]) = cvv;
+    __syncthreads();
+
+    // ---- the combine of this workgroup's columns
+    if (tid >= 2 * T) return;
+    const int t = tid / 2, h8 = tid % 2 * 8, zero0 = c.d.n_ffn, copy0 = zero0 + c.d.n_zero, const0 = copy0 + c.d.n_copy;
+    float sum[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) sum[i] = 0.f;
+    for (int s = 0; s < K; ++s) {
+        const int e = s_idx[t * K + s], row = s_row[t * K + s];
+        const float g = s_w[t * K + s];
+        if (row == -2) continue;                               // over the expert's capacity: dropped
+        if (e < zero0) {
+            const bf16x8 v = *reinterpret_cast<const bf16x8 *>(&y[row][h8]);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) sum[i] = fmaf(g, (float)v[i], sum[i]);
+        } else if (e >= const0) {
+            const float al = s_a1[t * nc + e - const0], g_x = g * al, g_v = g * (1.f - al);
+            const bf16x8 v = *reinterpret_cast<const bf16x8 *>(&s_cv[e - const0][h8]);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) sum[i] += g_x * (float)xv[i] + g_v * (float)v[i];
+        } else if (e >= copy0 && g != 0.f) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) sum[i] = fmaf(g, (float)xv[i], sum[i]);
+        }
+    }
+    bf16x8 o;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) o[i] = (bf16_t)sum[i];
+    __builtin_nontemporal_store(o, reinterpret_cast<bf16x8 *>((bf16_t *)c.out + out_at));
+}
+
+template <int SMAX>
+static hipError_t dispatch_out(int S, const DecodeOutArgs &a, hipStream_t s) {
+    if constexpr (SMAX < 1) {
+        return hipErrorInvalidValue;
+    } else {
+        if (S != SMAX) return dispatch_out<SMAX - 1>(S, a, s);
+        hipLaunchKernelGGL((k_ffn_decode<SMAX>), dim3(a.c.d.D / 16), dim3(kDecThreads), 0, s, a);
+        return hipGetLastError();
+    }
+}
+
 // launch k_ffn_decode<., S, FR> for the run-time S
 template <int SMAX>
 static hipError_t dispatch_steps(int S, int which, int fr, int n_wg, const DecodeArgs &a, hipStream_t s) {
@@ -276,8 +432,7 @@ bool ffn_decode_supported(const Dims &d) {
            d.D % 256 == 0 && d.F % 256 == 0 && d.D <= kDecMaxSteps * 256 && d.F <= kDecMaxSteps * 256;
 }
 
-hipError_t launch_ffn_decode(const FfnArgs &f, int which, hipStream_t s) {
-    if (f.d.T == 0 || f.d.n_ffn == 0) return hipSuccess;
+static DecodeArgs decode_args(const FfnArgs &f, int which) {
     DecodeArgs a;
     a.offsets = f.offsets;
     a.src_of = f.src_of;
@@ -298,6 +453,29 @@ hipError_t launch_ffn_decode(const FfnArgs &f, int which, hipStream_t s) {
         a.K = f.d.F;
         a.Nb = f.d.D;
     }
+    return a;
+}
+
+// A CU of the kernel that combines, too, reads 27 KB of weights a us, all of them together 6.1 MB: where fewer than 226 workgroups
+// (D < 3614) share them the stream takes longer, which is worth it up to the 3.2 us that a launch and the combine cost.  Layers, us, apart /
+// together: D = 4096, F = 5632 T = 1 65.8 / 62.1, T = 16 327 / 321, T = 45 368 / 367, T = 64 370 / 372 (the token rows are read by every
+// workgroup); three layers of D = 768, F = 2048 T = 1 59.6 / 58.5, T = 2 65.0 / 68.9; D = 2048, F = 1024 T = 1 72.5 / 68.4;
+// D = 2048, F = 2048 T = 2 94.2 / 90.8, T = 8 187 / 193; D = 512, F = 512, 8 experts T = 4 66.4 / 58.1.
+bool ffn_decode_combines(const Dims &d) {
+    if (!ffn_decode_supported(d) || d.T > kDecOutT) return false;
+    const double blocks = d.n_ffn * (1.0 - pow(1.0 - 1.0 / d.N, (double)d.T * d.k));     // experts with rows
+    return blocks * d.F * (32.0 / 27e3 - 2.0 * d.D / 6.1e6) < 3.2;
+}
+
+hipError_t launch_ffn_decode_combine(const FfnArgs &f, const CombineArgs &c, hipStream_t s) {
+    if (f.d.T == 0 || !ffn_decode_combines(f.d)) return hipErrorInvalidValue;
+    const DecodeOutArgs a{decode_args(f, 1), c};
+    return dispatch_out<kDecMaxSteps>(a.g.K / (32 * kDecWaves), a, s);
+}
+
+hipError_t launch_ffn_decode(const FfnArgs &f, int which, hipStream_t s) {
+    if (f.d.T == 0 || f.d.n_ffn == 0) return hipSuccess;
+    const DecodeArgs a = decode_args(f, which);
     static int n_cu = 0;
     if (n_cu == 0) {
         int dev = 0, v = 0;

@@ -283,8 +283,23 @@ moepp_status do_permute(moepp_ctx *c, hipStream_t s, int T, int k) {
     return e == hipSuccess ? MOEPP_OK : MOEPP_EHIP;
 }
 
+CombineArgs combine_args(const moepp_ctx *c, int T, const void *x, const void *const_vecs, int k, void *out) {
+    CombineArgs a;
+    a.d = dims_of(c, T, k);
+    a.x = x;
+    a.const_vecs = const_vecs;
+    a.yffn = c->ws.yffn;
+    a.topk_idx = c->ws.topk_idx;
+    a.row_of = c->ws.row_of;
+    a.topk_w = c->ws.topk_w;
+    a.alpha1 = c->ws.alpha1;
+    a.out = out;
+    return a;
+}
+
+// comb: may be null; if not, GEMM2 may do the combine as well (*combined)
 moepp_status do_ffn(moepp_ctx *c, hipStream_t s, int T, const void *x, const void *experts,
-                    int k) {
+                    int k, const CombineArgs *comb = nullptr, bool *combined = nullptr) {
     FfnArgs a;
     a.d = dims_of(c, T, k);
     moepp_status st = MOEPP_OK;
@@ -310,6 +325,11 @@ moepp_status do_ffn(moepp_ctx *c, hipStream_t s, int T, const void *x, const voi
     hipError_t e = hipSuccess;
     for (int which = 0; which < 2 && e == hipSuccess; ++which) {
         KernelTimer kt(c, s, which == 0 ? MOEPP_K_GEMM1 : MOEPP_K_GEMM2);
+        if (which == 1 && decode && comb && c->variant == 0 && ffn_decode_combines(a.d)) {
+            e = launch_ffn_decode_combine(a, *comb, s);
+            *combined = true;
+            break;
+        }
         e = decode ? launch_ffn_decode(a, which, s)
             : tiled ? launch_ffn_mfma(a, which, s)
             : f32   ? launch_ffn_f32(a, which, s)
@@ -321,16 +341,7 @@ moepp_status do_ffn(moepp_ctx *c, hipStream_t s, int T, const void *x, const voi
 moepp_status do_combine(moepp_ctx *c, hipStream_t s, int T, const void *x, const void *const_vecs,
                         int k, void *out) {
     if (T == 0) return MOEPP_OK;
-    CombineArgs a;
-    a.d = dims_of(c, T, k);
-    a.x = x;
-    a.const_vecs = const_vecs;
-    a.yffn = c->ws.yffn;
-    a.topk_idx = c->ws.topk_idx;
-    a.row_of = c->ws.row_of;
-    a.topk_w = c->ws.topk_w;
-    a.alpha1 = c->ws.alpha1;
-    a.out = out;
+    const CombineArgs a = combine_args(c, T, x, const_vecs, k, out);
     KernelTimer kt(c, s, MOEPP_K_COMBINE);
     hipError_t e = launch_combine(a, c->desc.act == MOEPP_BF16, s);
     return e == hipSuccess ? MOEPP_OK : MOEPP_EHIP;
@@ -385,8 +396,10 @@ moepp_status run_forward(moepp_ctx *ctx, void *stream, int32_t T, const void *x,
     if (st != MOEPP_OK) return st;
     st = do_permute(ctx, s, T, k);
     if (st != MOEPP_OK) return st;
-    st = do_ffn(ctx, s, T, x, experts, k);
-    if (st != MOEPP_OK) return st;
+    const CombineArgs comb = combine_args(ctx, T, x, const_vecs, k, out);
+    bool combined = false;
+    st = do_ffn(ctx, s, T, x, experts, k, &comb, &combined);
+    if (st != MOEPP_OK || combined) return st;
     return do_combine(ctx, s, T, x, const_vecs, k, out);
 }
 

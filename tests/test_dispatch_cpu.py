@@ -225,3 +225,24 @@ def test_halves_of_wide_float32_tiles(launches):
             assert want in (None, name), (kw, got)
             if "128, 256" in name:
                 assert grid == ((T * k // 128 + n) * -(-cols // 256) + 7) // 8 * 8 + 128
+
+
+@pytest.mark.parametrize("T,D,F,n_ffn,k,together", [
+    (1, 768, 2048, 16, 2, True), (2, 768, 2048, 16, 2, False), (1, 768, 2048, 16, 4, False), (16, 4096, 5632, 16, 2, True), (48, 4096, 5632, 16, 2, True),
+    (49, 4096, 5632, 16, 2, False), (8, 2048, 2048, 16, 2, False), (4, 512, 512, 8, 2, True), (48, 3840, 256, 16, 2, True)])
+def test_which_calls_combine_in_gemm2(launches, T, D, F, n_ffn, k, together):
+    """16 columns a workgroup; the step calls and the variants keep the two kernels."""
+    call = "forward %d %d" % (T, k)
+    r = launches([ctx(T, D, F, n_ffn, k=k), call, "ffn %d %d" % (T, k), "combine %d %d" % (T, k), "variant 2", call])
+    last = [n for n in names(r[1]) if n.startswith(("k_ffn", "k_combine"))]
+    if together:
+        assert last[1:] == ["k_ffn_decode<%d>" % (F // 256)] and r[1][1][-1][1] == (D // 16, 1, 1)
+    for got in (last, [n for n in names(r[2]) + names(r[3])], [n for n in names(r[5]) if n.startswith(("k_ffn", "k_combine"))])[together:]:
+        assert got[1].startswith("k_ffn_decode<false, ") and got[2].startswith("k_combine<"), got
+
+
+def test_shapes_of_the_gpu_test_combine_in_gemm2(launches):
+    from test_gpu_ffn_edges import DECODE_COMBINE
+    for T, D, F, n_ffn, n, k in DECODE_COMBINE:
+        r = launches([ctx(T, D, F, n_ffn, k=k, n_zero=n, n_copy=n, n_const=n), "forward %d %d" % (T, k)])
+        assert names(r[1])[-1] == "k_ffn_decode<%d>" % (F // 256), (T, D, F, names(r[1]))

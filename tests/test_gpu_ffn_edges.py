@@ -376,3 +376,34 @@ def test_f32_halves_and_whole_tiles_are_the_same_numbers():
     expert): no other token's row changes, nor with operands for the float32 instruction in a half."""
     for T in (3366, 3300, 3400):
         test_f32_rows_do_not_depend_on_their_neighbours(T, 608, 1568)
+
+
+# GEMM2 with the combine in it: (T, D, F = 256 steps of a wave, FFN experts, others each, slots)
+DECODE_COMBINE = [(1, 256, 256, 3, 1, 2), (48, 3840, 256, 16, 1, 2), (2, 512, 512, 4, 1, 7), (17, 4096, 768, 8, 2, 4), (33, 4096, 1280, 12, 0, 2),
+                  (1, 768, 2048, 16, 1, 2), (5, 3840, 2816, 4, 8, 8), (16, 4096, 4096, 6, 1, 2), (9, 6144, 4352, 2, 1, 3),
+                  (3, 4096, 5632, 4, 1, 2), (2, 3840, 6144, 3, 1, 2)]
+
+
+@pytest.mark.parametrize("T,D,F,n_ffn,n,k", DECODE_COMBINE)
+@pytest.mark.parametrize("tight", [False, True])
+def test_decode_with_the_combine(T, D, F, n_ffn, n, k, tight):
+    """Against the oracle, and bit by bit what the separate kernels of the step calls give; slots dropped, too."""
+    import torch
+    from helpers import to_device
+    s = LayerShape("edge", T=T, D=D, F=F, n_ffn=n_ffn, n_zero=n, n_copy=n, n_const=n, k=k, bias="normal", seed=8500 + T)
+    print("shape", s, flush=True)
+    inp = make_inputs(s)
+    dev, L = to_device(s, inp), make_layer(s)
+    cap = [max(0, c // 2) for c in L.capacity(T, 1.1, 0.75)] if tight else None
+    res = gpu_forward(s, inp, layer=L, dev=dev, cap=cap)
+    print("  ", check_layer(s, inp, res, cap=None if cap is None else np.array(cap, np.int32)), flush=True)
+    packed = L.pack_experts(dev["w1"], dev["w3"], dev["w2"])
+    L.route(dev["x"], dev["prev_gate"], dev["W_g"], dev["W_res"], dev["W_c"] if n else None)
+    L.permute()
+    L.expert_ffn(dev["x"], packed)
+    out = L.combine(dev["x"], dev["const_vecs"] if n else None)
+    torch.cuda.synchronize()
+    assert np.array_equal(out.float().cpu().numpy().astype(np.float64), res["out"])
+    R = int(res["offsets"][-1])
+    for name, v in L.get_intermediates(R).items():
+        assert np.array_equal(v.float().cpu().numpy(), res[name]), name
