@@ -63,9 +63,10 @@ struct GemmArgs {
 // silu(z) = z / (1 + e^-z) with the hardware exp2 and reciprocal (1 ulp each:
 // far inside the rounding of the bf16 result).  A correctly rounded division
 // costs ten more instructions per element, a third of the epilogue.  The ragged
-// instances (RAG, below) use silu_f all the same: their layers ran with it before they had
-// matrix-core kernels, and below z = -87 the hardware reciprocal's result is flushed to zero
-// (T = 1999, D = 1000, F = 1416: GEMM1 36 us, with the hardware functions 33).
+// instances (RAG, below) use silu_f's values all the same, silu_near's bits where no element of a
+// wave is beyond it: their layers ran with it before they had matrix-core kernels, and below z = -87
+// the hardware reciprocal's result is flushed to zero (T = 1999, D = 1000, F = 1416: GEMM1 34.4 us
+// with silu_f alone, 32.7 now, 32 with the hardware functions).
 __device__ inline float fast_silu(float z) {
     return z * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(-1.44269504088896340736f * z));
 }
@@ -583,33 +584,49 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs &a, const GroupTiles &
                 // B row wn*TN + j*16 + 4*lq + v; B rows come in blocks of 32
                 // rows of W1 then 32 rows of W3 (GEMM1), so 16-row block j
                 // pairs with block j + 2
+                auto to_patch = [&](auto silu) {
 #pragma unroll
-                for (int i = 0; i < MBX; ++i) {
-                    const int m = wm * TM + i * 16 + l16 - ep * HB;
-                    char *orow = patch + m * OUT_STRIDE;
-                    if constexpr (SWIGLU) {
+                    for (int i = 0; i < MBX; ++i) {
+                        const int m = wm * TM + i * 16 + l16 - ep * HB;
+                        char *orow = patch + m * OUT_STRIDE;
+                        if constexpr (SWIGLU) {
 #pragma unroll
-                        for (int jp = 0; jp < NBX / 2; ++jp) {
-                            const int jg = (jp / 2) * 4 + jp % 2;             // silu's argument
-                            const int c0 = (wn * TN) / 2 + (jp / 2) * 32 + (jp % 2) * 16 + 4 * lq;
-                            bf16x4 o;
+                            for (int jp = 0; jp < NBX / 2; ++jp) {
+                                const int jg = (jp / 2) * 4 + jp % 2;             // silu's argument
+                                const int c0 = (wn * TN) / 2 + (jp / 2) * 32 + (jp % 2) * 16 + 4 * lq;
+                                bf16x4 o;
 #pragma unroll
-                            for (int q = 0; q < 4; ++q) {
-                                const float z = acc[jg][i][q];
-                                o[q] = (bf16_t)((RAG ? silu_f(z) : fast_silu(z)) * acc[jg + 2][i][q]);
+                                for (int q = 0; q < 4; ++q) {
+                                    const float z = acc[jg][i][q];
+                                    o[q] = (bf16_t)(silu(z) * acc[jg + 2][i][q]);
+                                }
+                                *reinterpret_cast<bf16x4 *>(orow + c0 * 2) = o;
                             }
-                            *reinterpret_cast<bf16x4 *>(orow + c0 * 2) = o;
-                        }
-                    } else {
+                        } else {
 #pragma unroll
-                        for (int j = 0; j < NBX; ++j) {
-                            const int c0 = wn * TN + j * 16 + 4 * lq;
-                            bf16x4 o;
+                            for (int j = 0; j < NBX; ++j) {
+                                const int c0 = wn * TN + j * 16 + 4 * lq;
+                                bf16x4 o;
 #pragma unroll
-                            for (int q = 0; q < 4; ++q) o[q] = (bf16_t)acc[j][i][q];
-                            *reinterpret_cast<bf16x4 *>(orow + c0 * 2) = o;
+                                for (int q = 0; q < 4; ++q) o[q] = (bf16_t)acc[j][i][q];
+                                *reinterpret_cast<bf16x4 *>(orow + c0 * 2) = o;
+                            }
                         }
                     }
+                };
+                if constexpr (!SWIGLU || !RAG) {
+                    to_patch([](float z) { return fast_silu(z); });
+                } else {
+                    float most = 0.f;
+#pragma unroll
+                    for (int j = 0; j < NBX; ++j)
+#pragma unroll
+                        for (int i = 0; i < MBX; ++i)
+#pragma unroll
+                            for (int q = 0; q < 4; ++q)
+                                if (j % 4 < 2) most = fmaxf(most, fabsf(acc[j][i][q]));
+                    if (__any(most > kSiluNear)) to_patch([](float z) { return silu_both(z); });
+                    else to_patch([](float z) { return silu_near(z); });
                 }
             }
             lds_sync();

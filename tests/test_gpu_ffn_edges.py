@@ -407,3 +407,32 @@ def test_decode_with_the_combine(T, D, F, n_ffn, n, k, tight):
     R = int(res["offsets"][-1])
     for name, v in L.get_intermediates(R).items():
         assert np.array_equal(v.float().cpu().numpy(), res[name]), name
+
+
+# SiLU of the float32 and ragged kernels: a wave whose arguments all have |z| <= 87 takes the shorter form. z is exact in
+# every kernel (one 1 in x), near 0, up to 87, at the limit and far beyond it, alone and mixed in a wave. float32: e^-z
+# and the quotient to 1.5 and 1 ulp of 2^-23 each at most, z = W1 exactly; h is compared where the true value is normal.
+@pytest.mark.parametrize("act,D,F", [("f32", 32, 4096), ("f32", 40, 1000), ("bf16", 40, 1000)])
+@pytest.mark.parametrize("far", [False, True])
+def test_silu_near_and_far(act, D, F, far):
+    rng = np.random.default_rng(8400)
+    z = np.concatenate([np.exp2(rng.uniform(-20, 6.44, F - 8)) * rng.choice([-1, 1], F - 8),
+                        [0.0, 87.0, -87.0, 1e-30, 86.99, -86.99, 0.5, -0.5]])
+    if far:
+        z[rng.permutation(F)[:F // 64]] = rng.choice([88.0, -88.0, 1e4, -1e4, 3e38, -3e38, 87.5, -87.5], F // 64)
+    z = (np.float32(z).view(np.uint32) & (0xFFFF0000 if act == "bf16" else 0xFFFFFFFF)).view(np.float32)
+    s = LayerShape("silu2", T=300, D=D, F=F, n_ffn=1, n_zero=0, n_copy=0, n_const=0, k=1, act=act, residual=False, seed=8401)
+    inp = make_inputs(s)
+    inp["x"][:] = 0.0
+    inp["x"][:, 3] = 1.0
+    inp["w1"][:] = 0.0
+    inp["w1"][0, :, 3] = z
+    inp["w3"][:] = 0.0
+    inp["w3"][0, :, 3] = 1.0
+    inp["w2"][:] = 0.0
+    h = np.asarray(gpu_forward(s, inp)["h"], np.float64)
+    z = z.astype(np.float64)
+    with np.errstate(over="ignore"):
+        want = z / (1.0 + np.exp(-z))
+    bound = np.abs(want) * (1.0 / 256 if act == "bf16" else 2.5 * 2.0 ** -23) + 2.0 ** -126
+    assert np.isfinite(h).all() and (np.abs(h - want) <= bound).all(), np.abs((h - want) / bound).max()
