@@ -28,6 +28,7 @@
 //  * the eight partial sums of a unit meet in LDS (two buffers, one barrier per
 //    unit) and are added in wave order by all threads (the same on every
 //    run), which apply SwiGLU and store.
+// For a few tokens a kernel whose workgroups own columns of the output takes GEMM2 and the combine together (below).
 // Rows past the end of a row block are clamped on load and masked on store.
 #include "common.h"
 
