@@ -320,10 +320,13 @@ __device__ inline float wave_max(float v) {
 
 __device__ inline float silu_f(float z) { return z / (1.f + expf(-z)); }
 
-// The same for |z| <= kSiluNear (and NaN) in two thirds of the instructions, and the same bits (4 million values over each of
-// |z| <= 1, 8, 32, 87): nothing overflows there, so the power of two goes straight into the exponent of e^-z = 2^n 2^f (the
-// addition that rounds -z log2 e leaves n in its low bits) and the division neither scales nor tests its operands (a reciprocal
-// and a Newton step on the quotient).  No contraction: f counts on t as rounded.
+// The same function for |z| <= kSiluNear (and NaN) in two thirds of the instructions: nothing overflows
+// there.  e^-z = 2^n 2^f by the reduction of Cody and Waite (Software Manual for the Elementary Functions,
+// 1980): log2 e in two floats, the product's rounding error by an FMA (Dekker, 1971), the addition that rounds to
+// n leaves it in its low bits, from where it goes straight into the exponent.  The quotient is a reciprocal and one
+// correction by its residual (Markstein, 1990); the residual is taken as -(q d - z), so that zero keeps its sign.
+// Over all 2.24e9 floats of |z| <= 87 the error against float64 is 3.1 x 2^-24 at most, like that of silu_f, and
+// 15 results differ from silu_f's (f a rounding apart), by one or two ulps.  No contraction: f counts on t as rounded.
 constexpr float kSiluNear = 87.f;            // e^87 < 2^126: the reciprocal is a normal number
 __device__ inline float silu_near(float z) {
 #pragma clang fp contract(off)
@@ -333,7 +336,7 @@ __device__ inline float silu_near(float z) {
     const float f = (t - n) + fmaf(-z, lo, fmaf(-z, hi, -t));
     const float p = __uint_as_float((__float_as_uint(m) << 23) + __float_as_uint(__builtin_amdgcn_exp2f(f)));
     const float d = 1.f + p, inv = __builtin_amdgcn_rcpf(d), q = z * inv;
-    return fmaf(fmaf(-q, d, z), inv, q);
+    return fmaf(-fmaf(q, d, -z), inv, q);
 }
 // By element, so that no row's bits depend on another's.
 __device__ inline float silu_both(float z) { return fabsf(z) <= kSiluNear ? silu_near(z) : silu_f(z); }

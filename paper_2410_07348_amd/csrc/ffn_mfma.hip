@@ -63,10 +63,10 @@ struct GemmArgs {
 // silu(z) = z / (1 + e^-z) with the hardware exp2 and reciprocal (1 ulp each:
 // far inside the rounding of the bf16 result).  A correctly rounded division
 // costs ten more instructions per element, a third of the epilogue.  The ragged
-// instances (RAG, below) use silu_f's values all the same, silu_near's bits where no element of a
-// wave is beyond it: their layers ran with it before they had matrix-core kernels, and below z = -87
-// the hardware reciprocal's result is flushed to zero (T = 1999, D = 1000, F = 1416: GEMM1 34.4 us
-// with silu_f alone, 32.7 now, 32 with the hardware functions).
+// instances (RAG, below) use silu_f all the same, and silu_near, which is as exact, for elements within its range:
+// their layers ran with silu_f before they had matrix-core kernels, and below z = -87 the hardware reciprocal's
+// result is flushed to zero (T = 1999, D = 1000, F = 1416: GEMM1 34.4 us with silu_f alone, 32.7 now, 32 with
+// the hardware functions).
 __device__ inline float fast_silu(float z) {
     return z * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(-1.44269504088896340736f * z));
 }

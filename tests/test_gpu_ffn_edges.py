@@ -436,3 +436,15 @@ def test_silu_near_and_far(act, D, F, far):
         want = z / (1.0 + np.exp(-z))
     bound = np.abs(want) * (1.0 / 256 if act == "bf16" else 2.5 * 2.0 ** -23) + 2.0 ** -126
     assert np.isfinite(h).all() and (np.abs(h - want) <= bound).all(), np.abs((h - want) / bound).max()
+
+
+# sums of negative products that all underflow are a zero with its sign: silu(-0) is -0 here and in the plain kernels
+def test_silu_keeps_the_sign_of_zero():
+    s = LayerShape("silu3", T=300, D=32, F=64, n_ffn=1, n_zero=0, n_copy=0, n_const=0, k=1, act="f32", residual=False, seed=8402)
+    inp = make_inputs(s)
+    inp["x"][:] = 2.0 ** -100
+    inp["w1"][:] = np.where(np.arange(s.F) % 3 == 1, -2.0 ** -100, 2.0 ** -100)[None, :, None]
+    inp["w3"][:] = 2.0 ** 100
+    a, b = (np.asarray(gpu_forward(s, inp, variant=v)["h"], np.float32) for v in (0, 1))
+    print("zeros", (a == 0).all(), (b == 0).all(), "negative", np.signbit(a).sum(), np.signbit(b).sum(), flush=True)
+    assert (a == 0).all() and np.signbit(b).any() and np.array_equal(np.signbit(a), np.signbit(b))
