@@ -457,15 +457,38 @@ static DecodeArgs decode_args(const FfnArgs &f, int which) {
     return a;
 }
 
-// A CU of the kernel that combines, too, reads 27 KB of weights a us, all of them together 6.1 MB: where fewer than 226 workgroups
-// (D < 3614) share them the stream takes longer, which is worth it up to the 3.2 us that a launch and the combine cost.  Layers, us, apart /
-// together: D = 4096, F = 5632 T = 1 65.8 / 62.1, T = 16 327 / 321, T = 45 368 / 367, T = 64 370 / 372 (the token rows are read by every
-// workgroup); three layers of D = 768, F = 2048 T = 1 59.6 / 58.5, T = 2 65.0 / 68.9; D = 2048, F = 1024 T = 1 72.5 / 68.4;
-// D = 2048, F = 2048 T = 2 94.2 / 90.8, T = 8 187 / 193; D = 512, F = 512, 8 experts T = 4 66.4 / 58.1.
+// CUs of the device, a multiple of the 16 workgroups that share a panel.
+static int decode_cus() {
+    static int n_cu = 0;
+    if (n_cu == 0) {
+        int dev = 0, v = 0;
+        if (hipGetDevice(&dev) != hipSuccess ||
+            hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || v < 16)
+            v = 256;
+        n_cu = v / 16 * 16;
+    }
+    return n_cu;
+}
+
+// A CU of the kernel that combines, too, reads 27 KB of weights a us, all of them together 6.1 MB: where
+// fewer than 226 workgroups (D < 3614) share them the stream takes longer, which is worth it up to the 3.2 us that
+// a launch and the combine cost.  Layers, us, apart / together: D = 4096, F = 5632 T = 1 65.8 / 62.1, T = 16
+// 327 / 321, T = 45 368 / 367, T = 64 370 / 372 (the token rows are read by every workgroup); three layers of D =
+// 768, F = 2048 T = 1 59.6 / 58.5, T = 2 65.0 / 68.9; D = 2048, F = 1024 T = 1 72.5 / 68.4; D = 2048, F = 2048
+// T = 2 94.2 / 90.8, T = 8 187 / 193; D = 512, F = 512, 8 experts T = 4 66.4 / 58.1.
+// More workgroups than CUs (D > 4096) are a second round with most CUs idle: a CU has one of them from F = 2816 on
+// (over 128 registers), and two of them share its 27 KB a us.  16 experts: D = 4352, F = 5632 T = 1 73.0 / 78.1,
+// T = 16 298 / 336, T = 40 385 / 446; D = 5120, F = 5632 T = 16 377 / 404; D = 6144, F = 4352 T = 1 76.6 / 83.0; D =
+// 4352, F = 1024 T = 16 72.9 / 78.4; D = 6144, F = 2048 T = 1 46.9 / 46.7, T = 4 68.5 / 70.5.  Up to F = 512 the
+// launch it saves is more: D = 6144, F = 512 T = 1 31.6 / 30.5, T = 4 39.8 / 38.1; D = 4352, F = 512 T = 4 30.9 /
+// 29.7, but T = 16 47.6 / 49.0.
 bool ffn_decode_combines(const Dims &d) {
     if (!ffn_decode_supported(d) || d.T > kDecOutT) return false;
+    const double wgs = d.D / 16, cus = decode_cus(), cu_rate = 27e3, all_rate = 6.1e6;     // (bytes a us)
+    if (wgs > cus && d.F > 512) return false;
+    const double rounds = (wgs > cus ? cus / all_rate : 0.0) + 1.0 / cu_rate;
     const double blocks = d.n_ffn * (1.0 - pow(1.0 - 1.0 / d.N, (double)d.T * d.k));     // experts with rows
-    return blocks * d.F * (32.0 / 27e3 - 2.0 * d.D / 6.1e6) < 3.2;
+    return 32.0 * blocks * d.F * (rounds - wgs / all_rate) < 3.2;
 }
 
 hipError_t launch_ffn_decode_combine(const FfnArgs &f, const CombineArgs &c, hipStream_t s) {
@@ -477,14 +500,7 @@ hipError_t launch_ffn_decode_combine(const FfnArgs &f, const CombineArgs &c, hip
 hipError_t launch_ffn_decode(const FfnArgs &f, int which, hipStream_t s) {
     if (f.d.T == 0 || f.d.n_ffn == 0) return hipSuccess;
     const DecodeArgs a = decode_args(f, which);
-    static int n_cu = 0;
-    if (n_cu == 0) {
-        int dev = 0, v = 0;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || v < 16)
-            v = 256;
-        n_cu = v / 16 * 16;           // workgroups come in sets that share a panel
-    }
+    const int n_cu = decode_cus();
     const long long slots = (long long)f.d.T * f.d.k;
     const long long experts = slots < f.d.n_ffn ? slots : f.d.n_ffn;
     // Two fragments (32 rows of weights) per workgroup and panel, where there were four: the work
