@@ -815,17 +815,21 @@ hipError_t launch_ffn_mfma(const FfnArgs &f, int which, hipStream_t s) {
     const bool ragged = f.d.D % 64 != 0 || f.d.F % 64 != 0 || K < 128;
     // Few rows per expert (small batches): the GEMMs only stream the weights, so use
     // 128-row tiles: half of the (mostly wasted) matrix work of a 256-row tile per byte
-    // of weights, bound by HBM instead.  Near 128 rows half of the experts have a second such
-    // tile, which reads the weights again, and one 256-row tile is faster where such tiles fill the chip or
-    // are few enough to run as halves.  Four layers in turn, so that no weights are cached, us with 128 / 256-row
-    // tiles, 121 and 127 rows per expert: 16 experts, D = 4096, F = 5632 (two layers) 1064 / 1024 and 1175 / 1031; D = 1024, F =
-    // 2048 339 / 319 and 337 / 319; D = 1536, F = 4096 684 / 722 and 831 / 726; 32 experts, D = 768, F = 2048 416 / 442 and 494 / 445;
-    // D = 2048, F = 1408 668 / 684 and 697 / 688; 8 experts, D = 2048 265 / 277 and 304 / 278; 4 experts, D = 4096 (176
-    // tall tiles, one layer) 127 rows 157 / 182.
+    // of weights, bound by HBM instead.  Towards 128 rows more and more experts have a second such tile, which reads
+    // the weights again, and one 256-row tile is faster except where tall tiles fill one round badly (128 to 224 of them).
+    // Layers in turn, so that no weights are cached, time with 128-row tiles over that with 256-row ones at 103 / 106 /
+    // 109 / 112 / 115 / 118 / 120 / 122 rows per expert, means of 15 layers (8, 16 and 32 experts, D = 768 .. 4096): with
+    // zero-computation experts beside them 0.93 0.92 0.97 0.95 0.98 0.99 1.04 1.02, without 0.93 0.92 0.95 0.97 1.00 1.03
+    // 1.05 1.05; on two other cards 0.89 at 104, 0.93 at 114, 0.975 at 118 with them, without 0.95 at 114, 0.97 at 117, 0.99
+    // at 121.
+    // What a layer loses depends on whether the second tiles start another round: 16 experts, D = 4096, F = 5632 106 rows
+    // 421 / 486 us, 112 415 / 478, 118 533 / 489; D = 1024, F = 2048 (256 tiles of GEMM1, one round) 106 rows 81 / 93, 112
+    // 95 / 93.  128 to 224 tall tiles: 16 experts, D = 2048, F = 1408 118 rows 101 / 109, 122 99 / 107, 125 107 / 111; 4
+    // experts, D = 4096 122 rows 0.86.
     const long long rows = slots / f.d.N + 1;              // per expert, if the router spreads its slots evenly
     const int n_tiles_n = (int)(((which == 0 ? 2ll * f.d.F : f.d.D) + 255) / 256);
     const long long tall = (rows + 255) / 256 * f.d.n_ffn * n_tiles_n;
-    const bool few = ragged || (slots <= 128ll * f.d.n_ffn && (rows <= 122 || (tall > 128 && tall < 224)));
+    const bool few = ragged || rows <= 118 || (rows <= 128 && tall > 128 && tall < 224);
     // How many tiles that makes.
     const long long n_tiles = few ? (rows + 127) / 128 * f.d.n_ffn * n_tiles_n : tall;
     // Small tiles where the others leave the chip half empty.  GEMM2, us with / without:

@@ -103,6 +103,22 @@ def test_which_ffn_takes_few_rows(launches, T, D, F, n_ffn, n_const, k, decode):
         assert len(ffn) == 2 and all(n.startswith("k_ffn_decode<" if few else "k_grouped_gemm<") for n in ffn), ffn
 
 
+# 128-row tiles by rows per expert, T k / N + 1, alike with zero-computation experts and without
+@pytest.mark.parametrize("T,D,F,n_ffn,n_const,tile", [
+    (777, 4096, 5632, 16, 2, "128, 256"), (1025, 4096, 5632, 16, 2, "128, 256"), (1179, 4096, 5632, 16, 2, "128, 256"),
+    (1180, 4096, 5632, 16, 2, "256, 256"), (1220, 4096, 5632, 16, 2, "256, 256"), (2359, 768, 2048, 32, 6, "128, 256"),
+    (2360, 768, 2048, 32, 6, "256, 256"), (943, 1536, 4096, 16, 0, "128, 256"), (944, 1536, 4096, 16, 0, "256, 256"),
+    (1024, 1536, 4096, 16, 0, "256, 256"),
+    # 176 tiles of 256 rows, which without this rule would go to small ones
+    (1180, 2048, 1408, 16, 2, "128, 256"), (1279, 2048, 1408, 16, 2, "128, 256"), (1280, 2048, 1408, 16, 2, "128, 128"),
+    (255, 4096, 5632, 4, 0, "128, 256"), (256, 4096, 5632, 4, 0, "128, 128")])
+def test_which_tiles_take_few_rows(launches, T, D, F, n_ffn, n_const, tile):
+    zc = 1 if n_const else 0
+    r = launches([ctx(T, D, F, n_ffn, n_zero=zc, n_copy=zc, n_const=n_const), "forward %d 2" % T])
+    gemm1 = [n for n in names(r[1]) if n.startswith("k_grouped")][0]
+    assert gemm1.startswith("k_grouped_gemm<Geo<%s," % tile), gemm1
+
+
 def test_shapes_reach_the_instances_their_gpu_tests_name(launches):
     from test_gpu_ffn_edges import INSTANCES
     for kw, gemm1, gemm2 in INSTANCES:
