@@ -21,9 +21,10 @@ constexpr int kRouterFusedT = 64;
 
 // Permutation: one wave owns a chunk of consecutive slots: kPermChunk of them,
 // or the slots of one block of tokens of the router when that has counted
-// them (at least 64 tokens).
+// them: 64 and more, or 16 or 32 (router_block_tokens), whose few hundred histogram rows are
+// in the router's partial sums and need no chunk_base.
 constexpr int kPermChunk = 4 * kWave;
-constexpr int kPermMinChunkTokens = 64;
+constexpr int kPermMinChunkTokens = 64;      // of the chunks that chunk_hist and chunk_base have rows for
 // Up to this many chunks every scatter wave adds up the histogram rows itself
 // (work grows with the square of the chunk count); beyond it a scan kernel does.
 constexpr int kPermDirectChunks = 2048;
@@ -167,8 +168,9 @@ hipError_t launch_router_small(const RouterArgs &a, bool bf16, hipStream_t s, co
 constexpr int kRouterSlicedTok = 64;
 bool router_sliced_wins(const Dims &d);
 hipError_t launch_router_sliced(const RouterArgs &a, bool bf16, hipStream_t s);
-// One kernel on blocks of 16 or 32 tokens, where it is faster; leaves the same, its histogram in blocks of that many tokens
-// (more rows than the workspace's table has: those are in RouterArgs::partial, which this router does not use).
+// One kernel on blocks of 16 or 32 tokens, where it is faster and as exact; leaves the same, its histogram in blocks of
+// that many tokens (more rows than the workspace's table has: those are in RouterArgs::partial, which this router does
+// not use).
 int router_block_tokens(const Dims &d, bool bf16);
 hipError_t launch_router_block(const RouterArgs &a, bool bf16, hipStream_t s);
 size_t router_small_bytes();

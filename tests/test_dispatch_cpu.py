@@ -148,11 +148,12 @@ def test_float32_layers_on_split_operands(launches):
     (2, 1024, BF16, 16, ["k_router_small_partial", "k_router_small_final_perm"]),
     (17, 256, BF16, 16, ["k_router_small_partial", "k_router_small_final_perm"]),
     (64, 4096, BF16, 40, ["k_router_small_partial", "k_router_small_final_perm"]),
-    (65, 768, BF16, 16, ["k_router_small_partial", "k_router_final"]), (65, 640, BF16, 16, ["k_router_mfma"]),
-    (2048, 768, BF16, 16, ["k_router_small_partial", "k_router_final"]), (2049, 768, BF16, 16, ["k_router_mfma"]),
-    (4096, 1536, BF16, 16, ["k_router_small_partial", "k_router_final"]), (4097, 1536, BF16, 16, ["k_router_mfma"]),
-    (3000, 1000, BF16, 16, ["k_router_small_partial", "k_router_final"]),
-    (3000, 768, F32, 16, ["k_router_small_partial", "k_router_final"]), (40000, 64, F32, 16, ["k_router_generic"])])
+    (65, 1024, BF16, 16, ["k_router_small_partial", "k_router_final"]), (65, 640, BF16, 16, ["k_router_block"]),
+    (2048, 4096, BF16, 16, ["k_router_small_partial", "k_router_final"]), (2049, 768, BF16, 16, ["k_router_block"]),
+    (4096, 4096, BF16, 16, ["k_router_small_partial", "k_router_final"]), (4097, 4096, BF16, 16, ["k_router_block"]),
+    (8193, 1536, BF16, 16, ["k_router_mfma"]), (3000, 3080, BF16, 16, ["k_router_small_partial", "k_router_final"]),
+    (5000, 1000, BF16, 16, ["k_router_small_partial", "k_router_final"]), (300, 1000, BF16, 56, ["k_router_small_partial", "k_router_final"]),
+    (3000, 1032, F32, 16, ["k_router_small_partial", "k_router_final"]), (40000, 64, F32, 16, ["k_router_generic"])])
 def test_which_router(launches, T, D, act, n_ffn, router):
     """By tokens, columns and type; the partial sums of every slice fit their 2.6 MB."""
     r = launches([ctx(T, D, 64, n_ffn, act=act), "route %d 2" % T])
@@ -166,11 +167,11 @@ def test_which_router(launches, T, D, act, n_ffn, router):
 # for a wide layer's few tokens; float32: as many as fit; always within the partial sums (T x rows x slices floats)
 # and with a slice of 32 columns for every wave
 @pytest.mark.parametrize("T,D,act,n_ffn,n_const,grid", [
-    (80, 768, BF16, 16, 2, (4, 5)), (300, 4096, BF16, 16, 2, (8, 10)), (1500, 4096, BF16, 16, 2, (5, 47)),
-    (2048, 768, BF16, 16, 2, (4, 64)), (2048, 4096, BF16, 16, 2, (8, 64)), (3000, 4096, BF16, 4, 0, (8, 94)),
+    (80, 1536, BF16, 16, 2, (7, 5)), (300, 4096, BF16, 16, 2, (8, 10)), (1500, 4096, BF16, 16, 2, (5, 47)),
+    (300, 776, BF16, 50, 6, (7, 10)), (2048, 4096, BF16, 16, 2, (8, 64)), (3000, 8192, BF16, 4, 0, (8, 94)),
     (1024, 4096, BF16, 32, 6, (8, 32)), (1200, 4096, BF16, 32, 6, (6, 38)), (2048, 4096, BF16, 32, 6, (4, 64)),
     (4096, 4096, BF16, 32, 6, (3, 128)), (300, 8192, BF16, 16, 2, (24, 10)), (1024, 8192, BF16, 16, 2, (8, 32)),
-    (256, 128, F32, 4, 2, (1, 16)), (2048, 768, F32, 16, 2, (7, 64)), (30000, 768, F32, 4, 0, (3, 938))])
+    (256, 128, F32, 50, 6, (2, 16)), (2048, 1056, F32, 16, 2, (9, 64)), (30000, 768, F32, 4, 0, (3, 938))])
 def test_slices_of_the_router(launches, T, D, act, n_ffn, n_const, grid):
     r = launches([ctx(T, D, 64, n_ffn, act=act, n_const=n_const), "route %d 2" % T])
     assert names(r[1])[0].startswith("k_router_small_partial<") and r[1][1][0][1] == grid + (1,)
@@ -188,45 +189,63 @@ MFMA = "k_router_mfma<%d, %d, %d, %d, %d>"
     (300, 512, 34, (2, 2, 64, 2, 2)), (2100, 768, 34, (2, 2, 64, 2, 2)), (2100, 1024, 34, (2, 2, 64, 2, 2)),
     (300, 640, 34, (2, 2, 64, 2, 1)), (2100, 1408, 34, (2, 2, 64, 2, 1)), (24576, 512, 6, (1, 4, 128, 2, 1))])
 def test_instances_of_the_matrix_core_router(launches, T, D, n_ffn, instance):
-    """The shapes of tests/test_gpu_router_numerics.py and tests/test_gpu_ffn_edges.py that are there for them."""
-    r = launches([ctx(T, D, 64, n_ffn, n_zero=2, n_copy=2), "route %d 2" % T])
-    assert names(r[1]) == [MFMA % instance]
+    """The shapes of tests/test_gpu_router_numerics.py and tests/test_gpu_ffn_edges.py that are there for them, which ask
+    for this router."""
+    r = launches([ctx(T, D, 64, n_ffn, n_zero=2, n_copy=2), "variant 2", "route %d 2" % T])
+    assert names(r[2]) == [MFMA % instance]
 
 
 def test_the_lists_of_routers_name_the_kernels_they_reach(launches):
-    from test_gpu_router_numerics import MATRIX_CORE, ROUTERS, TWO_BLOCKS
-    for act, T, D in ROUTERS:
-        r = launches([ctx(T, D, 64, 6, n_zero=2, n_copy=2, act=F32 if act == "f32" else BF16), "route %d 2" % T])
-        assert names(r[1])[0].startswith("k_router_mfma<") == ((act, T, D) in MATRIX_CORE), (act, T, D)
+    from test_gpu_router_numerics import MATRIX_CORE, ROUTERS, SLICED, TWO_BLOCKS
+    for act, T, D, variant in ROUTERS:
+        r = launches([ctx(T, D, 64, 6, n_zero=2, n_copy=2, act=F32 if act == "f32" else BF16), "variant %d" % variant, "route %d 2" % T])
+        assert names(r[2])[0].startswith("k_router_mfma<") == ((act, T, D, variant) in MATRIX_CORE), (act, T, D)
+        assert (names(r[2])[-1].startswith("k_router_final<")) == ((act, T, D, variant) in SLICED), (act, T, D)
     for T, D in TWO_BLOCKS:
-        r = launches([ctx(T, D, 64, 34, n_zero=2, n_copy=2), "route %d 2" % T])
-        assert names(r[1])[0].startswith("k_router_mfma<2,"), (T, D)
+        r = launches([ctx(T, D, 64, 34, n_zero=2, n_copy=2), "variant 2", "route %d 2" % T])
+        assert names(r[2])[0].startswith("k_router_mfma<2,"), (T, D)
 
 
+# (n_ffn + 8 weight rows)
 @pytest.mark.parametrize("T,D,act,n_ffn,tok", [
-    (2304, 768, BF16, 16, 0), (2305, 768, BF16, 16, 16), (4096, 1024, BF16, 32, 16), (4096, 1152, BF16, 16, 0),
-    (4097, 768, BF16, 16, 0), (4352, 768, BF16, 16, 0), (4353, 4096, BF16, 16, 32), (8192, 256, BF16, 32, 32), (8193, 256, BF16, 16, 0),
-    (4400, 1000, BF16, 8, 0), (4096, 1000, BF16, 8, 16), (65, 264, BF16, 8, 16), (64, 264, BF16, 8, 0), (300, 248, BF16, 8, 0),
-    (300, 1000, BF16, 9, 0), (2048, 768, F32, 8, 16), (2048, 768, F32, 9, 0), (65, 256, F32, 4, 16), (300, 1032, F32, 4, 0),
-    (4097, 256, F32, 4, 0)])
+    # beside the matrix-core router
+    (64, 256, BF16, 16, 0), (65, 128, BF16, 16, 16), (300, 640, BF16, 32, 16), (2049, 1408, BF16, 56, 16), (4096, 1408, BF16, 16, 16),
+    (4097, 128, BF16, 16, 32), (4352, 4096, BF16, 32, 32), (8192, 256, BF16, 32, 32), (8193, 256, BF16, 16, 0), (300, 256, BF16, 57, 0),
+    # beside the slices
+    (65, 1000, BF16, 16, 16), (255, 1024, BF16, 16, 0), (256, 1024, BF16, 16, 16), (256, 1536, BF16, 16, 0), (1535, 1536, BF16, 8, 16),
+    (1535, 2048, BF16, 16, 0), (1536, 2048, BF16, 16, 16), (1535, 1024, BF16, 32, 0), (2048, 1024, BF16, 32, 16), (2048, 1536, BF16, 32, 0),
+    (2049, 1536, BF16, 32, 0), (1535, 1544, BF16, 8, 0), (1536, 1544, BF16, 8, 16), (4096, 1032, BF16, 32, 0), (4096, 2048, BF16, 16, 16), (2049, 4096, BF16, 16, 0), (2049, 4096, BF16, 8, 16),
+    (300, 8, BF16, 8, 16), (4096, 1000, BF16, 32, 16), (4097, 1000, BF16, 8, 0), (4097, 512, BF16, 8, 32), (8192, 504, BF16, 56, 32),
+    (4400, 520, BF16, 8, 0),
+    # float32
+    (65, 8, F32, 4, 16), (2048, 768, F32, 9, 16), (4096, 1024, F32, 16, 16), (4096, 1024, F32, 24, 16), (4096, 1032, F32, 8, 0),
+    (4096, 512, F32, 56, 16), (4096, 520, F32, 25, 0), (4097, 256, F32, 4, 0), (300, 64, F32, 57, 0), (128, 1024, F32, 16, 0)])
 def test_where_the_router_on_blocks_runs(launches, T, D, act, n_ffn, tok):
-    """By tokens, columns, type and weight rows (n_ffn + 8); variants keep the others, and the permutation has as many chunks as
-    there were blocks (four chunks a workgroup)."""
+    """By tokens, columns, type and weight rows; variants keep the others, and the permutation has as many chunks as
+    there were blocks (four chunks a workgroup), at most what its histogram's place and its kernel take."""
     r = launches([ctx(T, D, 64, n_ffn, act=act), "route %d 2" % T, "permute %d 2" % T, "variant 1", "route %d 2" % T])
     assert [n.startswith("k_router_block<") for n in names(r[1])][:1] == [tok > 0], names(r[1])
     assert "k_router_block" not in names(r[4])[0]
     if tok:
         (name, grid, threads), = r[1][1]
         assert grid == ((T + tok - 1) // tok, 1, 1) and name.split(",")[1].strip() == str(tok // 16)
+        assert grid[0] <= 2048 and grid[0] * (n_ffn + 4) * 4 <= 32 * 256 * 80 * 4
         (name, perm, _), = r[2][1]
         assert name == "k_perm_scan_scatter" and perm == ((grid[0] + 3) // 4, 1, 1)
 
 
 def test_blocks_of_the_gpu_tests(launches):
-    from test_gpu_router_block import BLOCK
-    for act, T, D, n_ffn, n, k, (tok, rb) in BLOCK:
+    """... and every instance is among them."""
+    from test_gpu_router_block import BLOCK, INSTANCES
+    reached = set()
+    for act, T, D, n_ffn, n, k, inst in BLOCK:
         r = launches([ctx(T, D, 64, n_ffn, k=k, act=F32 if act == "f32" else BF16, n_zero=n, n_copy=n, n_const=n), "route %d %d" % (T, k)])
-        assert re.match(r"k_router_block<(float|bf16), %d, %d, " % (tok // 16, rb), names(r[1])[0]), (T, D, names(r[1]))
+        m = re.match(r"k_router_block<(float|bf16), (\d), (\d), \d+, (\d+), (\d)>$", names(r[1])[0])
+        assert m, (T, D, names(r[1]))
+        got = (16 * int(m.group(2)),) + tuple(int(v) for v in m.groups()[2:])
+        assert got == inst, (act, T, D, got)
+        reached.add((act,) + got)
+    assert reached == INSTANCES
 
 
 def test_halves_of_wide_float32_tiles(launches):

@@ -45,27 +45,28 @@ def test_bf16_short_reduction(D, F):
     check(T=900, D=D, F=F, n_ffn=4, k=3)
 
 
-# routers between the few-token one (T <= 64) and the 128-token blocks (T >= 24576): the matrix-core one with
-# two groups of waves (D = 128, 256, 512: one pass of its loop over K tiles, or two), one and two blocks of
-# weight rows; slices of 32 columns (wider layers, odd widths, more than 64 rows)
+# routers between the few-token one (T <= 64) and the 128-token blocks (T >= 24576): blocks of 16 tokens in one
+# kernel; the matrix-core one (variant 2) with two groups of waves (D = 128, 256, 512: one pass of its loop over K
+# tiles, or two), one and two blocks of weight rows; slices of 32 columns (wider layers, more than 64 rows)
 @pytest.mark.parametrize("D", [128, 256, 512, 1408, 1536, 4096, 72])
 @pytest.mark.parametrize("n_ffn,n_const,k", [(3, 2, 2), (37, 7, 3), (52, 8, 8)])
 @pytest.mark.parametrize("T", [257, 321])
-def test_router(T, D, n_ffn, n_const, k):
+def test_router(T, D, n_ffn, n_const, k, variant=0):
     s = LayerShape("edge", T=T, D=D, F=64, n_ffn=n_ffn, n_zero=1, n_copy=1, n_const=n_const, k=k,
                    bias="normal", seed=8200)
     inp = make_inputs(s)
     L = make_layer(s)
     cap = L.capacity(T, 1.1, 0.75)
-    res = gpu_forward(s, inp, layer=L, cap=cap, balance_tau=0.75)
+    res = gpu_forward(s, inp, variant, layer=L, cap=cap, balance_tau=0.75)
     print("  ", s, check_layer(s, inp, res, cap=np.array(cap, np.int32), balance_tau=0.75), flush=True)
 
 
 # the matrix-core router with several passes of its loop: one group of waves (D = 640, 1408), two (D = 768, 1024)
 @pytest.mark.parametrize("n_ffn,n_const,k", [(3, 2, 2), (37, 7, 3)])
-@pytest.mark.parametrize("T,D", [(257, 640), (2111, 768), (2111, 1024), (2111, 1408)])
-def test_matrix_core_router(T, D, n_ffn, n_const, k):
-    test_router(T, D, n_ffn, n_const, k)
+@pytest.mark.parametrize("T,D", [(257, 640), (2111, 768), (2111, 1024), (2111, 1408), (257, 128), (321, 256), (257, 512)])
+@pytest.mark.parametrize("variant", [0, 2])
+def test_matrix_core_router(T, D, n_ffn, n_const, k, variant):
+    test_router(T, D, n_ffn, n_const, k, variant)
 
 
 # the routers on slices of 32 columns: the whole router in one workgroup (T <= 16, up to 80 KB of x and

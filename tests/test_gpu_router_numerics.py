@@ -9,12 +9,14 @@ from helpers import gpu_forward
 
 pytestmark = pytest.mark.gpu
 
-# (act, T, D).  Few tokens; slices of 32 columns beyond 64 tokens (float32, a bf16 width that they alone take,
-# widths where they are faster); the matrix-core router: blocks of 64 tokens, one and two groups of waves, several
-# passes of its loop over K tiles, and blocks of 128 tokens (tests/test_dispatch_cpu.py looks at the instances)
-MATRIX_CORE = [("bf16", 300, 640), ("bf16", 2100, 768), ("bf16", 2100, 1024), ("bf16", 24576, 512)]
-ROUTERS = [("f32", 40, 64), ("bf16", 40, 512), ("f32", 100, 64), ("bf16", 300, 1000), ("bf16", 100, 768),
-           ("bf16", 300, 768), ("bf16", 300, 4096)] + MATRIX_CORE
+# (act, T, D, variant).  Few tokens; blocks of 16 tokens in one kernel; slices of 32 columns beyond 64 tokens (wide layers,
+# float32 and bf16, a bf16 width that the matrix-core router does not take); the matrix-core router, asked for where
+# the automatic choice is another: blocks of 64 tokens, one and two groups of waves, several passes of its
+# loop over K tiles, and blocks of 128 tokens (tests/test_dispatch_cpu.py looks at the instances)
+MATRIX_CORE = [("bf16", 300, 640, 2), ("bf16", 2100, 768, 2), ("bf16", 2100, 1024, 2), ("bf16", 24576, 512, 0)]
+SLICED = [("f32", 100, 1032, 0), ("bf16", 300, 3080, 0), ("bf16", 100, 2048, 0), ("bf16", 300, 4096, 0)]
+ROUTERS = [("f32", 40, 64, 0), ("bf16", 40, 512, 0), ("f32", 100, 64, 0), ("bf16", 300, 1000, 0), ("bf16", 100, 768, 0),
+           ("bf16", 300, 768, 0)] + SLICED + MATRIX_CORE
 
 
 def one_hot_shape(act, T, D, **kw):
@@ -32,14 +34,14 @@ def exact_logits(s, inp, col=5):
     return -2.75 * np.arange(s.N)[None, :] * (1.0 + np.arange(s.T) % 4)[:, None]
 
 
-@pytest.mark.parametrize("act,T,D", ROUTERS)
-def test_softmax_is_accurate_to_float32(act, T, D):
+@pytest.mark.parametrize("act,T,D,variant", ROUTERS)
+def test_softmax_is_accurate_to_float32(act, T, D, variant):
     """Relative error, weight by weight, down to logits 77 apart: expf within 1 ulp (2^-23) in
     numerator and sum, N / 4 + 2 additions and a division of half an ulp each."""
     s = one_hot_shape(act, T, D)
     inp = make_inputs(s)
     L = exact_logits(s, inp)
-    res = gpu_forward(s, inp, balance_tau=0.75, intermediates=False)
+    res = gpu_forward(s, inp, variant, balance_tau=0.75, intermediates=False)
     assert np.array_equal(res["out_gate"].astype(np.float64), L)
     assert np.array_equal(res["topk_idx"], np.tile(np.arange(s.k), (T, 1)))
     p = np.exp(L)                                   # the largest logit is 0
@@ -54,7 +56,7 @@ def test_softmax_is_accurate_to_float32(act, T, D):
 
 
 # (variant 1: the router with one wave per token)
-@pytest.mark.parametrize("act,T,D,variant", [r + (0,) for r in ROUTERS] + [("f32", 40, 64, 1), ("bf16", 300, 512, 1)])
+@pytest.mark.parametrize("act,T,D,variant", ROUTERS + [("f32", 40, 64, 1), ("bf16", 300, 512, 1)])
 def test_a_nan_token_stays_alone(act, T, D, variant):
     """A NaN in one row of x makes all its logits NaN.  Its slots still go to k different experts
     (the lowest indices, as with equal logits), the counts add up, and every other token gets the
@@ -79,7 +81,7 @@ def test_a_nan_token_stays_alone(act, T, D, variant):
         assert np.isnan(res[name][t]).all(), name
 
 
-@pytest.mark.parametrize("act,T,D,variant", [r + (0,) for r in ROUTERS] + [("f32", 40, 64, 1), ("bf16", 300, 512, 1)])
+@pytest.mark.parametrize("act,T,D,variant", ROUTERS + [("f32", 40, 64, 1), ("bf16", 300, 512, 1)])
 def test_masked_experts(act, T, D, variant):
     """A bias of -infinity on all experts but one: it takes weight 1, the other slots go to the
     masked experts of the lowest indices, each once, with weight 0."""
@@ -95,7 +97,7 @@ def test_masked_experts(act, T, D, variant):
     assert np.isfinite(res["out"]).all()
 
 
-@pytest.mark.parametrize("act,T,D,variant", [r + (0,) for r in ROUTERS] + [("bf16", 300, 512, 1)])
+@pytest.mark.parametrize("act,T,D,variant", ROUTERS + [("bf16", 300, 512, 1)])
 def test_infinite_router_operands(act, T, D, variant):
     """W_g = -infinity for one expert in a column where x is positive takes that expert out of the
     race, W_g = +infinity gives an infinite logit, and an infinite activation infinite logits of the
@@ -125,19 +127,19 @@ def test_infinite_router_operands(act, T, D, variant):
 
 # (every router, the matrix-core one for one and two blocks of weight rows, and the few-token one in one
 # workgroup)
-@pytest.mark.parametrize("act,T,D,n_ffn", [r + (6,) for r in ROUTERS] + [("bf16", 300, 512, 6), ("bf16", 300, 512, 34),
-                                                                        ("bf16", 300, 640, 34), ("bf16", 2100, 768, 34),
-                                                                        ("bf16", 3, 64, 6), ("f32", 3, 512, 6)])
-def test_infinite_previous_logits_stay_with_their_token(act, T, D, n_ffn):
+@pytest.mark.parametrize("act,T,D,variant,n_ffn", [r + (6,) for r in ROUTERS] + [
+    ("bf16", 300, 512, 2, 6), ("bf16", 300, 512, 2, 34), ("bf16", 300, 640, 2, 34), ("bf16", 2100, 768, 2, 34), ("bf16", 3, 64, 0, 6),
+    ("f32", 3, 512, 0, 6)])
+def test_infinite_previous_logits_stay_with_their_token(act, T, D, variant, n_ffn):
     """The gating residual is added to the logits of its own token and to nothing else: not to another
     token's, and not to the logits of the constant experts (a1)."""
     s = one_hot_shape(act, T, D, n_ffn=n_ffn, residual=True)
     inp = make_inputs(s)
-    ref = gpu_forward(s, inp)
+    ref = gpu_forward(s, inp, variant)
     t = T // 2
     inp["prev_gate"][t, 1] = -np.inf
     inp["prev_gate"][t, 2] = np.nan
-    res = gpu_forward(s, inp)
+    res = gpu_forward(s, inp, variant)
     assert np.isnan(res["out_gate"][t]).all()
     others = np.arange(T) != t
     for name in ("out_gate", "topk_idx", "topk_w"):
@@ -149,7 +151,7 @@ def test_infinite_previous_logits_stay_with_their_token(act, T, D, n_ffn):
 NANS = np.array([0x7fc00000, 0xffc00000, 0x7f800001, 0xff80ffff], np.uint32).view(np.float32)
 
 
-@pytest.mark.parametrize("act,T,D,variant", [r + (0,) for r in ROUTERS] + [("bf16", 3, 64, 0), ("bf16", 300, 512, 1)])
+@pytest.mark.parametrize("act,T,D,variant", ROUTERS + [("bf16", 3, 64, 0), ("bf16", 300, 512, 1)])
 def test_nan_weights(act, T, D, variant):
     """A NaN among the weights of an expert makes its logit NaN, whatever the NaN's bits, and nothing
     else; a NaN in W_c the a1 of its constant expert."""
@@ -172,7 +174,7 @@ def test_nan_weights(act, T, D, variant):
 
 # (every router but the matrix-core one, whose three bf16 pieces of a weight end at 2^-133)
 @pytest.mark.parametrize("exponent", [-118, -130, -145])
-@pytest.mark.parametrize("act,T,D,variant", [r + (0,) for r in ROUTERS if r not in MATRIX_CORE] +
+@pytest.mark.parametrize("act,T,D,variant", [r for r in ROUTERS if r not in MATRIX_CORE] +
                          [("bf16", 3, 64, 0), ("bf16", 1500, 1536, 0), ("bf16", 300, 512, 1)])
 def test_small_weights_keep_their_bits(act, T, D, variant, exponent):
     """Logits of one product each, of a weight with all its significand bits down to the smallest
@@ -192,17 +194,17 @@ TWO_BLOCKS = [(300, 512), (300, 640), (2100, 768), (2100, 1024), (2100, 1408)]
 
 
 @pytest.mark.parametrize("T,D", TWO_BLOCKS)
-def test_two_blocks_of_weight_rows(T, D):
+def test_two_blocks_of_weight_rows(T, D, variant=2, act="bf16"):
     """Exact logits -i (1 + t % 4) / 4 of 40 experts: the softmax as accurate as with one block, and infinite
     and NaN weights of experts in the second block stay where they are."""
-    s = one_hot_shape("bf16", T, D, n_ffn=34)
+    s = one_hot_shape(act, T, D, n_ffn=34)
     assert s.N == 40
     inp = make_inputs(s)
     exact_logits(s, inp)
     inp["W_g"][:, 5] = -0.25 * np.arange(s.N)
     inp["x"][:, 7] = 0.5
     L = -0.25 * np.arange(s.N)[None, :] * (1.0 + np.arange(T) % 4)[:, None]
-    res = gpu_forward(s, inp, intermediates=False)
+    res = gpu_forward(s, inp, variant, intermediates=False)
     assert np.array_equal(res["out_gate"].astype(np.float64), L)
     assert np.array_equal(res["topk_idx"], np.tile(np.arange(s.k), (T, 1)))
     p = np.exp(L)
@@ -212,12 +214,12 @@ def test_two_blocks_of_weight_rows(T, D):
     assert err <= (2 + (s.N // 4 + 2 + 1) / 2) * 2.0 ** -23
     inp["W_g"][33, 7] = np.inf
     inp["W_g"][36, 7] = -np.inf
-    res = gpu_forward(s, inp, intermediates=False)
+    res = gpu_forward(s, inp, variant, intermediates=False)
     L[:, 33], L[:, 36] = np.inf, -np.inf
     assert np.array_equal(res["out_gate"].astype(np.float64), L)
     assert np.all(res["topk_idx"][:, 0] == 33)
     for nan in NANS:
         inp["W_g"][33, 7], inp["W_g"][36, 7] = 0.0, nan
-        res = gpu_forward(s, inp, intermediates=False)
+        res = gpu_forward(s, inp, variant, intermediates=False)
         L[:, 33], L[:, 36] = -0.25 * 33 * (1.0 + np.arange(T) % 4), np.nan
         assert np.array_equal(res["out_gate"].astype(np.float64), L, equal_nan=True)
