@@ -262,6 +262,20 @@ def test_halves_of_wide_float32_tiles(launches):
                 assert grid == ((T * k // 128 + n) * -(-cols // 256) + 7) // 8 * 8 + 128
 
 
+def test_halves_and_whole_tiles_of_the_gpu_test(launches):
+    """Wide tiles in both calls, and as many as the test's own list of them has, which must be enough halves in the first."""
+    from test_gpu_ffn_edges import F32_HALF_WHOLE, WIDE, tile_kinds
+    for D, F, k, few, many, name in F32_HALF_WHOLE:
+        halves = []
+        for T in (few, many):
+            r = launches([ctx(T, D, F, 4, k=k, act=F32, n_zero=0, n_copy=0, n_const=0), "forward %d %d" % (T, k)])
+            gemm = [n for n in names(r[1]) if n.startswith("k_ffn")][name == "yffn"]
+            assert gemm == WIDE % ("true" if name == "h" else "false"), gemm
+            kinds = tile_kinds([(T * k + 3 - e) // 4 for e in range(4)], 2 * F if name == "h" else D)
+            halves.append(sum(kinds.values()) / len(kinds))
+        assert halves[0] > 0.25 and halves[1] == 0.0, halves
+
+
 @pytest.mark.parametrize("T,D,F,n_ffn,k,together", [
     (1, 768, 2048, 16, 2, True), (2, 768, 2048, 16, 2, False), (1, 768, 2048, 16, 4, False), (16, 4096, 5632, 16, 2, True), (48, 4096, 5632, 16, 2, True),
     (49, 4096, 5632, 16, 2, False), (8, 2048, 2048, 16, 2, False), (4, 512, 512, 8, 2, True), (48, 3840, 256, 16, 2, True),
