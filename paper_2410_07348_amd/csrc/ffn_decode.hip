@@ -256,7 +256,7 @@ struct DecodeOutArgs {
 };
 constexpr int kDecOutT = 48, kDecOutSlots = kDecOutT * kMaxTopK;
 template <int S>
-__global__ __launch_bounds__(kDecThreads, 1) void k_ffn_decode(DecodeOutArgs oa) {
+__global__ __launch_bounds__(kDecThreads, 1) void k_ffn_decode_combine(DecodeOutArgs oa) {
     constexpr int RING = 16, S4 = (S + RING - 1) / RING * RING;
     const DecodeArgs &a = oa.g;
     const CombineArgs &c = oa.c;
@@ -393,7 +393,7 @@ static hipError_t dispatch_out(int S, const DecodeOutArgs &a, hipStream_t s) {
         return hipErrorInvalidValue;
     } else {
         if (S != SMAX) return dispatch_out<SMAX - 1>(S, a, s);
-        hipLaunchKernelGGL((k_ffn_decode<SMAX>), dim3(a.c.d.D / 16), dim3(kDecThreads), 0, s, a);
+        hipLaunchKernelGGL((k_ffn_decode_combine<SMAX>), dim3(a.c.d.D / 16), dim3(kDecThreads), 0, s, a);
         return hipGetLastError();
     }
 }

@@ -100,7 +100,8 @@ def test_which_ffn_takes_few_rows(launches, T, D, F, n_ffn, n_const, k, decode):
             assert r[i] == (EUNSUPPORTED, [])
             continue
         ffn = [n for n in names(r[i]) if n.startswith(("k_ffn", "k_grouped"))]
-        assert len(ffn) == 2 and all(n.startswith("k_ffn_decode<" if few else "k_grouped_gemm<") for n in ffn), ffn
+        assert len(ffn) == 2 and all(n.startswith(("k_ffn_decode<", "k_ffn_decode_combine<") if few else "k_grouped_gemm<") for n in ffn), ffn
+        assert not ffn[0].startswith("k_ffn_decode_combine<")
 
 
 # 128-row tiles by rows per expert, T k / N + 1, alike with zero-computation experts and without
@@ -288,7 +289,7 @@ def test_which_calls_combine_in_gemm2(launches, T, D, F, n_ffn, k, together):
     r = launches([ctx(T, D, F, n_ffn, k=k), call, "ffn %d %d" % (T, k), "combine %d %d" % (T, k), "variant 2", call])
     last = [n for n in names(r[1]) if n.startswith(("k_ffn", "k_combine"))]
     if together:
-        assert last[1:] == ["k_ffn_decode<%d>" % (F // 256)] and r[1][1][-1][1] == (D // 16, 1, 1)
+        assert last[1:] == ["k_ffn_decode_combine<%d>" % (F // 256)] and r[1][1][-1][1] == (D // 16, 1, 1)
     for got in (last, [n for n in names(r[2]) + names(r[3])], [n for n in names(r[5]) if n.startswith(("k_ffn", "k_combine"))])[together:]:
         assert got[1].startswith("k_ffn_decode<false, ") and got[2].startswith("k_combine<"), got
 
@@ -297,4 +298,4 @@ def test_shapes_of_the_gpu_test_combine_in_gemm2(launches):
     from test_gpu_ffn_edges import DECODE_COMBINE
     for T, D, F, n_ffn, n, k in DECODE_COMBINE:
         r = launches([ctx(T, D, F, n_ffn, k=k, n_zero=n, n_copy=n, n_const=n), "forward %d %d" % (T, k)])
-        assert names(r[1])[-1] == "k_ffn_decode<%d>" % (F // 256), (T, D, F, names(r[1]))
+        assert names(r[1])[-1] == "k_ffn_decode_combine<%d>" % (F // 256), (T, D, F, names(r[1]))
