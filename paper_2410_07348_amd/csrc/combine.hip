@@ -8,9 +8,9 @@
 //     copy expert     : E = x_t
 //     constant expert : E = a1 x_t + (1 - a1) v_j
 //     any expert, slot dropped by the expert capacity (row_of = -2): nothing
-// fp32 accumulation, one rounding to the activation type.  HBM-bound: one
-// wavefront streams one token with 16-byte accesses per lane.  (Few tokens of the weight-streaming FFN are combined by the
-// kernel of their GEMM2, in the same order with the same roundings.)
+// fp32 accumulation, one rounding to the activation type.  HBM-bound: one wavefront streams one token with
+// 16-byte accesses per lane.  (Few tokens of the weight-streaming FFN are combined by the kernel of their
+// GEMM2, in the same order with the same roundings.)
 #include "common.h"
 
 #include <type_traits>

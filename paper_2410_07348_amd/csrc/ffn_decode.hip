@@ -203,11 +203,12 @@ __global__ __launch_bounds__(kDecThreads, 1) void k_ffn_decode(DecodeArgs a) {
     };
 
     // ---- the stream: unit after unit, S4 positions each --------------------------
-    // While position s of a unit is multiplied, position s + kDecRing of the stream
-    // is loaded into the ring slot that s just left: of this unit, or of the next one, also where that has other
-    // token rows.  Past the last unit every load takes the first line of the weights, which the caches hold: the
-    // last unit's own first steps, once more, were 33 MB from memory at the end of either GEMM (T = 16, D = 4096 GEMM2 106 ->
-    // 101 us; T = 8, D = 1536 29 -> 24; T = 64, D = 768, 32 experts 25.5 -> 19.5, where most workgroups have three units).
+    // While position s of a unit is multiplied, position s + kDecRing of the stream is loaded into the ring
+    // slot that s just left: of this unit, or of the next one, also where that has other token rows.  Past
+    // the last unit every load takes the first line of the weights, which the caches hold: the last unit's
+    // own first steps, once more, were 33 MB from memory at the end of either GEMM (T = 16, D = 4096 GEMM2
+    // 106 -> 101 us; T = 8, D = 1536 29 -> 24; T = 64, D = 768, 32 experts 25.5 -> 19.5, where most
+    // workgroups have three units).
     int buf = 0;
     int u = u0;
     Unit cur = locate(u);
@@ -244,12 +245,13 @@ __global__ __launch_bounds__(kDecThreads, 1) void k_ffn_decode(DecodeArgs a) {
     }
 }
 
-// GEMM2 and the combine (combine.hip, the same operations in the same order) in one kernel, for at most kDecOutT tokens:
-// a workgroup owns 16 columns of the output and takes them through all row blocks of all experts, so that nobody waits for
-// another workgroup.  Weights and the token rows of h travel in one ring of 16 steps (h comes from the caches, 16 rows for
-// every 16 of weights), so nothing drains it between row blocks.  Waves split K; sums and yffn are those of the kernel above, bit
-// by bit.  The code runs once and waits for its instructions: one row block at a time (several in a pass of the ring, where K is
-// short, put more loads in flight and took 8.5 us for one token at D = 768 where this takes 7.3).
+// GEMM2 and the combine (combine.hip, the same operations in the same order) in one kernel, for at most
+// kDecOutT tokens: a workgroup owns 16 columns of the output and takes them through all row blocks of all
+// experts, so that nobody waits for another workgroup.  Weights and the token rows of h travel in one ring
+// of 16 steps (h comes from the caches, 16 rows for every 16 of weights), so nothing drains it between row
+// blocks.  Waves split K; sums and yffn are those of the kernel above, bit by bit.  The code runs once and
+// waits for its instructions: one row block at a time (several in a pass of the ring, where K is short, put
+// more loads in flight and took 8.5 us for one token at D = 768 where this takes 7.3).
 struct DecodeOutArgs {
     DecodeArgs g;
     CombineArgs c;
@@ -291,7 +293,8 @@ __global__ __launch_bounds__(kDecThreads, 1) void k_ffn_decode_combine(DecodeOut
     // step s of a block (of none: the first lines of the weights and of h)
     bf16x8 wf[RING], tf[RING];
     auto load = [&](const Block &b, int s) {
-        const size_t at = b.nrows ? (size_t)b.e * a.Nb * a.K + (size_t)panel * kPanel * a.K + (size_t)(wave * S + s) * kPanel * kSlab + c0 % kPanel * kSlab : 0;
+        const size_t slab = (size_t)b.e * a.Nb * a.K + (size_t)panel * kPanel * a.K + (size_t)(wave * S + s) * kPanel * kSlab;
+        const size_t at = b.nrows ? slab + c0 % kPanel * kSlab : 0;
         wf[s % RING] = __builtin_nontemporal_load(reinterpret_cast<const bf16x8 *>(a.B + at + l16 * kSlab + lq * 8));
         const int last = b.nrows ? b.row0 + b.nrows - 1 : 0, row = b.row0 + l16 < last ? b.row0 + l16 : last;
         tf[s % RING] = *reinterpret_cast<const bf16x8 *>(a.A + (size_t)(wave * S + s) * a.h_rows * kSlab + (size_t)row * kSlab + lq * 8);

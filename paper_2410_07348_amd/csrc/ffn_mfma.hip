@@ -304,8 +304,9 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs &a, const GroupTiles &
             src[i] = SWIGLU ? a.src_of[r] : r;
         }
     };
-    // b_rows: a.Nb, or 1 for a tile that does not exist, which loads one row of weights over and over (the ragged instances,
-    // whose launches end no earlier by it, T = 1999, D = 1000 79.2 / 79.3 us a layer, load those of the last tile again)
+    // b_rows: a.Nb, or 1 for a tile that does not exist, which loads one row of weights over and over (the
+    // ragged instances, whose launches end no earlier by it, T = 1999, D = 1000 79.2 / 79.3 us a layer,
+    // load those of the last tile again)
     auto set_pointers = [&](int t_e, int t_nt, int *src, int b_rows) {
 #pragma unroll
         for (int i = 0; i < CA; ++i) {
@@ -814,19 +815,19 @@ hipError_t launch_ffn_mfma(const FfnArgs &f, int which, hipStream_t s) {
     const int K = which == 0 ? f.d.D : f.d.F;
     const long long slots = (long long)f.d.T * f.d.k;
     const bool ragged = f.d.D % 64 != 0 || f.d.F % 64 != 0 || K < 128;
-    // Few rows per expert (small batches): the GEMMs only stream the weights, so use
-    // 128-row tiles: half of the (mostly wasted) matrix work of a 256-row tile per byte
-    // of weights, bound by HBM instead.  Towards 128 rows more and more experts have a second such tile, which reads
-    // the weights again, and one 256-row tile is faster except where tall tiles fill one round badly (128 to 224 of them).
-    // Layers in turn, so that no weights are cached, time with 128-row tiles over that with 256-row ones at 103 / 106 /
-    // 109 / 112 / 115 / 118 / 120 / 122 rows per expert, means of 15 layers (8, 16 and 32 experts, D = 768 .. 4096): with
-    // zero-computation experts beside them 0.93 0.92 0.97 0.95 0.98 0.99 1.04 1.02, without 0.93 0.92 0.95 0.97 1.00 1.03
-    // 1.05 1.05; on two other cards 0.89 at 104, 0.93 at 114, 0.975 at 118 with them, without 0.95 at 114, 0.97 at 117, 0.99
-    // at 121.
-    // What a layer loses depends on whether the second tiles start another round: 16 experts, D = 4096, F = 5632 106 rows
-    // 421 / 486 us, 112 415 / 478, 118 533 / 489; D = 1024, F = 2048 (256 tiles of GEMM1, one round) 106 rows 81 / 93, 112
-    // 95 / 93.  128 to 224 tall tiles: 16 experts, D = 2048, F = 1408 118 rows 101 / 109, 122 99 / 107, 125 107 / 111; 4
-    // experts, D = 4096 122 rows 0.86.
+    // Few rows per expert (small batches): the GEMMs only stream the weights, so use 128-row tiles: half of
+    // the (mostly wasted) matrix work of a 256-row tile per byte of weights, bound by HBM instead.  Towards
+    // 128 rows more and more experts have a second such tile, which reads the weights again, and one
+    // 256-row tile is faster except where tall tiles fill one round badly (128 to 224 of them).  Layers in
+    // turn, so that no weights are cached, time with 128-row tiles over that with 256-row ones at 103 / 106
+    // / 109 / 112 / 115 / 118 / 120 / 122 rows per expert, means of 15 layers (8, 16 and 32 experts, D =
+    // 768 .. 4096): with zero-computation experts beside them 0.93 0.92 0.97 0.95 0.98 0.99 1.04 1.02,
+    // without 0.93 0.92 0.95 0.97 1.00 1.03 1.05 1.05; on two other cards 0.89 at 104, 0.93 at 114, 0.975
+    // at 118 with them, without 0.95 at 114, 0.97 at 117, 0.99 at 121.  What a layer loses depends on
+    // whether the second tiles start another round: 16 experts, D = 4096, F = 5632 106 rows 421 / 486 us,
+    // 112 415 / 478, 118 533 / 489; D = 1024, F = 2048 (256 tiles of GEMM1, one round) 106 rows 81 / 93,
+    // 112 95 / 93.  128 to 224 tall tiles: 16 experts, D = 2048, F = 1408 118 rows 101 / 109, 122 99 / 107,
+    // 125 107 / 111; 4 experts, D = 4096 122 rows 0.86.
     const long long rows = slots / f.d.N + 1;              // per expert, if the router spreads its slots evenly
     const int n_tiles_n = (int)(((which == 0 ? 2ll * f.d.F : f.d.D) + 255) / 256);
     const long long tall = (rows + 255) / 256 * f.d.n_ffn * n_tiles_n;

@@ -217,9 +217,9 @@ __device__ inline void few_dots(const RouterArgs &a, int t0, int first, int stri
             }
         }
     };
-    // previous logits: eight columns of the slice per lane, as above, float32
-    // (16 bytes at a time where rows are whole 16-byte pieces, which then are in the row or past it: T = 300, D = 768, 52
-    // rows 15.5 -> 13.9 us, T = 64 17.6 -> 16.3)
+    // previous logits: eight columns of the slice per lane, as above, float32 (16 bytes at a time where
+    // rows are whole 16-byte pieces, which then are in the row or past it: T = 300, D = 768, 52 rows 15.5
+    // -> 13.9 us, T = 64 17.6 -> 16.3)
     auto residual = [&](int m0) {
         float pv[TB][8], wv[RB][8];
         if (N % 4 == 0) {
@@ -661,24 +661,28 @@ bool router_sliced_wins(const Dims &d) { return (d.D >= 768 && d.T <= 2048) || (
 // Tokens of a workgroup where the one-kernel router on blocks is faster than the sliced or the matrix-core router
 // and its logits no further from float64, else 0.  Router and permutation, us, and in brackets the logits' error
 // against float64, 1e-8.  Blocks of 16 / the matrix-core router, where it is the other choice:
-//   24 weight rows: D = 128 T = 65 8.3 [6.0] / 11.9 [6.6], T = 2048 9.1 / 13.6; D = 512 T = 300 9.8 [6.9] / 13.8 [7.9]; D = 1024
-//   T = 4096 13.8 [7.3] / 17.2 [10]; 52 rows: D = 256 T = 2048 11.9 [6.8] / 17.9 [7.2]; D = 768 T = 4096 17.4 [7.4] / 22.1 [9.2].
+//   24 weight rows: D = 128 T = 65 8.3 [6.0] / 11.9 [6.6], T = 2048 9.1 / 13.6; D = 512 T = 300 9.8 [6.9] /
+//   13.8 [7.9]; D = 1024 T = 4096 13.8 [7.3] / 17.2 [10]; 52 rows: D = 256 T = 2048 11.9 [6.8] / 17.9
+//   [7.2]; D = 768 T = 4096 17.4 [7.4] / 22.1 [9.2].
 // Against slices, which spread a wide layer's few tokens over more CUs: what a block takes grows with D times its
 // 16, 32 or 64 weight rows and eight for x, what slices take with T.  bf16, block / slices:
-//   D = 768, 24 rows T = 65 10.2 / 11.9, T = 2048 11.0 [7.1] / 14.2 [7.2]; D = 1024, 24 rows T = 65 11.4 / 12.1, T = 300 11.6 /
-//   13.5; D = 1536, 24 rows T = 65 13.1 / 12.1, T = 300 13.4 / 13.4, T = 2048 14.0 [7.7] / 16.4 [7.7]; D = 2048, 24 rows
-//   T = 1024 15.7 / 14.1, T = 2048 16.3 / 17.7, T = 4096 17.4 / 20.4; D = 4096, 24 rows T = 2048 24.0 / 20.1, T = 4096 24.6 / 25.3;
-//   D = 2048, 12 rows T = 300 12.0 / 13.0; D = 4096, 12 rows T = 300 16.8 / 14.2, T = 3000 18.2 / 21.1; D = 768, 52 rows T = 65
-//   14.8 / 15.4, T = 1024 15.4 [7.4] / 17.7 [7.3]; D = 1024, 52 rows T = 65 16.3 / 15.3, T = 2048 17.5 [7.5] / 19.6 [7.5].
-// The width ends where slices are more exact (float32 sums round at every fourth product and get worse with longer
-// chains).  bf16: D = 2048, 12 rows T = 700 12.2 [8.0] / 13.8 [7.6], T = 2048 13.1 [7.9] / 16.8 [7.9]; D = 1536, 52 rows T = 2100
-// 22.2 [8.1] / 23.0 [7.8].  float32: D = 1024, 24 rows T = 2048 13.7 [9.1] / 18.9 [9.2], D = 1536 15.8 [10.1] / 20.6 [9.5];
-// D = 512, 52 rows T = 300 13.5 [8.9] / 16.0 [9.1], D = 768 16.1 [9.9] / 15.9 [9.0]; D = 128, 12 rows T = 256 8.8 / 12.4.
-// One workgroup per CU: blocks of 16 up to T = 4096 (24 rows, D = 768 T = 4300 15.4 [7.5], of 32 13.4, matrix cores
-// 16.2; float32, D = 1024, 24 rows T = 4096 14.6 / 19.5, T = 5000 22.9 / 21.6), of 32 up to 8192 (24 rows, D = 768 T = 8192
-// 14.1 / 16.8, T = 9000 18.3 / 17.6; 52 rows, D = 4096 T = 4097 44.6 [14] / 46.2 [19], T = 8192 46.3 / 47.6, T = 9000 84 / 49;
-// 12 rows, D = 512 T = 9000 12.4 / 14.2, but D = 2048 21.8 / 20.7).  Blocks of 32 are eight waves with one set of sums:
-// widths that slices would take go up to 512 there (D = 520 T = 8192 12.0 [7.0] / 18.3 [7.0], D = 1000 13.9 [8.1] / 18.4 [7.4]).
+//   D = 768, 24 rows T = 65 10.2 / 11.9, T = 2048 11.0 [7.1] / 14.2 [7.2]; D = 1024, 24 rows T = 65 11.4 /
+//   12.1, T = 300 11.6 / 13.5; D = 1536, 24 rows T = 65 13.1 / 12.1, T = 300 13.4 / 13.4, T = 2048 14.0
+//   [7.7] / 16.4 [7.7]; D = 2048, 24 rows T = 1024 15.7 / 14.1, T = 2048 16.3 / 17.7, T = 4096 17.4 / 20.4;
+//   D = 4096, 24 rows T = 2048 24.0 / 20.1, T = 4096 24.6 / 25.3; D = 2048, 12 rows T = 300 12.0 / 13.0; D
+//   = 4096, 12 rows T = 300 16.8 / 14.2, T = 3000 18.2 / 21.1; D = 768, 52 rows T = 65 14.8 / 15.4, T =
+//   1024 15.4 [7.4] / 17.7 [7.3]; D = 1024, 52 rows T = 65 16.3 / 15.3, T = 2048 17.5 [7.5] / 19.6 [7.5].
+// The width ends where slices are more exact (float32 sums round at every fourth product and get worse with
+// longer chains).  bf16: D = 2048, 12 rows T = 700 12.2 [8.0] / 13.8 [7.6], T = 2048 13.1 [7.9] / 16.8
+// [7.9]; D = 1536, 52 rows T = 2100 22.2 [8.1] / 23.0 [7.8].  float32: D = 1024, 24 rows T = 2048 13.7
+// [9.1] / 18.9 [9.2], D = 1536 15.8 [10.1] / 20.6 [9.5]; D = 512, 52 rows T = 300 13.5 [8.9] / 16.0 [9.1],
+// D = 768 16.1 [9.9] / 15.9 [9.0]; D = 128, 12 rows T = 256 8.8 / 12.4.
+// One workgroup per CU: blocks of 16 up to T = 4096 (24 rows, D = 768 T = 4300 15.4 [7.5], of 32 13.4,
+// matrix cores 16.2; float32, D = 1024, 24 rows T = 4096 14.6 / 19.5, T = 5000 22.9 / 21.6), of 32 up to
+// 8192 (24 rows, D = 768 T = 8192 14.1 / 16.8, T = 9000 18.3 / 17.6; 52 rows, D = 4096 T = 4097 44.6 [14] /
+// 46.2 [19], T = 8192 46.3 / 47.6, T = 9000 84 / 49; 12 rows, D = 512 T = 9000 12.4 / 14.2, but D = 2048
+// 21.8 / 20.7).  Blocks of 32 are eight waves with one set of sums: widths that slices would take go up to
+// 512 there (D = 520 T = 8192 12.0 [7.0] / 18.3 [7.0], D = 1000 13.9 [8.1] / 18.4 [7.4]).
 // More than 64 weight rows (five blocks of the instruction): no instance.
 constexpr int kRouterBlocks = 256;
 static_assert(kRouterBlocks <= kPermDirectChunks, "the permutation's table of first ranks has no rows for these blocks");
@@ -694,10 +698,11 @@ int router_block_tokens(const Dims &d, bool bf16) {
     return (long long)d.D * (padded + 8) <= most ? 16 : 0;
 }
 
-// Waves and sets of sums: eight waves have two slices each up to D = 512, then sixteen with two sets (eight of them with
-// more than 32 rows, whose registers do not fit sixteen), so that chains of sums stay as short as on slices: bf16,
-// 24 rows, D = 1024 T = 2048 12.0 us [7.3e-8], eight waves with one set 11.9 [8.0], D = 256 10.0 and 9.1 [6.4 both]; float32, 24
-// rows, D = 256 eight waves 9.1, sixteen 10.3 [8.2 both], D = 768 11.6 [9.7] and 11.8 [8.9]; 12 rows, D = 768 sixteen 10.3 [8.9].
+// Waves and sets of sums: eight waves have two slices each up to D = 512, then sixteen with two sets (eight
+// of them with more than 32 rows, whose registers do not fit sixteen), so that chains of sums stay as short
+// as on slices: bf16, 24 rows, D = 1024 T = 2048 12.0 us [7.3e-8], eight waves with one set 11.9 [8.0], D =
+// 256 10.0 and 9.1 [6.4 both]; float32, 24 rows, D = 256 eight waves 9.1, sixteen 10.3 [8.2 both], D = 768
+// 11.6 [9.7] and 11.8 [8.9]; 12 rows, D = 768 sixteen 10.3 [8.9].
 hipError_t launch_router_block(const RouterArgs &a, bool bf16, hipStream_t s) {
     const int tok = router_block_tokens(a.d, bf16), rows = a.d.N + 2 * a.d.n_const;
     if (tok == 0 || (size_t)kRouterBlocks * a.d.N * sizeof(int32_t) > router_small_bytes()) return hipErrorInvalidValue;

@@ -100,7 +100,8 @@ def test_which_ffn_takes_few_rows(launches, T, D, F, n_ffn, n_const, k, decode):
             assert r[i] == (EUNSUPPORTED, [])
             continue
         ffn = [n for n in names(r[i]) if n.startswith(("k_ffn", "k_grouped"))]
-        assert len(ffn) == 2 and all(n.startswith(("k_ffn_decode<", "k_ffn_decode_combine<") if few else "k_grouped_gemm<") for n in ffn), ffn
+        want = ("k_ffn_decode<", "k_ffn_decode_combine<") if few else "k_grouped_gemm<"
+        assert len(ffn) == 2 and all(n.startswith(want) for n in ffn), ffn
         assert not ffn[0].startswith("k_ffn_decode_combine<")
 
 
@@ -153,7 +154,8 @@ def test_float32_layers_on_split_operands(launches):
     (2048, 4096, BF16, 16, ["k_router_small_partial", "k_router_final"]), (2049, 768, BF16, 16, ["k_router_block"]),
     (4096, 4096, BF16, 16, ["k_router_small_partial", "k_router_final"]), (4097, 4096, BF16, 16, ["k_router_block"]),
     (8193, 1536, BF16, 16, ["k_router_mfma"]), (3000, 3080, BF16, 16, ["k_router_small_partial", "k_router_final"]),
-    (5000, 1000, BF16, 16, ["k_router_small_partial", "k_router_final"]), (300, 1000, BF16, 56, ["k_router_small_partial", "k_router_final"]),
+    (5000, 1000, BF16, 16, ["k_router_small_partial", "k_router_final"]),
+    (300, 1000, BF16, 56, ["k_router_small_partial", "k_router_final"]),
     (3000, 1032, F32, 16, ["k_router_small_partial", "k_router_final"]), (40000, 64, F32, 16, ["k_router_generic"])])
 def test_which_router(launches, T, D, act, n_ffn, router):
     """By tokens, columns and type; the partial sums of every slice fit their 2.6 MB."""
@@ -210,17 +212,25 @@ def test_the_lists_of_routers_name_the_kernels_they_reach(launches):
 # (n_ffn + 8 weight rows)
 @pytest.mark.parametrize("T,D,act,n_ffn,tok", [
     # beside the matrix-core router
-    (64, 256, BF16, 16, 0), (65, 128, BF16, 16, 16), (300, 640, BF16, 32, 16), (2049, 1408, BF16, 56, 16), (4096, 1408, BF16, 16, 16),
-    (4097, 128, BF16, 16, 32), (4352, 4096, BF16, 32, 32), (8192, 256, BF16, 32, 32), (8193, 256, BF16, 16, 0), (300, 256, BF16, 57, 0),
+    (64, 256, BF16, 16, 0), (65, 128, BF16, 16, 16), (300, 640, BF16, 32, 16), (2049, 1408, BF16, 56, 16),
+    (4096, 1408, BF16, 16, 16),
+    (4097, 128, BF16, 16, 32), (4352, 4096, BF16, 32, 32), (8192, 256, BF16, 32, 32), (8193, 256, BF16, 16, 0),
+    (300, 256, BF16, 57, 0),
     # beside the slices
-    (65, 1000, BF16, 16, 16), (255, 1024, BF16, 16, 0), (256, 1024, BF16, 16, 16), (256, 1536, BF16, 16, 0), (1535, 1536, BF16, 8, 16),
-    (1535, 2048, BF16, 16, 0), (1536, 2048, BF16, 16, 16), (1535, 1024, BF16, 32, 0), (2048, 1024, BF16, 32, 16), (2048, 1536, BF16, 32, 0),
-    (2049, 1536, BF16, 32, 0), (1535, 1544, BF16, 8, 0), (1536, 1544, BF16, 8, 16), (4096, 1032, BF16, 32, 0), (4096, 2048, BF16, 16, 16), (2049, 4096, BF16, 16, 0), (2049, 4096, BF16, 8, 16),
-    (300, 8, BF16, 8, 16), (4096, 1000, BF16, 32, 16), (4097, 1000, BF16, 8, 0), (4097, 512, BF16, 8, 32), (8192, 504, BF16, 56, 32),
+    (65, 1000, BF16, 16, 16), (255, 1024, BF16, 16, 0), (256, 1024, BF16, 16, 16), (256, 1536, BF16, 16, 0),
+    (1535, 1536, BF16, 8, 16),
+    (1535, 2048, BF16, 16, 0), (1536, 2048, BF16, 16, 16), (1535, 1024, BF16, 32, 0), (2048, 1024, BF16, 32, 16),
+    (2048, 1536, BF16, 32, 0),
+    (2049, 1536, BF16, 32, 0), (1535, 1544, BF16, 8, 0), (1536, 1544, BF16, 8, 16), (4096, 1032, BF16, 32, 0),
+    (4096, 2048, BF16, 16, 16), (2049, 4096, BF16, 16, 0), (2049, 4096, BF16, 8, 16),
+    (300, 8, BF16, 8, 16), (4096, 1000, BF16, 32, 16), (4097, 1000, BF16, 8, 0), (4097, 512, BF16, 8, 32),
+    (8192, 504, BF16, 56, 32),
     (4400, 520, BF16, 8, 0),
     # float32
-    (65, 8, F32, 4, 16), (2048, 768, F32, 9, 16), (4096, 1024, F32, 16, 16), (4096, 1024, F32, 24, 16), (4096, 1032, F32, 8, 0),
-    (4096, 512, F32, 56, 16), (4096, 520, F32, 25, 0), (4097, 256, F32, 4, 0), (300, 64, F32, 57, 0), (128, 1024, F32, 16, 0)])
+    (65, 8, F32, 4, 16), (2048, 768, F32, 9, 16), (4096, 1024, F32, 16, 16), (4096, 1024, F32, 24, 16),
+    (4096, 1032, F32, 8, 0),
+    (4096, 512, F32, 56, 16), (4096, 520, F32, 25, 0), (4097, 256, F32, 4, 0), (300, 64, F32, 57, 0),
+    (128, 1024, F32, 16, 0)])
 def test_where_the_router_on_blocks_runs(launches, T, D, act, n_ffn, tok):
     """By tokens, columns, type and weight rows; variants keep the others, and the permutation has as many chunks as
     there were blocks (four chunks a workgroup), at most what its histogram's place and its kernel take."""
@@ -278,10 +288,12 @@ def test_halves_and_whole_tiles_of_the_gpu_test(launches):
 
 
 @pytest.mark.parametrize("T,D,F,n_ffn,k,together", [
-    (1, 768, 2048, 16, 2, True), (2, 768, 2048, 16, 2, False), (1, 768, 2048, 16, 4, False), (16, 4096, 5632, 16, 2, True), (48, 4096, 5632, 16, 2, True),
+    (1, 768, 2048, 16, 2, True), (2, 768, 2048, 16, 2, False), (1, 768, 2048, 16, 4, False), (16, 4096, 5632, 16, 2, True),
+    (48, 4096, 5632, 16, 2, True),
     (49, 4096, 5632, 16, 2, False), (8, 2048, 2048, 16, 2, False), (4, 512, 512, 8, 2, True), (48, 3840, 256, 16, 2, True),
     # more workgroups than the 256 CUs
-    (1, 4352, 5632, 16, 2, False), (16, 4352, 5632, 16, 2, False), (16, 5120, 5632, 16, 2, False), (1, 5120, 2560, 16, 2, False),
+    (1, 4352, 5632, 16, 2, False), (16, 4352, 5632, 16, 2, False), (16, 5120, 5632, 16, 2, False),
+    (1, 5120, 2560, 16, 2, False),
     (1, 6144, 768, 16, 2, False), (4, 6144, 512, 16, 2, True), (4, 4352, 512, 16, 2, True), (16, 4352, 512, 16, 2, False)])
 def test_which_calls_combine_in_gemm2(launches, T, D, F, n_ffn, k, together):
     """16 columns a workgroup; the step calls and the variants keep the two kernels."""

@@ -425,8 +425,10 @@ def test_f32_halves_and_whole_tiles_are_the_same_numbers(D, F, k, few, many, nam
 
 
 # GEMM2 with the combine in it: (T, D, F = 256 steps of a wave, FFN experts, others each, slots)
-DECODE_COMBINE = [(1, 256, 256, 3, 1, 2), (48, 3840, 256, 16, 1, 2), (2, 512, 512, 4, 1, 7), (17, 4096, 768, 8, 2, 4), (33, 4096, 1280, 12, 0, 2),
-                  (1, 768, 2048, 16, 1, 2), (5, 3840, 2816, 4, 8, 8), (16, 4096, 4096, 6, 1, 2), (9, 3840, 4352, 2, 1, 3), (9, 6144, 512, 2, 1, 3),
+DECODE_COMBINE = [(1, 256, 256, 3, 1, 2), (48, 3840, 256, 16, 1, 2), (2, 512, 512, 4, 1, 7), (17, 4096, 768, 8, 2, 4),
+                  (33, 4096, 1280, 12, 0, 2),
+                  (1, 768, 2048, 16, 1, 2), (5, 3840, 2816, 4, 8, 8), (16, 4096, 4096, 6, 1, 2), (9, 3840, 4352, 2, 1, 3),
+                  (9, 6144, 512, 2, 1, 3),
                   (3, 4096, 5632, 4, 1, 2), (2, 3840, 6144, 3, 1, 2)]
 
 
