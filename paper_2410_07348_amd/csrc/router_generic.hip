@@ -662,8 +662,8 @@ bool router_sliced_wins(const Dims &d) { return (d.D >= 768 && d.T <= 2048) || (
 // and its logits no further from float64, else 0.  Router and permutation, us, and in brackets the logits' error
 // against float64, 1e-8.  Blocks of 16 / the matrix-core router, where it is the other choice:
 //   24 weight rows: D = 128 T = 65 8.3 [6.0] / 11.9 [6.6], T = 2048 9.1 / 13.6; D = 512 T = 300 9.8 [6.9] /
-//   13.8 [7.9]; D = 1024 T = 4096 13.8 [7.3] / 17.2 [10]; 52 rows: D = 256 T = 2048 11.9 [6.8] / 17.9
-//   [7.2]; D = 768 T = 4096 17.4 [7.4] / 22.1 [9.2].
+//   13.8 [7.9]; D = 1024 T = 4096 13.7 [8.1] / 17.2 [10]; 52 rows: D = 256 T = 2048 11.9 [6.8] / 17.9
+//   [7.2]; D = 768 T = 4096 17.4 [7.6] / 22.1 [9.2].
 // Against slices, which spread a wide layer's few tokens over more CUs: what a block takes grows with D times its
 // 16, 32 or 64 weight rows and eight for x, what slices take with T.  bf16, block / slices:
 //   D = 768, 24 rows T = 65 10.2 / 11.9, T = 2048 11.0 [7.1] / 14.2 [7.2]; D = 1024, 24 rows T = 65 11.4 /
@@ -698,11 +698,13 @@ int router_block_tokens(const Dims &d, bool bf16) {
     return (long long)d.D * (padded + 8) <= most ? 16 : 0;
 }
 
-// Waves and sets of sums: eight waves have two slices each up to D = 512, then sixteen with two sets (eight
-// of them with more than 32 rows, whose registers do not fit sixteen), so that chains of sums stay as short
-// as on slices: bf16, 24 rows, D = 1024 T = 2048 12.0 us [7.3e-8], eight waves with one set 11.9 [8.0], D =
-// 256 10.0 and 9.1 [6.4 both]; float32, 24 rows, D = 256 eight waves 9.1, sixteen 10.3 [8.2 both], D = 768
-// 11.6 [9.7] and 11.8 [8.9]; 12 rows, D = 768 sixteen 10.3 [8.9].
+// Waves and sets of sums.  Eight waves have at most two slices each up to D = 512; wider layers take sixteen with two
+// sets where they replace slices, so that chains of sums stay as short as there (eight of them with more than
+// 32 rows, whose registers do not fit sixteen): bf16, 24 rows, D = 1024 T = 2048 12.0 us [7.3], eight waves with
+// one set 11.9 [8.0].  The matrix-core router's chains are longer than either's, and eight waves with one set are
+// the fastest beside it: 52 rows, D = 768 T = 4096 17.4 us [7.6], with two sets 17.7 [7.4], matrix cores [9.2]; 24 rows, D =
+// 256 9.1 us, sixteen waves 10.0.  float32, 24 rows, D = 256 eight waves 9.1, sixteen 10.3 [8.2 both], D = 768 11.6
+// [9.7] and 11.8 [8.9]; 12 rows, D = 768 sixteen 10.3 [8.9].
 hipError_t launch_router_block(const RouterArgs &a, bool bf16, hipStream_t s) {
     const int tok = router_block_tokens(a.d, bf16), rows = a.d.N + 2 * a.d.n_const;
     if (tok == 0 || (size_t)kRouterBlocks * a.d.N * sizeof(int32_t) > router_small_bytes()) return hipErrorInvalidValue;
@@ -710,7 +712,7 @@ hipError_t launch_router_block(const RouterArgs &a, bool bf16, hipStream_t s) {
         hipLaunchKernelGGL(kernel, dim3((a.d.T + tok - 1) / tok), dim3(waves * kWave), 0, s, a, inverse_rows(rows));
         return hipGetLastError();
     };
-    const bool few = a.d.D <= 512;
+    const bool few = a.d.D <= 512 || (bf16 && router_mfma_supported(a.d) && !router_sliced_wins(a.d));
     if (!bf16) {
         if (rows <= 16) return go(k_router_block<float, 1, 1, 16, 16, 2>, 16);
         if (rows <= 32) return few ? go(k_router_block<float, 1, 2, 32, 8, 2>, 8) : go(k_router_block<float, 1, 2, 32, 16, 2>, 16);

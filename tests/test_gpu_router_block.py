@@ -23,9 +23,9 @@ BLOCK = [("f32", 65, 256, 4, 1, 2, (16, 1, 16, 2)), ("f32", 4096, 264, 4, 1, 3, 
          ("bf16", 2050, 4096, 8, 1, 2, (16, 1, 16, 2)),
          ("bf16", 2305, 256, 8, 1, 2, (16, 1, 8, 1)), ("bf16", 2305, 384, 14, 1, 4, (16, 2, 8, 1)),
          ("bf16", 65, 8, 16, 1, 2, (16, 2, 8, 1)),
-         ("bf16", 4096, 1024, 16, 2, 2, (16, 2, 16, 2)), ("bf16", 300, 1000, 20, 2, 1, (16, 2, 16, 2)),
+         ("bf16", 4096, 1024, 16, 2, 2, (16, 2, 8, 1)), ("bf16", 300, 1000, 20, 2, 1, (16, 2, 16, 2)),
          ("bf16", 1536, 2048, 18, 2, 3, (16, 2, 16, 2)),
-         ("bf16", 4095, 768, 32, 2, 2, (16, 4, 8, 2)), ("bf16", 257, 776, 40, 2, 8, (16, 4, 8, 2)),
+         ("bf16", 4095, 768, 32, 2, 2, (16, 4, 8, 1)), ("bf16", 257, 776, 40, 2, 8, (16, 4, 8, 2)), ("bf16", 2048, 1024, 30, 2, 2, (16, 4, 8, 2)),
          ("bf16", 2311, 256, 48, 1, 8, (16, 4, 8, 1)),
          ("bf16", 300, 512, 48, 3, 2, (16, 4, 8, 1)), ("bf16", 4353, 256, 3, 1, 2, (32, 1, 8, 1)),
          ("bf16", 4097, 504, 3, 1, 2, (32, 1, 8, 1)),
