@@ -293,8 +293,8 @@ __global__ __launch_bounds__(kDecThreads, 1) void k_ffn_decode_combine(DecodeOut
     // step s of a block (of none: the first lines of the weights and of h)
     bf16x8 wf[RING], tf[RING];
     auto load = [&](const Block &b, int s) {
-        const size_t slab = (size_t)b.e * a.Nb * a.K + (size_t)panel * kPanel * a.K + (size_t)(wave * S + s) * kPanel * kSlab;
-        const size_t at = b.nrows ? slab + c0 % kPanel * kSlab : 0;
+        const size_t at = b.nrows ? (size_t)b.e * a.Nb * a.K + (size_t)panel * kPanel * a.K +
+                                        (size_t)(wave * S + s) * kPanel * kSlab + c0 % kPanel * kSlab : 0;
         wf[s % RING] = __builtin_nontemporal_load(reinterpret_cast<const bf16x8 *>(a.B + at + l16 * kSlab + lq * 8));
         const int last = b.nrows ? b.row0 + b.nrows - 1 : 0, row = b.row0 + l16 < last ? b.row0 + l16 : last;
         tf[s % RING] = *reinterpret_cast<const bf16x8 *>(a.A + (size_t)(wave * S + s) * a.h_rows * kSlab + (size_t)row * kSlab + lq * 8);
@@ -473,25 +473,29 @@ static int decode_cus() {
     return n_cu;
 }
 
-// A CU of the kernel that combines, too, reads 27 KB of weights a us, all of them together 6.1 MB: where
-// fewer than 226 workgroups (D < 3614) share them the stream takes longer, which is worth it up to the 3.2 us that
-// a launch and the combine cost.  Layers, us, apart / together: D = 4096, F = 5632 T = 1 65.8 / 62.1, T = 16
-// 327 / 321, T = 45 368 / 367, T = 64 370 / 372 (the token rows are read by every workgroup); three layers of D =
-// 768, F = 2048 T = 1 59.6 / 58.5, T = 2 65.0 / 68.9; D = 2048, F = 1024 T = 1 72.5 / 68.4; D = 2048, F = 2048
-// T = 2 94.2 / 90.8, T = 8 187 / 193; D = 512, F = 512, 8 experts T = 4 66.4 / 58.1.
+// A CU of the kernel that combines, too, reads 32 KB of weights a us, all of them together 6.4 MB, and each
+// row block costs every workgroup 0.14 us: where fewer than 200 workgroups (D < 3200) share the weights the
+// stream takes longer, and with many row blocks so do their ends, which is worth it up to the 3.0 us that a launch and
+// the combine cost.  The constants fit 1358 timings (D = 256 .. 4096, F = 256 .. 5632, 2 to 32 experts, T = 1 .. 48, cold
+// and cached weights, calls one by one and in a graph): of 1560 us that the better choices would save they find 1407,
+// the streams alone (27 KB, 6.1 MB and 3.2 us) 1342.  Layers, us, apart / together: D = 4096, F = 5632, 16 experts T = 1
+// 65.8 / 62.1, T = 16 327 / 321, T = 45 368 / 367, T = 64 370 / 372 (the token rows are read by every workgroup); D = 768,
+// F = 2048 three layers of T = 1 59.6 / 58.5, T = 2 65.0 / 68.9; D = 3072, F = 2048 T = 8 89.8 / 86.6; D = 2048, F = 2048 T =
+// 2 94.2 / 90.8, T = 8 187 / 193; D = 512, F = 512, 8 experts T = 4 66.4 / 58.1; D = 1024, F = 256 T = 18 (14 row
+// blocks) 20.6 / 23.8; D = 3072, F = 512, 32 experts T = 39 67.5 / 68.6.
 // More workgroups than CUs (D > 4096) are a second round with most CUs idle: a CU has one of them from F = 2816 on
-// (over 128 registers), and two of them share its 27 KB a us.  16 experts: D = 4352, F = 5632 T = 1 73.0 / 78.1,
-// T = 16 298 / 336, T = 40 385 / 446; D = 5120, F = 5632 T = 16 377 / 404; D = 6144, F = 4352 T = 1 76.6 / 83.0; D =
-// 4352, F = 1024 T = 16 72.9 / 78.4; D = 6144, F = 2048 T = 1 46.9 / 46.7, T = 4 68.5 / 70.5.  Up to F = 512 the
-// launch it saves is more: D = 6144, F = 512 T = 1 31.6 / 30.5, T = 4 39.8 / 38.1; D = 4352, F = 512 T = 4 30.9 /
-// 29.7, but T = 16 47.6 / 49.0.
+// (over 128 registers).  16 experts: D = 4352, F = 5632 T = 1 73.0 / 78.1, T = 16 298 / 336, T = 40 385 / 446; D = 5120,
+// F = 5632 T = 16 377 / 404; D = 6144, F = 4352 T = 1 76.6 / 83.0; D = 4352, F = 1024 T = 16 72.9 / 78.4; D = 6144, F =
+// 2048 T = 1 46.9 / 46.7, T = 4 68.5 / 70.5.  Up to F = 512 two share a CU and the launch they save is more: D =
+// 6144, F = 512 T = 1 31.6 / 30.5, T = 16 59.9 / 58.1; D = 4352, F = 512 T = 4 30.9 / 29.7, but T = 16 47.6 / 49.0.
 bool ffn_decode_combines(const Dims &d) {
     if (!ffn_decode_supported(d) || d.T > kDecOutT) return false;
-    const double wgs = d.D / 16, cus = decode_cus(), cu_rate = 27e3, all_rate = 6.1e6;     // (bytes a us)
+    const double wgs = d.D / 16, cus = decode_cus(), cu_rate = 32e3, all_rate = 6.4e6;     // (bytes a us)
     if (wgs > cus && d.F > 512) return false;
-    const double rounds = (wgs > cus ? cus / all_rate : 0.0) + 1.0 / cu_rate;
+    const double stream = wgs > cus ? cus / all_rate + 0.5 / cu_rate : 1.0 / cu_rate;      // us a byte of a workgroup
+    const double longer = fmax(0.0, stream - wgs / all_rate);
     const double blocks = d.n_ffn * (1.0 - pow(1.0 - 1.0 / d.N, (double)d.T * d.k));     // experts with rows
-    return 32.0 * blocks * d.F * (rounds - wgs / all_rate) < 3.2;
+    return blocks * (0.14 + 32.0 * d.F * longer) < 3.0;
 }
 
 hipError_t launch_ffn_decode_combine(const FfnArgs &f, const CombineArgs &c, hipStream_t s) {

@@ -291,10 +291,11 @@ def test_halves_and_whole_tiles_of_the_gpu_test(launches):
     (1, 768, 2048, 16, 2, True), (2, 768, 2048, 16, 2, False), (1, 768, 2048, 16, 4, False), (16, 4096, 5632, 16, 2, True),
     (48, 4096, 5632, 16, 2, True),
     (49, 4096, 5632, 16, 2, False), (8, 2048, 2048, 16, 2, False), (4, 512, 512, 8, 2, True), (48, 3840, 256, 16, 2, True),
+    (8, 3072, 2048, 16, 2, True), (18, 1024, 256, 16, 2, False), (6, 1024, 256, 16, 2, True),
     # more workgroups than the 256 CUs
     (1, 4352, 5632, 16, 2, False), (16, 4352, 5632, 16, 2, False), (16, 5120, 5632, 16, 2, False),
     (1, 5120, 2560, 16, 2, False),
-    (1, 6144, 768, 16, 2, False), (4, 6144, 512, 16, 2, True), (4, 4352, 512, 16, 2, True), (16, 4352, 512, 16, 2, False)])
+    (1, 6144, 768, 16, 2, False), (16, 6144, 512, 16, 2, True), (4, 4352, 512, 16, 2, True), (16, 4352, 512, 16, 2, False)])
 def test_which_calls_combine_in_gemm2(launches, T, D, F, n_ffn, k, together):
     """16 columns a workgroup; the step calls and the variants keep the two kernels."""
     call = "forward %d %d" % (T, k)

@@ -146,7 +146,7 @@ def test_bf16_few_rows(T, D, F, n_ffn):
     check(T=T, D=D, F=F, n_ffn=n_ffn, bias="normal")
 
 
-# SiLU of the ragged bf16 layers is expf and a division, as in the plain FMA kernels.  x has a
+# SiLU of the ragged bf16 layers is as exact as expf and a division, which the plain FMA kernels have.  x has a
 # single one and W3 is one, so both kernels see the same z = W1 exactly, and it runs through
 # every bfloat16 of magnitude 2^-8 .. 88: h must be the same bit for bit, and within half a
 # bfloat16 ulp (2^-9 of the value, and a few float32 ulps) of z / (1 + e^-z) * 1.
