@@ -92,12 +92,13 @@ def test_sliced_router(T, D, n_ffn, n_const, k, act):
 @pytest.mark.parametrize("T,D,F,n_ffn,bias", [(40, 192, 320, 3, "none"), (300, 320, 192, 2, "normal"),
                                               (1300, 256, 256, 4, "normal"), (2600, 1024, 128, 16, "none"),
                                               (3000, 704, 1408, 5, "normal"), (700, 3072, 448, 33, "normal"),
-                                              (1500, 64, 1000, 7, "none")])
+                                              (1500, 64, 1000, 7, "none"), (1179, 1024, 512, 16, "none")])
 def test_bf16_tile_geometries(T, D, F, n_ffn, bias):
     check(T=T, D=D, F=F, n_ffn=n_ffn, bias=bias)
 
 
-@pytest.mark.parametrize("T", [130, 600])
+# (700: 117 rows per expert, the most that take 128-row tiles, and groups beyond 128 rows)
+@pytest.mark.parametrize("T", [130, 600, 700])
 def test_bf16_streamed_weights(T):
     check(T=T, D=1536, F=4096, n_ffn=8)
 
