@@ -147,6 +147,11 @@ def test_bf16_few_rows(T, D, F, n_ffn):
     check(T=T, D=D, F=F, n_ffn=n_ffn, bias="normal")
 
 
+# more workgroups of 16 columns than CUs: GEMM2 and the combine apart
+def test_bf16_few_rows_of_a_wide_layer():
+    check(T=9, D=6144, F=4352, n_ffn=2, k=3, bias="normal")
+
+
 # SiLU of the ragged bf16 layers is as exact as expf and a division, which the plain FMA kernels have.  x has a
 # single one and W3 is one, so both kernels see the same z = W1 exactly, and it runs through
 # every bfloat16 of magnitude 2^-8 .. 88: h must be the same bit for bit, and within half a
